@@ -31,22 +31,11 @@
 #include <hip/hip_ext.h>
 
 #include "pbkd_internal.h"
+#include "split_bf16.h"
 
 namespace pbkd {
 
 typedef float sfloatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-
-// two floats -> their nearest bf16, packed (low half = a)
-__device__ __forceinline__ unsigned pack_bf16_rn(float a, float b) {
-  const floatx2 v = {a, b};
-  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-}
-
 // One tile of a workgroup's list: where it is, and which chunks of K it takes.
 struct __attribute__((aligned(16))) SplitTile {
   int x0, y0, n0;      // first output column, row and image
@@ -64,14 +53,6 @@ __device__ __forceinline__ SplitTile uniform_tile(const SplitTile &d) {
   u.mt = __builtin_amdgcn_readfirstlane(d.mt); u.kb = __builtin_amdgcn_readfirstlane(d.kb); u.nk = __builtin_amdgcn_readfirstlane(d.nk);
   u.kz = __builtin_amdgcn_readfirstlane(d.kz); u.pt = __builtin_amdgcn_readfirstlane(d.pt);
   return u;
-}
-
-// 16 bytes per lane from a buffer straight into LDS: lane l lands 16 l bytes behind `lds`, which must be the same for
-// the whole wave; soff likewise.  Completion counts as a vector-memory load's.
-__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t r, char *lds, unsigned voff, unsigned soff) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, voff, soff, 0, 0);
-#endif
 }
 
 template <int WGM, int MB, int NB, int BSLOTS>
@@ -280,15 +261,10 @@ __global__ __launch_bounds__(512) void conv_split_kernel(ConvArgs p) {
         for (int t = 0; t < 4; ++t) {              // channels 2t, 2t+1
           const float x0 = gok[sl] ? fmaxf(fmaf(raw[sl][2 * t], sc[2 * t], sh[2 * t]), lo) : 0.f;
           const float x1 = gok[sl] ? fmaxf(fmaf(raw[sl][2 * t + 1], sc[2 * t + 1], sh[2 * t + 1]), lo) : 0.f;
-          const unsigned a = pack_bf16_rn(x0, x1);
-          const float r0 = x0 - __builtin_bit_cast(float, a << 16);
-          const float r1 = x1 - __builtin_bit_cast(float, a & 0xffff0000u);
-          const unsigned b = pack_bf16_rn(r0, r1);
-          const float s0 = r0 - __builtin_bit_cast(float, b << 16);
-          const float s1 = r1 - __builtin_bit_cast(float, b & 0xffff0000u);
-          pp[0][t] = a;
-          pp[1][t] = b;
-          pp[2][t] = pack_bf16_rn(s0, s1);
+          unsigned q[3];
+          split3_bf16(x0, x1, q);
+#pragma unroll
+          for (int pc = 0; pc < 3; ++pc) pp[pc][t] = q[pc];
         }
 #pragma unroll
         for (int pc = 0; pc < 3; ++pc) *reinterpret_cast<uintx4 *>(Sd + loff[sl] * 48 + pc * 16) = pp[pc];

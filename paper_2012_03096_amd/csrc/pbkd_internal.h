@@ -304,12 +304,25 @@ hipError_t launch_conv_first(const ConvArgs &a, const ConvFirstGeom &g, hipStrea
 // projection shortcut).  Weights packed like the 3x3 kernel's with one tap and 32 channels per chunk.
 struct PwGeom {
   int variant;             // 0..3: scalar kernel, (channel blocks per workgroup, pixel blocks per wave) (4,2) (4,1) (2,2) (2,1);
-                           // 4..9: vector kernel (stride 1, even H*W), see pw_mfma.hip
+                           // 4..9: vector kernel (stride 1, even H*W), see pw_mfma.hip; from kPwSplitFirst: pw_split.hip
   int bm, mtiles, nchunks, a_floats, n_ptiles;
   size_t lds_bytes;
+  int split;               // 1: products on the bf16 matrix cores, weights packed as three bf16 pieces (pw_split_pack_index)
+  int K;                   // input channels (split variants)
 };
 PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride);
-inline size_t pw_pack_floats(const PwGeom &g) { return (size_t)g.mtiles * g.nchunks * g.a_floats; }
+constexpr int kPwSplitFirst = 13;
+// Split weights: [32-channel block][chunk of 16 input channels][piece 0..2][lane][8 bf16], lane l = row l%32, channels
+// 8*(l/32)..+7 of the chunk.  A ragged last chunk starts at channel K-16; what it shares with the chunk before is zero.
+constexpr int kPwSplitPiece = 512;       // bf16 values from one piece of a weight to the next
+inline size_t pw_split_pack_index(const PwGeom &g, int m, int k) {
+  const int ch = k / 16, slot = (ch == g.nchunks - 1) ? k - (g.K - 16) : k % 16;
+  return ((size_t)(m / 32) * g.nchunks + ch) * (3 * kPwSplitPiece) + (size_t)((slot / 8) * 32 + m % 32) * 8 + slot % 8;
+}
+inline size_t pw_pack_floats(const PwGeom &g) {
+  if (g.split) return (size_t)g.mtiles * (g.bm / 32) * g.nchunks * (3 * kPwSplitPiece / 2);
+  return (size_t)g.mtiles * g.nchunks * g.a_floats;
+}
 inline size_t pw_pack_index(const PwGeom &g, int m, int k) {
   const int mt = m / g.bm, mi = m % g.bm, ch = k / 32, ki = k % 32;
   return ((size_t)(mt * g.nchunks + ch) * g.a_floats) + (size_t)ki * g.bm + mi;
@@ -324,6 +337,12 @@ struct PwArgs {
 };
 hipError_t launch_pw(const PwArgs &a, hipStream_t s);
 hipError_t init_pw_attributes();
+bool pw_split_ok(int N, int Cin, int Cout, int HWin, int Ho, int Wo);       // the tensors' sizes allow it
+bool pw_split_fits(int i, int HW, int stride);                              // variant kPwSplitFirst + i takes the shape
+int pw_split_choice(long long P, int Cout, int HW, int stride);             // the variant the library takes for P output pixels
+PwGeom pw_split_geom(int i, int N, int Cin, int Cout, int Ho, int Wo);
+hipError_t launch_pw_split(const PwArgs &a, hipStream_t s);
+hipError_t init_pw_split_attributes();
 
 // ------------------------------------------------------------------ pointwise weight gradient (MFMA, split-K)
 // dP[o,c] = sum_{n,p} dz[n,o,p] * u[n,c,p];  partial[split][Co][Ci], summed by the update kernel (launch_reduce_update).
@@ -523,9 +542,12 @@ constexpr int kGradJobFlatMaxParts = 16;
 inline int grad_job_blocks(const GradJob &j) { return (j.count + (j.flat ? 1023 : 63)) / (j.flat ? 1024 : 64); }
 // Finishes every gradient (fixed order, fp64) and applies SGD-momentum to it in one launch:
 // v <- mu*v + g ; theta <- theta - lr*v; the updated value is also written into the packed
-// copies the MFMA kernels read: pk[map_f[i]] and pk[map_b[i]] (entries < 0: no copy).
+// copies the MFMA kernels read: pk[map_f[i]] and pk[map_b[i]].  An entry of -1: no copy; below -1: the copy is three bf16
+// pieces, kPwSplitPiece values apart, the first at the 2-byte index -2 - entry.
 hipError_t launch_reduce_update(const GradJob *jobs_dev, const int *job_of_block_dev, int n_blocks, float *theta, float *vel,
                                 float *grad, float lr, float mu, const int *map_f, const int *map_b, float *pk, hipStream_t s);
+// the packed copies of n parameters as they are
+hipError_t launch_pack_params(const float *theta, size_t n, const int *map_f, const int *map_b, float *pk, hipStream_t s);
 
 
 // scratch257[0..255]: partial sums, scratch257[256] <- mean((a-b)^2) over n elements (fp64, fixed order)

@@ -470,16 +470,13 @@ size_t layout(pbkd_block &b, char *base) {
 
 void copy_desc(const pbkd_arch_desc *a, std::vector<pbkd_layer_desc> &dst) { dst.assign(a->layers, a->layers + a->n_layers); }
 
-// Packs canonical conv weights on the host into the layout the MFMA kernel stages (zero padded).
-// fwd: A[m=o][k=c][tap] = w[(o*K + c)*taps + tap]; transposed (pointwise data gradient): A[m=c][k=o] = P[o][c].
-std::vector<float> pack_host(const float *w, const ConvGeom &g, int taps, int M, int K, bool transposed) {
+// Packs canonical 3x3 weights on the host into the layout the MFMA kernel stages (zero padded):
+// A[m=o][k=c][tap] = w[(o*K + c)*9 + tap].
+std::vector<float> pack_host(const float *w, const ConvGeom &g, int M, int K) {
   std::vector<float> out(conv_pack_floats(g), 0.f);
   for (int m = 0; m < M; ++m)
     for (int k = 0; k < K; ++k)
-      for (int tap = 0; tap < taps; ++tap) {
-        const float v = transposed ? w[(size_t)k * M + m] : w[((size_t)m * K + k) * taps + tap];
-        out[conv_pack_index(g, m, k, tap)] = v;
-      }
+      for (int tap = 0; tap < 9; ++tap) out[conv_pack_index(g, m, k, tap)] = w[((size_t)m * K + k) * 9 + tap];
   return out;
 }
 
@@ -501,7 +498,9 @@ static float bf16_value(uint16_t h) {
 std::vector<uint16_t> pack_host_split(const float *w, const ConvGeom &g, int M, int K) {
   std::vector<uint16_t> out(conv_split_pack_floats(g) * 2, 0);
   for (int m = 0; m < M; ++m)
-    for (int k = 0; k < K; ++k)
+    for (int k = 0; k < K; ++k) {
+      uint16_t *const dst = out.data() + conv_split_pack_index(g, m, k, 0, 0, 0);
+      const size_t step = (size_t)g.bm * 8;       // from half-wave 0 of a tap pair to half-wave 1; tap pairs, then slots, follow
       for (int tap = 0; tap < 9; ++tap) {
         float v = w[((size_t)m * K + k) * 9 + tap];
         uint16_t piece[3];
@@ -511,47 +510,57 @@ std::vector<uint16_t> pack_host_split(const float *w, const ConvGeom &g, int M, 
         }
         for (int c = 0; c < 3; ++c) {
           if (tap < 8) {
-            out[conv_split_pack_index(g, m, k, c, tap / 2, tap % 2)] = piece[c];
+            dst[(size_t)(c * 10 + tap) * step] = piece[c];
           } else {          // the ninth tap: pieces paired with each other
-            for (int h = 0; h < 2; ++h) out[conv_split_pack_index(g, m, k, c, 4, h)] = piece[kSplitLastW[c][h]];
+            for (int h = 0; h < 2; ++h) dst[(size_t)(c * 10 + 8 + h) * step] = piece[kSplitLastW[c][h]];
           }
         }
       }
+    }
   return out;
 }
 
-// Uploads the packed copies of one layer's conv weights (host pointer to the canonical tensor).
-pbkd_status upload_packed_pointwise(LayerRT &r, const float *p_host, bool with_dgrad, hipStream_t s);
+// A packed 1x1 weight's index is a function of its output channel plus one of its input channel: both as tables (bf16
+// values where the kernel takes split weights, floats elsewhere).
+struct PwIndex {
+  std::vector<unsigned> m, k;
+  PwIndex(const PwGeom &g, int M, int K) : m(M), k(K) {
+    for (int i = 0; i < M; ++i) m[i] = (unsigned)(g.split ? pw_split_pack_index(g, i, 0) : pw_pack_index(g, i, 0));
+    for (int i = 0; i < K; ++i) k[i] = (unsigned)(g.split ? pw_split_pack_index(g, 0, i) : pw_pack_index(g, 0, i));
+  }
+};
+std::vector<float> pack_host_pw(const float *w, const PwGeom &g, int M, int K) {
+  std::vector<float> out(pw_pack_floats(g), 0.f);
+  const PwIndex ix(g, M, K);
+  uint16_t *const h = reinterpret_cast<uint16_t *>(out.data());
+  for (int m = 0; m < M; ++m)
+    for (int k = 0; k < K; ++k) {
+      float v = w[(size_t)m * K + k];
+      if (!g.split) {
+        out[ix.m[m] + ix.k[k]] = v;
+        continue;
+      }
+      uint16_t *const dst = h + ix.m[m] + ix.k[k];
+      for (int pc = 0; pc < 3; ++pc) {
+        dst[pc * kPwSplitPiece] = bf16_rn(v);
+        v -= bf16_value(dst[pc * kPwSplitPiece]);
+      }
+    }
+  return out;
+}
+
+// Uploads the packed copy of a teacher layer's convolution weights (host pointer to the canonical tensor: the 3x3 or the
+// 1x1 one, depthwise weights are read as they are).
 pbkd_status upload_packed(LayerRT &r, const float *w_host, hipStream_t s) {
-  if (r.kind == PBKD_DWSEP3X3) return PBKD_OK;   // depthwise weights are read directly; the pointwise ones come separately
-  if (r.taps == 1) return upload_packed_pointwise(r, w_host, false, s);   // projection shortcut
-  if (r.cg.split) {
+  if (r.taps == 9 && r.cg.split) {
     std::vector<uint16_t> pk = pack_host_split(w_host, r.cg, r.cout, r.cin);
     HIPCHK(hipMemcpyAsync(r.wpk, pk.data(), pk.size() * sizeof(uint16_t), hipMemcpyHostToDevice, s));
-    HIPCHK(hipStreamSynchronize(s));
+    HIPCHK(hipStreamSynchronize(s));   // pk is a temporary
     return PBKD_OK;
   }
-  std::vector<float> pk = pack_host(w_host, r.cg, r.taps, r.cout, r.cin, false);
-  HIPCHK(hipMemcpyAsync(r.wpk, pk.data(), pk.size() * sizeof(float), hipMemcpyHostToDevice, s));
-  HIPCHK(hipStreamSynchronize(s));   // pk is a temporary
-  return PBKD_OK;
-}
-std::vector<float> pack_host_pw(const float *w, const PwGeom &g, int M, int K, bool transposed) {
-  std::vector<float> out(pw_pack_floats(g), 0.f);
-  for (int m = 0; m < M; ++m)
-    for (int k = 0; k < K; ++k) out[pw_pack_index(g, m, k)] = transposed ? w[(size_t)k * M + m] : w[(size_t)m * K + k];
-  return out;
-}
-
-pbkd_status upload_packed_pointwise(LayerRT &r, const float *p_host, bool with_dgrad, hipStream_t s) {
-  std::vector<float> pk = pack_host_pw(p_host, r.pg, r.cout, r.cin, false);
+  std::vector<float> pk = r.taps == 9 ? pack_host(w_host, r.cg, r.cout, r.cin) : pack_host_pw(w_host, r.pg, r.cout, r.cin);
   HIPCHK(hipMemcpyAsync(r.wpk, pk.data(), pk.size() * sizeof(float), hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));
-  if (with_dgrad) {
-    std::vector<float> pb = pack_host_pw(p_host, r.pdg, r.cin, r.cout, true);
-    HIPCHK(hipMemcpyAsync(r.wpk_b, pb.data(), pb.size() * sizeof(float), hipMemcpyHostToDevice, s));
-    HIPCHK(hipStreamSynchronize(s));
-  }
   return PBKD_OK;
 }
 
@@ -895,47 +904,47 @@ pbkd_status pbkd_block_create(const pbkd_arch_desc *teacher, const float *const 
   if (st != PBKD_OK) return st;
   st = upload(b->s, sp);
   if (st != PBKD_OK) return st;
-  if (b->n_pk > 0x7fffffffull) return fail(PBKD_EUNSUPPORTED, "packed student weights exceed 2^31 floats");
+  if (2 * b->n_pk > 0x7ffffff0ull) return fail(PBKD_EUNSUPPORTED, "packed student weights exceed 2^30 floats");
   {
     // packed copies of every conv weight, and the arena -> packed index maps the optimizer uses
-    auto pack_net = [&](Net &net, const float *const *src, bool student) -> pbkd_status {
-      int k = 0;
-      auto one = [&](LayerRT &r) -> pbkd_status {
-        pbkd_status e;
-        if (r.kind == PBKD_DWSEP3X3) { e = upload_packed_pointwise(r, src[k + 1], student, s); k += 4; }
-        else { e = upload_packed(r, src[k], s); k += 3; }
-        return e;
-      };
-      for (auto &r : net.L) { pbkd_status e = one(r); if (e != PBKD_OK) return e; }
-      if (net.shortcut == 1) { pbkd_status e = one(net.sc); if (e != PBKD_OK) return e; }
-      return PBKD_OK;
+    // (the student's copies are written on the device, through the maps)
+    int k = 0;
+    auto pack = [&](LayerRT &r) -> pbkd_status {
+      const float *w = tp[r.kind == PBKD_DWSEP3X3 ? k + 1 : k];
+      k += r.kind == PBKD_DWSEP3X3 ? 4 : 3;
+      return upload_packed(r, w, s);
     };
-    st = pack_net(b->t, tp, false);
-    if (st != PBKD_OK) return st;
-    st = pack_net(b->s, sp, true);
-    if (st != PBKD_OK) return st;
+    for (auto &r : b->t.L) { pbkd_status e = pack(r); if (e != PBKD_OK) return e; }
+    if (b->t.shortcut == 1) { pbkd_status e = pack(b->t.sc); if (e != PBKD_OK) return e; }
     std::vector<int> mf(b->n_student, -1), mb(b->n_student, -1);
+    // where the parameters of a 1x1 weight sit in the packed copy at float offset `off` (see launch_reduce_update): entry
+    // of output channel m, input channel k = sign * (m's part + k's part) + first
+    auto entries = [](std::vector<int> &map, size_t base, const PwGeom &g, size_t off, int M, int K, bool transposed) {
+      const PwIndex ix(g, M, K);
+      const int sign = g.split ? -1 : 1, first = g.split ? -2 - (int)(2 * off) : (int)off;
+      const std::vector<unsigned> &row = transposed ? ix.k : ix.m, &col = transposed ? ix.m : ix.k;
+      for (size_t i = 0; i < row.size(); ++i)
+        for (size_t j = 0; j < col.size(); ++j) map[base + i * col.size() + j] = first + sign * (int)(row[i] + col[j]);
+    };
     auto maps = [&](LayerRT &r) {
       if (r.kind == PBKD_DWSEP3X3) {
-        const size_t base = r.w1 - b->s_params, off_f = r.wpk - b->s_pk, off_b = r.wpk_b - b->s_pk;
-        for (int o = 0; o < r.cout; ++o)
-          for (int c = 0; c < r.cin; ++c) {
-            mf[base + (size_t)o * r.cin + c] = (int)(off_f + pw_pack_index(r.pg, o, c));
-            mb[base + (size_t)o * r.cin + c] = (int)(off_b + pw_pack_index(r.pdg, c, o));
-          }
+        entries(mf, r.w1 - b->s_params, r.pg, r.wpk - b->s_pk, r.cout, r.cin, false);
+        entries(mb, r.w1 - b->s_params, r.pdg, r.wpk_b - b->s_pk, r.cin, r.cout, true);
+      } else if (r.taps == 1) {
+        entries(mf, r.w0 - b->s_params, r.pg, r.wpk - b->s_pk, r.cout, r.cin, false);
       } else {
         const size_t base = r.w0 - b->s_params, off_f = r.wpk - b->s_pk;
         for (int o = 0; o < r.cout; ++o)
           for (int c = 0; c < r.cin; ++c)
-            for (int tap = 0; tap < r.taps; ++tap)
-              mf[base + ((size_t)o * r.cin + c) * r.taps + tap] =
-                  (int)(off_f + (r.taps == 9 ? conv_pack_index(r.cg, o, c, tap) : pw_pack_index(r.pg, o, c)));
+            for (int tap = 0; tap < 9; ++tap) mf[base + ((size_t)o * r.cin + c) * 9 + tap] = (int)(off_f + conv_pack_index(r.cg, o, c, tap));
       }
     };
     for (auto &r : b->s.L) maps(r);
     if (b->s.shortcut == 1) maps(b->s.sc);
     HIPCHK(hipMemcpyAsync(b->map_f, mf.data(), mf.size() * sizeof(int), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(b->map_b, mb.data(), mb.size() * sizeof(int), hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemsetAsync(b->s_pk, 0, b->n_pk * sizeof(float), s));      // padding stays zero
+    HIPCHK(launch_pack_params(b->s_params, b->n_student, b->map_f, b->map_b, b->s_pk, s));
     HIPCHK(hipStreamSynchronize(s));
   }
   {
@@ -1664,10 +1673,11 @@ pbkd_status pbkd_block_set_tensor(pbkd_block_t *blk, int which, int layer, int s
     const bool student = which == PBKD_STUDENT_PARAM;
     Net &net = student ? blk->s : blk->t;
     LayerRT &r = (layer < (int)net.L.size()) ? net.L[layer] : net.sc;
-    if (r.kind == PBKD_DWSEP3X3 && slot == 1) {
-      e = upload_packed_pointwise(r, host_in, student, nullptr);
-      if (e != PBKD_OK) return e;
-    } else if (r.kind != PBKD_DWSEP3X3 && slot == 0) {
+    const bool has_copy = slot == (r.kind == PBKD_DWSEP3X3 ? 1 : 0);
+    if (has_copy && student) {
+      const size_t at = (size_t)(p - blk->s_params);
+      HIPCHK(launch_pack_params(p, n, blk->map_f + at, blk->map_b + at, blk->s_pk, nullptr));
+    } else if (has_copy) {
       e = upload_packed(r, host_in, nullptr);
       if (e != PBKD_OK) return e;
     }

@@ -1,5 +1,6 @@
 // 1x1 convolution (the student's pointwise conv, its data gradient, the projection shortcut) on the fp32
-// matrix cores, written for what bounds it: HBM.  z[n,o,p] = sum_c A[o,c] * in[n,c,p].
+// matrix cores, written for what bounds it: HBM.  z[n,o,p] = sum_c A[o,c] * in[n,c,p].  Serves what the split kernels
+// (pw_split.hip) do not take: fewer than 16 input channels (a chunk there is 16) and tensors of 4 GiB and more.
 //
 // The weight matrix is small, the pixel dimension huge, and in NCHW consecutive pixels of one channel are
 // contiguous bytes.  So the activations never touch LDS: every wave loads its B operands straight from
@@ -7,7 +8,7 @@
 // (all K rows of the workgroup's channel tile, at most 128 x 128 floats per stage) are staged in LDS once
 // per 128 input channels.  After that staging no barrier is needed: the four waves of a workgroup run
 // independently.  Two kernels: pw_mfma_kernel (one pixel per lane and MFMA column, any stride and shape) and
-// pw_mfma_vec_kernel (2 or 4 adjacent pixels per lane, stride 1 and even H*W; the one the benchmarks run).
+// pw_mfma_vec_kernel (2 or 4 adjacent pixels per lane, stride 1 and even H*W).
 #include <cstdlib>
 
 #include "conv_mfma_kernel.h"
@@ -342,125 +343,18 @@ __global__ __launch_bounds__(256) void pw_mfma_vec_kernel(PwArgs p) {
 }
 
 
-// ---- few pixels, many channels (4x4 and 2x2 feature maps with 256..512 channels): the tiles above would leave
-// most of the chip idle and run a long K loop per wave.  Here a workgroup owns one block of 32 channels x VW*32
-// pixels and its four waves split K in four contiguous parts; with 32-channel weight tiles the packed layout
-// makes a step's A operand 64 consecutive floats, so both operands come straight from global memory through
-// the ring and LDS only carries the final sum of the four partial accumulators (added in wave order).
-template <int VW>
-__global__ __launch_bounds__(256) void pw_mfma_ksplit_kernel(PwArgs p) {
-  // operand loads in flight per wave, in MFMA steps: with one pixel per lane a step is a single MFMA and the short
-  // K loop is bound by load latency, so the ring is deeper there (measured: 10 -> 8.5 us per launch at 2x2x512)
-  constexpr int KS_D = (VW == 1) ? 16 : 8;
-  static_assert(16 % KS_D == 0, "a wave's K range is a whole number of ring rounds");
-  typedef float vec_t __attribute__((ext_vector_type(VW)));
-  extern __shared__ float smem[];   // [4 waves][16*VW][64]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l31 = lane & 31, lh = lane >> 5;
-  // workgroup -> (pixel tile bxl, channel tile byl): the channel tiles of one pixel tile read the same activations, so
-  // they are made neighbours on one die (channel tile fastest, a contiguous range of pixel tiles per die)
-  const int lin = xcd_contiguous(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-  const int byl = lin % gridDim.y, bxl = lin / gridDim.y;
-  const int m0 = byl * 32;
-  const int HW = p.Ho * p.Wo;
-  const long long P = (long long)p.N * HW;
-  const int total = p.nchunks * 16;                 // MFMA steps over the zero-padded K
-  const int per_wave = ((total + 3) / 4 + KS_D - 1) / KS_D * KS_D;
-  const int t_begin = wave * per_wave;
-  const int t_end = (t_begin + per_wave < total) ? t_begin + per_wave : total;   // multiple of KS_D (total % 16 == 0)
-
-  long long g = (long long)bxl * (VW * 32) + VW * l31;
-  const bool pvalid = g < P;
-  if (!pvalid) g = P - VW;                          // read real pixels, never store them
-  const int n = (int)(g / HW);
-  const int r0 = (int)(g - (long long)n * HW);
-  const float *src = p.in + (size_t)n * p.Cin * HW + r0;
-  const float *wsrc = p.wpk + (size_t)byl * p.nchunks * 1024 + lane;
-  auto bload = [&](int t) -> vec_t {
-    int k = 2 * t + lh;
-    if (k > p.Cin - 1) k = p.Cin - 1;               // padded K: the weight rows are zero there
-    return *reinterpret_cast<const vec_t *>(src + (size_t)k * HW);
-  };
-
-  floatx16 acc[VW];
-#pragma unroll
-  for (int e = 0; e < VW; ++e)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[e][r] = 0.f;
-
-  if (t_begin < t_end) {
-    vec_t rb[KS_D];
-    float ra[KS_D];
-#pragma unroll
-    for (int d = 0; d < KS_D; ++d) {
-      ra[d] = wsrc[(size_t)(t_begin + d) * 64];
-      rb[d] = bload(t_begin + d);
-    }
-    for (int t = t_begin; t < t_end; t += KS_D) {
-#pragma unroll
-      for (int d = 0; d < KS_D; ++d) {
-        const float av = ra[d];
-        const vec_t bv = rb[d];
-        int tn = t + d + KS_D;
-        if (tn > total - 1) tn = total - 1;         // past the end: a valid address, the value is never used
-        ra[d] = wsrc[(size_t)tn * 64];
-        rb[d] = bload(tn);
-#pragma unroll
-        for (int e = 0; e < VW; ++e) acc[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv[e], acc[e], 0, 0, 0);
-      }
-    }
-  }
-
-  // ---- the four partial accumulators meet in LDS; wave w then finishes accumulator registers 4w..4w+3,
-  // i.e. rows 8w + 4*(lane/32) + 0..3 of the channel block, for all of the tile's pixels
-#pragma unroll
-  for (int e = 0; e < VW; ++e)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) smem[((wave * 16 + r) * VW + e) * 64 + lane] = acc[e][r];
-  __syncthreads();
-  float *dst = p.out + (size_t)n * p.Cout * HW + r0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int r = 4 * wave + j;
-    const int o = m0 + 8 * wave + 4 * lh + j;
-    vec_t v;
-#pragma unroll
-    for (int e = 0; e < VW; ++e) {
-      float sum = smem[((0 * 16 + r) * VW + e) * 64 + lane];
-#pragma unroll
-      for (int w = 1; w < 4; ++w) sum += smem[((w * 16 + r) * VW + e) * 64 + lane];
-      v[e] = sum;
-    }
-    if (o < p.Cout && pvalid) *reinterpret_cast<vec_t *>(dst + (size_t)o * HW) = v;
-    if (p.stat_partial) {                           // per-channel statistics partial over this tile's pixels, about its first
-      const float pv = __shfl(v[0], lane & 32, 64);
-      float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-      for (int e = 0; e < VW; ++e) {
-        const float d = pvalid ? v[e] - pv : 0.f;
-        s1 += d;
-        s2 += d * d;
-      }
-      s1 = half32_sum(s1);
-      s2 = half32_sum(s2);
-      const float cnt = half32_sum(pvalid ? (float)VW : 0.f);
-      if (l31 == 0 && o < p.Cout) {
-        StatPart a;
-        a.pivot = pv; a.s1 = s1; a.s2 = s2; a.n = cnt;
-        stat_store(p.stat_partial, (size_t)o * gridDim.x + bxl, a);
-      }
-    }
-  }
-}
-
 // Vector variants 4..9 = (WM, WP, VW): (4,1,4) (4,1,2) (2,2,4) (2,2,2) (1,4,4) (1,4,2)
 static const int kVecWM[6] = {4, 4, 2, 2, 1, 1}, kVecWP[6] = {1, 1, 2, 2, 4, 4}, kVecVW[6] = {4, 2, 4, 2, 4, 2};
 
 PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride) {
   const long long P = (long long)N * Ho * Wo;
   const int HW = Ho * Wo;
-  int forced = -1;                                            // PBKD_PW_VARIANT=0..9: tuning aid
+  int forced = -1;                                            // PBKD_PW_VARIANT: tuning aid
   if (const char *env = std::getenv("PBKD_PW_VARIANT")) forced = std::atoi(env);
+  const bool split_ok = pw_split_ok(N, Cin, Cout, stride * Ho * stride * Wo, Ho, Wo);
+  if (forced >= kPwSplitFirst && split_ok && pw_split_fits(forced - kPwSplitFirst, HW, stride))
+    return pw_split_geom(forced - kPwSplitFirst, N, Cin, Cout, Ho, Wo);
+  if (forced < 0 && split_ok) return pw_split_geom(pw_split_choice(P, Cout, HW, stride), N, Cin, Cout, Ho, Wo);
   const bool small_in = (unsigned long long)N * Cin * HW * sizeof(float) < (1ull << 32);   // 32-bit lane offsets
   if (stride == 1 && HW % 2 == 0 && small_in && !(forced >= 0 && forced <= 3)) {
     const int wmi = Cout > 64 ? 0 : (Cout > 32 ? 2 : 4);     // index of the (WM, WP) pair with VW = 4
@@ -476,26 +370,7 @@ PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride) {
     if (wmi == 2 && HW % 4 == 0 && blocks(4) >= 2048) i = 4;
     if (HW % 4 != 0 || blocks(i) < 256) i = wmi + 1;          // narrower vectors: twice the workgroups
     if (forced >= 4 && forced <= 9 && (kVecVW[forced - 4] == 2 || HW % 4 == 0)) i = forced - 4;
-    // still fewer workgroups than compute units, or only the narrow vectors reach that many, and a K loop worth
-    // splitting: 32 x VW*32 blocks, K over the waves
-    const bool narrow = HW % 4 == 0 && i == wmi + 1 && Cin >= 256;   // (measured: at K = 128 the two are level)
-    if ((forced < 0 && (blocks(i) < 256 || narrow) && Cin >= 128) || (forced >= 10 && forced <= 12)) {
-      auto kblocks = [&](int vw) { return (long long)cdiv(Cout, 32) * ((P + 32 * vw - 1) / (32 * vw)); };
-      int vw = (HW % 4 == 0 && kblocks(4) >= 256) ? 4 : (kblocks(2) >= 256 ? 2 : 1);
-      if (forced == 10 && HW % 4 == 0) vw = 4;
-      if (forced == 11) vw = 2;
-      if (forced == 12) vw = 1;
-      PwGeom g;
-      g.variant = vw == 4 ? 10 : (vw == 2 ? 11 : 12);
-      g.bm = 32;
-      g.mtiles = cdiv(Cout, 32);
-      g.nchunks = cdiv(Cin, KC1);
-      g.a_floats = KC1 * g.bm;
-      g.n_ptiles = (int)((P + 32 * vw - 1) / (32 * vw));
-      g.lds_bytes = (size_t)4 * 16 * vw * 64 * sizeof(float);
-      return g;
-    }
-    PwGeom g;
+    PwGeom g{};
     g.variant = 4 + i;
     g.bm = kVecWM[i] * 32;
     g.mtiles = cdiv(Cout, g.bm);
@@ -515,7 +390,7 @@ PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride) {
   for (int i = first; i < 4; ++i)
     if (blocks(i) >= 512) { v = i; break; }
   if (forced >= 0 && forced <= 3) v = forced;
-  PwGeom g;
+  PwGeom g{};
   g.variant = v;
   g.bm = kMB[v] * 32;
   g.mtiles = cdiv(Cout, g.bm);
@@ -540,17 +415,12 @@ hipError_t init_pw_attributes() {
   if (e != hipSuccess) return e;
   PBKD_SETV(4, 1, 4) PBKD_SETV(4, 1, 2) PBKD_SETV(2, 2, 4) PBKD_SETV(2, 2, 2) PBKD_SETV(1, 4, 4) PBKD_SETV(1, 4, 2)
 #undef PBKD_SETV
-#define PBKD_SETK(VW)                                                                                       \
-  e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pw_mfma_ksplit_kernel<VW>),                       \
-                          hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);                             \
-  if (e != hipSuccess) return e;
-  PBKD_SETK(4) PBKD_SETK(2) PBKD_SETK(1)
-#undef PBKD_SETK
-  return hipSuccess;
+  return init_pw_split_attributes();
 }
 
 hipError_t launch_pw(const PwArgs &a, hipStream_t s) {
   if (a.N <= 0 || a.Cin <= 0 || a.Cout <= 0 || a.g.mtiles > 65535) return hipErrorInvalidValue;
+  if (a.g.split) return launch_pw_split(a, s);
   const dim3 grid(a.g.n_ptiles, a.g.mtiles), block(256);
   switch (a.g.variant) {
     case 0: hipLaunchKernelGGL((pw_mfma_kernel<4, 2>), grid, block, a.g.lds_bytes, s, a); break;
@@ -570,16 +440,6 @@ hipError_t launch_pw(const PwArgs &a, hipStream_t s) {
         case 8: hipLaunchKernelGGL((pw_mfma_vec_kernel<1, 4, 4>), grid, block, a.g.lds_bytes, s, a); break;
         default: hipLaunchKernelGGL((pw_mfma_vec_kernel<1, 4, 2>), grid, block, a.g.lds_bytes, s, a); break;
       }
-      break;
-    }
-    case 10: case 11: case 12: {
-      const int vw = a.g.variant == 10 ? 4 : (a.g.variant == 11 ? 2 : 1);
-      if (a.stride != 1 || (a.Ho * a.Wo) % vw || a.HWin != a.Ho * a.Wo || a.g.bm != 32 || (reinterpret_cast<uintptr_t>(a.in) & (4 * vw - 1)) ||
-          (reinterpret_cast<uintptr_t>(a.out) & (4 * vw - 1)))
-        return hipErrorInvalidValue;
-      if (vw == 4) hipLaunchKernelGGL((pw_mfma_ksplit_kernel<4>), grid, block, a.g.lds_bytes, s, a);
-      else if (vw == 2) hipLaunchKernelGGL((pw_mfma_ksplit_kernel<2>), grid, block, a.g.lds_bytes, s, a);
-      else hipLaunchKernelGGL((pw_mfma_ksplit_kernel<1>), grid, block, a.g.lds_bytes, s, a);
       break;
     }
     default: return hipErrorInvalidValue;

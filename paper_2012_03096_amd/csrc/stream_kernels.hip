@@ -14,6 +14,7 @@
 #include <mutex>
 
 #include "pbkd_internal.h"
+#include "split_bf16.h"
 
 namespace pbkd {
 
@@ -1419,6 +1420,33 @@ hipError_t feature_mse_static_scratch(double **ptr_out) {
 
 // ------------------------------------------------------------------------------------------------ optimizer
 
+// The packed copies of an updated parameter (launch_reduce_update).
+__device__ __forceinline__ void store_packed(float *pk, int f, int b, float v) {
+  if (f >= 0) pk[f] = v;
+  if (b >= 0) pk[b] = v;
+  if (f < -1 || b < -1) {
+    unsigned p[3];
+    split3_bf16(v, 0.f, p);
+    unsigned short *const h = reinterpret_cast<unsigned short *>(pk);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (f < -1) h[(size_t)(-2 - f) + k * kPwSplitPiece] = (unsigned short)p[k];
+      if (b < -1) h[(size_t)(-2 - b) + k * kPwSplitPiece] = (unsigned short)p[k];
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void pack_params_kernel(const float *theta, size_t n, const int *map_f, const int *map_b, float *pk) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) store_packed(pk, map_f[i], map_b[i], theta[i]);
+}
+
+hipError_t launch_pack_params(const float *theta, size_t n, const int *map_f, const int *map_b, float *pk, hipStream_t s) {
+  if (n == 0 || (n + 255) / 256 > 0x7fffffffull) return n ? hipErrorInvalidValue : hipSuccess;
+  hipLaunchKernelGGL(pack_params_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, theta, n, map_f, map_b, pk);
+  return hipGetLastError();
+}
+
 // Gradient reduction and parameter update in one pass.  With many partials a workgroup serves 64 consecutive
 // elements of one job's tensor: 16 waves each sum every 16th partial of those elements (fp64, index order, four loads in flight),
 // wave 0 adds the 16 results in wave order, stores the gradient and updates the parameter.
@@ -1463,9 +1491,7 @@ __global__ __launch_bounds__(64 * RP_SLICES) void reduce_update_kernel(const Gra
     vel[a] = v;
     const float th = theta[a] - lr * v;
     theta[a] = th;
-    const int f = map_f[a], b = map_b[a];
-    if (f >= 0) pk[f] = th;
-    if (b >= 0) pk[b] = th;
+    store_packed(pk, map_f[a], map_b[a], th);
     return;
   }
   const int o = threadIdx.x & 63, pl = threadIdx.x >> 6;
@@ -1516,9 +1542,7 @@ __global__ __launch_bounds__(64 * RP_SLICES) void reduce_update_kernel(const Gra
     vel[a] = v;
     const float t = theta[a] - lr * v;
     theta[a] = t;
-    const int f = map_f[a], b = map_b[a];
-    if (f >= 0) pk[f] = t;
-    if (b >= 0) pk[b] = t;
+    store_packed(pk, map_f[a], map_b[a], t);
   }
 }
 

@@ -316,6 +316,57 @@ def test_every_tile_variant_on_ragged_blocks(gpu, monkeypatch, var, value):
         assert not fails, (var, value, name, fails)
 
 
+def pointwise_split_blocks():
+    """Blocks for the 1x1 kernels that form fp32 products from bf16 pieces (at least 16 input channels): chunks of 16
+    channels that end ragged (17, 20, 33 channels) or whole (16, 64), channel tiles of one and several blocks of 32 with
+    ragged last ones, pixel counts that leave tails for one, two and four pixels a lane, a strided shortcut, more than one
+    stage of 128 input channels."""
+    by_name = {v.name: v for v in wl.small_variants()}
+    t = wl.Arch(3, 19, 9, 11, wl._convs([19, 37, 37], stride0=2), shortcut=1, shortcut_stride=2)
+    s = wl.Arch(3, 19, 9, 11, wl._dws([19, 37, 37], stride0=2), shortcut=1, shortcut_stride=2)
+    res = wl.Workload("residual_19ch", t, s, seed=51, copy_shortcut=True)
+    t = wl.Arch(3, 64, 8, 12, wl._convs([64, 145]))
+    s = wl.Arch(3, 64, 8, 12, wl._dws([64, 270, 145]))
+    return [by_name["three_layers_oddc"], by_name["paper_task_2x2"], wl.cfg1_tiny(), res, wl.Workload("wide_270ch", t, s, seed=52)]
+
+
+@pytest.mark.parametrize("variant", range(13, 23))
+def test_pointwise_split_variants_on_ragged_blocks(gpu, monkeypatch, variant):
+    """Every tile of the split 1x1 kernels, forced onto ragged blocks: forward, data gradient and the weights that the
+    update kernel re-packs for them, against the oracle."""
+    monkeypatch.setenv("PBKD_PW_VARIANT", str(variant))
+    for w in pointwise_split_blocks():
+        fails = run_parity(gpu, w, steps=3)
+        assert not fails, (variant, w.name, fails)
+
+
+def test_pointwise_split_is_as_accurate_as_fp32(gpu, monkeypatch):
+    """The six bf16 products of three-way split operands leave out at most 2^-24 of each product, so against the fp64 oracle
+    the split 1x1 kernels must not be worse than the fp32 MFMA one by more than rounding noise: z of two layers (K = 512
+    and 260, many-pixel and K-over-waves tiles)."""
+    t = wl.Arch(6, 512, 8, 8, wl._convs([512, 96]))
+    s = wl.Arch(6, 512, 8, 8, wl._dws([512, 260, 96]))
+    w = wl.Workload("pointwise_accuracy", t, s, seed=53)
+    torch, pb = gpu
+    x, tp, sp = w.tensors(random_affine=True)
+    ref = _ref_block(w, tp, sp)
+    t_ref = ref.teacher_forward(x)
+    ref.student_step(x, t_ref, w.lr)
+    xd, td = torch.from_numpy(x).cuda(), torch.from_numpy(t_ref.astype(np.float32)).cuda()
+    errs = {}
+    for variant in (3, 14, 21):
+        monkeypatch.setenv("PBKD_PW_VARIANT", str(variant))
+        blk = pb.Block(w.teacher, tp, w.student, sp)
+        blk.student_step(xd, td, w.lr)
+        zs = [blk.get_tensor(pb.STUDENT_ACT, l, 1, shp) for l, (_, shp, _) in enumerate(_layer_act_shapes(w.student))]
+        errs[variant] = [relerr(z, r["z"]) for z, r in zip(zs, ref.cache["layers"])]
+        blk.close()
+    print("[pointwise accuracy] max|err|/max|ref| of z0, z1:", errs)
+    for variant in (14, 21):
+        for a, b in zip(errs[3], errs[variant]):
+            assert b <= 2.0 * a + 2e-7, errs
+
+
 FIRST_LAYER_SWITCHES = [("PBKD_CF_TH", 4), ("PBKD_CF_TH", 8), ("PBKD_CF_OCC", 1), ("PBKD_CF_OCC", 6), ("PBKD_DW_EDGE", 0),
                         ("PBKD_DW_EDGE", 2), ("PBKD_WGRAD_BN_FUSED", 0)]
 

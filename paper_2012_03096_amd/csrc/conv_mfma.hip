@@ -95,6 +95,9 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
     if (want > g.nchunks) want = g.nchunks;
     if (want > 1) g.ksplit = (int)want;
   }
+  g.rows = false;
+  g.TW = g.TH = g.SH = 0;
+  g.stat_parts = g.n_ptiles;
   g.kchunks = cdiv(g.nchunks, g.ksplit);
   g.ksplit = cdiv(g.nchunks, g.kchunks);          // no empty split
   // bf16-split kernel where its staging fits.  A tile must have at least two chunks wherever statistics are taken (its
@@ -123,6 +126,74 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
     }
   }
   return g;
+}
+
+// Tiles of stacked rows (conv_rows_kernel.h).  Every (workgroup tile, columns per tile, K split) is priced in shader
+// cycles: rounds of 256 workgroups x (chunks x stage + tile end), stage and tile end as measured per workgroup tile, plus
+// the kernel that adds up a K split; the cheapest wins.
+bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGeom &best) {
+  static const int kWGN[4] = {2, 4, 4, 2};
+  static const double kStage[4] = {3960, 3960, 2150, 1250}, kEnd[4] = {8600, 8600, 4500, 2300};
+  const long long rows = (long long)N * Ho;
+  const double out_bytes = 4.0 * N * Cout * Ho * Wo;
+  int only = -1;
+  if (const char *env = std::getenv("PBKD_CONV_TILE")) only = std::atoi(env);
+  double best_cost = 0;
+  for (int tile = 0; tile < 4; ++tile) {
+    if (only >= 0 && only < 4 ? tile != only : (tile == 0 && Cout <= 64)) continue;
+    const int BN = kBN[tile], max_slots = tile >= 2 ? 3 : 2;
+    int last_tw = 0;
+    for (int tx = cdiv(Wo, BN); tx <= Wo; ++tx) {
+      const int tw = cdiv(Wo, tx);
+      if (tw == last_tw) continue;
+      if (last_tw && tw < 8) break;                                   // halo columns would outnumber the tile's own
+      last_tw = tw;
+      ConvGeom g{};
+      g.tile = tile;
+      g.bm = kBM[tile];
+      g.kc = KC9;
+      g.mtiles = cdiv(Cout, g.bm);
+      g.nchunks = cdiv(Cin, KC9);
+      g.split = g.rows = true;
+      g.TW = tw;
+      g.tiles_x = cdiv(Wo, g.TW);
+      g.SH = stride * (Ho - 1) + 3;
+      g.IW = stride * (g.TW - 1) + 3;
+      const auto staged_rows = [&](int th) { return stride * (th - 1) + 3 + (3 - stride) * cdiv(th - 1, Ho); };
+      g.TH = BN / g.TW;
+      if (g.TH > rows) g.TH = (int)rows;
+      while (g.TH > 1 && cdiv(staged_rows(g.TH) * g.IW, 256) > max_slots) --g.TH;
+      g.IH = staged_rows(g.TH);
+      g.PLd = g.IH * g.IW;
+      if (cdiv(g.PLd, 256) > max_slots) continue;
+      // narrow tiles: a row stride congruent to the tile's width modulo 8 keeps 8 lanes that span rows off one another's banks
+      g.IWS = g.IW;
+      if (g.TW < 8 && stride == 1) while (g.IWS % 8 != g.TW % 8) ++g.IWS;
+      g.PL = g.IH * g.IWS;
+      if (conv_rows_lds_bytes(g.bm, kWGN[tile], g.PL) > (size_t)MAX_LDS) g.IWS = g.IW, g.PL = g.PLd;
+      g.lds_bytes = conv_rows_lds_bytes(g.bm, kWGN[tile], g.PL);
+      if (g.lds_bytes > (size_t)MAX_LDS) continue;
+      const long long tiles_r = (rows + g.TH - 1) / g.TH;
+      if (tiles_r * g.tiles_x * g.mtiles > 0x7ffffff) continue;
+      g.n_ptiles = (int)(tiles_r * g.tiles_x);
+      g.tiles_y = (int)tiles_r;
+      g.tiles_n = 1;
+      for (int want = 1; want <= 8; ++want) {
+        g.kchunks = cdiv(g.nchunks, want);
+        g.ksplit = cdiv(g.nchunks, g.kchunks);
+        if (g.ksplit != want || (want == 1 ? g.nchunks < 2 : g.kchunks < 4)) continue;
+        if (g.ksplit * out_bytes >= 4294967296.0) continue;           // 32-bit store offsets
+        g.nimg = want > 1 ? cdiv(64, Ho * Wo) : 1;                    // images per statistics partial of a K split
+        g.stat_parts = want > 1 ? cdiv(N, g.nimg) : g.n_ptiles;
+        const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
+        const double per_wg = g.kchunks * kStage[tile] + kEnd[tile];
+        const double cost = (double)((items + 255) / 256) * per_wg + 2 * kStage[tile] +
+                            (want > 1 ? 8000 + (g.ksplit + 1) * out_bytes / 1500 : 0);
+        if (best_cost == 0 || cost < best_cost) best_cost = cost, best = g;
+      }
+    }
+  }
+  return best_cost > 0;
 }
 
 // One wave per (group of nimg images, channel): adds the splits' partial outputs in split order, stores the sum and
@@ -163,8 +234,8 @@ __global__ __launch_bounds__(64) void conv_ksplit_finish_kernel(const float *par
 }
 
 hipError_t launch_conv_ksplit_finish(const ConvArgs &a, hipStream_t s) {
-  if (a.g.ksplit < 2 || !a.split_out || a.g.tiles_x != 1 || a.g.tiles_y != 1 || a.Cout > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(conv_ksplit_finish_kernel, dim3(a.g.n_ptiles, a.Cout), dim3(64), 0, s, a.split_out, a.g.ksplit,
+  if (a.g.ksplit < 2 || !a.split_out || a.g.stat_parts != cdiv(a.N, a.g.nimg) || a.Cout > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(conv_ksplit_finish_kernel, dim3(a.g.stat_parts, a.Cout), dim3(64), 0, s, a.split_out, a.g.ksplit,
                      (size_t)a.N * a.Cout * a.Ho * a.Wo, a.out, a.stat_partial, a.N, a.Cout, a.Ho * a.Wo, a.g.nimg);
   return hipGetLastError();
 }

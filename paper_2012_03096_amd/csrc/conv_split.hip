@@ -5,7 +5,7 @@
 #include <type_traits>
 
 #include "conv_mfma_kernel.h"
-#include "conv_split_kernel.h"
+#include "conv_rows_kernel.h"
 
 namespace pbkd {
 
@@ -23,6 +23,9 @@ template <int WGM, int MB, int NB>
 struct SplitLaunch {
   template <int BSLOTS>
   static hipError_t attr() {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_rows_kernel<WGM, MB, NB, BSLOTS>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
+    if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_split_kernel<WGM, MB, NB, BSLOTS>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
   }
@@ -35,10 +38,11 @@ struct SplitLaunch {
   }
   template <int BSLOTS>
   static void go(const dim3 &grid, const dim3 &block, const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    void (*const kernel)(ConvArgs) = a.g.rows ? &conv_rows_kernel<WGM, MB, NB, BSLOTS> : &conv_split_kernel<WGM, MB, NB, BSLOTS>;
     if (e0 && e1)
-      hipExtLaunchKernelGGL((conv_split_kernel<WGM, MB, NB, BSLOTS>), grid, block, (unsigned)a.g.lds_bytes, s, e0, e1, 0, a);
+      hipExtLaunchKernelGGL(kernel, grid, block, (unsigned)a.g.lds_bytes, s, e0, e1, 0, a);
     else
-      hipLaunchKernelGGL((conv_split_kernel<WGM, MB, NB, BSLOTS>), grid, block, a.g.lds_bytes, s, a);
+      hipLaunchKernelGGL(kernel, grid, block, a.g.lds_bytes, s, a);
   }
   static hipError_t launch(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     // persistent: one workgroup per compute unit (their LDS allows no more), each walking every G-th tile; more
@@ -65,7 +69,47 @@ struct SplitLaunch {
     return hipGetLastError();
   }
 };
+// Canonical 3x3 weights [Cout][Cin][9] -> the LDS images of every (channel tile, chunk), see kSplitLastW.  One
+// thread per output channel (of whole tiles: channels past Cout are zeros) and chunk; bound by its scattered reads, 72
+// floats a thread: 512 -> 512 channels in about 10 us, where the host took 20 ms.
+__global__ __launch_bounds__(256) void conv_split_pack_kernel(const float *w, uintx4 *out, int bm, int nchunks, int a_stride, int M,
+                                                              int Cout, int Cin) {
+  const int m = blockIdx.x * 256 + threadIdx.x, ch = blockIdx.y;
+  if (m >= M) return;
+  uintx4 *const dst = out + ((size_t)(m / bm) * nchunks + ch) * (a_stride / 16) + m % bm;
+  for (int tap = 0; tap < 9; ++tap) {
+    uintx4 pp[3];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      float v[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int c = ch * 8 + 2 * t + e;
+        v[e] = (m < Cout && c < Cin) ? w[((size_t)m * Cin + c) * 9 + tap] : 0.f;
+      }
+      unsigned q[3];
+      split3_bf16(v[0], v[1], q);
+#pragma unroll
+      for (int pc = 0; pc < 3; ++pc) pp[pc][t] = q[pc];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (tap < 8) dst[(size_t)(c * 10 + tap) * bm] = pp[c];
+      else
+#pragma unroll
+        for (int h = 0; h < 2; ++h) dst[(size_t)(c * 10 + 8 + h) * bm] = pp[kSplitLastW[c][h]];
+    }
+  }
+}
 }  // namespace
+
+hipError_t launch_conv_split_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s) {
+  if (!g.split || g.nchunks > 65535) return hipErrorInvalidValue;
+  const int M = g.mtiles * g.bm;
+  hipLaunchKernelGGL(conv_split_pack_kernel, dim3(cdiv(M, 256), g.nchunks), dim3(256), 0, s, w, reinterpret_cast<uintx4 *>(wpk),
+                     g.bm, g.nchunks, conv_split_a_stride(g.bm), M, Cout, Cin);
+  return hipGetLastError();
+}
 
 hipError_t conv_split_init() {
   hipError_t e;
@@ -76,7 +120,13 @@ hipError_t conv_split_init() {
 }
 
 hipError_t launch_conv_split(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (!a.g.split || !conv_split_fits_width(a.g, a.H, a.W, a.stride) || a.g.lds_bytes > (size_t)MAX_LDS || a.g.raw_rounds > conv_split_rounds_max(conv_bslots_for(a.g.PLd)) || a.g.raw_w % 4 != 0)
+  if (!a.g.split || a.g.lds_bytes > (size_t)MAX_LDS) return hipErrorInvalidValue;
+  if (!a.g.rows && (!conv_split_fits_width(a.g, a.H, a.W, a.stride) || a.g.raw_rounds > conv_split_rounds_max(conv_bslots_for(a.g.PLd)) ||
+                    a.g.raw_w % 4 != 0))
+    return hipErrorInvalidValue;
+  if (a.g.rows && ((unsigned long long)a.N * a.Cin * a.H * a.W * sizeof(float) >= (1ull << 32) || a.g.SH != a.stride * (a.Ho - 1) + 3 ||
+                   a.g.IW != a.stride * (a.g.TW - 1) + 3 || (long long)a.g.tiles_x * a.g.TW < a.Wo ||
+                   (long long)(a.g.n_ptiles / a.g.tiles_x) * a.g.TH < (long long)a.N * a.Ho || a.g.PL < a.g.IH * a.g.IWS))
     return hipErrorInvalidValue;
   if (a.g.ksplit < 1 || a.g.kchunks < 1 || (long long)(a.g.ksplit - 1) * a.g.kchunks >= a.g.nchunks ||
       (long long)a.g.ksplit * a.g.kchunks < a.g.nchunks || (a.g.ksplit > 1 && !a.split_out))

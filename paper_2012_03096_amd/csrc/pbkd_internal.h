@@ -218,12 +218,18 @@ struct ConvGeom {
   int raw_w, raw_rounds;   // split kernel: columns of a staged raw row (a multiple of 4); rounds of 256 16-byte groups per raw copy
   int raw_bytes;           // bytes of a raw copy: 8 channels x staged rows x raw_w columns of fp32
   int raw_lead;            // columns a raw row starts left of the tile's first column: 4, or 0 where a tile is as wide as the map
+  bool rows;               // split kernel on tiles of TH x TW pixels of the stacked rows of all images (conv_rows_kernel.h): any map
+  int TW, TH, SH;          // rows: tile columns and rows; staged rows an image takes in the stack
+  int stat_parts;          // statistics partials per channel: one per pixel tile, or per group of nimg images where K is split
   int raw_plane;           // 1: a tile is whole images (stride 1) and a raw "row" is a whole channel plane of raw_w = H*W values
   size_t lds_bytes;
 };
 // want_split: take the bf16-split kernel where its staging fits the LDS (frozen weights only: they are split once, on
 // the host); g.split tells whether it was taken.
 ConvGeom conv_geom(int taps, int N, int Cin, int Cout, int Ho, int Wo, int stride, bool want_split = false);
+// The split kernel's geometry for maps of any width and alignment; false where it cannot run (at most eight input
+// channels, staging too large).
+bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGeom &g);
 // The split kernel fetches its input in aligned groups of four columns: input width and the tiles' first input column
 // must be multiples of 4.
 // Where a tile is whole images the unit is the channel plane instead of the row: then H*W must be a multiple of 4.
@@ -250,11 +256,10 @@ inline size_t conv_split_lds_bytes(int bm, int wgn, int PL, int raw_bytes) {
 // per thread (a raw copy has 8 channels x staged rows x groups per row of them; shapes that need more take the fp32 kernel)
 constexpr int conv_split_rounds_max(int slots) { return slots == 1 ? 3 : slots == 2 ? 4 : slots == 3 ? 6 : 0; }
 inline size_t conv_split_pack_floats(const ConvGeom &g) { return (size_t)g.mtiles * g.nchunks * conv_split_a_stride(g.bm) / sizeof(float); }
-// index, in 2-byte units, of weight (output channel m, input channel k) in slot `slot` of tap pair j, half-wave h
-inline size_t conv_split_pack_index(const ConvGeom &g, int m, int k, int slot, int j, int h) {
-  const int mt = m / g.bm, mi = m % g.bm, ch = k / 8, ki = k % 8;
-  return ((size_t)(mt * g.nchunks + ch) * conv_split_a_stride(g.bm)) / 2 + ((size_t)(((slot * 5 + j) * 2 + h) * g.bm + mi)) * 8 + ki;
-}
+// ... and of its form for any map (no raw copy)
+inline size_t conv_rows_lds_bytes(int bm, int wgn, int PL) { return conv_split_lds_bytes(bm, wgn, PL, 0); }
+// w: canonical [Cout][Cin][9] on the device -> the kernel's weight image
+hipError_t launch_conv_split_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s);
 // Weights are handed to the kernel re-packed as the exact LDS image of every (channel tile, chunk of 8
 // input channels): wpk[mtile][chunk][tap][half][bm][4], zero padded, so that staging them is a contiguous
 // vector copy and an MFMA lane (row m, half-wave h) reads the four channels 4h..4h+3 of a tap as one

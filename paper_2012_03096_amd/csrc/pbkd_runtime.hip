@@ -102,7 +102,7 @@ struct LayerRT {
   float *conv_part = nullptr;       // partial outputs of a 3x3 convolution whose K is split over workgroups
   float *wg_part = nullptr;         // partial sums of the conv weight gradient (pointwise: [splits][cout][cin]; full: [tiles][cout][cin][9])
   float *dw_part = nullptr;         // depthwise backward partials [tiles][cin][11]
-  int stat_parts() const { return first_conv ? cfg.n_wgs : (taps == 9 ? cg.n_ptiles : pg.n_ptiles); }
+  int stat_parts() const { return first_conv ? cfg.n_wgs : (taps == 9 ? cg.stat_parts : pg.n_ptiles); }
   size_t n_w0 = 0, n_w1 = 0;
   int taps = 9;                     // of the MFMA conv producing z (9 full, 1 pointwise / shortcut)
   ConvGeom cg;                      // geometry of that conv when it is a 3x3
@@ -189,6 +189,13 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
       if (r.cg.split && (!conv_split_fits_width(r.cg, h, w, d.stride) ||
                          (unsigned long long)r.cg.ksplit * a->n * d.cout * r.hout * r.wout * sizeof(float) >= (1ull << 32)))
         r.cg = conv_geom(9, a->n, d.cin, d.cout, r.hout, r.wout, d.stride, false);   // aligned 16-byte fetches, 32-bit store offsets
+      // Maps without aligned 16-byte groups: tiles of stacked rows, loaded 4 bytes at a time.  Where the aligned form
+      // exists it stays (64 -> 128 and 128 -> 128 at 16x16, batch 128: 38 us a launch against 41, 128 -> 256 at 56x56,
+      // batch 32: 518 against 557).  PBKD_CONV_ROWS=1 takes the stacked rows everywhere (tuning aid).
+      if (!student && !env_is("PBKD_CONV_SPLIT", 0) && (!r.cg.split || env_is("PBKD_CONV_ROWS", 1))) {
+        ConvGeom rows{};
+        if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, rows)) r.cg = rows;
+      }
       r.cw = cw_geom(a->n, d.cin, r.hout, r.wout, d.stride);
       r.first_conv = (l == 0) && conv_first_ok(d.cin, d.stride) &&
                      (unsigned long long)a->n * d.cout * r.hout * r.wout * sizeof(float) < (1ull << 32);   // its stores use 32-bit offsets
@@ -493,33 +500,6 @@ static float bf16_value(uint16_t h) {
   std::memcpy(&v, &u, sizeof v);
   return v;
 }
-// The bf16-split kernel's weight image: w = w0 + w1 + w2 exactly (w0 = bf16 nearest w, w1 = bf16 nearest w - w0,
-// w2 = the rest, which has at most eight significant bits left).
-std::vector<uint16_t> pack_host_split(const float *w, const ConvGeom &g, int M, int K) {
-  std::vector<uint16_t> out(conv_split_pack_floats(g) * 2, 0);
-  for (int m = 0; m < M; ++m)
-    for (int k = 0; k < K; ++k) {
-      uint16_t *const dst = out.data() + conv_split_pack_index(g, m, k, 0, 0, 0);
-      const size_t step = (size_t)g.bm * 8;       // from half-wave 0 of a tap pair to half-wave 1; tap pairs, then slots, follow
-      for (int tap = 0; tap < 9; ++tap) {
-        float v = w[((size_t)m * K + k) * 9 + tap];
-        uint16_t piece[3];
-        for (int pc = 0; pc < 3; ++pc) {
-          piece[pc] = bf16_rn(v);
-          v -= bf16_value(piece[pc]);
-        }
-        for (int c = 0; c < 3; ++c) {
-          if (tap < 8) {
-            dst[(size_t)(c * 10 + tap) * step] = piece[c];
-          } else {          // the ninth tap: pieces paired with each other
-            for (int h = 0; h < 2; ++h) dst[(size_t)(c * 10 + 8 + h) * step] = piece[kSplitLastW[c][h]];
-          }
-        }
-      }
-    }
-  return out;
-}
-
 // A packed 1x1 weight's index is a function of its output channel plus one of its input channel: both as tables (bf16
 // values where the kernel takes split weights, floats elsewhere).
 struct PwIndex {
@@ -549,13 +529,12 @@ std::vector<float> pack_host_pw(const float *w, const PwGeom &g, int M, int K) {
   return out;
 }
 
-// Uploads the packed copy of a teacher layer's convolution weights (host pointer to the canonical tensor: the 3x3 or the
-// 1x1 one, depthwise weights are read as they are).
+// Writes the packed copy of a teacher layer's convolution weights, whose canonical tensor is already on its way to the
+// device in stream order (w_host: the same values on the host: the 3x3 or the 1x1 tensor, depthwise weights are read as
+// they are).
 pbkd_status upload_packed(LayerRT &r, const float *w_host, hipStream_t s) {
   if (r.taps == 9 && r.cg.split) {
-    std::vector<uint16_t> pk = pack_host_split(w_host, r.cg, r.cout, r.cin);
-    HIPCHK(hipMemcpyAsync(r.wpk, pk.data(), pk.size() * sizeof(uint16_t), hipMemcpyHostToDevice, s));
-    HIPCHK(hipStreamSynchronize(s));   // pk is a temporary
+    HIPCHK(launch_conv_split_pack(r.w0, r.wpk, r.cg, r.cout, r.cin, s));
     return PBKD_OK;
   }
   std::vector<float> pk = r.taps == 9 ? pack_host(w_host, r.cg, r.cout, r.cin) : pack_host_pw(w_host, r.pg, r.cout, r.cin);

@@ -442,6 +442,38 @@ def test_split_convolution_on_drawn_shapes(gpu):
         blk.close()
 
 
+# (n, channels, h, w, strides): tiles of stacked rows that run over several images and end with the batch (14x14, 27x23,
+# 7x7), K split over workgroups (7x7 with 300 channels), several column tiles with a ragged last one (5x131, 9x70 at 64
+# channels), a width and height of one, stride 2 on odd and even sizes, one output row per image
+STACKED_ROWS = [(3, (40, 72, 33), 14, 14, (1, 1)), (4, (67, 100, 67), 27, 23, (1, 1)), (5, (300, 130, 20), 7, 7, (1, 1)),
+                (2, (17, 9, 70), 5, 131, (1, 1)), (1, (64, 64, 64), 9, 70, (1, 1)), (6, (12, 20, 9), 13, 1, (1, 1)),
+                (9, (10, 33, 16), 1, 11, (1, 1)), (3, (24, 40, 31), 15, 17, (2, 1)), (2, (9, 65, 48), 18, 30, (1, 2)),
+                (7, (16, 16, 16), 2, 3, (2, 1)), (1, (129, 9, 10), 3, 3, (1, 1))]
+
+
+@pytest.mark.parametrize("n,chans,h,w_,strides", STACKED_ROWS)
+def test_split_convolution_on_any_map(gpu, n, chans, h, w_, strides):
+    """Teacher forward on maps whose rows are not whole 16-byte groups, where the bf16-split kernel takes tiles out of the
+    stacked rows of all images: every layer's pre-activation and statistics against the fp64 oracle at ACT_TOL."""
+    torch, pb = gpu
+    layers = [wl.Layer(wl.CONV3X3, a, b, st, 0) for a, b, st in zip(chans[:-1], chans[1:], strides)]
+    slayers = [wl.Layer(wl.DWSEP3X3, a, b, st, 1) for a, b, st in zip(chans[:-1], chans[1:], strides)]
+    t, s = wl.Arch(n, chans[0], h, w_, layers), wl.Arch(n, chans[0], h, w_, slayers)
+    x, tp, sp = wl.Workload("any_map", t, s, seed=7).tensors(random_affine=True)
+    t_ref, tcache = ob.block_forward(t, tp, x, keep=True)
+    blk = pb.Block(t, tp, s, sp)
+    xd = torch.from_numpy(x).cuda()
+    td = torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
+    blk.teacher_forward(xd, td)
+    torch.cuda.synchronize()
+    for l, rec in enumerate(tcache["layers"]):
+        for k, key in ((1, "z"), (2, "mean"), (3, "rstd")):
+            got = blk.get_tensor(pb.TEACHER_ACT, l, k, rec[key].shape)
+            assert relerr(got, rec[key]) <= ACT_TOL, (l, key, relerr(got, rec[key]))
+    assert relerr(td.cpu().numpy(), t_ref) <= ACT_TOL
+    blk.close()
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

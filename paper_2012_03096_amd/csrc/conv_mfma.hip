@@ -96,6 +96,7 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
     if (want > 1) g.ksplit = (int)want;
   }
   g.rows = false;
+  g.pieces = 3;
   g.TW = g.TH = g.SH = 0;
   g.stat_parts = g.n_ptiles;
   g.kchunks = cdiv(g.nchunks, g.ksplit);
@@ -131,9 +132,10 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
 // Tiles of stacked rows (conv_rows_kernel.h).  Every (workgroup tile, columns per tile, K split) is priced in shader
 // cycles: rounds of 256 workgroups x (chunks x stage + tile end), stage and tile end as measured per workgroup tile, plus
 // the kernel that adds up a K split; the cheapest wins.
-bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGeom &best) {
+bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, int pieces, ConvGeom &best) {
   static const int kWGN[4] = {2, 4, 4, 2};
-  static const double kStage[4] = {3960, 3960, 2150, 1250}, kEnd[4] = {8600, 8600, 4500, 2300};
+  static const double kStages[2][4] = {{2650, 2650, 2350, 1500}, {4300, 4300, 2700, 1800}}, kEnd[4] = {8000, 8000, 5000, 3500};
+  const double *const kStage = kStages[pieces - 2];
   const long long rows = (long long)N * Ho;
   const double out_bytes = 4.0 * N * Cout * Ho * Wo;
   int only = -1;
@@ -155,6 +157,7 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGe
       g.mtiles = cdiv(Cout, g.bm);
       g.nchunks = cdiv(Cin, KC9);
       g.split = g.rows = true;
+      g.pieces = pieces;
       g.TW = tw;
       g.tiles_x = cdiv(Wo, g.TW);
       g.SH = stride * (Ho - 1) + 3;
@@ -166,12 +169,15 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGe
       g.IH = staged_rows(g.TH);
       g.PLd = g.IH * g.IW;
       if (cdiv(g.PLd, 256) > max_slots) continue;
-      // narrow tiles: a row stride congruent to the tile's width modulo 8 keeps 8 lanes that span rows off one another's banks
+      const int slots = cdiv(g.PLd, 256);
+      // narrow tiles: a row stride congruent to plus or minus the tile's width modulo 8 keeps 8 lanes that span rows off one
+      // another's banks, where the planes have room for it
       g.IWS = g.IW;
-      if (g.TW < 8 && stride == 1) while (g.IWS % 8 != g.TW % 8) ++g.IWS;
+      if (g.TW < 8 && stride == 1)
+        while (g.IWS % 8 != g.TW % 8 && (g.IWS + g.TW) % 8 != 0) ++g.IWS;
+      if (g.IH * g.IWS >= conv_rows_positions(slots)) g.IWS = g.IW;
       g.PL = g.IH * g.IWS;
-      if (conv_rows_lds_bytes(g.bm, kWGN[tile], g.PL) > (size_t)MAX_LDS) g.IWS = g.IW, g.PL = g.PLd;
-      g.lds_bytes = conv_rows_lds_bytes(g.bm, kWGN[tile], g.PL);
+      g.lds_bytes = conv_rows_lds_bytes(g.bm, BN, kWGN[tile], slots, pieces);
       if (g.lds_bytes > (size_t)MAX_LDS) continue;
       const long long tiles_r = (rows + g.TH - 1) / g.TH;
       if (tiles_r * g.tiles_x * g.mtiles > 0x7ffffff) continue;
@@ -181,14 +187,15 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGe
       for (int want = 1; want <= 8; ++want) {
         g.kchunks = cdiv(g.nchunks, want);
         g.ksplit = cdiv(g.nchunks, g.kchunks);
-        if (g.ksplit != want || (want == 1 ? g.nchunks < 2 : g.kchunks < 4)) continue;
-        if (g.ksplit * out_bytes >= 4294967296.0) continue;           // 32-bit store offsets
+        // (the last split has two chunks at least: a finished tile is stored during the next one's first)
+        if (g.ksplit != want || (want == 1 ? g.nchunks < 2 : g.kchunks < 4 || g.nchunks - (want - 1) * g.kchunks < 2)) continue;
+        if (g.ksplit * out_bytes >= 4294967296.0 - 64) continue;      // 32-bit store offsets, and one that is past the end
         g.nimg = want > 1 ? cdiv(64, Ho * Wo) : 1;                    // images per statistics partial of a K split
         g.stat_parts = want > 1 ? cdiv(N, g.nimg) : g.n_ptiles;
         const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
         const double per_wg = g.kchunks * kStage[tile] + kEnd[tile];
         const double cost = (double)((items + 255) / 256) * per_wg + 2 * kStage[tile] +
-                            (want > 1 ? 8000 + (g.ksplit + 1) * out_bytes / 1500 : 0);
+                            (want > 1 ? 14000 + (g.ksplit + 1) * out_bytes / 1500 : 0);
         if (best_cost == 0 || cost < best_cost) best_cost = cost, best = g;
       }
     }

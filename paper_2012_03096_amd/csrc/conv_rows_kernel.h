@@ -1,5 +1,15 @@
-// Device code of the bf16-split 3x3 convolution for maps of any width and any alignment (arithmetic, pipeline and MFMA
-// side: conv_split_kernel.h).  It differs in what a tile is and in how the activations arrive.
+// Device code of the split 3x3 convolution for maps of any width and any alignment (pipeline and MFMA side:
+// conv_split_kernel.h).  It differs in what a tile is, in how the activations arrive, and (NP = 2) in the arithmetic.
+//
+// NP = 3: three bf16 pieces and six products, conv_split_kernel.h.  NP = 2: two fp16 pieces, x = x0 + x1 to within
+// 2^-22 |x| (2^-24 rms), and the three products w1x0 + w0x0 + w0x1: half the MFMAs.  fp16's range is the condition: it is
+// taken only where the input is another layer's BatchNorm + ReLU over the batch, which bounds channel c by
+// |gamma_c| sqrt(N H W) + |beta_c|.  A power of two per input channel brings that bound (with margin) below 2^15, its
+// inverse goes into the channel's weights, and a power of two per output channel brings its largest weight to 2^14; the
+// epilogue takes the latter back.  All of these are exact, and what fp16's smallest step drops is below 2^-39 of a
+// channel's largest weight and 2^-28 of a standard deviation.  The split's own error is larger than that of the bf16
+// pieces (2^-24 against 2^-27 rms of a product), but half the accumulator roundings go with the three products, and they
+// are the larger part from K = 80 on: the error of z against fp64 is smaller in total (test_fp16_pair_...).
 //
 // A tile is TH output rows x TW output columns, neither a power of two, out of the STACK of all images' rows: row R of
 // the stack is row R % Ho of image R / Ho, so a tile runs on from one image into the next and only the last tile of the
@@ -10,27 +20,36 @@
 //
 // A loader thread owns staged positions and loads their eight channels of a chunk itself, 4 bytes each, straight into
 // registers a stage ahead of the split: any alignment, no raw copy in LDS (whole 16-byte groups need a width that is a
-// multiple of 4).  The channel goes into the scalar offset, so a load costs no vector instruction beyond itself.
-// Bound by the MFMA stream and, on tiles of one round, by start-up and stores.  Measured against the fp32-MFMA kernel
-// that these maps ran before: 512 -> 512 channels at 14x14, batch 32, 282 -> 134 us (220 TFLOP/s); 67 -> 100 and
-// 100 -> 67 at 27x23, batch 77, 169 -> 59 us.
+// multiple of 4).  The channel goes into the scalar offset, so a load costs no vector instruction beyond itself.  The weights
+// go from memory into the MFMA waves' operand registers, and a finished tile leaves through LDS and the loader waves.
+//
+// Bound by the MFMA waves' stage, 2 650 cycles for 1 792 of MFMAs with two pieces (operand fetches and the loader wave beside
+// them on the SIMD 450, the barrier 300; in-kernel clock stamps), on maps of one round of tiles by start-up and last stores,
+// on 224x224 maps by the loads.  Measured: against the fp32-MFMA kernel that unaligned maps ran before, 512 -> 512 channels
+// at 14x14, batch 32, 282 -> 144 us (three pieces, the block's input) and 86 us (two); 67 -> 100 and 100 -> 67 at 27x23, batch
+// 77, 169 -> 54 and 44 us.  Two pieces against the aligned bf16 kernel: 256 -> 256 at 56x56, batch 32, 610 -> 415 us; 64 -> 64
+// at 224x224 575 -> 420; 128 -> 128 at 16x16, batch 128, 46 -> 31.
 #pragma once
+#include <type_traits>
+
 #include "conv_split_kernel.h"
 
 namespace pbkd {
 
-template <int WGM, int MB, int NB, int BSLOTS>
+template <int WGM, int MB, int NB, int BSLOTS, int NP, bool VEC>
 __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
   constexpr int WGN = 4 / WGM;
   constexpr int BM = WGM * MB * 32;     // output channels per workgroup
   constexpr int WN = NB * 32;           // pixels per wave
-  constexpr int A_STRIDE = conv_split_a_stride(BM);
-  constexpr int NA = A_STRIDE / 4096;
+  constexpr int A_STRIDE = conv_rows_a_stride(BM, NP);
   extern __shared__ float smem[];
-  const int PL = p.g.PL + 1;                               // staged positions + one that is never read
-  char *const As = reinterpret_cast<char *>(smem);         // [2][A_STRIDE]
-  char *const Ss = As + 2 * A_STRIDE;                      // [2][PL][3 pieces][8 bf16]
-  StatPart *const red = reinterpret_cast<StatPart *>(Ss + (size_t)2 * 3 * PL * 16);
+  constexpr int BN = WGN * WN;          // pixels per workgroup
+  constexpr int CAP = conv_rows_positions(BSLOTS);         // staged positions a plane has room for; the last is never read
+  constexpr int PLANE = CAP * 16, COPY = NP * PLANE;       // bytes of a piece's plane, of a copy of all pieces
+  constexpr int OROW = BN + 4;                             // floats of a channel's row of the finished tile
+  char *const Ss = reinterpret_cast<char *>(smem);         // [2][NP pieces][CAP][8 channels of bf16 or fp16]
+  float *const Os = reinterpret_cast<float *>(Ss + 2 * COPY);                      // [BM][OROW]: a finished tile
+  StatPart *const red = reinterpret_cast<StatPart *>(Os + BM * OROW);              // [WGN][BM]
   SplitTile *const tiles = reinterpret_cast<SplitTile *>(red + WGN * BM);          // [kSplitMaxTiles]
 
   const bool loader = threadIdx.x >= 256;
@@ -69,35 +88,10 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
   for (int t = 0; t < n_mine; ++t) TC += tiles[t].nk;
   TC = __builtin_amdgcn_readfirstlane(TC);
 
-  // After the barrier that follows a tile's end: the WGN MFMA waves' statistics partials (in red), re-expressed about the
-  // first one's pivot and added.  The loader waves do it: they have nothing else to do while they wait for their copies.
-  auto finish_stats = [&](const SplitTile &d) {
-    if (p.stat_partial && p.g.ksplit == 1) {
-      for (int e = tid; e < BM; e += 256) {
-        const int o = d.mt * BM + e;
-        if (o < p.Cout) {
-          StatPart a = red[e];
-#pragma unroll
-          for (int w = 1; w < WGN; ++w) stat_rebase_add(a, red[w * BM + e]);
-          stat_store(p.stat_partial, (size_t)o * p.g.n_ptiles + d.pt, a);
-        }
-      }
-    }
-  };
-
   if (loader) {
-    // ------------------------------------------------------------------ loader waves: copies, split, and the statistics' last step
+    // ------------------------------------------------------------------ loader waves: loads, split; statistics' last step and stores
     const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(p.in), 0, (int)((unsigned)p.N * p.Cin * HW * sizeof(float)), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(p.wpk), 0, (int)((unsigned)p.g.mtiles * nchunks * A_STRIDE), 0x00020000);
-    const unsigned aoff = (unsigned)(tid * 16);
-    auto copy_a = [&](int mt, int k, int buf) {
-      const unsigned wk = (unsigned)(((size_t)mt * nchunks + k) * A_STRIDE);
-      char *Ad = As + buf * A_STRIDE + __builtin_amdgcn_readfirstlane(wave) * 1024;
-#pragma unroll
-      for (int i = 0; i < NA; ++i) load16_to_lds(rw, Ad + i * 4096, aoff, wk + (unsigned)(i * 4096));
-    };
     // the staged positions this thread loads and splits: row and column in the tile do not depend on the tile
     int srow[BSLOTS], scol[BSLOTS], loff[BSLOTS];          // row -1: no such position (it works on the spare one)
 #pragma unroll
@@ -107,130 +101,199 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
       const int r = q / IW;
       srow[sl] = in_tile ? r : -1;
       scol[sl] = q - r * IW;
-      loff[sl] = in_tile ? r * IWS + scol[sl] : PL - 1;
+      loff[sl] = (in_tile ? r * IWS + scol[sl] : CAP - 1) * 16;
     }
     // where the positions' values are: byte offset in the tensor of channel 0, and whether there is one (halo positions
-    // outside the image are zeros: they load the tensor's first value and a select drops it, so every load is in bounds)
+    // outside the image are zeros: they load the tensor's first value and are clamped to zero, so every load is in bounds)
     unsigned goff[BSLOTS];
-    bool gok[BSLOTS];
-    auto enter = [&](const SplitTile &d) {
+    float hi[BSLOTS];                   // what a position's value is clamped to from above: zero where there is none
+    constexpr float kMost = NP == 3 ? __builtin_inff() : 65504.f;   // (two pieces: fp16's largest value; the scaling keeps far below)
+    auto enter = [&](const SplitTile &d) __attribute__((always_inline)) {
 #pragma unroll
       for (int sl = 0; sl < BSLOTS; ++sl) {
         const int V = d.n0 * SH + d.y0 * s + srow[sl];
         const int n = V / SH, y = V - n * SH - 1, x = d.x0 * s - 1 + scol[sl];
-        gok[sl] = srow[sl] >= 0 && n < p.N && y >= 0 && y < p.H && x >= 0 && x < p.W;
-        goff[sl] = gok[sl] ? ((unsigned)n * p.Cin * HW + (unsigned)(y * p.W + x)) * 4u : 0u;
+        const bool ok = srow[sl] >= 0 && n < p.N && y >= 0 && y < p.H && x >= 0 && x < p.W;
+        hi[sl] = ok ? kMost : 0.f;
+        goff[sl] = ok ? ((unsigned)n * p.Cin * HW + (unsigned)(y * p.W + x)) * 4u : 0u;
       }
     };
-    // chunk k's values (a ragged last chunk's missing channels repeat the last one: their weights are zero)
-    auto fetch = [&](int k, float (&v)[BSLOTS][8]) {
+    // A chunk's first channel: a ragged last chunk reaches back to the last eight channels, with zero weights for those
+    // the chunk before has had (Cin > 8: the host checks).
+    auto first_channel = [&](int k) __attribute__((always_inline)) { return k * 8 < p.Cin - 8 ? k * 8 : p.Cin - 8; };
+    const unsigned HWb = (unsigned)HW * 4u;
+    auto fetch = [&](int c0, float (&v)[BSLOTS][8]) __attribute__((always_inline)) {
+      unsigned soff = (unsigned)c0 * HWb;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        int c = k * 8 + e;
-        if (c > p.Cin - 1) c = p.Cin - 1;
-        const unsigned soff = (unsigned)c * (unsigned)HW * 4u;
 #pragma unroll
         for (int sl = 0; sl < BSLOTS; ++sl)
           v[sl][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rin, goff[sl], soff, 0));
+        soff += HWb;
       }
     };
-    const bool bn = (p.in_scale != nullptr);
-    const float lo = bn ? 0.f : -__builtin_inff();             // ReLU only where there is a BatchNorm to apply
     // the producing layer's scale and shift for a chunk's channels, through the scalar cache (the constant address
-    // space: an earlier kernel wrote them): two loads of eight for a whole chunk instead of sixteen vector loads
+    // space: an earlier kernel wrote them): two loads of eight
+    const bool bn = NP == 2 || p.in_scale != nullptr;
+    const float lo = bn ? 0.f : -__builtin_inff();             // ReLU only where there is a BatchNorm to apply
+    typedef float Floats8 __attribute__((ext_vector_type(8), aligned(4)));
+    typedef const Floats8 __attribute__((address_space(4))) *ConstFloats8;
     typedef const float __attribute__((address_space(4))) *ConstFloats;
     const ConstFloats cscale = (ConstFloats)(p.in_scale), cshift = (ConstFloats)(p.in_shift);
-    float sc[8], sh[8];
-    auto fetch_bn = [&](int kc) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sc[e] = 1.f, sh[e] = 0.f;
+    struct Bn {
+      Floats8 sc, sh;
+    };
+    auto fetch_bn = [&](int c0) __attribute__((always_inline)) {
+      Bn v;
       if (bn) {
-        if (kc * 8 + 8 <= p.Cin) {
-          typedef float Floats8 __attribute__((ext_vector_type(8), aligned(4)));
-          typedef const Floats8 __attribute__((address_space(4))) *ConstFloats8;
-          const Floats8 a = *(ConstFloats8)(cscale + kc * 8), b = *(ConstFloats8)(cshift + kc * 8);
+        v.sc = *(ConstFloats8)(cscale + c0), v.sh = *(ConstFloats8)(cshift + c0);
+      } else {
+        v.sc = 1.f, v.sh = 0.f;
+      }
+      return v;
+    };
+    auto split = [&](const float (&raw)[BSLOTS][8], const float (&most)[BSLOTS], const Bn &v, int rc) __attribute__((always_inline)) {
+      char *Sd = Ss + rc * COPY;
+      float shv[8];                     // an fma takes one scalar operand: the shifts in vector registers
 #pragma unroll
-          for (int e = 0; e < 8; ++e) sc[e] = a[e], sh[e] = b[e];
-        } else {                         // a ragged last chunk: its missing channels take the last one's (their weights are zero)
+      for (int e = 0; e < 8; ++e) {
+        shv[e] = v.sh[e];
+        asm("" : "+v"(shv[e]));
+      }
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            int c = kc * 8 + e;
-            if (c > p.Cin - 1) c = p.Cin - 1;
-            sc[e] = cscale[c], sh[e] = cshift[c];
+      for (int sl = 0; sl < BSLOTS; ++sl) {
+        uintx4 pp[NP];
+        const float least = most[sl] > 0.f ? lo : 0.f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {              // channels 2t, 2t+1
+          float x[2];
+#pragma unroll
+          for (int e = 0; e < 2; ++e)              // BatchNorm, then ReLU and the halo's zeros in one step
+            x[e] = __builtin_amdgcn_fmed3f(fmaf(raw[sl][2 * t + e], v.sc[2 * t + e], shv[2 * t + e]), NP == 2 ? 0.f : least, most[sl]);
+          unsigned q[NP];
+          if constexpr (NP == 3) split3_bf16(x[0], x[1], q);
+          else split2_f16(x[0], x[1], q);
+#pragma unroll
+          for (int pc = 0; pc < NP; ++pc) pp[pc][t] = q[pc];
+        }
+#pragma unroll
+        for (int pc = 0; pc < NP; ++pc) *reinterpret_cast<uintx4 *>(Sd + loff[sl] + pc * PLANE) = pp[pc];
+      }
+    };
+    // Stage i splits chunk i-1, then issues the loads of chunk i+1's activations into the registers it has just emptied: they
+    // stay in flight across the barrier and have the whole next stage to arrive.  Two sets take turns: set c & 1 holds chunk c.
+    struct Held {
+      float v[BSLOTS][8];
+      float hi[BSLOTS];
+      int c0;                           // first channel
+    };
+    Held held[2];
+    int lt = 0, lc = 0;                 // tile and chunk of the fetching side
+    SplitTile ld = uniform_tile(tiles[0]);
+    enter(ld);
+    auto fetch_next = [&](Held &h) __attribute__((always_inline)) {
+      h.c0 = first_channel(ld.kb + lc);
+      fetch(h.c0, h.v);
+#pragma unroll
+      for (int sl = 0; sl < BSLOTS; ++sl) h.hi[sl] = hi[sl];
+      if (++lc == ld.nk) {
+        if (lt + 1 < n_mine) {
+          lc = 0;
+          ld = uniform_tile(tiles[++lt]);
+          enter(ld);
+        } else {
+          --lc;                         // past the end the last chunk is loaded again, and dropped
+        }
+      }
+    };
+    // A finished tile lies in Os from the stage after its last chunk until the next tile's end.  The loader waves finish its
+    // statistics and store it, a quarter a stage where the next tile has the stages for it, beside their own work: by the MFMA
+    // waves, stores and sums took 20 000 cycles a tile in which nothing multiplied (a quarter of a 32-chunk tile's time).
+    // VEC (rows start on 16-byte boundaries): a thread stores four pixels of a channel, else one, for every CSTEP-th channel.
+    // (Stores that are always issued, past the buffer where there is nothing to store, would keep the count of younger
+    // operations fixed that a wait for a load allows for; measured level with VEC and 20 % slower without.)
+    constexpr int CSTEP = (VEC ? 1024 : 256) / BN, PASSES = BM / CSTEP, PQ = PASSES / 4;
+    const int opx = VEC ? 4 * (tid & (BN / 4 - 1)) : tid & (BN - 1);
+    const int oc0 = VEC ? tid / (BN / 4) : tid / BN;
+    const int orow = opx / TW, ocol = opx - orow * TW;
+    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(
+        p.g.ksplit > 1 ? p.split_out : p.out, 0, (int)((unsigned)p.g.ksplit * p.N * p.Cout * HWo * sizeof(float)), 0x00020000);
+    constexpr unsigned kNowhere = kPastBuffer - 15u;           // (the host keeps the buffer's end below it)
+    int quarter = 4, at_once = 1;                              // quarters stored of the finished tile, and how many a stage
+    int och = 0;                                               // this thread's first channel
+    unsigned ooff = kNowhere;
+    auto finish_tile = [&](int t, int stages) __attribute__((always_inline)) {     // stages: until the next tile's end overwrites Os
+      const SplitTile d = uniform_tile(tiles[t]);
+      const int rr = d.y0 + orow, di = rr / p.Ho, y = rr - di * p.Ho, n = d.n0 + di;
+      och = d.mt * BM + oc0;
+      ooff = (orow < TH && n < p.N && d.x0 + ocol < p.Wo)
+                 ? ((unsigned)((d.kz * p.N + n) * p.Cout + och) * (unsigned)HWo + (unsigned)(y * p.Wo + d.x0 + ocol)) * 4u
+                 : kNowhere;
+      quarter = 0;
+      at_once = stages >= 4 ? 1 : 4;
+      if (p.stat_partial && p.g.ksplit == 1) {
+        // the MFMA waves' partials, re-expressed about the first one's pivot and added
+        for (int e = tid; e < BM; e += 256) {
+          const int o = d.mt * BM + e;
+          if (o < p.Cout) {
+            StatPart v = red[e];
+#pragma unroll
+            for (int w = 1; w < WGN; ++w) stat_rebase_add(v, red[w * BM + e]);
+            stat_store(p.stat_partial, (size_t)o * p.g.n_ptiles + d.pt, v);
           }
         }
       }
     };
-    auto split = [&](const float (&raw)[BSLOTS][8], const bool (&ok)[BSLOTS], int rc) {
-      char *Sd = Ss + (size_t)rc * 3 * PL * 16;
+    auto store_quarter = [&]() __attribute__((always_inline)) {
+      const unsigned step = (unsigned)(CSTEP * HWo) * 4u;
+      const int first = quarter * PQ;
+      const float *src = Os + (oc0 + first * CSTEP) * OROW + opx;
+      const bool some = ooff != kNowhere;
 #pragma unroll
-      for (int sl = 0; sl < BSLOTS; ++sl) {
-        uintx4 pp[3];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {              // channels 2t, 2t+1
-          const float x0 = ok[sl] ? fmaxf(fmaf(raw[sl][2 * t], sc[2 * t], sh[2 * t]), lo) : 0.f;
-          const float x1 = ok[sl] ? fmaxf(fmaf(raw[sl][2 * t + 1], sc[2 * t + 1], sh[2 * t + 1]), lo) : 0.f;
-          unsigned q[3];
-          split3_bf16(x0, x1, q);
-#pragma unroll
-          for (int pc = 0; pc < 3; ++pc) pp[pc][t] = q[pc];
+      for (int k = 0; k < PQ; ++k) {
+        const unsigned off = (some && och + (first + k) * CSTEP < p.Cout) ? ooff + (unsigned)(first + k) * step : kNowhere;
+        if constexpr (VEC) {
+          __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const uintx4 *>(src + k * CSTEP * OROW), rout, off, 0, 0);
+        } else {
+          const float v = src[k * CSTEP * OROW];
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rout, off, 0, 0);
         }
-#pragma unroll
-        for (int pc = 0; pc < 3; ++pc) *reinterpret_cast<uintx4 *>(Sd + loff[sl] * 48 + pc * 16) = pp[pc];
       }
+      ++quarter;
     };
-    // Stage i: fetches the activations of chunk i into registers and the weights of chunk i-1 into LDS and, while those
-    // are on their way, splits chunk i-1.
-    float cur[BSLOTS][8], nxt[BSLOTS][8];
-    bool okc[BSLOTS];                   // the positions of the chunk in `cur` that exist
-#pragma unroll
-    for (int sl = 0; sl < BSLOTS; ++sl) {
-      okc[sl] = false;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) cur[sl][e] = nxt[sl][e] = 0.f;
-    }
-    int lt = 0, lc = 0, a_mt = 0, a_k = 0;
-    SplitTile ld = uniform_tile(tiles[0]);
-    enter(ld);
-    int ft = 0, fc = 0;                 // the multiplying side's tile and chunk (it is at chunk i-2 in stage i)
-    bool pending = false;
-    SplitTile fd = ld, pd = ld;
-    for (int i = 0; i <= TC + 1; ++i) {
-      const bool splits = i >= 1 && i <= TC;
-      if (splits) fetch_bn(a_k);
-      if (splits) copy_a(a_mt, a_k, (i - 1) & 1);
-      if (i < TC) fetch(ld.kb + lc, nxt);
-      if (pending) {                    // the tile that ended in the stage before this one
-        finish_stats(pd);
-        pending = false;
+    // the multiplying side's tile, and its chunks left (it is at chunk i-2 in stage i)
+    int ft = 0, left = ld.nk + 1;
+    int ended = -1;                     // the tile that ended in the stage before this one
+    fetch_next(held[0]);                // stage 0
+    fetch_next(held[1]);
+    Bn now = fetch_bn(held[0].c0);
+    auto load_stage = [&](int odd, Held &h, const Held &other) __attribute__((always_inline)) {       // odd: chunk i-1's parity
+      const Bn next = fetch_bn(other.c0);                              // chunk i's scale and shift
+      split(h.v, h.hi, now, odd);
+      if (ended >= 0) {
+        finish_tile(ended, left - 1);
+        ended = -1;
       }
-      if (splits) split(cur, okc, (i - 1) & 1);
-      if (i >= 2) {
-        if (++fc == fd.nk) {
-          pd = fd;
-          pending = true;
-          fc = 0;
-          if (ft + 1 < n_mine) fd = uniform_tile(tiles[++ft]);
-        }
+      if (--left == 0) {
+        ended = ft;
+        if (++ft < n_mine) left = __builtin_amdgcn_readfirstlane(tiles[ft].nk);
       }
-      a_mt = ld.mt;
-      a_k = ld.kb + lc;
-#pragma unroll
-      for (int sl = 0; sl < BSLOTS; ++sl) okc[sl] = gok[sl];
-      if (i + 1 < TC) {
-        if (++lc == ld.nk) {
-          lc = 0;
-          ld = uniform_tile(tiles[++lt]);
-          enter(ld);
-        }
-      }
+      fetch_next(h);
+      for (int k = 0; k < at_once && quarter < 4; ++k) store_quarter();
+      now = next;
       __syncthreads();
-#pragma unroll
-      for (int sl = 0; sl < BSLOTS; ++sl)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) cur[sl][e] = nxt[sl][e];
+    };
+    __syncthreads();
+    // Stages 1 .. TC in pairs.  With an odd TC the last pair's second half is stage TC + 1, in which the MFMA waves multiply
+    // the last chunk: what it splits (the last chunk again) goes where they do not read.  (An exit between the two halves
+    // costs more: the compiler then waits in the first for loads that are a stage old at most.)
+    for (int i = 1; i <= TC; i += 2) {
+      load_stage(0, held[0], held[1]);
+      load_stage(1, held[1], held[0]);
     }
-    if (pending) finish_stats(pd);
+    if (!(TC & 1)) __syncthreads();     // stage TC + 1 (the tile before the last, of two chunks at least each, is stored)
+    finish_tile(n_mine - 1, 1);
+    while (quarter < 4) store_quarter();
   } else {
     // ------------------------------------------------------------------ MFMA waves
     sfloatx16 acc[MB][NB];
@@ -240,64 +303,71 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
       for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-    // this lane's pixel columns: row and column in the tile, and (per tile) their place in the staged tile and the output
-    int prow[NB], pcol[NB], pixoff[NB], py[NB], pimg[NB];
-    bool pvalid[NB];
+    // The pixels are the MFMA's rows and the channels its columns, so that a lane's accumulators are 16 pixels per block of
+    // ONE channel and the statistics need no step across lanes (but one between the half-waves).  As operand row, lane l31 of
+    // block nb supplies pixel wn*WN + nb*32 + l31: its row and column in the tile, and per tile its place in the staged
+    // positions for every tap pair (tap 2j+h of this half-wave; in the last step both half-waves read tap 8).
+    int prow[NB], pcol[NB], padr[NB][5];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int pn = wn * WN + nb * 32 + l31;
       prow[nb] = pn / TW;
       pcol[nb] = pn - prow[nb] * TW;
     }
-    auto enter = [&](const SplitTile &d) {
+    unsigned valid[NB];                 // bit l31: pixel l31 of the block exists (the same in all lanes)
+    float unscale[MB];                  // NP == 2: the power of two that leaves this lane's channel
+    auto enter = [&](const SplitTile &d) __attribute__((always_inline)) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) unscale[mb] = NP == 2 ? p.out_pow2[(d.mt * WGM + wm) * (MB * 32) + mb * 32 + l31] : 1.f;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const int r = d.y0 + prow[nb], di = r / p.Ho, y = r - di * p.Ho;
-        pimg[nb] = d.n0 + di;
-        py[nb] = y;
-        pvalid[nb] = prow[nb] < TH && pimg[nb] < p.N && d.x0 + pcol[nb] < p.Wo;
-        // (a column without a pixel repeats the tile's first one: the statistics' pivot is always a value of the tile)
-        pixoff[nb] = pvalid[nb] ? (di * SH + s * (y - d.y0)) * IWS + s * pcol[nb] : 0;
+        const bool ok = prow[nb] < TH && d.n0 + di < p.N && d.x0 + pcol[nb] < p.Wo;
+        valid[nb] = (unsigned)__ballot(ok);
+        // (a row without a pixel repeats the tile's first one: the statistics' pivot is always a value of the tile)
+        const int at = ok ? (di * SH + s * (y - d.y0)) * IWS + s * pcol[nb] : 0;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+          const int tap = (2 * j + lh < 9) ? 2 * j + lh : 8;
+          padr[nb][j] = (at + (tap / 3) * IWS + (tap % 3)) * 16;
+        }
       }
     };
-    // tap 2j+h of this half-wave as an offset in the staged tile (in the last step both half-waves read tap 8)
-    int toff[5];
+    // The weights come straight from memory (the L1 and L2 hold them) into operand registers: a register set per tap pair,
+    // refilled for the next chunk as soon as the pair's MFMAs are issued, so a load has a whole stage to arrive.  Through LDS
+    // they would double its reads, and LDS gives 64 bytes a cycle: 512 cycles a tap pair for 384 of MFMAs.
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(p.wpk), 0, (int)((unsigned)p.g.mtiles * nchunks * A_STRIDE), 0x00020000);
+    const unsigned aoff = (unsigned)(lh * BM + wm * (MB * 32) + l31) * 16u;
+    uintx4 a[5][NP][MB];
+    auto load_a = [&](int j, unsigned wk) __attribute__((always_inline)) {               // wk: byte offset of the chunk's weights
 #pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      const int tap = (2 * j + lh < 9) ? 2 * j + lh : 8;
-      toff[j] = (tap / 3) * IWS + (tap % 3);
-    }
-    const int arow = (wm * (MB * 32) + l31) * 16;      // byte offset of this lane's weight row within a [BM][8] slab
+      for (int pc = 0; pc < NP; ++pc)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          const int slot = NP == 3 ? pc * 5 + j : j < 4 ? pc * 4 + j : 8 + pc;
+          a[j][pc][mb] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rw, aoff + mb * 512, wk + (unsigned)(slot * BM * 32), 0));
+        }
+    };
+    auto mul = [&](const uintx4 &w, const uintx4 &x, sfloatx16 &c) __attribute__((always_inline)) {
+      if constexpr (NP == 3)
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, w), c, 0, 0, 0);
+      else
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, w), c, 0, 0, 0);
+    };
 
-    // One pipeline stage of the MFMA waves: multiplies the chunk whose weights and bf16 planes are in copy mc.
-    //
-    // The six products of a tap pair run in the order (weight piece, activation piece) = 10 11 20 00 01 02.  Every
-    // operand piece then falls free at least two products (eight MFMAs) before the next tap pair needs it again, so
-    // the next tap pair's pieces are fetched into the same registers: no second set of operand registers.  The ninth
-    // tap's three products (operand slot c with operand slot c) follow in the order 1 0 2, the order their operands
-    // arrive in.  The fences keep the compiler from moving the LDS reads down to their first use.
-    auto stage = [&](int mc) {
-      const char *Ab = As + mc * A_STRIDE + arow;
-      const char *Sb = Ss + (size_t)mc * 3 * PL * 16;
-      auto lda = [&](int pc, int j, int mb) {
-        return *reinterpret_cast<const uintx4 *>(Ab + ((pc * 5 + j) * 2 + lh) * (BM * 16) + mb * 512);
-      };
-      auto ldb = [&](int pc, int j, int nb) {
+    // One pipeline stage of the MFMA waves: multiplies the chunk whose planes are in copy mc; wnext: the next chunk's weights.
+    // Three pieces: the order of products and the ninth tap's pairing of pieces are conv_split_kernel.h's.
+    auto stage3 = [&](auto copy, unsigned wnext) __attribute__((always_inline)) {
+      const char *Sb = Ss + decltype(copy)::value * COPY;
+      uintx4 bv[3][NB];
+      auto fill_b = [&](int pc, int j) __attribute__((always_inline)) {
         // operand slot pc is piece pc, but for the ninth tap, where the half-waves read two different pieces of it
-        const int piece = j < 4 ? pc : kSplitLastX[pc][0] + lh * (kSplitLastX[pc][1] - kSplitLastX[pc][0]);
-        return *reinterpret_cast<const uintx4 *>(Sb + (pixoff[nb] + toff[j]) * 48 + piece * 16);
-      };
-      uintx4 av[3][MB], bv[3][NB];
-      auto fill_a = [&](int pc, int j) {
+        const int plane = (j < 4 ? pc : kSplitLastX[pc][0] + lh * (kSplitLastX[pc][1] - kSplitLastX[pc][0])) * PLANE;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) av[pc][mb] = lda(pc, j, mb);
+        for (int nb = 0; nb < NB; ++nb) bv[pc][nb] = *reinterpret_cast<const uintx4 *>(Sb + padr[nb][j] + plane);
       };
-      auto fill_b = [&](int pc, int j) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) bv[pc][nb] = ldb(pc, j, nb);
-      };
-      // tap pair 0, in the order of first use
-      fill_a(1, 0); fill_b(0, 0); fill_b(1, 0); fill_a(2, 0); fill_a(0, 0); fill_b(2, 0);
+      fill_b(0, 0); fill_b(1, 0); fill_b(2, 0);
 #pragma unroll
       for (int j = 0; j < 5; ++j) {
         __builtin_amdgcn_sched_barrier(0);
@@ -308,101 +378,171 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-              acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[qa][mb]),
-                                                                    __builtin_bit_cast(bf16x8, bv[qb][nb]), acc[mb][nb], 0, 0, 0);
+            for (int nb = 0; nb < NB; ++nb) mul(a[j][qa][mb], bv[qb][nb], acc[mb][nb]);
           __builtin_amdgcn_sched_barrier(0);
           if (j + 1 < 5) {          // the next tap pair's pieces, into the registers that have just fallen free
-            if (q == 1) fill_a(1, j + 1);
-            if (q == 2) fill_a(2, j + 1);
             if (q == 3) fill_b(0, j + 1);
             if (q == 4) fill_b(1, j + 1);
-            if (q == 5) { fill_a(0, j + 1); fill_b(2, j + 1); }
+            if (q == 5) fill_b(2, j + 1);
           }
         }
+        load_a(j, wnext);
       }
     };
-    // the multiplying side leaves a tile (conv_split_kernel.h)
-    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(
-        p.g.ksplit > 1 ? p.split_out : p.out, 0, (int)((unsigned)p.g.ksplit * p.N * p.Cout * HWo * sizeof(float)), 0x00020000);
-    auto leave = [&](const SplitTile &d) {
-      const int m0 = d.mt * BM + wm * (MB * 32);      // first channel of this wave
-      unsigned voff[NB];
+    // Two pieces.  Two sets of activation registers take turns over the four tap pairs, each fetched while the other's twelve
+    // MFMAs run; the ninth tap's have a set of their own and its eight MFMAs wait for the NEXT stage's start (or the tile's
+    // end), where they cover the first fetch after the barrier.  Fetches go one behind each MFMA (sched_group_barrier): in
+    // blocks between the MFMAs they cost a stage 2 400 cycles for 1 792 of MFMAs.
+    uintx4 b2[2][2][NB], b9[2][NB];
+    auto ninth = [&]() __attribute__((always_inline)) {    // w0x0 + w1x0 in one MFMA, w0x1 (+ 0) in the other
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        voff[nb] = (unsigned)(((d.kz * p.N + pimg[nb]) * p.Cout + 4 * lh) * HWo + py[nb] * p.Wo + d.x0 + pcol[nb]) * 4u;
-      // per-channel statistics partial of this pixel tile (as in the fp32-MFMA kernel): every wave sums about the value
-      // of its own first pixel column
-      // (all of it on the vector ALU: the pivot through two lane reads, the half-wave sums through DPP with the
-      // total arriving in the half-wave's upper 16 lanes; LDS permutes would make 64 dependent round trips of it)
-      if (p.stat_partial && p.g.ksplit == 1) {
-        float cnt = 0.f;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) cnt += pvalid[nb] ? 1.f : 0.f;
-        cnt = half32_sum_upper(cnt);
-        StatPart *const rw = red + wn * BM + wm * (MB * 32) + 4 * lh;
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float a0 = acc[mb][0][r];
-            const float p0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, a0), 0));
-            const float p1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, a0), 32));
-            const float pv = lh ? p1 : p0;
-            float s1 = 0.f, s2 = 0.f;
+          for (int nb = 0; nb < NB; ++nb) mul(a[4][q][mb], b9[q][nb], acc[mb][nb]);
+    };
+    auto stage2 = [&](auto copy, unsigned wnow, unsigned wnext, bool owes_ninth) __attribute__((always_inline)) {
+      const char *Sb = Ss + decltype(copy)::value * COPY;
+      auto fill = [&](int j, uintx4 (&bv)[2][NB]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-              const float dv = pvalid[nb] ? acc[mb][nb][r] - pv : 0.f;
-              s1 += dv;
-              s2 += dv * dv;
-            }
-            s1 = half32_sum_upper(s1);
-            s2 = half32_sum_upper(s2);
-            if (l31 == 16) {
-              StatPart sp;
-              sp.pivot = pv; sp.s1 = s1; sp.s2 = s2; sp.n = cnt;
-              rw[mb * 32 + 8 * (r / 4) + (r % 4)] = sp;
-            }
-          }
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            bv[q][nb] = *reinterpret_cast<const uintx4 *>(Sb + padr[nb][j] + q * PLANE);
+      };
+      fill(0, b2[0]);
+      load_a(3, wnow);
+      __builtin_amdgcn_sched_barrier(0);
+      if (owes_ninth) ninth();
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (j < 3) fill(j + 1, b2[(j + 1) & 1]);
+        else fill(4, b9);
+        // the set used last: the ninth tap's for this chunk, else the pair before's for the next
+        if (j == 0) load_a(4, wnow);
+        else load_a(j - 1, wnext);
+        constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 0, 1};
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) mul(a[j][PA[q]][mb], b2[j & 1][PB[q]][nb], acc[mb][nb]);
+        constexpr int N_MFMA = 3 * MB * NB, N_DS = 2 * NB, N_VM = 2 * MB, VM0 = N_MFMA >= N_DS + N_VM ? N_DS : 0;
+#pragma unroll
+        for (int k = 0; k < N_MFMA; ++k) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                // an MFMA,
+          if (k < N_DS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                  // an LDS read,
+          if (k >= VM0 && k < VM0 + N_VM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // a load
+        }
       }
-      const bool whole8 = (p.Cout & 7) == 0;          // then the eight channels of an accumulator row group exist or do not together
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // The multiplying side leaves a tile: statistics partials into red, the tile into Os, accumulators cleared.  Accumulator
+    // register r of lane l holds pixel 8*(r/4) + 4*(l/32) + r%4 of the block, channel l%32.
+    auto leave = [&](const SplitTile &d) __attribute__((always_inline)) {
+      const bool stats = p.stat_partial && p.g.ksplit == 1;
+      const int ch = wm * (MB * 32) + l31;            // this lane's channel of the tile, block 0
+      unsigned mask[NB];                              // bit 8q + e: register 4q + e holds a pixel that exists
+      bool all = true;
+      float cnt = 0.f;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+      for (int nb = 0; nb < NB; ++nb) {
+        mask[nb] = valid[nb] >> (4 * lh);
+        all = all && valid[nb] == 0xffffffffu;
+        cnt += (float)__popc(mask[nb] & 0x0f0f0f0fu);
+      }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int ou = m0 + mb * 32 + 8 * (r / 4) + (r % 4);     // wave-uniform part of the channel
-          const unsigned soff = (unsigned)ou * (unsigned)HWo * 4u;
-          const bool ch_ok = whole8 ? (ou < p.Cout) : (ou + 4 * lh < p.Cout);
+      for (int mb = 0; mb < MB; ++mb) {
+        if constexpr (NP == 2) {                       // the weights' power of two per output channel, taken back (exactly)
+          const float u = unscale[mb];
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            const float v = acc[mb][nb][r];       // (a bit cast applied to the vector element itself reads element 0)
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rout,
-                                                  (pvalid[nb] && ch_ok) ? voff[nb] + soff : kPastBuffer, 0, 0);
+          for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] *= u;
+        }
+        float *const dst = Os + (ch + mb * 32) * OROW + wn * WN + 4 * lh;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            typedef float f4 __attribute__((ext_vector_type(4)));
+            const f4 v = {acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]};
+            *reinterpret_cast<f4 *>(dst + nb * 32 + 8 * q) = v;
           }
+        if (stats) {
+          // sums about the wave's first pixel (register 0 of the lower half-wave); four chains of each
+          const float pv = __shfl(acc[mb][0][0], l31, 64);
+          float s1[4] = {0.f, 0.f, 0.f, 0.f}, s2[4] = {0.f, 0.f, 0.f, 0.f};
+          if (all) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const float dv = acc[mb][nb][r] - pv;
+                s1[r & 3] += dv;
+                s2[r & 3] = fmaf(dv, dv, s2[r & 3]);
+              }
+          } else {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const float dv = (mask[nb] >> (8 * (r / 4) + r % 4) & 1u) ? acc[mb][nb][r] - pv : 0.f;
+                s1[r & 3] += dv;
+                s2[r & 3] = fmaf(dv, dv, s2[r & 3]);
+              }
+          }
+          StatPart sp;
+          sp.pivot = pv;
+          sp.s1 = (s1[0] + s1[1]) + (s1[2] + s1[3]);
+          sp.s2 = (s2[0] + s2[1]) + (s2[2] + s2[3]);
+          sp.s1 += __shfl_xor(sp.s1, 32, 64);
+          sp.s2 += __shfl_xor(sp.s2, 32, 64);
+          sp.n = cnt + __shfl_xor(cnt, 32, 64);
+          if (lh == 0) red[wn * BM + ch + mb * 32] = sp;
         }
 #pragma unroll
-      for (int a = 0; a < MB; ++a)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+          for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
+      }
     };
     int mt = 0, mc = 0;
     SplitTile md = uniform_tile(tiles[0]);
+    auto tile_weights = [&](int t) __attribute__((always_inline)) {              // byte offset of the first chunk's weights of tile t
+      return (unsigned)__builtin_amdgcn_readfirstlane(tiles[t].mt * nchunks + tiles[t].kb) * (unsigned)A_STRIDE;
+    };
+    unsigned wnow = tile_weights(0), wtile = tile_weights(n_mine > 1 ? 1 : 0);       // this chunk's, the next tile's
     enter(md);
+#pragma unroll
+    for (int j = 0; j < (NP == 3 ? 5 : 3); ++j) load_a(j, wnow);
     __syncthreads();                              // stage 0: the loaders fetch chunk 0
     __syncthreads();                              // stage 1: ... and split it
-    for (int i = 2; i <= TC + 1; ++i) {           // stage i: multiplies chunk i-2
-      stage(i & 1);
-      if (++mc == md.nk) {
+    auto multiply = [&](auto copy) __attribute__((always_inline)) {              // stage i: multiplies chunk i-2, whose planes are in copy i & 1
+      const bool last = mc + 1 == md.nk;
+      const unsigned wnext = last ? wtile : wnow + (unsigned)A_STRIDE;
+      if constexpr (NP == 3) stage3(copy, wnext);
+      else stage2(copy, wnow, wnext, mc > 0);
+      wnow = wnext;
+      ++mc;
+      if (last) {
+        if constexpr (NP == 2) ninth();
         leave(md);
         mc = 0;
         if (mt + 1 < n_mine) {
           md = uniform_tile(tiles[++mt]);
+          wtile = tile_weights(mt + 1 < n_mine ? mt + 1 : mt);
           enter(md);
         }
       }
       __syncthreads();
+    };
+    for (int i = 2; i <= TC + 1; i += 2) {
+      multiply(std::integral_constant<int, 0>{});
+      if (i + 1 <= TC + 1) multiply(std::integral_constant<int, 1>{});
     }
   }
 }

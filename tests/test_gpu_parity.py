@@ -525,6 +525,57 @@ def test_split_convolution_is_as_accurate_as_fp32(gpu, monkeypatch):
         assert b <= 2.0 * a + 2e-7, errs
 
 
+@pytest.mark.parametrize("n,h,w_,chans", [(24, 16, 16, (128, 256, 96)), (6, 13, 11, (16, 9, 40)), (9, 7, 7, (64, 500, 512)),
+                                            (40, 2, 2, (32, 260, 64))])
+def test_fp16_pair_is_as_accurate_as_three_bf16_pieces(gpu, monkeypatch, n, h, w_, chans):
+    """Behind a BatchNorm the teacher's convolutions form three products of fp16 pairs instead of six of bf16 triples.  Against
+    the fp64 oracle their root-mean-square error must not be larger: the pair's own error is 2^-24 of a product (rms) and half
+    the accumulator's roundings go.  Gammas, betas and the weights behind them spread over powers of two (channel c's
+    BatchNorm times 2^k, its weights times 2^-k), so that without the per-channel scaling fp16 would overflow or lose them."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+    w = wl.Workload("pair_accuracy", t, s, seed=21)
+    x, tp, sp = w.tensors(random_affine=True)
+    k = np.exp2(np.random.default_rng(5).integers(-18, 19, chans[1])).astype(np.float32)
+    tp[0][1] = tp[0][1] * k
+    tp[0][2] = tp[0][2] * k
+    tp[1][0] = (tp[1][0] / k[None, :, None, None]).astype(np.float32)
+    _, tcache = ob.block_forward(t, [[a.astype(np.float64) for a in lp] for lp in tp], x.astype(np.float64), keep=True)
+    ref = tcache["layers"][1]["z"]
+    xd = torch.from_numpy(x).cuda()
+    errs = {}
+    for f16 in (0, 1):
+        monkeypatch.setenv("PBKD_CONV_F16", str(f16))
+        blk = pb.Block(t, tp, s, sp)
+        td = torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
+        blk.teacher_forward(xd, td)
+        torch.cuda.synchronize()
+        z = blk.get_tensor(pb.TEACHER_ACT, 1, 1, ref.shape).astype(np.float64)
+        errs[f16] = float(np.sqrt(np.mean((z - ref) ** 2) / np.mean(ref ** 2)))
+        blk.close()
+    print(f"[pair accuracy] {chans} rms error of z1: bf16 triples {errs[0]:.3e}, fp16 pairs {errs[1]:.3e}")
+    assert errs[1] <= 1.05 * errs[0] and errs[1] < 2e-6, errs
+
+
+def test_batchnorm_parameters_replaced_rescale_the_layer_behind(gpu):
+    """pbkd_block_set_tensor on a teacher's gamma and beta: the fp16 pairs of the convolution behind are scaled by them."""
+    torch, pb = gpu
+    t, s = wl.Arch(3, 12, 10, 10, wl._convs([12, 20, 17])), wl.Arch(3, 12, 10, 10, wl._dws([12, 20, 17]))
+    x, tp, sp = wl.Workload("rescale", t, s, seed=3).tensors(random_affine=True)
+    blk = pb.Block(t, tp, s, sp)
+    tp[0][1] = tp[0][1] * np.float32(3e7)
+    tp[0][2] = tp[0][2] * np.float32(1e-3)
+    for slot in (1, 2):
+        blk.set_tensor(pb.TEACHER_PARAM, 0, slot, tp[0][slot])
+    t_ref = ob.block_forward(t, tp, x)
+    xd = torch.from_numpy(x).cuda()
+    td = torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
+    blk.teacher_forward(xd, td)
+    torch.cuda.synchronize()
+    assert relerr(td.cpu().numpy(), t_ref) <= ACT_TOL
+    blk.close()
+
+
 def test_zero_loss_when_student_is_the_factored_teacher(gpu):
     torch, pb = gpu
     chans = [6, 8, 5]

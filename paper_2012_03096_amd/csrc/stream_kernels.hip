@@ -171,12 +171,13 @@ DwGeom dw_geom(int N, int Ho, int Wo, int stride, bool backward, int H, int W, b
     g.lds_bytes = 0;
     return g;
   }
-  if (stride == 1 && Wo % 4 == 0 && dw_fits_buffer(N, C, Ho, Wo)) {
-    // register-window kernels: one thread per 2 rows x 4 columns, 256 threads per workgroup.  A thread reads the row
+  if (stride == 1 && Wo >= 4 && dw_fits_buffer(N, C, Ho, Wo)) {
+    // register-window kernels, any width from 4 on (the LDS halo-tile kernels, which maps of other widths ran before, took
+    // 21 us forward and 33 us backward for 512 channels on 14x14 maps, batch 32: these 10 and 13.5): one thread per 2 rows x 4 columns, 256 threads per workgroup.  A thread reads the row
     // above and the row below its own as well, so every input row is read twice; on maps large enough to be bound by
     // bandwidth rather than latency a thread takes 4 rows (every row read 1.5 times)
-    if (Ho % 4 == 0 && (long long)N * (Ho / 4) * (Wo / 4) >= 32768) g.rows = 4;
-    const long long strips = (long long)N * cdiv(Ho, g.rows) * (Wo / 4);
+    if (Ho % 4 == 0 && (long long)N * (Ho / 4) * cdiv(Wo, 4) >= 32768) g.rows = 4;
+    const long long strips = (long long)N * cdiv(Ho, g.rows) * cdiv(Wo, 4);
     g.fast = 1;
     g.lTW = g.lTH = 0;
     g.nimg = 1;
@@ -266,17 +267,19 @@ __global__ __launch_bounds__(256) void dw_fwd_kernel(DwFwdArgs p) {
 }
 
 
-// ---- stride 1, width a multiple of 4: no LDS.  Workgroup b of a channel takes the strips of logical block
+// ---- stride 1, width at least 4: no LDS.  Workgroup b of a channel takes the strips of logical block
 // xcd_contiguous(b): neighbouring row bands, which share a halo row, then run on one die and meet in its L2.
 // A thread owns 2 (or 4) rows x 4 columns of one (image, channel)
 // plane and reads the window around them straight from global memory (dw_load_row: one 16-byte load and two edge
 // loads per row; neighbouring threads' windows overlap in L1), applying the producer's BatchNorm + ReLU to what it
 // loads.  Padding stays an exact zero.
-// strip index -> (image, first row, first column); false past the end
+// strip index -> (image, first row, first column); false past the end.  Where the width is no multiple of 4 the last strip
+// of a row starts at column W-4 and shares `dup` columns with the one before it: both store the same values there, and
+// sums leave the second one's out.  (Its 16-byte accesses are then 4-byte aligned, which buffer instructions allow.)
 // (the launch checks that the strips are fewer than 2^31: 32-bit divisions, a fifth of the kernel's instructions otherwise)
 template <int R>
-__device__ __forceinline__ bool dw_strip(unsigned e, int N, int H, int W, int &n, int &y0, int &x) {
-  const unsigned W4 = (unsigned)W >> 2, HG = (unsigned)(H + R - 1) / R;
+__device__ __forceinline__ bool dw_strip(unsigned e, int N, int H, int W, int &n, int &y0, int &x, int *dup = nullptr) {
+  const unsigned W4 = (unsigned)(W + 3) >> 2, HG = (unsigned)(H + R - 1) / R;
   const unsigned total = (unsigned)N * HG * W4;
   const bool active = e < total;
   if (!active) e = total - 1;
@@ -285,7 +288,8 @@ __device__ __forceinline__ bool dw_strip(unsigned e, int N, int H, int W, int &n
   const unsigned nn = q / HG;
   y0 = R * (int)(q - nn * HG);
   n = (int)nn;
-  x = 4 * (int)xs;
+  x = 4 * (int)xs < W - 4 ? 4 * (int)xs : W - 4;
+  if (dup) *dup = 4 * (int)xs - x;
   return active;
 }
 
@@ -340,9 +344,11 @@ static bool aligned16(const void *q) { return (reinterpret_cast<uintptr_t>(q) & 
 // of a 16-lane row when the strips of an image row fill such rows exactly, else from the neighbouring lanes of the whole
 // wave (measured at 224 x 224 x 64 against two more loads per row: forward 183 -> 176 us, backward 268 -> 239 us).
 // PBKD_DW_EDGE=0 forces the loads (a measurement aid).
+// Where the last strip overlaps its neighbour (W % 4 != 0) the lanes do not hold neighbouring columns: two more loads.
 static int dw_edge_mode(int W) {
   const int w4 = W / 4;
-  if (W % 4 == 0 && w4 <= 16 && (w4 & (w4 - 1)) == 0) return 1;
+  if (W % 4) return 0;
+  if (w4 <= 16 && (w4 & (w4 - 1)) == 0) return 1;
   if (const char *e = std::getenv("PBKD_DW_EDGE")) return std::atoi(e) == 0 ? 0 : 2;
   return 2;
 }
@@ -554,7 +560,7 @@ hipError_t launch_dw_fwd(const DwFwdArgs &a, hipStream_t s) {
     return hipGetLastError();
   }
   if (a.g.fast) {
-    if (a.stride != 1 || a.W % 4 || a.H != a.Ho || a.W != a.Wo || !aligned16(a.in) || !aligned16(a.out) || !dw_fits_buffer(a.N, a.C, a.H, a.W))
+    if (a.stride != 1 || a.W < 4 || a.H != a.Ho || a.W != a.Wo || !aligned16(a.in) || !aligned16(a.out) || !dw_fits_buffer(a.N, a.C, a.H, a.W))
       return hipErrorInvalidValue;
     const dim3 grid(a.g.n_tiles, a.C);
     const bool bn = a.in_scale || a.pend.partial;
@@ -693,7 +699,7 @@ __global__ __launch_bounds__(256) void dw_bwd_kernel(DwBwdArgs p) {
 }
 
 
-// Fused backward for stride 1 and width a multiple of 4, register windows as in the forward kernel: the
+// Fused backward for stride 1 and width at least 4, register windows as in the forward kernel: the
 // thread's 2 x 4 positions take the weight gradient from (du centre) x (input window), the data gradient
 // from (du window) x D, the previous layer's ReLU decision from the transformed centre, and the
 // BatchNorm-backward sums from the raw centre.
@@ -702,8 +708,8 @@ __global__ __launch_bounds__(256) void dw_bwd_fast_kernel(DwBwdArgs p) {
   __shared__ float red[4][11];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = blockIdx.y;
-  int n, y0, x;
-  const bool active = dw_strip<R>((unsigned)xcd_contiguous(blockIdx.x, gridDim.x) * 256u + tid, p.N, p.H, p.W, n, y0, x);
+  int n, y0, x, dup;
+  const bool active = dw_strip<R>((unsigned)xcd_contiguous(blockIdx.x, gridDim.x) * 256u + tid, p.N, p.H, p.W, n, y0, x, &dup);
   const float sc = FIRST ? 1.f : p.in_scale[c], sh = FIRST ? 0.f : p.in_shift[c];
   float w[9];
 #pragma unroll
@@ -729,7 +735,7 @@ __global__ __launch_bounds__(256) void dw_bwd_fast_kernel(DwBwdArgs p) {
   for (int i = 0; i < R; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float g = d[i + 1][j + 1];
+      const float g = (EDGE == 0 && j < dup) ? 0.f : d[i + 1][j + 1];      // (only EDGE 0 has overlapping strips)
 #pragma unroll
       for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
@@ -754,8 +760,9 @@ __global__ __launch_bounds__(256) void dw_bwd_fast_kernel(DwBwdArgs p) {
         // (a row that does not exist has zeros in a: nothing passes the ReLU's mask)
         const float g = (a[i + 1][j + 1] > 0.f) ? da : 0.f;
         o[j] = __builtin_bit_cast(unsigned, g);
-        acc[9] += g;
-        acc[10] += g * ((rawc[i][j] - mean) * rstd);
+        const float gs = (EDGE == 0 && j < dup) ? 0.f : g;
+        acc[9] += gs;
+        acc[10] += gs * ((rawc[i][j] - mean) * rstd);
       }
       __builtin_amdgcn_raw_buffer_store_b128(o, rg, rowok ? pl + (unsigned)((y0 + i) * p.W + x) * 4u : kPastBuffer, 0, 0);
     }
@@ -791,7 +798,7 @@ hipError_t launch_dw_bwd(const DwBwdArgs &a, hipStream_t s) {
     return hipGetLastError();
   }
   if (a.g.fast) {
-    if (a.stride != 1 || a.W % 4 || a.H != a.Ho || a.W != a.Wo || !aligned16(a.in) || !aligned16(a.du) ||
+    if (a.stride != 1 || a.W < 4 || a.H != a.Ho || a.W != a.Wo || !aligned16(a.in) || !aligned16(a.du) ||
         (!a.first_layer && !aligned16(a.gout)) || !dw_fits_buffer(a.N, a.C, a.H, a.W))
       return hipErrorInvalidValue;
     const dim3 grid(a.g.n_tiles, a.C);

@@ -474,6 +474,17 @@ def test_split_convolution_on_any_map(gpu, n, chans, h, w_, strides):
     blk.close()
 
 
+@pytest.mark.parametrize("n,c,h,w_", [(5, 9, 6, 5), (3, 7, 5, 6), (4, 6, 3, 7), (2, 5, 14, 14), (7, 4, 27, 23), (1, 3, 1, 9), (3, 4, 9, 67),
+                                      (130, 2, 128, 33)])
+def test_depthwise_on_widths_that_are_no_multiple_of_four(gpu, n, c, h, w_):
+    """Forward and backward of two depthwise-separable layers where the last four-column strip of a row overlaps the one
+    before it by one, two or three columns (and on 33x128 maps with four-row strips): gradients must count those once."""
+    t = wl.Arch(n, c, h, w_, wl._convs([c, c + 1, c]))
+    s = wl.Arch(n, c, h, w_, wl._dws([c, c + 1, c]))
+    fails = run_parity(gpu, wl.Workload("dw_any_width", t, s, seed=13), steps=2)
+    assert not fails, fails
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

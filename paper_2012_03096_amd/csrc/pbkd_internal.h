@@ -397,7 +397,7 @@ struct WgradArgs {
   float *partial;
   int N, Co, Ci, HW;
   WgradGeom g;
-  int W;                   // g.vec == 3 only: image width (H = HW / W)
+  int W;                   // g.vec == 3 and 4 only: image width (H = HW / W)
 };
 hipError_t launch_pw_wgrad(const WgradArgs &a, hipStream_t s);
 hipError_t init_pw_wgrad_attributes();

@@ -485,6 +485,17 @@ def test_depthwise_on_widths_that_are_no_multiple_of_four(gpu, n, c, h, w_):
     assert not fails, fails
 
 
+@pytest.mark.parametrize("n,h,w_,chans", [(3, 2, 2, (5, 70, 6)), (7, 1, 5, (9, 8, 66)), (2, 14, 14, (40, 33, 64)), (5, 3, 3, (20, 129, 5)),
+                                          (4, 23, 27, (7, 66, 9)), (2, 3, 1, (6, 5, 4)), (1, 1, 4, (3, 5, 7)), (300, 2, 3, (8, 9, 10))])
+def test_pointwise_weight_gradient_on_any_map(gpu, n, h, w_, chans):
+    """Pointwise weight gradients where an image is no whole number of 32-pixel chunks: its last group of four pixels
+    overlaps the one before it by zero to three, a chunk spans several images (4, 5, 6 and 9 pixels), and maps of three
+    pixels keep the kernel that loads single values."""
+    t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+    fails = run_parity(gpu, wl.Workload("wgrad_any_map", t, s, seed=17), steps=2)
+    assert not fails, fails
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

@@ -426,8 +426,18 @@ struct BnScaled {
 };
 hipError_t launch_bn_finalize(const BnPending &b, int C, hipStream_t s, const BnScaled &scaled = BnScaled{});
 // inference mode: scale = gamma/sqrt(rvar+eps), shift = beta - rmean*scale (mean <- rmean, rstd <- 1/sqrt(rvar+eps))
-hipError_t launch_bn_running(const float *gamma, const float *beta, const float *rmean, const float *rvar, float eps,
-                             float *mean, float *rstd, float *scale, float *shift, int C, hipStream_t s);
+struct BnRunning {
+  const float *gamma, *beta, *rmean, *rvar;
+  float *mean, *rstd, *scale, *shift;
+  int C;
+  float eps;
+};
+constexpr int kBnRunningMax = 32;   // layers of one launch: 72 bytes of kernel arguments each
+struct BnRunningArgs {
+  BnRunning layer[kBnRunningMax];
+  int n;
+};
+hipError_t launch_bn_running(const BnRunningArgs &a, hipStream_t s);
 
 // ------------------------------------------------------------------ depthwise 3x3
 struct DwGeom {

@@ -586,19 +586,30 @@ bool head_defers(const Net &net) {
   return defer_ok(net.L.back(), nb) && (net.shortcut != 1 || defer_ok(net.sc, nb));
 }
 
+// Inference mode: the scale and shift of every layer of `nets`, from the running pairs, before any of them runs forward.
+pbkd_status finish_running(const std::vector<Net *> &nets, hipStream_t st, Prof *pf) {
+  BnRunningArgs a{};
+  auto flush = [&]() -> pbkd_status {
+    if (a.n > 0) LAUNCH(pf, KK_BN_FINALIZE, st, launch_bn_running(a, st));
+    a.n = 0;
+    return PBKD_OK;
+  };
+  auto add = [&](const Net &net, const LayerRT &r) -> pbkd_status {
+    a.layer[a.n++] = BnRunning{r.gamma, r.beta, r.rmean, r.rvar, r.mean, r.rstd, r.scale, r.shift, r.cout, net.eps};
+    return a.n == kBnRunningMax ? flush() : PBKD_OK;
+  };
+  for (const Net *net : nets) {
+    for (const auto &r : net->L) { pbkd_status e = add(*net, r); if (e != PBKD_OK) return e; }
+    if (net->shortcut == 1) { pbkd_status e = add(*net, net->sc); if (e != PBKD_OK) return e; }
+  }
+  return flush();
+}
+
 pbkd_status forward_net(Net &net, const float *x, hipStream_t st, Prof *pf) {
   const int N = net.n;
   const float *in = x, *in_scale = nullptr, *in_shift = nullptr;
   BnPending pend{};       // statistics of `in` that no kernel has finished yet
-  const bool running = net.use_running;
-  if (running) {          // every layer's scale and shift follow from its running pair before anything runs
-    auto fixed = [&](LayerRT &r) -> pbkd_status {
-      LAUNCH(pf, KK_BN_FINALIZE, st, launch_bn_running(r.gamma, r.beta, r.rmean, r.rvar, net.eps, r.mean, r.rstd, r.scale, r.shift, r.cout, st));
-      return PBKD_OK;
-    };
-    for (auto &r : net.L) { pbkd_status e = fixed(r); if (e != PBKD_OK) return e; }
-    if (net.shortcut == 1) { pbkd_status e = fixed(net.sc); if (e != PBKD_OK) return e; }
-  }
+  const bool running = net.use_running;    // every layer's scale and shift are there already (finish_running)
   auto pointwise = [&](LayerRT &r, const float *src, int hin, int win, int stride) -> pbkd_status {
     PwArgs pa{};
     pa.in = src; pa.wpk = r.wpk; pa.out = r.z; pa.stat_partial = running ? nullptr : r.stat;
@@ -1461,6 +1472,12 @@ pbkd_status pbkd_network_forward(int n_blocks, pbkd_block_t *const *blocks, cons
     }
   }
   const float *in = x_dev;
+  if (bn_mode == 1) {
+    std::vector<Net *> nets;
+    for (int k = 0; k < n_blocks; ++k) nets.push_back(use_student[k] ? &blocks[k]->s : &blocks[k]->t);
+    const pbkd_status e = finish_running(nets, static_cast<hipStream_t>(hip_stream), &blocks[0]->prof);
+    if (e != PBKD_OK) return e;
+  }
   for (int k = 0; k < n_blocks; ++k) {
     if (misaligned16(outs_dev[k])) return fail(PBKD_EINVAL, "device tensors must be 16-byte aligned");
     const pbkd_status e = net_forward_impl(blocks[k], use_student[k] ? blocks[k]->s : blocks[k]->t, in, outs_dev[k],

@@ -123,25 +123,24 @@ hipError_t launch_bn_finalize(const BnPending &b, int C, hipStream_t s, const Bn
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void bn_running_kernel(const float *gamma, const float *beta, const float *rmean,
-                                                         const float *rvar, float eps, float *mean, float *rstd,
-                                                         float *scale, float *shift, int C) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= C) return;
-  const double mu = (double)rmean[c];
-  const double r = 1.0 / sqrt((double)rvar[c] + (double)eps);
-  const double sc = (double)gamma[c] * r;
-  mean[c] = (float)mu;
-  rstd[c] = (float)r;
-  scale[c] = (float)sc;
-  shift[c] = (float)((double)beta[c] - mu * sc);
+// All layers of a network in one launch, a workgroup per layer: a few hundred channels each, so a launch per layer was
+// nothing but launches (15 of them, 2.3 us each, in a forward pass of 160 us for one image).
+__global__ __launch_bounds__(256) void bn_running_kernel(BnRunningArgs a) {
+  const BnRunning &r = a.layer[blockIdx.x];
+  for (int c = threadIdx.x; c < r.C; c += 256) {
+    const double mu = (double)r.rmean[c];
+    const double q = 1.0 / sqrt((double)r.rvar[c] + (double)r.eps);
+    const double sc = (double)r.gamma[c] * q;
+    r.mean[c] = (float)mu;
+    r.rstd[c] = (float)q;
+    r.scale[c] = (float)sc;
+    r.shift[c] = (float)((double)r.beta[c] - mu * sc);
+  }
 }
 
-hipError_t launch_bn_running(const float *gamma, const float *beta, const float *rmean, const float *rvar, float eps,
-                             float *mean, float *rstd, float *scale, float *shift, int C, hipStream_t s) {
-  if (C < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bn_running_kernel, dim3(cdiv(C, 256)), dim3(256), 0, s, gamma, beta, rmean, rvar, eps, mean, rstd,
-                     scale, shift, C);
+hipError_t launch_bn_running(const BnRunningArgs &a, hipStream_t s) {
+  if (a.n < 1 || a.n > kBnRunningMax) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(bn_running_kernel, dim3(a.n), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -171,10 +171,11 @@ DwGeom dw_geom(int N, int Ho, int Wo, int stride, bool backward, int H, int W, b
     return g;
   }
   if (stride == 1 && Wo >= 4 && dw_fits_buffer(N, C, Ho, Wo)) {
-    // register-window kernels, any width from 4 on (the LDS halo-tile kernels, which maps of other widths ran before, took
-    // 21 us forward and 33 us backward for 512 channels on 14x14 maps, batch 32: these 10 and 13.5): one thread per 2 rows x 4 columns, 256 threads per workgroup.  A thread reads the row
-    // above and the row below its own as well, so every input row is read twice; on maps large enough to be bound by
-    // bandwidth rather than latency a thread takes 4 rows (every row read 1.5 times)
+    // register-window kernels, any width from 4 on: one thread per 2 rows x 4 columns, 256 threads per workgroup.  (The LDS
+    // halo-tile kernels, which widths that are no multiple of 4 ran before, took 21 us forward and 33 us backward for 512
+    // channels on 14x14 maps, batch 32: these 10 and 13.5.)  A thread reads the row above and the row below its own as
+    // well, so every input row is read twice; on maps large enough to be bound by bandwidth rather than latency a thread
+    // takes 4 rows (every row read 1.5 times)
     if (Ho % 4 == 0 && (long long)N * (Ho / 4) * cdiv(Wo, 4) >= 32768) g.rows = 4;
     const long long strips = (long long)N * cdiv(Ho, g.rows) * cdiv(Wo, 4);
     g.fast = 1;

@@ -40,31 +40,15 @@ if ROOT not in sys.path:
 
 MFMA_F32_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
 MFMA_BF16_PEAK_TFLOPS = 2500.0    # MI355X dense bf16 matrix peak
-# The teacher's 3x3 convolutions form every fp32 product from MFMA products of split operands (fp32 accumulation): six of
-# bf16 triples in a block's first layer, three of fp16 pairs behind a BatchNorm (same matrix peak).  Their ceiling in
-# fp32-equivalent flops is the peak over the products, averaged over the layers by their flops.
+# The teacher's 3x3 convolutions form every fp32 product from six bf16 MFMA products of operands split three ways (fp32
+# accumulation): their ceiling in fp32-equivalent flops is a sixth of the bf16 peak.
 SPLIT_PRODUCTS = 6
-PAIR_PRODUCTS = 3
+MFMA_SPLIT_PEAK_TFLOPS = round(MFMA_BF16_PEAK_TFLOPS / SPLIT_PRODUCTS, 1)
 
 
 def conv_split_in_use():
     """The library's rule for the frozen teacher's 3x3 convolutions: the bf16-split kernel unless PBKD_CONV_SPLIT=0."""
     return os.environ.get("PBKD_CONV_SPLIT", "") != "0"
-
-
-def split_products(w):
-    """Mean number of MFMA products per fp32 product over the teacher's 3x3 convolutions (those with more than three input
-    channels: the others run a kernel of their own)."""
-    from paper_2012_03096_amd import workloads as wl
-    pairs = os.environ.get("PBKD_CONV_F16", "") != "0"
-    total = products = 0
-    for l, ((ci, hi, wi, co, ho, wo), layer) in enumerate(zip(wl.layer_shapes(w.teacher), w.teacher.layers)):
-        if l == 0 and ci <= 3:
-            continue
-        flops = ci * co * ho * wo
-        total += flops
-        products += flops * (PAIR_PRODUCTS if l > 0 and ci > 8 and pairs else SPLIT_PRODUCTS)
-    return products / total if total else SPLIT_PRODUCTS
 
 
 HBM_PEAK_GBS = 8000.0
@@ -318,18 +302,16 @@ def mfma_roofline(w, roof, region_note):
            "flops_per_launch": rec["flops_per_step"] // lps, "flops_per_step": rec["flops_per_step"],
            "algorithmic_bytes_per_launch": rec["algorithmic_bytes_per_step"] // lps, "region": region_note}
     if conv_split_in_use():
-        # `achieved` stays the convolution's own (fp32) flops over its time; the peak is the 16-bit one over the products
-        # each of them costs.  The same rate against the fp32 matrix peak is given beside it.
-        products = split_products(w)
-        peak = round(MFMA_BF16_PEAK_TFLOPS / products, 1)
-        out.update({"kernel": "pbkd::conv_rows_kernel / conv_split_kernel (3x3 implicit GEMM, fp32 operands split into two "
-                              "fp16 or three bf16 terms, three or six v_mfma_f32_32x32x16 products per fp32 product, "
-                              "fp32 accumulation)",
-                    "peak": peak, "frac": round(rec["TFLOPps"] / peak, 4),
-                    "peak_is": "dense 16-bit MFMA peak %.0f TFLOP/s / %.2f products per fp32 product" % (MFMA_BF16_PEAK_TFLOPS, products),
+        # `achieved` stays the convolution's own (fp32) flops over its time; the peak is the bf16 one over the six bf16
+        # products each of them costs.  The same rate against the fp32 matrix peak is given beside it.
+        out.update({"kernel": "pbkd::conv_split_kernel, on maps without aligned rows pbkd::conv_rows_kernel (3x3 implicit GEMM, "
+                              "fp32 operands split into three bf16 terms, six v_mfma_f32_32x32x16_bf16 products per fp32 "
+                              "product, fp32 accumulation)",
+                    "peak": MFMA_SPLIT_PEAK_TFLOPS, "frac": round(rec["TFLOPps"] / MFMA_SPLIT_PEAK_TFLOPS, 4),
+                    "peak_is": "dense bf16 MFMA peak %.0f TFLOP/s / %d bf16 products per fp32 product" % (MFMA_BF16_PEAK_TFLOPS, SPLIT_PRODUCTS),
                     "frac_of_fp32_mfma_peak": rec["frac_of_mfma_peak"],
-                    "bf16_TFLOPps_issued": round(rec["TFLOPps"] * products, 1),
-                    "traffic": measured_traffic(w.name, "conv_rows_kernel") or measured_traffic(w.name, "conv_split_kernel")})
+                    "bf16_TFLOPps_issued": round(rec["TFLOPps"] * SPLIT_PRODUCTS, 1),
+                    "traffic": measured_traffic(w.name, "conv_split_kernel")})
     return out
 
 

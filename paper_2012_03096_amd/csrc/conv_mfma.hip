@@ -96,7 +96,6 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
     if (want > 1) g.ksplit = (int)want;
   }
   g.rows = false;
-  g.pieces = 3;
   g.TW = g.TH = g.SH = 0;
   g.stat_parts = g.n_ptiles;
   g.kchunks = cdiv(g.nchunks, g.ksplit);
@@ -132,10 +131,9 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
 // Tiles of stacked rows (conv_rows_kernel.h).  Every (workgroup tile, columns per tile, K split) is priced in shader
 // cycles: rounds of 256 workgroups x (chunks x stage + tile end), stage and tile end as measured per workgroup tile, plus
 // the kernel that adds up a K split; the cheapest wins.
-bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, int pieces, ConvGeom &best) {
+bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGeom &best) {
   static const int kWGN[4] = {2, 4, 4, 2};
-  static const double kStages[2][4] = {{2650, 2650, 2350, 1500}, {4300, 4300, 2700, 1800}}, kEnd[4] = {8000, 8000, 5000, 3500};
-  const double *const kStage = kStages[pieces - 2];
+  static const double kStage[4] = {4300, 4300, 2700, 1800}, kEnd[4] = {8000, 8000, 5000, 3500};
   const long long rows = (long long)N * Ho;
   const double out_bytes = 4.0 * N * Cout * Ho * Wo;
   int only = -1;
@@ -157,7 +155,6 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, int pi
       g.mtiles = cdiv(Cout, g.bm);
       g.nchunks = cdiv(Cin, KC9);
       g.split = g.rows = true;
-      g.pieces = pieces;
       g.TW = tw;
       g.tiles_x = cdiv(Wo, g.TW);
       g.SH = stride * (Ho - 1) + 3;
@@ -177,7 +174,7 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, int pi
         while (g.IWS % 8 != g.TW % 8 && (g.IWS + g.TW) % 8 != 0) ++g.IWS;
       if (g.IH * g.IWS >= conv_rows_positions(slots)) g.IWS = g.IW;
       g.PL = g.IH * g.IWS;
-      g.lds_bytes = conv_rows_lds_bytes(g.bm, BN, kWGN[tile], slots, pieces);
+      g.lds_bytes = conv_rows_lds_bytes(g.bm, BN, kWGN[tile], slots);
       if (g.lds_bytes > (size_t)MAX_LDS) continue;
       const long long tiles_r = (rows + g.TH - 1) / g.TH;
       if (tiles_r * g.tiles_x * g.mtiles > 0x7ffffff) continue;

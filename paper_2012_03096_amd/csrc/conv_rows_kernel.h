@@ -1,15 +1,5 @@
-// Device code of the split 3x3 convolution for maps of any width and any alignment (pipeline and MFMA side:
-// conv_split_kernel.h).  It differs in what a tile is, in how the activations arrive, and (NP = 2) in the arithmetic.
-//
-// NP = 3: three bf16 pieces and six products, conv_split_kernel.h.  NP = 2: two fp16 pieces, x = x0 + x1 to within
-// 2^-22 |x| (2^-24 rms), and the three products w1x0 + w0x0 + w0x1: half the MFMAs.  fp16's range is the condition: it is
-// taken only where the input is another layer's BatchNorm + ReLU over the batch, which bounds channel c by
-// |gamma_c| sqrt(N H W) + |beta_c|.  A power of two per input channel brings that bound (with margin) below 2^15, its
-// inverse goes into the channel's weights, and a power of two per output channel brings its largest weight to 2^14; the
-// epilogue takes the latter back.  All of these are exact, and what fp16's smallest step drops is below 2^-39 of a
-// channel's largest weight and 2^-28 of a standard deviation.  The split's own error is larger than that of the bf16
-// pieces (2^-24 against 2^-27 rms of a product), but half the accumulator roundings go with the three products, and they
-// are the larger part from K = 80 on: the error of z against fp64 is smaller in total (test_fp16_pair_...).
+// Device code of the split 3x3 convolution for maps of any width and any alignment (arithmetic, pipeline and MFMA side:
+// conv_split_kernel.h).  It differs in what a tile is and in how the activations arrive.
 //
 // A tile is TH output rows x TW output columns, neither a power of two, out of the STACK of all images' rows: row R of
 // the stack is row R % Ho of image R / Ho, so a tile runs on from one image into the next and only the last tile of the
@@ -23,12 +13,9 @@
 // multiple of 4).  The channel goes into the scalar offset, so a load costs no vector instruction beyond itself.  The weights
 // go from memory into the MFMA waves' operand registers, and a finished tile leaves through LDS and the loader waves.
 //
-// Bound by the MFMA waves' stage, 2 650 cycles for 1 792 of MFMAs with two pieces (operand fetches and the loader wave beside
-// them on the SIMD 450, the barrier 300; in-kernel clock stamps), on maps of one round of tiles by start-up and last stores,
-// on 224x224 maps by the loads.  Measured: against the fp32-MFMA kernel that unaligned maps ran before, 512 -> 512 channels
-// at 14x14, batch 32, 282 -> 144 us (three pieces, the block's input) and 86 us (two); 67 -> 100 and 100 -> 67 at 27x23, batch
-// 77, 169 -> 54 and 44 us.  Two pieces against the aligned bf16 kernel: 256 -> 256 at 56x56, batch 32, 610 -> 415 us; 64 -> 64
-// at 224x224 575 -> 420; 128 -> 128 at 16x16, batch 128, 46 -> 31.
+// Bound by the MFMA waves' stage, on maps of one round of tiles by start-up and last stores, on 224x224 maps by the loads.
+// Measured against the fp32-MFMA kernel that unaligned maps ran before: 512 -> 512 channels at 14x14, batch 32, 282 -> 144 us;
+// 67 -> 100 and 100 -> 67 at 27x23, batch 77, 169 -> 54 us.
 #pragma once
 #include <type_traits>
 
@@ -36,18 +23,18 @@
 
 namespace pbkd {
 
-template <int WGM, int MB, int NB, int BSLOTS, int NP, bool VEC>
+template <int WGM, int MB, int NB, int BSLOTS, bool VEC>
 __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
   constexpr int WGN = 4 / WGM;
   constexpr int BM = WGM * MB * 32;     // output channels per workgroup
   constexpr int WN = NB * 32;           // pixels per wave
-  constexpr int A_STRIDE = conv_rows_a_stride(BM, NP);
+  constexpr int A_STRIDE = conv_split_a_stride(BM);
   extern __shared__ float smem[];
   constexpr int BN = WGN * WN;          // pixels per workgroup
   constexpr int CAP = conv_rows_positions(BSLOTS);         // staged positions a plane has room for; the last is never read
-  constexpr int PLANE = CAP * 16, COPY = NP * PLANE;       // bytes of a piece's plane, of a copy of all pieces
+  constexpr int PLANE = CAP * 16, COPY = 3 * PLANE;        // bytes of a piece's plane, of a copy of all pieces
   constexpr int OROW = BN + 4;                             // floats of a channel's row of the finished tile
-  char *const Ss = reinterpret_cast<char *>(smem);         // [2][NP pieces][CAP][8 channels of bf16 or fp16]
+  char *const Ss = reinterpret_cast<char *>(smem);         // [2][3 pieces][CAP][8 channels of bf16]
   float *const Os = reinterpret_cast<float *>(Ss + 2 * COPY);                      // [BM][OROW]: a finished tile
   StatPart *const red = reinterpret_cast<StatPart *>(Os + BM * OROW);              // [WGN][BM]
   SplitTile *const tiles = reinterpret_cast<SplitTile *>(red + WGN * BM);          // [kSplitMaxTiles]
@@ -107,14 +94,13 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
     // outside the image are zeros: they load the tensor's first value and are clamped to zero, so every load is in bounds)
     unsigned goff[BSLOTS];
     float hi[BSLOTS];                   // what a position's value is clamped to from above: zero where there is none
-    constexpr float kMost = NP == 3 ? __builtin_inff() : 65504.f;   // (two pieces: fp16's largest value; the scaling keeps far below)
     auto enter = [&](const SplitTile &d) __attribute__((always_inline)) {
 #pragma unroll
       for (int sl = 0; sl < BSLOTS; ++sl) {
         const int V = d.n0 * SH + d.y0 * s + srow[sl];
         const int n = V / SH, y = V - n * SH - 1, x = d.x0 * s - 1 + scol[sl];
         const bool ok = srow[sl] >= 0 && n < p.N && y >= 0 && y < p.H && x >= 0 && x < p.W;
-        hi[sl] = ok ? kMost : 0.f;
+        hi[sl] = ok ? __builtin_inff() : 0.f;
         goff[sl] = ok ? ((unsigned)n * p.Cin * HW + (unsigned)(y * p.W + x)) * 4u : 0u;
       }
     };
@@ -134,7 +120,7 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
     };
     // the producing layer's scale and shift for a chunk's channels, through the scalar cache (the constant address
     // space: an earlier kernel wrote them): two loads of eight
-    const bool bn = NP == 2 || p.in_scale != nullptr;
+    const bool bn = p.in_scale != nullptr;
     const float lo = bn ? 0.f : -__builtin_inff();             // ReLU only where there is a BatchNorm to apply
     typedef float Floats8 __attribute__((ext_vector_type(8), aligned(4)));
     typedef const Floats8 __attribute__((address_space(4))) *ConstFloats8;
@@ -162,22 +148,21 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
       }
 #pragma unroll
       for (int sl = 0; sl < BSLOTS; ++sl) {
-        uintx4 pp[NP];
+        uintx4 pp[3];
         const float least = most[sl] > 0.f ? lo : 0.f;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {              // channels 2t, 2t+1
           float x[2];
 #pragma unroll
           for (int e = 0; e < 2; ++e)              // BatchNorm, then ReLU and the halo's zeros in one step
-            x[e] = __builtin_amdgcn_fmed3f(fmaf(raw[sl][2 * t + e], v.sc[2 * t + e], shv[2 * t + e]), NP == 2 ? 0.f : least, most[sl]);
-          unsigned q[NP];
-          if constexpr (NP == 3) split3_bf16(x[0], x[1], q);
-          else split2_f16(x[0], x[1], q);
+            x[e] = __builtin_amdgcn_fmed3f(fmaf(raw[sl][2 * t + e], v.sc[2 * t + e], shv[2 * t + e]), least, most[sl]);
+          unsigned q[3];
+          split3_bf16(x[0], x[1], q);
 #pragma unroll
-          for (int pc = 0; pc < NP; ++pc) pp[pc][t] = q[pc];
+          for (int pc = 0; pc < 3; ++pc) pp[pc][t] = q[pc];
         }
 #pragma unroll
-        for (int pc = 0; pc < NP; ++pc) *reinterpret_cast<uintx4 *>(Sd + loff[sl] + pc * PLANE) = pp[pc];
+        for (int pc = 0; pc < 3; ++pc) *reinterpret_cast<uintx4 *>(Sd + loff[sl] + pc * PLANE) = pp[pc];
       }
     };
     // Stage i splits chunk i-1, then issues the loads of chunk i+1's activations into the registers it has just emptied: they
@@ -315,10 +300,7 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
       pcol[nb] = pn - prow[nb] * TW;
     }
     unsigned valid[NB];                 // bit l31: pixel l31 of the block exists (the same in all lanes)
-    float unscale[MB];                  // NP == 2: the power of two that leaves this lane's channel
     auto enter = [&](const SplitTile &d) __attribute__((always_inline)) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) unscale[mb] = NP == 2 ? p.out_pow2[(d.mt * WGM + wm) * (MB * 32) + mb * 32 + l31] : 1.f;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const int r = d.y0 + prow[nb], di = r / p.Ho, y = r - di * p.Ho;
@@ -339,26 +321,21 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(p.wpk), 0, (int)((unsigned)p.g.mtiles * nchunks * A_STRIDE), 0x00020000);
     const unsigned aoff = (unsigned)(lh * BM + wm * (MB * 32) + l31) * 16u;
-    uintx4 a[5][NP][MB];
+    uintx4 a[5][3][MB];
     auto load_a = [&](int j, unsigned wk) __attribute__((always_inline)) {               // wk: byte offset of the chunk's weights
 #pragma unroll
-      for (int pc = 0; pc < NP; ++pc)
+      for (int pc = 0; pc < 3; ++pc)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const int slot = NP == 3 ? pc * 5 + j : j < 4 ? pc * 4 + j : 8 + pc;
-          a[j][pc][mb] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rw, aoff + mb * 512, wk + (unsigned)(slot * BM * 32), 0));
-        }
+        for (int mb = 0; mb < MB; ++mb)
+          a[j][pc][mb] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rw, aoff + mb * 512, wk + (unsigned)((pc * 5 + j) * BM * 32), 0));
     };
     auto mul = [&](const uintx4 &w, const uintx4 &x, sfloatx16 &c) __attribute__((always_inline)) {
-      if constexpr (NP == 3)
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, w), c, 0, 0, 0);
-      else
-        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, w), c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, w), c, 0, 0, 0);
     };
 
     // One pipeline stage of the MFMA waves: multiplies the chunk whose planes are in copy mc; wnext: the next chunk's weights.
-    // Three pieces: the order of products and the ninth tap's pairing of pieces are conv_split_kernel.h's.
-    auto stage3 = [&](auto copy, unsigned wnext) __attribute__((always_inline)) {
+    // The order of products and the ninth tap's pairing of pieces are conv_split_kernel.h's.
+    auto stage = [&](auto copy, unsigned wnext) __attribute__((always_inline)) {
       const char *Sb = Ss + decltype(copy)::value * COPY;
       uintx4 bv[3][NB];
       auto fill_b = [&](int pc, int j) __attribute__((always_inline)) {
@@ -389,57 +366,6 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
         load_a(j, wnext);
       }
     };
-    // Two pieces.  Two sets of activation registers take turns over the four tap pairs, each fetched while the other's twelve
-    // MFMAs run; the ninth tap's have a set of their own and its eight MFMAs wait for the NEXT stage's start (or the tile's
-    // end), where they cover the first fetch after the barrier.  Fetches go one behind each MFMA (sched_group_barrier): in
-    // blocks between the MFMAs they cost a stage 2 400 cycles for 1 792 of MFMAs.
-    uintx4 b2[2][2][NB], b9[2][NB];
-    auto ninth = [&]() __attribute__((always_inline)) {    // w0x0 + w1x0 in one MFMA, w0x1 (+ 0) in the other
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) mul(a[4][q][mb], b9[q][nb], acc[mb][nb]);
-    };
-    auto stage2 = [&](auto copy, unsigned wnow, unsigned wnext, bool owes_ninth) __attribute__((always_inline)) {
-      const char *Sb = Ss + decltype(copy)::value * COPY;
-      auto fill = [&](int j, uintx4 (&bv)[2][NB]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            bv[q][nb] = *reinterpret_cast<const uintx4 *>(Sb + padr[nb][j] + q * PLANE);
-      };
-      fill(0, b2[0]);
-      load_a(3, wnow);
-      __builtin_amdgcn_sched_barrier(0);
-      if (owes_ninth) ninth();
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (j < 3) fill(j + 1, b2[(j + 1) & 1]);
-        else fill(4, b9);
-        // the set used last: the ninth tap's for this chunk, else the pair before's for the next
-        if (j == 0) load_a(4, wnow);
-        else load_a(j - 1, wnext);
-        constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 0, 1};
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) mul(a[j][PA[q]][mb], b2[j & 1][PB[q]][nb], acc[mb][nb]);
-        constexpr int N_MFMA = 3 * MB * NB, N_DS = 2 * NB, N_VM = 2 * MB, VM0 = N_MFMA >= N_DS + N_VM ? N_DS : 0;
-#pragma unroll
-        for (int k = 0; k < N_MFMA; ++k) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                // an MFMA,
-          if (k < N_DS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                  // an LDS read,
-          if (k >= VM0 && k < VM0 + N_VM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // a load
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
     // The multiplying side leaves a tile: statistics partials into red, the tile into Os, accumulators cleared.  Accumulator
     // register r of lane l holds pixel 8*(r/4) + 4*(l/32) + r%4 of the block, channel l%32.
     auto leave = [&](const SplitTile &d) __attribute__((always_inline)) {
@@ -456,13 +382,6 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
       }
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
-        if constexpr (NP == 2) {                       // the weights' power of two per output channel, taken back (exactly)
-          const float u = unscale[mb];
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mb][nb][r] *= u;
-        }
         float *const dst = Os + (ch + mb * 32) * OROW + wn * WN + 4 * lh;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -518,18 +437,16 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
     unsigned wnow = tile_weights(0), wtile = tile_weights(n_mine > 1 ? 1 : 0);       // this chunk's, the next tile's
     enter(md);
 #pragma unroll
-    for (int j = 0; j < (NP == 3 ? 5 : 3); ++j) load_a(j, wnow);
+    for (int j = 0; j < 5; ++j) load_a(j, wnow);
     __syncthreads();                              // stage 0: the loaders fetch chunk 0
     __syncthreads();                              // stage 1: ... and split it
     auto multiply = [&](auto copy) __attribute__((always_inline)) {              // stage i: multiplies chunk i-2, whose planes are in copy i & 1
       const bool last = mc + 1 == md.nk;
       const unsigned wnext = last ? wtile : wnow + (unsigned)A_STRIDE;
-      if constexpr (NP == 3) stage3(copy, wnext);
-      else stage2(copy, wnow, wnext, mc > 0);
+      stage(copy, wnext);
       wnow = wnext;
       ++mc;
       if (last) {
-        if constexpr (NP == 2) ninth();
         leave(md);
         mc = 0;
         if (mt + 1 < n_mine) {

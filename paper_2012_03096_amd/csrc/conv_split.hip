@@ -1,7 +1,6 @@
 // 3x3 convolution with frozen weights on the bf16 matrix cores, fp32 operands split three ways (device code and the
 // arithmetic: conv_split_kernel.h).  Same workgroup tiles and pixel-tile geometry as the fp32-MFMA kernel, launched as
 // a persistent grid; this file instantiates the tiles and launches.
-#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -24,10 +23,8 @@ template <int WGM, int MB, int NB>
 struct SplitLaunch {
   template <int BSLOTS>
   static hipError_t attr() {
-    for (const void *k : {reinterpret_cast<const void *>(&conv_rows_kernel<WGM, MB, NB, BSLOTS, 2, false>),
-                          reinterpret_cast<const void *>(&conv_rows_kernel<WGM, MB, NB, BSLOTS, 2, true>),
-                          reinterpret_cast<const void *>(&conv_rows_kernel<WGM, MB, NB, BSLOTS, 3, false>),
-                          reinterpret_cast<const void *>(&conv_rows_kernel<WGM, MB, NB, BSLOTS, 3, true>)}) {
+    for (const void *k : {reinterpret_cast<const void *>(&conv_rows_kernel<WGM, MB, NB, BSLOTS, false>),
+                          reinterpret_cast<const void *>(&conv_rows_kernel<WGM, MB, NB, BSLOTS, true>)}) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
       if (e != hipSuccess) return e;
     }
@@ -46,8 +43,8 @@ struct SplitLaunch {
     const bool vec = a.g.TW % 4 == 0 && a.Wo % 4 == 0;          // stacked rows: 16-byte stores
     void (*const kernel)(ConvArgs) =
         !a.g.rows ? &conv_split_kernel<WGM, MB, NB, BSLOTS>
-        : a.g.pieces == 3 ? (vec ? &conv_rows_kernel<WGM, MB, NB, BSLOTS, 3, true> : &conv_rows_kernel<WGM, MB, NB, BSLOTS, 3, false>)
-                          : (vec ? &conv_rows_kernel<WGM, MB, NB, BSLOTS, 2, true> : &conv_rows_kernel<WGM, MB, NB, BSLOTS, 2, false>);
+        : vec       ? &conv_rows_kernel<WGM, MB, NB, BSLOTS, true>
+                    : &conv_rows_kernel<WGM, MB, NB, BSLOTS, false>;
     if (e0 && e1)
       hipExtLaunchKernelGGL(kernel, grid, block, (unsigned)a.g.lds_bytes, s, e0, e1, 0, a);
     else
@@ -112,78 +109,10 @@ __global__ __launch_bounds__(256) void conv_split_pack_kernel(const float *w, ui
   }
 }
 
-// Two-piece fp16 image.  First the powers of two: one workgroup per output channel (channels past Cout: 1).
-__global__ __launch_bounds__(256) void conv_f16_scales_kernel(const float *w, const float *gamma, const float *beta, float sigmas,
-                                                              int Cout, int Cin, float *in_pow2, float *out_pow2) {
-  __shared__ float red[4];
-  const int m = blockIdx.x, tid = threadIdx.x;
-  float most = 0.f;
-  for (int c = tid; c < Cin; c += 256) {
-    const float bound = fabsf(gamma[c]) * sigmas + fabsf(beta[c]);
-    int e = 15;
-    if (bound > 0.f && bound < __builtin_inff()) (void)frexpf(bound, &e);       // bound <= 2^e
-    const int a = 15 - e < -60 ? -60 : 15 - e > 60 ? 60 : 15 - e;
-    if (m == 0) in_pow2[c] = ldexpf(1.f, a);
-    if (m < Cout)
-      for (int tap = 0; tap < 9; ++tap) most = fmaxf(most, fabsf(w[((size_t)m * Cin + c) * 9 + tap]) * ldexpf(1.f, -a));
-  }
-  for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d, 64));
-  if ((tid & 63) == 0) red[tid >> 6] = most;
-  __syncthreads();
-  if (tid == 0) {
-    most = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    int e = 14;
-    if (most > 0.f && most < __builtin_inff()) (void)frexpf(most, &e);
-    out_pow2[m] = ldexpf(1.f, e - 14 < -60 ? -60 : e - 14 > 60 ? 60 : e - 14);
-  }
-}
-__global__ __launch_bounds__(256) void conv_f16_pack_kernel(const float *w, uintx4 *out, int bm, int nchunks, int M, int Cout, int Cin,
-                                                            const float *in_pow2, const float *out_pow2) {
-  const int m = blockIdx.x * 256 + threadIdx.x, ch = blockIdx.y;
-  if (m >= M) return;
-  uintx4 *const dst = out + ((size_t)(m / bm) * nchunks + ch) * (20 * bm) + m % bm;
-  const uintx4 zero = {0u, 0u, 0u, 0u};
-  const int c0 = ch * 8 > Cin - 8 ? Cin - 8 : ch * 8;
-  float f[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f[e] = (m < Cout && c0 + e >= ch * 8) ? 1.f / (in_pow2[c0 + e] * out_pow2[m]) : 0.f;
-  for (int tap = 0; tap < 9; ++tap) {
-    uintx4 pp[2];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      float v[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int c = c0 + 2 * t + e;
-        v[e] = (m < Cout && c >= ch * 8) ? w[((size_t)m * Cin + c) * 9 + tap] * f[2 * t + e] : 0.f;
-      }
-      unsigned q[2];
-      split2_f16(v[0], v[1], q);
-      pp[0][t] = q[0], pp[1][t] = q[1];
-    }
-    if (tap < 8) {
-      for (int pc = 0; pc < 2; ++pc) dst[(size_t)(8 * pc + tap) * bm] = pp[pc];      // slot 4 pc + tap/2, half-wave tap%2
-    } else {
-      dst[(size_t)16 * bm] = pp[0], dst[(size_t)17 * bm] = pp[1];
-      dst[(size_t)18 * bm] = pp[0], dst[(size_t)19 * bm] = zero;
-    }
-  }
-}
 }  // namespace
 
-hipError_t launch_conv_f16_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, const float *gamma, const float *beta,
-                                double m, float *in_pow2, float *out_pow2, hipStream_t s) {
-  if (!g.split || !g.rows || g.pieces != 2 || Cin < 9 || g.nchunks > 65535) return hipErrorInvalidValue;
-  const int M = g.mtiles * g.bm;
-  const double sigmas = 2.0 * std::sqrt(m) > 4096.0 ? 2.0 * std::sqrt(m) : 4096.0;
-  hipLaunchKernelGGL(conv_f16_scales_kernel, dim3(M), dim3(256), 0, s, w, gamma, beta, (float)sigmas, Cout, Cin, in_pow2, out_pow2);
-  hipLaunchKernelGGL(conv_f16_pack_kernel, dim3(cdiv(M, 256), g.nchunks), dim3(256), 0, s, w, reinterpret_cast<uintx4 *>(wpk), g.bm,
-                     g.nchunks, M, Cout, Cin, in_pow2, out_pow2);
-  return hipGetLastError();
-}
-
 hipError_t launch_conv_split_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s) {
-  if (!g.split || g.pieces != 3 || (g.rows && Cin < 9) || g.nchunks > 65535) return hipErrorInvalidValue;
+  if (!g.split || (g.rows && Cin < 9) || g.nchunks > 65535) return hipErrorInvalidValue;
   const int M = g.mtiles * g.bm;
   hipLaunchKernelGGL(conv_split_pack_kernel, dim3(cdiv(M, 256), g.nchunks), dim3(256), 0, s, w, reinterpret_cast<uintx4 *>(wpk),
                      g.bm, g.nchunks, conv_split_a_stride(g.bm), M, Cout, Cin, g.rows);
@@ -203,7 +132,6 @@ hipError_t launch_conv_split(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hi
   if (!a.g.rows && (!conv_split_fits_width(a.g, a.H, a.W, a.stride) || a.g.raw_rounds > conv_split_rounds_max(conv_bslots_for(a.g.PLd)) ||
                     a.g.raw_w % 4 != 0))
     return hipErrorInvalidValue;
-  if (a.g.pieces != 3 && (a.g.pieces != 2 || !a.g.rows || !a.out_pow2 || !a.in_scale)) return hipErrorInvalidValue;
   if (a.g.rows && (a.Cin < 9 || a.g.nchunks - (a.g.ksplit - 1) * a.g.kchunks < 2 || a.g.PL >= conv_rows_positions(cdiv(a.g.PLd, 256)) || (unsigned long long)a.N * a.Cin * a.H * a.W * sizeof(float) >= (1ull << 32) || a.g.SH != a.stride * (a.Ho - 1) + 3 ||
                    a.g.IW != a.stride * (a.g.TW - 1) + 3 || (long long)a.g.tiles_x * a.g.TW < a.Wo ||
                    (long long)(a.g.n_ptiles / a.g.tiles_x) * a.g.TH < (long long)a.N * a.Ho || a.g.PL < a.g.IH * a.g.IWS))

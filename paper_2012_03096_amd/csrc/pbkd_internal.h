@@ -218,7 +218,6 @@ struct ConvGeom {
   int raw_w, raw_rounds;   // split kernel: columns of a staged raw row (a multiple of 4); rounds of 256 16-byte groups per raw copy
   int raw_bytes;           // bytes of a raw copy: 8 channels x staged rows x raw_w columns of fp32
   int raw_lead;            // columns a raw row starts left of the tile's first column: 4, or 0 where a tile is as wide as the map
-  int pieces;              // split: 3 bf16 pieces or 2 fp16 pieces per operand
   bool rows;               // split kernel on tiles of TH x TW pixels of the stacked rows of all images (conv_rows_kernel.h): any map
   int TW, TH, SH;          // rows: tile columns and rows; staged rows an image takes in the stack
   int stat_parts;          // statistics partials per channel: one per pixel tile, or per group of nimg images where K is split
@@ -230,8 +229,7 @@ struct ConvGeom {
 ConvGeom conv_geom(int taps, int N, int Cin, int Cout, int Ho, int Wo, int stride, bool want_split = false);
 // The split kernel's geometry for maps of any width and alignment; false where it cannot run (at most eight input
 // channels, staging too large).
-// pieces: 3 (bf16, any input) or 2 (fp16: the input must be a BatchNorm + ReLU over the batch).
-bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, int pieces, ConvGeom &g);
+bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGeom &g);
 // The split kernel fetches its input in aligned groups of four columns: input width and the tiles' first input column
 // must be multiples of 4.
 // Where a tile is whole images the unit is the channel plane instead of the row: then H*W must be a multiple of 4.
@@ -258,21 +256,13 @@ inline size_t conv_split_lds_bytes(int bm, int wgn, int PL, int raw_bytes) {
 // per thread (a raw copy has 8 channels x staged rows x groups per row of them; shapes that need more take the fp32 kernel)
 constexpr int conv_split_rounds_max(int slots) { return slots == 1 ? 3 : slots == 2 ? 4 : slots == 3 ? 6 : 0; }
 inline size_t conv_split_pack_floats(const ConvGeom &g) { return (size_t)g.mtiles * g.nchunks * conv_split_a_stride(g.bm) / sizeof(float); }
-// The two-piece fp16 form's weight image per (channel tile, chunk): [8 + 2 slots][h][bm rows][8 channels] of fp16; slot
-// 4 p + j: piece p of tap 2j+h; slot 8: piece h of tap 8; slot 9: piece 0 of tap 8 (h = 0) and zeros
-constexpr int conv_rows_a_stride(int bm, int pieces) { return pieces == 3 ? conv_split_a_stride(bm) : 320 * bm; }
-// positions a staged plane has room for (one of them spare) in the kernel built for `slots` positions per loader thread
+// stacked rows: positions a staged plane has room for (one of them spare) in the kernel built for `slots` positions per loader thread
 constexpr int conv_rows_positions(int slots) { return (slots <= 2 ? 512 : 256 * slots) + 1; }
 // its LDS: two copies of the pieces' planes, a finished tile (bm channels x bn pixels), statistics exchange, tile table
-constexpr size_t conv_rows_lds_bytes(int bm, int bn, int wgn, int slots, int pieces) {
-  return (size_t)32 * pieces * conv_rows_positions(slots) + (size_t)4 * bm * (bn + 4) + (size_t)16 * wgn * bm + 1536;
+constexpr size_t conv_rows_lds_bytes(int bm, int bn, int wgn, int slots) {
+  return (size_t)96 * conv_rows_positions(slots) + (size_t)4 * bm * (bn + 4) + (size_t)16 * wgn * bm + 1536;
 }
-inline size_t conv_rows_pack_floats(const ConvGeom &g, int pieces) { return (size_t)g.mtiles * g.nchunks * conv_rows_a_stride(g.bm, pieces) / 4; }
 // w: canonical [Cout][Cin][9] on the device -> the kernel's weight image
-// Two-piece form: powers of two per input channel (bounding |gamma| max(2^12, 2 sqrt(m)) + |beta| by 2^15) and per output
-// channel, then the image.  in_pow2 [Cin], out_pow2 [mtiles*bm] (inverse powers, see ConvArgs).
-hipError_t launch_conv_f16_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, const float *gamma, const float *beta,
-                                double m, float *in_pow2, float *out_pow2, hipStream_t s);
 hipError_t launch_conv_split_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s);
 // Weights are handed to the kernel re-packed as the exact LDS image of every (channel tile, chunk of 8
 // input channels): wpk[mtile][chunk][tap][half][bm][4], zero padded, so that staging them is a contiguous
@@ -295,7 +285,6 @@ struct ConvArgs {
   int N, Cin, Cout, H, W, Ho, Wo, stride;
   ConvGeom g;
   float *split_out;        // g.ksplit > 1: [ksplit][N,Cout,Ho,Wo] partial outputs, summed by launch_conv_ksplit_finish
-  const float *out_pow2;   // g.pieces == 2: [mtiles*bm] what the accumulators of an output channel are multiplied by
   const float *w_canon;    // launch_conv_first only: the canonical OIHW weights
 };
 // With g.ksplit > 1 the kernel writes partial outputs into split_out (out and stat_partial are left alone).
@@ -419,12 +408,7 @@ struct BnPending {
   float *rmean, *rvar;
   float decay;
 };
-// the finished scale and shift once more, times a power of two per channel (what a two-piece fp16 convolution reads)
-struct BnScaled {
-  const float *pow2;       // [C] or nullptr: not wanted
-  float *scale, *shift;
-};
-hipError_t launch_bn_finalize(const BnPending &b, int C, hipStream_t s, const BnScaled &scaled = BnScaled{});
+hipError_t launch_bn_finalize(const BnPending &b, int C, hipStream_t s);
 // inference mode: scale = gamma/sqrt(rvar+eps), shift = beta - rmean*scale (mean <- rmean, rstd <- 1/sqrt(rvar+eps))
 struct BnRunning {
   const float *gamma, *beta, *rmean, *rvar;

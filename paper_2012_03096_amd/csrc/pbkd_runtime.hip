@@ -102,14 +102,10 @@ struct LayerRT {
   float *conv_part = nullptr;       // partial outputs of a 3x3 convolution whose K is split over workgroups
   float *wg_part = nullptr;         // partial sums of the conv weight gradient (pointwise: [splits][cout][cin]; full: [tiles][cout][cin][9])
   float *dw_part = nullptr;         // depthwise backward partials [tiles][cin][11]
-  int stat_parts() const { return first_conv ? cfg.n_wgs : (taps == 9 ? (f16 ? cg16 : cg).stat_parts : pg.n_ptiles); }
+  int stat_parts() const { return first_conv ? cfg.n_wgs : (taps == 9 ? cg.stat_parts : pg.n_ptiles); }
   size_t n_w0 = 0, n_w1 = 0;
   int taps = 9;                     // of the MFMA conv producing z (9 full, 1 pointwise / shortcut)
   ConvGeom cg;                      // geometry of that conv when it is a 3x3
-  bool f16 = false;                 // frozen 3x3 behind a BatchNorm of the same network: with batch statistics it runs on
-  ConvGeom cg16{};                  // two fp16 pieces, this geometry and these weights (conv_rows_kernel.h)
-  float *wpk16 = nullptr, *in_pow2 = nullptr, *out_pow2 = nullptr;
-  float *in_scale16 = nullptr, *in_shift16 = nullptr;   // the producer's scale and shift times in_pow2
   PwGeom pg, pdg;                   // ... when it is a 1x1 (pointwise / shortcut): forward, data gradient
   DwGeom dwf, dwb;                  // depthwise forward / backward tiles
   WgradGeom wg;                     // pointwise weight gradient, or the full conv's when taps_wgrad
@@ -198,10 +194,8 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
       // batch 32: 518 against 557).  PBKD_CONV_ROWS=1 takes the stacked rows everywhere (tuning aid).
       if (!student && !env_is("PBKD_CONV_SPLIT", 0) && (!r.cg.split || env_is("PBKD_CONV_ROWS", 1))) {
         ConvGeom rows{};
-        if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, 3, rows)) r.cg = rows;
+        if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, rows)) r.cg = rows;
       }
-      r.f16 = !student && l > 0 && r.cg.split && !env_is("PBKD_CONV_F16", 0) &&
-              conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, 2, r.cg16);
       r.cw = cw_geom(a->n, d.cin, r.hout, r.wout, d.stride);
       r.first_conv = (l == 0) && conv_first_ok(d.cin, d.stride) &&
                      (unsigned long long)a->n * d.cout * r.hout * r.wout * sizeof(float) < (1ull << 32);   // its stores use 32-bit offsets
@@ -395,8 +389,7 @@ size_t layout(pbkd_block &b, char *base) {
     r.mean = bump.take(r.cout); r.rstd = bump.take(r.cout); r.scale = bump.take(r.cout); r.shift = bump.take(r.cout);
     r.rmean = bump.take(r.cout); r.rvar = bump.take(r.cout);
     r.stat = bump.take((size_t)r.stat_parts() * r.cout * kStatFloats);
-    const int ksplit = r.taps == 9 && !r.first_conv ? std::max(r.cg.ksplit, r.f16 ? r.cg16.ksplit : 1) : 1;
-    if (ksplit > 1) r.conv_part = bump.take((size_t)ksplit * N * r.cout * r.hout * r.wout);
+    if (r.taps == 9 && !r.first_conv && r.cg.ksplit > 1) r.conv_part = bump.take((size_t)r.cg.ksplit * N * r.cout * r.hout * r.wout);
   };
   // ---- teacher
   auto tparams = [&](LayerRT &r) {
@@ -404,11 +397,6 @@ size_t layout(pbkd_block &b, char *base) {
     if (r.n_w1) r.w1 = bump.take(r.n_w1);
     r.gamma = bump.take(r.cout); r.beta = bump.take(r.cout);
     r.wpk = bump.take(pack_floats_fwd(r));
-    if (r.f16) {
-      r.wpk16 = bump.take(conv_rows_pack_floats(r.cg16, 2));
-      r.in_pow2 = bump.take(r.cin); r.in_scale16 = bump.take(r.cin); r.in_shift16 = bump.take(r.cin);
-      r.out_pow2 = bump.take((size_t)r.cg16.mtiles * r.cg16.bm);
-    }
   };
   for (auto &r : b.t.L) { tparams(r); act(r); }
   if (b.t.shortcut == 1) { tparams(b.t.sc); act(b.t.sc); }
@@ -543,11 +531,8 @@ std::vector<float> pack_host_pw(const float *w, const PwGeom &g, int M, int K) {
 
 // Writes the packed copy of a teacher layer's convolution weights, whose canonical tensor is already on its way to the
 // device in stream order (w_host: the same values on the host: the 3x3 or the 1x1 tensor, depthwise weights are read as
-// they are).  before: the layer whose BatchNorm feeds this one (a two-piece convolution's scaling follows from it).
-pbkd_status upload_packed(LayerRT &r, const LayerRT *before, const Net &net, const float *w_host, hipStream_t s) {
-  if (r.f16)
-    HIPCHK(launch_conv_f16_pack(r.w0, r.wpk16, r.cg16, r.cout, r.cin, before->gamma, before->beta, (double)net.n * before->hout * before->wout,
-                                r.in_pow2, r.out_pow2, s));
+// they are).
+pbkd_status upload_packed(LayerRT &r, const float *w_host, hipStream_t s) {
   if (r.taps == 9 && r.cg.split) {
     HIPCHK(launch_conv_split_pack(r.w0, r.wpk, r.cg, r.cout, r.cin, s));
     return PBKD_OK;
@@ -621,25 +606,21 @@ pbkd_status forward_net(Net &net, const float *x, hipStream_t st, Prof *pf) {
   for (size_t l = 0; l < net.L.size(); ++l) {
     LayerRT &r = net.L[l];
     if (r.kind == PBKD_CONV3X3) {
-      // fp16 pieces where the batch's own statistics bound the input (with running ones nothing does)
-      const bool f16 = r.f16 && !running;
       if (pend.partial) {   // the convolution's loader reads finished scale/shift arrays
-        LAUNCH(pf, KK_BN_FINALIZE, st,
-               launch_bn_finalize(pend, net.L[l - 1].cout, st, f16 ? BnScaled{r.in_pow2, r.in_scale16, r.in_shift16} : BnScaled{}));
+        LAUNCH(pf, KK_BN_FINALIZE, st, launch_bn_finalize(pend, net.L[l - 1].cout, st));
         pend = BnPending{};
       }
       ConvArgs ca{};
-      ca.in = in; ca.in_scale = f16 ? r.in_scale16 : in_scale; ca.in_shift = f16 ? r.in_shift16 : in_shift; ca.wpk = f16 ? r.wpk16 : r.wpk;
-      ca.out_pow2 = r.out_pow2;
+      ca.in = in; ca.in_scale = in_scale; ca.in_shift = in_shift; ca.wpk = r.wpk;
       ca.Cin = r.cin; ca.H = r.hin; ca.W = r.win; ca.stride = r.stride;
       ca.out = r.z; ca.stat_partial = running ? nullptr : r.stat;
-      ca.N = N; ca.Cout = r.cout; ca.Ho = r.hout; ca.Wo = r.wout; ca.g = f16 ? r.cg16 : r.cg; ca.split_out = r.conv_part;
+      ca.N = N; ca.Cout = r.cout; ca.Ho = r.hout; ca.Wo = r.wout; ca.g = r.cg; ca.split_out = r.conv_part;
       if (r.first_conv) {
         ca.w_canon = r.w0;
         LAUNCH_CARRYING_EVENTS(pf, KK_CONV_FIRST, launch_conv_first(ca, r.cfg, st, e0_, e1_));
       } else {
         LAUNCH_CARRYING_EVENTS(pf, KK_CONV3X3, launch_conv(9, ca, st, e0_, e1_));
-        if (ca.g.ksplit > 1) LAUNCH(pf, KK_CONV3X3, st, launch_conv_ksplit_finish(ca, st));
+        if (r.cg.ksplit > 1) LAUNCH(pf, KK_CONV3X3, st, launch_conv_ksplit_finish(ca, st));
       }
     } else if (r.fused_fwd) {
       // a workgroup of the fused kernel spans all input channels: it reads finished scale/shift arrays
@@ -921,7 +902,7 @@ pbkd_status pbkd_block_create(const pbkd_arch_desc *teacher, const float *const 
     auto pack = [&](LayerRT &r) -> pbkd_status {
       const float *w = tp[r.kind == PBKD_DWSEP3X3 ? k + 1 : k];
       k += r.kind == PBKD_DWSEP3X3 ? 4 : 3;
-      return upload_packed(r, &r == b->t.L.data() || r.kind < 0 ? nullptr : &r - 1, b->t, w, s);
+      return upload_packed(r, w, s);
     };
     for (auto &r : b->t.L) { pbkd_status e = pack(r); if (e != PBKD_OK) return e; }
     if (b->t.shortcut == 1) { pbkd_status e = pack(b->t.sc); if (e != PBKD_OK) return e; }
@@ -1692,16 +1673,9 @@ pbkd_status pbkd_block_set_tensor(pbkd_block_t *blk, int which, int layer, int s
     if (has_copy && student) {
       const size_t at = (size_t)(p - blk->s_params);
       HIPCHK(launch_pack_params(p, n, blk->map_f + at, blk->map_b + at, blk->s_pk, nullptr));
-    } else if (!student) {
-      if (has_copy) {
-        e = upload_packed(r, layer > 0 && layer < (int)net.L.size() ? &net.L[layer - 1] : nullptr, net, host_in, nullptr);
-        if (e != PBKD_OK) return e;
-      }
-      // a BatchNorm's own parameters scale the two-piece convolution behind it
-      if (layer + 1 < (int)net.L.size() && net.L[layer + 1].f16)
-        HIPCHK(launch_conv_f16_pack(net.L[layer + 1].w0, net.L[layer + 1].wpk16, net.L[layer + 1].cg16, net.L[layer + 1].cout,
-                                    net.L[layer + 1].cin, r.gamma, r.beta, (double)net.n * r.hout * r.wout, net.L[layer + 1].in_pow2,
-                                    net.L[layer + 1].out_pow2, nullptr));
+    } else if (has_copy) {
+      e = upload_packed(r, host_in, nullptr);
+      if (e != PBKD_OK) return e;
     }
     HIPCHK(hipDeviceSynchronize());
   }

@@ -104,22 +104,15 @@ __device__ __forceinline__ void bn_store(const BnPending &b, int c, const BnStat
   }
 }
 
-__global__ __launch_bounds__(256) void bn_finalize_kernel(BnPending b, int C, BnScaled scaled) {
+__global__ __launch_bounds__(256) void bn_finalize_kernel(BnPending b, int C) {
   __shared__ double sred[8];
   const BnStat o = bn_finalize_block(b, C, blockIdx.x, sred);
-  if (threadIdx.x == 0) {
-    bn_store(b, blockIdx.x, o);
-    if (scaled.pow2) {
-      const float q = scaled.pow2[blockIdx.x];
-      scaled.scale[blockIdx.x] = o.scale * q;
-      scaled.shift[blockIdx.x] = o.shift * q;
-    }
-  }
+  if (threadIdx.x == 0) bn_store(b, blockIdx.x, o);
 }
 
-hipError_t launch_bn_finalize(const BnPending &b, int C, hipStream_t s, const BnScaled &scaled) {
+hipError_t launch_bn_finalize(const BnPending &b, int C, hipStream_t s) {
   if (!b.partial || C < 1 || b.n_parts < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bn_finalize_kernel, dim3(C), dim3(256), 0, s, b, C, scaled);
+  hipLaunchKernelGGL(bn_finalize_kernel, dim3(C), dim3(256), 0, s, b, C);
   return hipGetLastError();
 }
 

@@ -13,9 +13,13 @@
 // multiple of 4).  The channel goes into the scalar offset, so a load costs no vector instruction beyond itself.  The weights
 // go from memory into the MFMA waves' operand registers, and a finished tile leaves through LDS and the loader waves.
 //
+// Sums are in two levels (a chunk's products from zero, then one addition to the running sum), for accuracy: rms error of z
+// against fp64 at 67 channels on 27x23 maps 3.0e-7 for the fp32 MFMA kernel, 3.6e-7 with one running sum, 1.3e-7 so; at 512 on
+// 14x14 8.3e-7, 5.0e-7, 1.5e-7.  That costs 4 % of the time.
+//
 // Bound by the MFMA waves' stage, on maps of one round of tiles by start-up and last stores, on 224x224 maps by the loads.
-// Measured against the fp32-MFMA kernel that unaligned maps ran before: 512 -> 512 channels at 14x14, batch 32, 282 -> 144 us;
-// 67 -> 100 and 100 -> 67 at 27x23, batch 77, 169 -> 54 us.
+// Measured against the fp32-MFMA kernel that unaligned maps ran before, forward of two layers: 512 channels at 14x14,
+// batch 32, 571 -> 314 us; 128 at 27x23, batch 77, 474 -> 197; 64 there 141 -> 74; 256 at 10x10, batch 128, 692 -> 187.
 #pragma once
 #include <type_traits>
 
@@ -316,26 +320,31 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
       }
     };
     // The weights come straight from memory (the L1 and L2 hold them) into operand registers: a register set per tap pair,
-    // refilled for the next chunk as soon as the pair's MFMAs are issued, so a load has a whole stage to arrive.  Through LDS
+    // refilled for the next pass as soon as the pair's MFMAs are issued, so a load has a whole pass to arrive.  Through LDS
     // they would double its reads, and LDS gives 64 bytes a cycle: 512 cycles a tap pair for 384 of MFMAs.
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(p.wpk), 0, (int)((unsigned)p.g.mtiles * nchunks * A_STRIDE), 0x00020000);
     const unsigned aoff = (unsigned)(lh * BM + wm * (MB * 32) + l31) * 16u;
-    uintx4 a[5][3][MB];
-    auto load_a = [&](int j, unsigned wk) __attribute__((always_inline)) {               // wk: byte offset of the chunk's weights
+    // Channel blocks are multiplied MG at a time, so that a pass over the chunk has 32 registers of sums at most beside acc.
+    constexpr int MG = NB == 1 ? MB : 1, PASSES = MB / MG;
+    uintx4 a[5][3][MG];
+    auto load_a = [&](int j, int g, unsigned wk) __attribute__((always_inline)) {        // wk: byte offset of the chunk's weights
 #pragma unroll
       for (int pc = 0; pc < 3; ++pc)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-          a[j][pc][mb] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rw, aoff + mb * 512, wk + (unsigned)((pc * 5 + j) * BM * 32), 0));
+        for (int m = 0; m < MG; ++m)
+          a[j][pc][m] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rw, aoff + (g * MG + m) * 512, wk + (unsigned)((pc * 5 + j) * BM * 32), 0));
     };
     auto mul = [&](const uintx4 &w, const uintx4 &x, sfloatx16 &c) __attribute__((always_inline)) {
       c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, w), c, 0, 0, 0);
     };
 
-    // One pipeline stage of the MFMA waves: multiplies the chunk whose planes are in copy mc; wnext: the next chunk's weights.
-    // The order of products and the ninth tap's pairing of pieces are conv_split_kernel.h's.
-    auto stage = [&](auto copy, unsigned wnext) __attribute__((always_inline)) {
+    // One pipeline stage of the MFMA waves: multiplies the chunk whose planes are in copy mc; wnow and wnext: its weights and the
+    // next chunk's.  A chunk's 27 products are summed from zero and added to acc once, so that the roundings that happen
+    // at the size of the whole sum are one per eight channels instead of 27.  Small products come first: what
+    // w0x0 rounds away is then the only loss at a chunk's own size, and an activation piece's registers fall free three
+    // products before the next tap pair needs them.  The ninth tap's pairing of pieces is conv_split_kernel.h's.
+    auto stage = [&](auto copy, unsigned wnow, unsigned wnext) __attribute__((always_inline)) {
       const char *Sb = Ss + decltype(copy)::value * COPY;
       uintx4 bv[3][NB];
       auto fill_b = [&](int pc, int j) __attribute__((always_inline)) {
@@ -344,26 +353,40 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) bv[pc][nb] = *reinterpret_cast<const uintx4 *>(Sb + padr[nb][j] + plane);
       };
-      fill_b(0, 0); fill_b(1, 0); fill_b(2, 0);
+      fill_b(2, 0); fill_b(1, 0); fill_b(0, 0);
 #pragma unroll
-      for (int j = 0; j < 5; ++j) {
-        __builtin_amdgcn_sched_barrier(0);
-        constexpr int PA[6] = {1, 1, 2, 0, 0, 0}, PB[6] = {0, 1, 0, 0, 1, 2}, PL4[3] = {1, 0, 2};
+      for (int g = 0; g < PASSES; ++g) {
+        sfloatx16 sum[MG][NB];
 #pragma unroll
-        for (int q = 0; q < (j < 4 ? 6 : 3); ++q) {
-          const int qa = j < 4 ? PA[q] : PL4[q], qb = j < 4 ? PB[q] : PL4[q];
+        for (int m = 0; m < MG; ++m)
 #pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
+          for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) mul(a[j][qa][mb], bv[qb][nb], acc[mb][nb]);
+            for (int r = 0; r < 16; ++r) sum[m][nb][r] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
           __builtin_amdgcn_sched_barrier(0);
-          if (j + 1 < 5) {          // the next tap pair's pieces, into the registers that have just fallen free
-            if (q == 3) fill_b(0, j + 1);
-            if (q == 4) fill_b(1, j + 1);
-            if (q == 5) fill_b(2, j + 1);
+          constexpr int PA[6] = {0, 0, 1, 2, 1, 0}, PB[6] = {2, 1, 1, 0, 0, 0}, PL4[3] = {2, 1, 0};
+          const bool more = j + 1 < 5 || g + 1 < PASSES;
+          const int jn = j + 1 < 5 ? j + 1 : 0;
+#pragma unroll
+          for (int q = 0; q < (j < 4 ? 6 : 3); ++q) {
+            const int qa = j < 4 ? PA[q] : PL4[q], qb = j < 4 ? PB[q] : PL4[q];
+#pragma unroll
+            for (int m = 0; m < MG; ++m)
+#pragma unroll
+              for (int nb = 0; nb < NB; ++nb) mul(a[j][qa][m], bv[qb][nb], sum[m][nb]);
+            __builtin_amdgcn_sched_barrier(0);
+            // the next tap pair's pieces, into the registers that have just fallen free
+            if (more && (j == 4 || q == 0 || q == 2 || q == 5)) fill_b(j == 4 ? qb : PB[q], jn);
           }
+          if (g + 1 < PASSES) load_a(j, g + 1, wnow);
+          else load_a(j, 0, wnext);
         }
-        load_a(j, wnext);
+#pragma unroll
+        for (int m = 0; m < MG; ++m)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[g * MG + m][nb] += sum[m][nb];
       }
     };
     // The multiplying side leaves a tile: statistics partials into red, the tile into Os, accumulators cleared.  Accumulator
@@ -437,13 +460,13 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
     unsigned wnow = tile_weights(0), wtile = tile_weights(n_mine > 1 ? 1 : 0);       // this chunk's, the next tile's
     enter(md);
 #pragma unroll
-    for (int j = 0; j < 5; ++j) load_a(j, wnow);
+    for (int j = 0; j < 5; ++j) load_a(j, 0, wnow);
     __syncthreads();                              // stage 0: the loaders fetch chunk 0
     __syncthreads();                              // stage 1: ... and split it
     auto multiply = [&](auto copy) __attribute__((always_inline)) {              // stage i: multiplies chunk i-2, whose planes are in copy i & 1
       const bool last = mc + 1 == md.nk;
       const unsigned wnext = last ? wtile : wnow + (unsigned)A_STRIDE;
-      stage(copy, wnext);
+      stage(copy, wnow, wnext);
       wnow = wnext;
       ++mc;
       if (last) {

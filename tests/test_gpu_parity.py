@@ -608,6 +608,27 @@ def test_convolution_behind_a_batchnorm_keeps_fp32_accuracy(gpu, monkeypatch, n,
     assert errs[1] <= 2.0 * errs[0], errs
 
 
+@pytest.mark.parametrize("n,h,w_,chans", [(6, 13, 11, (16, 9, 40)), (9, 7, 7, (64, 500, 512)), (6, 27, 23, (67, 100, 67)), (4, 14, 14, (512, 128, 130)),
+                                          (2, 55, 57, (33, 64, 48)), (40, 5, 5, (256, 260, 20)), (64, 2, 1, (48, 64, 64))])
+def test_stacked_rows_are_no_less_accurate_than_fp32(gpu, monkeypatch, n, h, w_, chans):
+    """On maps whose rows are not whole 16-byte groups the split kernel stands in for the fp32 MFMA kernel, so its rms error
+    against fp64 must not be the larger one, in a layer on the block input and one behind a BatchNorm.  It sums a chunk's 27
+    MFMAs from zero and adds that to the running sum: n chunks leave about 27/2 + n/2 squared roundings at the size of the
+    result where the fp32 kernel's leave 36 n/2 over its K split of up to eight, four chunks a split at least.  (2 %: what
+    the rms of a thousand elements of either kernel is uncertain by.)"""
+    t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+    w = wl.Workload("stacked_rows_accuracy", t, s, seed=23)
+    x, tp, _ = w.tensors(random_affine=True)
+    x = np.maximum(x, 0)
+    errs = {}
+    for split in (0, 1):
+        monkeypatch.setenv("PBKD_CONV_SPLIT", str(split))
+        errs[split] = teacher_layer_errors(gpu, w, tp, x)
+    print(f"[stacked rows accuracy] {chans} {h}x{w_}: rms error of z0, z1: fp32 MFMA {errs[0]}, split {errs[1]}")
+    for a, b in zip(errs[0], errs[1]):
+        assert b <= 1.02 * a, errs
+
+
 def test_batchnorm_parameters_replaced_rescale_the_layer_behind(gpu):
     """pbkd_block_set_tensor on a teacher's gamma and beta, by seven orders of magnitude: the convolution behind follows."""
     torch, pb = gpu

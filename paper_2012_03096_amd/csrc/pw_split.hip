@@ -93,12 +93,12 @@ __device__ __forceinline__ void split_operand(const typename PixVec<VW>::type (&
   }
 }
 
-// the six products (activation piece, weight piece) = 01 11 02 00 10 20 of MB blocks of 32 channels.  Activations are the
-// A operand: an accumulator's rows are pixels and its columns channels, so a lane holds pixels of ONE channel and takes
+// the six products (activation piece, weight piece) = 20 10 11 02 01 00 of MB blocks of 32 channels, small ones first: what
+// they round away is then below the last one's rounding.  Activations are the A operand: an accumulator's rows are pixels and its columns channels, so a lane holds pixels of ONE channel and takes
 // its statistics without leaving its registers.
 template <int MB>
 __device__ __forceinline__ void six_products(const uintx4 (&w)[MB][3], const uintx4 (&x)[3], floatx16 (&acc)[MB]) {
-  constexpr int PW[6] = {1, 1, 2, 0, 0, 0}, PX[6] = {0, 1, 0, 0, 1, 2};
+  constexpr int PW[6] = {0, 0, 1, 2, 1, 0}, PX[6] = {2, 1, 1, 0, 0, 0};
 #pragma unroll
   for (int q = 0; q < 6; ++q)
 #pragma unroll
@@ -145,6 +145,11 @@ __device__ __forceinline__ float group_sum(float v) {
 // ---- many pixels: a workgroup owns 32*MB channels x 4 waves x 32*VW pixels.  The weights of up to kStage chunks are staged
 // in LDS at a time; each wave then runs on its own, its activations two chunks ahead of the multiplication, the split of
 // the next operand between the MFMAs of the current one.
+// With one pixel per lane a stage's chunks (128 channels) are summed from zero and added to the running sum: long sums over few
+// pixels were split four ways on the fp32 matrix cores, and one running sum leaves more error than that (rms against fp64
+// at 433 -> 169 channels, 41x48, batch 7: 1.9e-7 then, 3.3e-7 with one sum, 1.7e-7 so; a sum every 32 channels 1.1e-7 but
+// 28 us for 23).  With two pixels a lane (many pixels: no sum was split) one running sum rounds 6 times per 16
+// channels, fp32 multiply-adds 16 times.
 template <int MB, int VW, int SV>
 __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
   constexpr int D = 2;                         // chunks of activations in flight
@@ -194,6 +199,21 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[e][mb][r] = 0.f;
 
+  floatx16 sum[MB];                            // VW == 1: of this stage's chunks
+  auto clear_sum = [&]() {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum[mb][r] = 0.f;
+  };
+  auto add_sum = [&]() {
+    if constexpr (VW == 1) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) acc[0][mb] += sum[mb];
+      clear_sum();
+    }
+  };
+  clear_sum();
   vec_t ring[D][8];
   uintx4 x[3];                                 // the operand multiplied next
   stage_weights(0, nch < ST ? nch : ST);       // ahead of the activations: loads complete in order
@@ -214,7 +234,7 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
       if (e + 1 < VW) split_operand<VW>(ring[d], e + 1, nx);
       else split_operand<VW>(ring[d ^ 1], 0, nx);
       if (e == (VW > 1 ? VW - 2 : 0)) fetch(ch + D, ring[d]);   // (its last pixel has just been split; with VW = 1 a chunk ago)
-      six_products<MB>(w, x, acc[e]);
+      six_products<MB>(w, x, VW == 1 ? sum : acc[e]);
 #pragma unroll
       for (int q = 0; q < 6 * MB; ++q) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                // one MFMA
@@ -246,6 +266,7 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
       weights(c, w0);
       chunk(0, s0 + c, w0);
     }
+    add_sum();
   }
 
   // ---- per-channel statistics partial over this wave's pixels: each lane sums about the first of its own values, the two

@@ -367,6 +367,44 @@ def test_pointwise_split_is_as_accurate_as_fp32(gpu, monkeypatch):
             assert b <= 2.0 * a + 2e-7, errs
 
 
+def fp32_matrix_product(P, u, parts):
+    """P @ u as the fp32 matrix instructions sum it, a fused multiply-add per product (the kernels that used them measured
+    1.97e-7 and 2.0e-7 against fp64 at K = 433 and 512 in four parts, which this gives); K in `parts` contiguous parts,
+    added in order."""
+    k = P.shape[1]
+    step = -(-k // parts)
+    total = None
+    for k0 in range(0, k, step):
+        acc = np.zeros((P.shape[0], u.shape[1]), dtype=np.float32)
+        for i in range(k0, min(k, k0 + step)):
+            acc = (acc + np.multiply.outer(P[:, i].astype(np.float64), u[i].astype(np.float64))).astype(np.float32)
+        total = acc if total is None else total + acc
+    return total
+
+
+@pytest.mark.parametrize("n,h,w_,ci,co,parts", [(7, 41, 48, 433, 169, 4), (21, 14, 14, 512, 512, 4), (16, 4, 4, 512, 512, 4), (33, 16, 16, 128, 130, 1),
+                                                (8, 27, 23, 67, 100, 1), (4, 13, 11, 16, 24, 1), (20, 41, 48, 64, 33, 1), (130, 32, 32, 160, 64, 1)])
+def test_pointwise_split_leaves_no_larger_error_than_fp32_products(gpu, n, h, w_, ci, co, parts):
+    """rms error of the 1x1 kernel the library chooses, against fp64 on its own input, for 400 of its
+    pixels: not larger than that of fp32 multiply-adds summed in `parts` parts (4: as the fp32 kernels did with long sums
+    over few pixels)."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, ci, h, w_, wl._convs([ci, co])), wl.Arch(n, ci, h, w_, wl._dws([ci, co]))
+    x, tp, sp = wl.Workload("pointwise_error", t, s, seed=31).tensors(random_affine=True)
+    blk = pb.Block(t, tp, s, sp)
+    td = torch.zeros(wl.output_shape(t), dtype=torch.float32, device="cuda")
+    blk.student_step(torch.from_numpy(x).cuda(), td, 0.0, want_loss=False)
+    u = blk.get_tensor(pb.STUDENT_ACT, 0, 0, (n, ci, h, w_)).transpose(1, 0, 2, 3).reshape(ci, -1)
+    z = blk.get_tensor(pb.STUDENT_ACT, 0, 1, (n, co, h, w_)).transpose(1, 0, 2, 3).reshape(co, -1)
+    blk.close()
+    some = np.unique(np.linspace(0, u.shape[1] - 1, 400).astype(int))
+    P, u, z = sp[0][1].reshape(co, ci), u[:, some], z[:, some]
+    ref = P.astype(np.float64) @ u.astype(np.float64)
+    got, fp32 = rms_error(z, ref), rms_error(fp32_matrix_product(P, u, parts), ref)
+    print(f"[pointwise error] {ci}->{co} {h}x{w_}x{n}: rms {got:.3e}, fp32 products {fp32:.3e}")
+    assert got <= 1.02 * fp32
+
+
 FIRST_LAYER_SWITCHES = [("PBKD_CF_TH", 4), ("PBKD_CF_TH", 8), ("PBKD_CF_OCC", 1), ("PBKD_CF_OCC", 6), ("PBKD_DW_EDGE", 0),
                         ("PBKD_DW_EDGE", 2), ("PBKD_WGRAD_BN_FUSED", 0)]
 
@@ -585,9 +623,9 @@ def test_convolution_behind_a_batchnorm_keeps_fp32_accuracy(gpu, monkeypatch, n,
     that of fp32 products: relative to each product, never to a channel's bound or to its row's largest weight.  Beside
     ordinary values: a producer whose variance is far below eps (outputs of a hundredth of gamma), and one input channel
     whose weights are 1e6 times the others' and whose activations are all zero.  At most twice the fp32 MFMA kernel's rms
-    error: the split leaves out 2^-27 (rms) of a product and both kernels round once per MFMA at the running sum's size, 27
-    times per eight channels against 36, some of which add exact zeros (post-ReLU operands), so alike to within 1.4.  Pieces
-    held relative to a bound stand at 2.4 to 38 times."""
+    error: the split leaves out 2^-27 (rms) of a product, and with one running sum it rounds 27 times per eight channels at that
+    sum's size, the fp32 kernel 72 times, half of them adding exact zeros (post-ReLU operands) and over shorter sums where
+    it splits K: alike to within 1.4.  Pieces held relative to a bound stand at 2.4 to 38 times."""
     t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
     w = wl.Workload("behind_batchnorm", t, s, seed=21)
     x, tp, _ = w.tensors(random_affine=True)
@@ -614,7 +652,8 @@ def test_stacked_rows_are_no_less_accurate_than_fp32(gpu, monkeypatch, n, h, w_,
     """On maps whose rows are not whole 16-byte groups the split kernel stands in for the fp32 MFMA kernel, so its rms error
     against fp64 must not be the larger one, in a layer on the block input and one behind a BatchNorm.  It sums a chunk's 27
     MFMAs from zero and adds that to the running sum: n chunks leave about 27/2 + n/2 squared roundings at the size of the
-    result where the fp32 kernel's leave 36 n/2 over its K split of up to eight, four chunks a split at least.  (2 %: what
+    result where the fp32 kernel's leave 36 n/2 (72 products a chunk, half of them zeros) over its K split of up to eight, four
+    chunks a split at least.  (2 %: what
     the rms of a thousand elements of either kernel is uncertain by.)"""
     t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
     w = wl.Workload("stacked_rows_accuracy", t, s, seed=23)

@@ -341,6 +341,8 @@ struct PwArgs {
   const float *wpk;        // packed weights
   float *out;              // [N,Cout,Ho,Wo]
   float *stat_partial;     // [Cout][n_ptiles] StatPart (one per pixel tile) or nullptr
+  const float *w;          // the weights as they are: of output channel o, input channel k at w[o*w_row + k*w_col]
+  size_t w_row, w_col;
   int N, Cin, Cout, HWin, Win, Ho, Wo, stride, nchunks;
   PwGeom g;
 };

@@ -598,6 +598,7 @@ pbkd_status forward_net(Net &net, const float *x, hipStream_t st, Prof *pf) {
   auto pointwise = [&](LayerRT &r, const float *src, int hin, int win, int stride) -> pbkd_status {
     PwArgs pa{};
     pa.in = src; pa.wpk = r.wpk; pa.out = r.z; pa.stat_partial = running ? nullptr : r.stat;
+    pa.w = r.kind == PBKD_DWSEP3X3 ? r.w1 : r.w0; pa.w_row = r.cin; pa.w_col = 1;
     pa.N = N; pa.Cin = r.cin; pa.Cout = r.cout; pa.HWin = hin * win; pa.Win = win; pa.Ho = r.hout; pa.Wo = r.wout;
     pa.stride = stride; pa.nchunks = r.pg.nchunks; pa.g = r.pg;
     LAUNCH(pf, KK_CONV1X1, st, launch_pw(pa, st));
@@ -710,6 +711,7 @@ pbkd_status student_backward(pbkd_block &b, const float *x, hipStream_t st) {
       if (b.aux) HIPCHK(hipEventRecord(b.ev_wg[l], ws));
       PwArgs pa{};   // du[n,c,p] = sum_o P[o,c] dz[n,o,p]: a 1x1 conv with P read as [K=cout][M=cin]
       pa.in = dz; pa.wpk = r.wpk_b; pa.out = b.du; pa.stat_partial = nullptr;
+      pa.w = r.w1; pa.w_row = 1; pa.w_col = r.cin;
       pa.N = N; pa.Cin = r.cout; pa.Cout = r.cin; pa.HWin = r.hout * r.wout; pa.Win = r.wout; pa.Ho = r.hout; pa.Wo = r.wout;
       pa.stride = 1; pa.nchunks = r.pdg.nchunks; pa.g = r.pdg;
       LAUNCH(pf, KK_PW_DGRAD, st, launch_pw(pa, st));

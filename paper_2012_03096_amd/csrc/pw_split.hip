@@ -11,6 +11,10 @@
 // channels 8h..8h+7 of a chunk for them, which after the split ARE the MFMA operand of those pixels: no LDS, no
 // transposition.  MFMA e of the VW takes element e, so its column n is pixel VW*n + e.
 //
+// Infinities, and numbers past bfloat16's largest (3.39e38): the difference from the first piece is then no number, so every
+// sum that holds such an operand comes out as a NaN.  Sums that are NaN are formed again in fp32 from the operands
+// themselves (plain_sum), which makes of them what fp32 products make: an infinity, a number, or a NaN.
+//
 // Cin not a multiple of 16: the last chunk starts at channel Cin-16 and the weights of the channels it shares with the
 // one before are zero there, so that every load is of a real channel.
 #include "conv_mfma_kernel.h"
@@ -129,6 +133,19 @@ __device__ __forceinline__ void transpose_to_lds(const floatx16 (&acc)[VW][MB], 
       dst[j] = t;
     }
   }
+}
+
+// one output value in fp32 multiply-adds (g: its pixel, of which there is one)
+__device__ __forceinline__ float plain_sum(const PwArgs &p, int o, long long g) {
+  const int HWo = p.Ho * p.Wo;
+  const int n = (int)((unsigned)g / (unsigned)HWo), r = (int)((unsigned)g - (unsigned)n * (unsigned)HWo);
+  const int i = r / p.Wo, j = r - i * p.Wo;
+  const float *x = p.in + (size_t)n * p.Cin * p.HWin + (p.stride == 1 ? r : p.stride * (i * p.Win + j));
+  const float *w = p.w + (size_t)o * p.w_row;
+  float s = 0.f;
+#pragma unroll 1
+  for (int k = 0; k < p.Cin && s == s; ++k) s = fmaf(w[(size_t)k * p.w_col], x[(size_t)k * p.HWin], s);
+  return s;
 }
 
 // sum over a group of GPR = 8, 16 or 32 neighbouring lanes
@@ -269,12 +286,36 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
     add_sum();
   }
 
+  __syncthreads();                             // nobody reads the weights any more
+  float *const T = reinterpret_cast<float *>(Ws) + wave * (32 * kTileRow<VW>);      // this wave's part of LDS from here on
+  const int m0 = byl * (32 * MB);
+
   // ---- per-channel statistics partial over this wave's pixels: each lane sums about the first of its own values, the two
   // lanes of a channel and then the four waves are re-expressed about one pivot and added
   const bool whole = g0 + 32 * VW <= P;        // wave-uniform: every pixel of the wave exists
-  if (p.stat_partial) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
+  for (int mb = 0; mb < MB; ++mb) {
+    float odd = 0.f;                           // stays zero unless a value is no number, or infinite
+#pragma unroll
+    for (int e = 0; e < VW; ++e)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) odd = fmaf(acc[e][mb][r], 0.f, odd);
+    if (__any(odd != odd)) {
+      // each lane's own values through LDS, where a loop can index them
+      transpose_to_lds<VW, MB>(acc, mb, T, l31, lh);
+      float *const own = T + l31 * kTileRow<VW> + 4 * VW * lh;
+#pragma unroll 1
+      for (int i = 0; i < 16 * VW; ++i) {
+        const int px = 8 * VW * (i / (4 * VW)) + i % (4 * VW);
+        const long long g = g0 + 4 * VW * lh + px;
+        if (own[px] != own[px] && m0 + mb * 32 + l31 < p.Cout) own[px] = plain_sum(p, m0 + mb * 32 + l31, g < P ? g : P - 1);
+      }
+#pragma unroll
+      for (int e = 0; e < VW; ++e)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[e][mb][r] = own[(8 * (r / 4) + r % 4) * VW + e];
+    }
+    if (p.stat_partial) {
       StatPart a;
       a.pivot = acc[0][mb][0];
       a.s1 = a.s2 = 0.f;
@@ -311,16 +352,13 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
       if (lh == 0) red[wave * (32 * MB) + mb * 32 + l31] = a;
     }
   }
-  __syncthreads();                             // nobody reads the weights any more, and the partials are there
 
   // ---- stores: each block of 32 channels through LDS (every wave in a part of its own) and out along the pixels, SV
   // pixels = 4*SV bytes a lane, through a buffer descriptor: what does not exist gets an offset past the buffer
-  float *const T = reinterpret_cast<float *>(Ws) + wave * (32 * kTileRow<VW>);
   constexpr int GPR = 32 * VW / SV, RPI = 64 / GPR;       // lanes per row of pixels, rows per instruction
   const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(
       p.out, 0, (int)((unsigned)p.N * p.Cout * HWo * sizeof(float)), 0x00020000);
   const unsigned orow = (unsigned)HWo * 4u;
-  const int m0 = byl * (32 * MB);
   const int grp = lane % GPR, row0 = lane / GPR;
   const unsigned ooff = output_offset<SV>(p, g0 + grp * SV);
 #pragma unroll
@@ -334,6 +372,7 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
     }
   }
   if (p.stat_partial) {
+    __syncthreads();                           // the four waves' partials are there
     for (int i = tid; i < 32 * MB; i += 256) {
       const int o = m0 + i;
       if (o < p.Cout) {
@@ -437,6 +476,14 @@ __global__ __launch_bounds__(256) void pw_split_kwaves_kernel(PwArgs p) {
       const svec_t t = *reinterpret_cast<const svec_t *>(smem + (w * 32 * MB + row) * kTileRow<VW> + grp * SV);
 #pragma unroll
       for (int e = 0; e < SV; ++e) v[e] = w == 0 ? PixVec<SV>::get(t, e) : v[e] + PixVec<SV>::get(t, e);
+    }
+    bool number = true;
+#pragma unroll
+    for (int e = 0; e < SV; ++e) number = number && v[e] == v[e];
+    if (!number && valid && o < p.Cout) {
+#pragma unroll
+      for (int e = 0; e < SV; ++e)
+        if (v[e] != v[e]) v[e] = plain_sum(p, o, g0 + grp * SV + e);
     }
     PixVec<SV>::store(rout, PixVec<SV>::make(v), (valid && o < p.Cout) ? ooff + (unsigned)o * orow : kPastBuffer - 15u, 0);
     if (p.stat_partial) {                      // this wave holds the whole tile's pixels of the row, about its first
@@ -551,7 +598,7 @@ hipError_t init_pw_split_attributes() {
 
 hipError_t launch_pw_split(const PwArgs &a, hipStream_t s) {
   const int i = a.g.variant - kPwSplitFirst;
-  if (!pw_split_fits(i, a.Ho * a.Wo, a.stride) || !pw_split_ok(a.N, a.Cin, a.Cout, a.HWin, a.Ho, a.Wo) || a.g.K != a.Cin ||
+  if (!a.w || !pw_split_fits(i, a.Ho * a.Wo, a.stride) || !pw_split_ok(a.N, a.Cin, a.Cout, a.HWin, a.Ho, a.Wo) || a.g.K != a.Cin ||
       a.nchunks != cdiv(a.Cin, 16) || (a.stride == 1 && a.HWin != a.Ho * a.Wo) ||
       ((a.stride != 1) && ((a.Ho - 1) * a.stride * a.Win + (a.Wo - 1) * a.stride >= a.HWin)) ||
       (unsigned long long)a.g.mtiles * (a.g.bm / 32) * a.nchunks * 3072 >= (1ull << 32) ||

@@ -405,6 +405,64 @@ def test_pointwise_split_leaves_no_larger_error_than_fp32_products(gpu, n, h, w_
     assert got <= 1.02 * fp32
 
 
+def value_classes(a):
+    """0 for numbers, 1 and -1 for infinities, 2 for NaN."""
+    return np.where(np.isnan(a), 2, np.where(np.isinf(a), np.sign(a), 0)).astype(int)
+
+
+def same_nonfinite(got, want, what):
+    """The same elements are infinite or NaN, and the others agree (each to the scale of its channel: some are past 1e36)."""
+    g, w = value_classes(got), value_classes(want)
+    assert (g == w).all(), (what, int((g != w).sum()), "differ, first", got[g != w][0], want[g != w][0])
+    with np.errstate(all="ignore"):
+        ok = np.isfinite(want)
+        scale = np.max(np.where(ok, np.abs(want.astype(np.float64)), 0), axis=(0, 2, 3), keepdims=True)
+        err = np.where(ok, np.abs(got.astype(np.float64) - want), 0) / np.maximum(scale, 1e-30)
+    assert err.max() <= ACT_TOL, (what, err.max())
+
+
+@pytest.mark.parametrize("variant", [-1] + list(range(13, 23)))
+@pytest.mark.parametrize("n,h,w_,chans,stride", [(2, 6, 8, (20, 33, 40), 1), (40, 32, 32, (24, 70, 17), 1), (3, 9, 7, (130, 65, 30), 2)])
+def test_pointwise_split_infinities(gpu, monkeypatch, n, h, w_, chans, stride, variant):
+    """Infinities, NaNs and numbers past bfloat16's largest in the activations and the weights of 1x1 convolutions (pointwise and
+    strided shortcut): every output is the number, infinity or NaN that plain products of the kernel's own input make,
+    with the batch's and with running statistics."""
+    torch, pb = gpu
+    rng = np.random.default_rng(7)
+    t = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans), stride0=stride), shortcut=1, shortcut_stride=stride)
+    s = wl.Arch(n, chans[0], h, w_, wl._dws(list(chans), stride0=stride), shortcut=1, shortcut_stride=stride)
+    x, tp, sp = wl.Workload("infinities", t, s, seed=41, copy_shortcut=True).tensors(random_affine=True)
+    x = x.copy()
+    for v in (np.inf, -np.inf, np.nan, 3.4e38):
+        x[rng.integers(n), rng.integers(chans[0]), rng.integers(h), rng.integers(w_)] = v
+    x[-1, -1, -1, -1] = np.inf
+    for l in range(2):                     # (depthwise outputs of a few hundredths: 3.4e38 times them stays a number)
+        sp[l][0] = sp[l][0] * np.float32(1e-2)
+        sp[l][1] = sp[l][1].copy()
+        sp[l][1][3, 1], sp[l][1][5, 2] = np.inf, -3.4e38
+    if variant >= 0:
+        monkeypatch.setenv("PBKD_PW_VARIANT", str(variant))
+    blk = pb.Block(t, tp, s, sp)
+    xd = torch.from_numpy(x).cuda()
+    out = torch.empty(wl.output_shape(s), dtype=torch.float32, device="cuda")
+    shapes = _layer_act_shapes(s)
+    for mode in (0, 1):
+        pb.network_forward([blk], [1], xd, [out], bn_mode=mode)
+        torch.cuda.synchronize()
+        for l in range(2 if stride == 2 and 16 <= variant <= 20 else 3):     # (those tiles take no strided shortcut)
+            if l < 2:
+                u, P = blk.get_tensor(pb.STUDENT_ACT, l, 0, shapes[l][0]), sp[l][1]
+            else:
+                u, P = x[:, :, ::stride, ::stride], sp[2][0]
+            co, ci = P.shape[:2]
+            with np.errstate(all="ignore"):
+                want = P.reshape(co, ci).astype(np.float64) @ u.astype(np.float64).transpose(1, 0, 2, 3).reshape(ci, -1)
+                want = want.astype(np.float32).reshape(co, n, *u.shape[2:]).transpose(1, 0, 2, 3)
+            got = blk.get_tensor(pb.STUDENT_ACT, l, 1, want.shape)
+            same_nonfinite(got, want, (mode, l))
+    blk.close()
+
+
 FIRST_LAYER_SWITCHES = [("PBKD_CF_TH", 4), ("PBKD_CF_TH", 8), ("PBKD_CF_OCC", 1), ("PBKD_CF_OCC", 6), ("PBKD_DW_EDGE", 0),
                         ("PBKD_DW_EDGE", 2), ("PBKD_WGRAD_BN_FUSED", 0)]
 

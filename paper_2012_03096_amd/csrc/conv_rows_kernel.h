@@ -13,6 +13,10 @@
 // multiple of 4).  The channel goes into the scalar offset, so a load costs no vector instruction beyond itself.  The weights
 // go from memory into the MFMA waves' operand registers, and a finished tile leaves through LDS and the loader waves.
 //
+// Infinities, and numbers past bfloat16's largest, make every sum that holds one a NaN (their pieces are none).  Sums that are
+// NaN are formed again in fp32 from the operands themselves (plain_conv_sum): an infinity, a number, or a NaN, as fp32
+// products have it.
+//
 // Sums are in two levels (a chunk's products from zero, then one addition to the running sum), for accuracy: rms error of z
 // against fp64 at 67 channels on 27x23 maps 3.0e-7 for the fp32 MFMA kernel, 3.6e-7 with one running sum, 1.3e-7 so; at 512 on
 // 14x14 8.3e-7, 5.0e-7, 1.5e-7.  That costs 4 % of the time.
@@ -26,6 +30,25 @@
 #include "conv_split_kernel.h"
 
 namespace pbkd {
+
+// output channel o at row y, column x of image n in fp32 multiply-adds over the input channels [c0, c1)
+__device__ __forceinline__ float plain_conv_sum(const ConvArgs &p, int o, int n, int y, int x, int c0, int c1) {
+  float s = 0.f;
+#pragma unroll 1
+  for (int c = c0; c < c1 && s == s; ++c) {
+    const float *in = p.in + ((size_t)n * p.Cin + c) * p.H * p.W, *w = p.w_canon + ((size_t)o * p.Cin + c) * 9;
+    const float sc = p.in_scale ? p.in_scale[c] : 1.f, sh = p.in_scale ? p.in_shift[c] : 0.f;
+#pragma unroll 1
+    for (int t = 0; t < 9; ++t) {
+      const int yy = p.stride * y - 1 + t / 3, xx = p.stride * x - 1 + t % 3;
+      float v = 0.f;
+      if (yy >= 0 && yy < p.H && xx >= 0 && xx < p.W)
+        v = fmaxf(fmaf(in[(size_t)yy * p.W + xx], sc, sh), p.in_scale ? 0.f : -__builtin_inff());
+      s = fmaf(w[t], v, s);
+    }
+  }
+  return s;
+}
 
 template <int WGM, int MB, int NB, int BSLOTS, bool VEC>
 __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
@@ -414,6 +437,27 @@ __global__ __launch_bounds__(512) void conv_rows_kernel(ConvArgs p) {
             const f4 v = {acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]};
             *reinterpret_cast<f4 *>(dst + nb * 32 + 8 * q) = v;
           }
+        float odd = 0.f;                               // stays zero unless a value is no number, or infinite
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) odd = fmaf(acc[mb][nb][r], 0.f, odd);
+        if (__any(odd != odd)) {                       // each lane's own values, where a loop can index them: in Os
+          const int o = d.mt * BM + ch + mb * 32;
+#pragma unroll 1
+          for (int i = 0; i < 16 * NB; ++i) {
+            const int px = 32 * (i / 16) + 8 * (i / 4 % 4) + i % 4, pn = wn * WN + 4 * lh + px;
+            const int r = d.y0 + pn / TW, di = r / p.Ho, x = d.x0 + pn % TW;
+            const bool ok = pn / TW < TH && d.n0 + di < p.N && x < p.Wo;        // (else the tile's first pixel, see enter)
+            if (dst[px] != dst[px] && o < p.Cout)
+              dst[px] = plain_conv_sum(p, o, ok ? d.n0 + di : d.n0, ok ? r - di * p.Ho : d.y0, ok ? x : d.x0, d.kb * 8,
+                                       (d.kb + d.nk) * 8 < p.Cin ? (d.kb + d.nk) * 8 : p.Cin);
+          }
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = dst[nb * 32 + 8 * (r / 4) + r % 4];
+        }
         if (stats) {
           // sums about the wave's first pixel (register 0 of the lower half-wave); four chains of each
           const float pv = __shfl(acc[mb][0][0], l31, 64);

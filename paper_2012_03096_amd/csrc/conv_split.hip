@@ -132,7 +132,7 @@ hipError_t launch_conv_split(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hi
   if (!a.g.rows && (!conv_split_fits_width(a.g, a.H, a.W, a.stride) || a.g.raw_rounds > conv_split_rounds_max(conv_bslots_for(a.g.PLd)) ||
                     a.g.raw_w % 4 != 0))
     return hipErrorInvalidValue;
-  if (a.g.rows && (a.Cin < 9 || a.g.nchunks - (a.g.ksplit - 1) * a.g.kchunks < 2 || a.g.PL >= conv_rows_positions(cdiv(a.g.PLd, 256)) || (unsigned long long)a.N * a.Cin * a.H * a.W * sizeof(float) >= (1ull << 32) || a.g.SH != a.stride * (a.Ho - 1) + 3 ||
+  if (a.g.rows && (a.Cin < 9 || !a.w_canon || a.g.nchunks - (a.g.ksplit - 1) * a.g.kchunks < 2 || a.g.PL >= conv_rows_positions(cdiv(a.g.PLd, 256)) || (unsigned long long)a.N * a.Cin * a.H * a.W * sizeof(float) >= (1ull << 32) || a.g.SH != a.stride * (a.Ho - 1) + 3 ||
                    a.g.IW != a.stride * (a.g.TW - 1) + 3 || (long long)a.g.tiles_x * a.g.TW < a.Wo ||
                    (long long)(a.g.n_ptiles / a.g.tiles_x) * a.g.TH < (long long)a.N * a.Ho || a.g.PL < a.g.IH * a.g.IWS))
     return hipErrorInvalidValue;

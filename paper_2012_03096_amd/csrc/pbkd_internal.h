@@ -285,7 +285,7 @@ struct ConvArgs {
   int N, Cin, Cout, H, W, Ho, Wo, stride;
   ConvGeom g;
   float *split_out;        // g.ksplit > 1: [ksplit][N,Cout,Ho,Wo] partial outputs, summed by launch_conv_ksplit_finish
-  const float *w_canon;    // launch_conv_first only: the canonical OIHW weights
+  const float *w_canon;    // the canonical OIHW weights (launch_conv_first, stacked rows)
 };
 // With g.ksplit > 1 the kernel writes partial outputs into split_out (out and stat_partial are left alone).
 // ev_start / ev_stop (both or neither): the launch itself carries the two events, which then hold the dispatch's own

@@ -616,8 +616,8 @@ pbkd_status forward_net(Net &net, const float *x, hipStream_t st, Prof *pf) {
       ca.Cin = r.cin; ca.H = r.hin; ca.W = r.win; ca.stride = r.stride;
       ca.out = r.z; ca.stat_partial = running ? nullptr : r.stat;
       ca.N = N; ca.Cout = r.cout; ca.Ho = r.hout; ca.Wo = r.wout; ca.g = r.cg; ca.split_out = r.conv_part;
+      ca.w_canon = r.w0;
       if (r.first_conv) {
-        ca.w_canon = r.w0;
         LAUNCH_CARRYING_EVENTS(pf, KK_CONV_FIRST, launch_conv_first(ca, r.cfg, st, e0_, e1_));
       } else {
         LAUNCH_CARRYING_EVENTS(pf, KK_CONV3X3, launch_conv(9, ca, st, e0_, e1_));

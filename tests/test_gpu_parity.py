@@ -726,6 +726,52 @@ def test_stacked_rows_are_no_less_accurate_than_fp32(gpu, monkeypatch, n, h, w_,
         assert b <= 1.02 * a, errs
 
 
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3])
+@pytest.mark.parametrize("n,h,w_,chans,strides", [(3, 13, 15, (40, 72, 33), (1, 1)), (5, 7, 7, (300, 130, 20), (1, 1)), (3, 17, 13, (24, 40, 31), (2, 1)),
+                                                  (2, 5, 131, (17, 9, 70), (1, 1)), (6, 13, 1, (12, 20, 9), (1, 1))])
+def test_stacked_rows_infinities(gpu, monkeypatch, n, h, w_, chans, strides, tile):
+    """Infinities and numbers past bfloat16's largest in the block's input, in a layer's output (running statistics) and in the
+    weights: every pre-activation is the number, infinity or NaN that plain products make of them, K split or not."""
+    torch, pb = gpu
+    layers = [wl.Layer(wl.CONV3X3, a, b, st, 0) for a, b, st in zip(chans[:-1], chans[1:], strides)]
+    slayers = [wl.Layer(wl.DWSEP3X3, a, b, st, 1) for a, b, st in zip(chans[:-1], chans[1:], strides)]
+    t, s = wl.Arch(n, chans[0], h, w_, layers), wl.Arch(n, chans[0], h, w_, slayers)
+    x, tp, sp = wl.Workload("infinities", t, s, seed=43).tensors(random_affine=True)
+    rng = np.random.default_rng(9)
+    x = np.maximum(x, 0)
+    for v in (np.inf, 3.4e38, -np.inf):
+        x[rng.integers(n), rng.integers(chans[0]), rng.integers(h), rng.integers(w_)] = v
+    x[-1, -1, -1, -1] = np.inf
+    tp[0][0] = tp[0][0].copy()
+    tp[0][0][3] *= np.float32(1e-3)
+    tp[0][0][3, 1, 1, 1], tp[0][0][5, 2, 0, 0] = np.inf, np.float32(3.4e38)
+    x[:, 2] = np.minimum(x[:, 2], np.float32(0.5))          # (times 3.4e38: a number)
+    if tile >= 0:
+        monkeypatch.setenv("PBKD_CONV_TILE", str(tile))
+    blk = pb.Block(t, tp, s, sp)
+    xd = torch.from_numpy(x).cuda()
+    out = torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
+    for mode in (0, 1):
+        pb.network_forward([blk], [0], xd, [out], bn_mode=mode)
+        torch.cuda.synchronize()
+        a = x
+        for l, (_, shp, _) in enumerate(_layer_act_shapes(t)):
+            got = blk.get_tensor(pb.TEACHER_ACT, l, 1, shp)
+            st, (ho, wo) = strides[l], shp[2:]
+            xp = np.pad(a.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
+            want = np.zeros((chans[l + 1], n * ho * wo))
+            with np.errstate(all="ignore"):
+                for tap in range(9):
+                    i, j = tap // 3, tap % 3
+                    part = xp[:, :, i:i + st * (ho - 1) + 1:st, j:j + st * (wo - 1) + 1:st].transpose(1, 0, 2, 3).reshape(chans[l], -1)
+                    want += tp[l][0][:, :, i, j].astype(np.float64) @ part
+                want = want.astype(np.float32).reshape(chans[l + 1], n, ho, wo).transpose(1, 0, 2, 3)
+                same_nonfinite(got, want, (mode, l))
+                sc, sh = (blk.get_tensor(pb.TEACHER_ACT, l, k, (chans[l + 1],))[None, :, None, None].astype(np.float64) for k in (4, 5))
+                a = np.fmax((got * sc + sh).astype(np.float32), 0)          # fmaxf: a NaN becomes 0
+    blk.close()
+
+
 def test_batchnorm_parameters_replaced_rescale_the_layer_behind(gpu):
     """pbkd_block_set_tensor on a teacher's gamma and beta, by seven orders of magnitude: the convolution behind follows."""
     torch, pb = gpu

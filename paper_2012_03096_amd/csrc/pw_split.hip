@@ -524,13 +524,17 @@ bool pw_split_ok(int N, int Cin, int Cout, int HWin, int Ho, int Wo) {
 //   512 -> 512, 4x4 x 128:     21.5/20.5                     21.8/20.7    14.2/13.3
 //   512 -> 512, 2x2 x 128:     12.6/10.8                     23.1/20.7    11.2/10.7    32 ch x 32 px 9.9/9.4
 // So: 64 x 4*64 pixels where that is four workgroups or more per compute unit (its wider rows reach HBM's rate), else
-// 64 x 4*32 while every compute unit gets one, else K over the waves.
+// 64 x 4*32 while every compute unit gets one, else K over the waves.  32 channels where there are no more of them (median of
+// both directions from a kernel trace; fp32 kernel, 64 ch x 4 x 64 px, 32 ch x 4 x 64 px, 32 ch x 4 x 32 px):
+//   16 -> 16, 112x112 x 32:    16.8   19.2   13.1   15.0
+//   32 -> 32, 112x112 x 32:    24.0   26.2   20.1   21.5
+//   32 -> 32, 32x32 x 128:      9.9           9.2    8.6
 int pw_split_choice(long long P, int Cout, int HW, int stride) {
   auto wgs = [&](int i) {
     const long long px = (i < 7 ? 4ll : 1ll) * 32 * kVW[i];
     return (long long)cdiv(Cout, 32 * kMB[i]) * ((P + px - 1) / px);
   };
-  if (wgs(3) >= 1024 && pw_split_fits(3, HW, stride)) return 3;
+  if (wgs(3) >= 1024 && pw_split_fits(3, HW, stride)) return Cout > 32 ? 3 : 4;
   if (wgs(1) >= 256) return Cout > 32 ? 1 : 2;
   return Cout > 32 && wgs(8) >= 256 ? 8 : 9;
 }

@@ -95,3 +95,13 @@ def test_scheduler_on_vgg16_blocks_and_errors():
     assert e.value.status == pb.EINVAL
     with pytest.raises(pb.PbkdError):
         pb.schedule_blocks(weights, 2, 5)
+
+
+@pytest.mark.parametrize("pixels", [32768, 100352, 262144, 401408, 1605632])
+def test_pointwise_tiles_of_few_channels_are_not_half_empty(pixels):
+    """Up to 32 output channels of a 1x1 convolution take a tile of 32 channels, not the 64-channel one that more take."""
+    import ctypes
+    choice = pb.lib()._ZN4pbkd15pw_split_choiceExiii            # (pixels, output channels, pixels per image, stride)
+    choice.restype, choice.argtypes = ctypes.c_int, [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    for cout in (1, 16, 24, 32):
+        assert choice(pixels, cout, 1024, 1) != choice(pixels, 64, 1024, 1), cout

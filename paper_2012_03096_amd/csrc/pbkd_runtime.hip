@@ -191,8 +191,13 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
         r.cg = conv_geom(9, a->n, d.cin, d.cout, r.hout, r.wout, d.stride, false);   // aligned 16-byte fetches, 32-bit store offsets
       // Maps without aligned 16-byte groups: tiles of stacked rows, loaded 4 bytes at a time.  Where the aligned form
       // exists it stays (64 -> 128 and 128 -> 128 at 16x16, batch 128: 38 us a launch against 41, 128 -> 256 at 56x56,
-      // batch 32: 518 against 557).  PBKD_CONV_ROWS=1 takes the stacked rows everywhere (tuning aid).
-      if (!student && !env_is("PBKD_CONV_SPLIT", 0) && (!r.cg.split || env_is("PBKD_CONV_ROWS", 1))) {
+      // batch 32: 518 against 557; at stride 2 they are not measured apart).  The fp32 kernel stays on few pixels of tiny
+      // maps, where it splits K down to five chunks, and wherever it splits K on 1x1 maps: both are start-up and the second
+      // kernel then, and its chunks stage faster (two layers forward, us, fp32 and stacked rows: 1x1 maps, batch 512, 96
+      // channels 37 and 41; 3x1, batch 128, 192 channels 34.5 and 40; 7x7, batch 8, 256 channels 36 and 39; but 5x5, batch
+      // 64, 128 channels 47 and 38).  PBKD_CONV_ROWS=1 takes the stacked rows everywhere (tuning aid).
+      const bool fp32_stays = !r.cg.split && r.cg.ksplit > 1 && (r.cg.kchunks <= 5 || r.hout * r.wout == 1) && r.cg.n_ptiles <= 32;
+      if (!student && !env_is("PBKD_CONV_SPLIT", 0) && ((!r.cg.split && !fp32_stays) || env_is("PBKD_CONV_ROWS", 1))) {
         ConvGeom rows{};
         if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, rows)) r.cg = rows;
       }

@@ -544,14 +544,21 @@ def test_split_convolution_on_drawn_shapes(gpu):
 STACKED_ROWS = [(3, (40, 72, 33), 14, 14, (1, 1)), (4, (67, 100, 67), 27, 23, (1, 1)), (5, (300, 130, 20), 7, 7, (1, 1)),
                 (2, (17, 9, 70), 5, 131, (1, 1)), (1, (64, 64, 64), 9, 70, (1, 1)), (6, (12, 20, 9), 13, 1, (1, 1)),
                 (9, (10, 33, 16), 1, 11, (1, 1)), (3, (24, 40, 31), 15, 17, (2, 1)), (2, (9, 65, 48), 18, 30, (1, 2)),
-                (7, (16, 16, 16), 2, 3, (2, 1)), (1, (129, 9, 10), 3, 3, (1, 1))]
+                (7, (16, 16, 16), 2, 3, (2, 1)), (1, (129, 9, 10), 3, 3, (1, 1)), (9, (17, 24, 40), 20, 24, (1, 1)),
+                (30, (16, 30, 200), 5, 5, (1, 1))]
 
 
+@pytest.mark.parametrize("wgs", [0, 1, 3])
 @pytest.mark.parametrize("n,chans,h,w_,strides", STACKED_ROWS)
-def test_split_convolution_on_any_map(gpu, n, chans, h, w_, strides):
+def test_split_convolution_on_any_map(gpu, monkeypatch, n, chans, h, w_, strides, wgs):
     """Teacher forward on maps whose rows are not whole 16-byte groups, where the bf16-split kernel takes tiles out of the
-    stacked rows of all images: every layer's pre-activation and statistics against the fp64 oracle at ACT_TOL."""
+    stacked rows of all images: every layer's pre-activation and statistics against the fp64 oracle at ACT_TOL.  With a
+    workgroup per tile, and with one and three workgroups that walk all of them: tiles of two, three and more chunks behind one
+    another, odd and even numbers of chunks in all, scalar and 16-byte stores, K split and not."""
     torch, pb = gpu
+    monkeypatch.setenv("PBKD_CONV_ROWS", "1")
+    if wgs:
+        monkeypatch.setenv("PBKD_SPLIT_WGS", str(wgs))
     layers = [wl.Layer(wl.CONV3X3, a, b, st, 0) for a, b, st in zip(chans[:-1], chans[1:], strides)]
     slayers = [wl.Layer(wl.DWSEP3X3, a, b, st, 1) for a, b, st in zip(chans[:-1], chans[1:], strides)]
     t, s = wl.Arch(n, chans[0], h, w_, layers), wl.Arch(n, chans[0], h, w_, slayers)
@@ -720,6 +727,7 @@ def test_stacked_rows_are_no_less_accurate_than_fp32(gpu, monkeypatch, n, h, w_,
     errs = {}
     for split in (0, 1):
         monkeypatch.setenv("PBKD_CONV_SPLIT", str(split))
+        monkeypatch.setenv("PBKD_CONV_ROWS", str(split))
         errs[split] = teacher_layer_errors(gpu, w, tp, x)
     print(f"[stacked rows accuracy] {chans} {h}x{w_}: rms error of z0, z1: fp32 MFMA {errs[0]}, split {errs[1]}")
     for a, b in zip(errs[0], errs[1]):
@@ -746,6 +754,7 @@ def test_stacked_rows_infinities(gpu, monkeypatch, n, h, w_, chans, strides, til
     tp[0][0][3] *= np.float32(1e-3)
     tp[0][0][3, 1, 1, 1], tp[0][0][5, 2, 0, 0] = np.inf, np.float32(3.4e38)
     x[:, 2] = np.minimum(x[:, 2], np.float32(0.5))          # (times 3.4e38: a number)
+    monkeypatch.setenv("PBKD_CONV_ROWS", "1")
     if tile >= 0:
         monkeypatch.setenv("PBKD_CONV_TILE", str(tile))
     blk = pb.Block(t, tp, s, sp)

@@ -105,3 +105,13 @@ def test_pointwise_tiles_of_few_channels_are_not_half_empty(pixels):
     choice.restype, choice.argtypes = ctypes.c_int, [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     for cout in (1, 16, 24, 32):
         assert choice(pixels, cout, 1024, 1) != choice(pixels, 64, 1024, 1), cout
+
+
+@pytest.mark.parametrize("n,h,w,c,fp32", [(512, 1, 1, 96, True), (512, 2, 1, 64, True), (128, 1, 3, 256, True), (8, 7, 7, 128, True), (64, 2, 3, 192, True), (512, 1, 1, 384, True),
+                                          (64, 5, 5, 128, False), (128, 7, 7, 64, False), (8, 7, 7, 512, False), (32, 15, 13, 64, False)])
+def test_few_pixels_of_tiny_maps_keep_the_fp32_convolution(monkeypatch, n, h, w, c, fp32):
+    """The split kernels keep another weight image than the fp32 one, so the workspace tells which a teacher layer runs."""
+    t, s = wl.Arch(n, c, h, w, wl._convs([c, c])), wl.Arch(n, c, h, w, wl._dws([c, c]))
+    chosen = pb.workspace_bytes(t, s)
+    monkeypatch.setenv("PBKD_CONV_SPLIT", "0")
+    assert (chosen == pb.workspace_bytes(t, s)) == fp32

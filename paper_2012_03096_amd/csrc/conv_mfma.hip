@@ -179,7 +179,7 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGe
       if (g.IH * g.IWS >= conv_rows_positions(slots)) g.IWS = g.IW;
       g.PL = g.IH * g.IWS;
       g.lds_bytes = conv_rows_lds_bytes(g.bm, BN, kWGN[tile], slots);
-      if (g.lds_bytes > (size_t)MAX_LDS) continue;
+      if (g.lds_bytes > (size_t)MAX_LDS || !conv_split_pack_fits(g)) continue;
       const long long tiles_r = (rows + g.TH - 1) / g.TH;
       if (tiles_r * g.tiles_x * g.mtiles > 0x7ffffff) continue;
       g.n_ptiles = (int)(tiles_r * g.tiles_x);

@@ -255,6 +255,10 @@ inline size_t conv_split_lds_bytes(int bm, int wgn, int PL, int raw_bytes) {
 // 16-byte groups of activations a loader thread fetches per chunk, at most, in the kernel built for `slots` halo slots
 // per thread (a raw copy has 8 channels x staged rows x groups per row of them; shapes that need more take the fp32 kernel)
 constexpr int conv_split_rounds_max(int slots) { return slots == 1 ? 3 : slots == 2 ? 4 : slots == 3 ? 6 : 0; }
+// the image is addressed with 32-bit offsets, and written by a launch with a row of workgroups per chunk
+inline bool conv_split_pack_fits(const ConvGeom &g) {
+  return g.nchunks <= 65535 && (unsigned long long)g.mtiles * g.nchunks * conv_split_a_stride(g.bm) < (1ull << 32);
+}
 inline size_t conv_split_pack_floats(const ConvGeom &g) { return (size_t)g.mtiles * g.nchunks * conv_split_a_stride(g.bm) / sizeof(float); }
 // stacked rows: positions a staged plane has room for (one of them spare) in the kernel built for `slots` positions per loader thread
 constexpr int conv_rows_positions(int slots) { return (slots <= 2 ? 512 : 256 * slots) + 1; }
@@ -319,7 +323,8 @@ struct PwGeom {
   int split;               // 1: products on the bf16 matrix cores, weights packed as three bf16 pieces (pw_split_pack_index)
   int K;                   // input channels (split variants)
 };
-PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride);
+// split: false keeps to the fp32 kernels
+PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, bool split = true);
 constexpr int kPwSplitFirst = 13;
 // Split weights: [32-channel block][chunk of 16 input channels][piece 0..2][lane][8 bf16], lane l = row l%32, channels
 // 8*(l/32)..+7 of the chunk.  A ragged last chunk starts at channel K-16; what it shares with the chunk before is zero.

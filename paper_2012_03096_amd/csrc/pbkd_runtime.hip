@@ -150,6 +150,17 @@ struct Net {
   int out_h = 0, out_w = 0;                 // block output
 };
 
+// packed copies of a layer's convolution weights: the one for the forward pass, and a student's of both passes
+size_t pack_floats_fwd(const LayerRT &r) {
+  if (r.taps != 9) return pw_pack_floats(r.pg);
+  return r.cg.split ? conv_split_pack_floats(r.cg) : conv_pack_floats(r.cg);
+}
+size_t student_packed_floats(const Net &net) {
+  size_t n = net.shortcut == 1 ? pack_floats_fwd(net.sc) : 0;
+  for (const LayerRT &r : net.L) n += pack_floats_fwd(r) + (r.kind == PBKD_DWSEP3X3 ? pw_pack_floats(r.pdg) : 0);
+  return n;
+}
+
 pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
   if (!a) return fail(PBKD_EINVAL, "null architecture descriptor");
   if (a->n_layers < 1 || !a->layers) return fail(PBKD_EINVAL, "a block needs at least one layer");
@@ -186,7 +197,7 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
       // a frozen teacher's products run on the bf16 matrix cores from operands split three ways (its weights are split
       // once, at upload); PBKD_CONV_SPLIT=0 keeps the fp32 MFMA kernel
       r.cg = conv_geom(9, a->n, d.cin, d.cout, r.hout, r.wout, d.stride, !student && !env_is("PBKD_CONV_SPLIT", 0));
-      if (r.cg.split && (!conv_split_fits_width(r.cg, h, w, d.stride) ||
+      if (r.cg.split && (!conv_split_fits_width(r.cg, h, w, d.stride) || !conv_split_pack_fits(r.cg) ||
                          (unsigned long long)r.cg.ksplit * a->n * d.cout * r.hout * r.wout * sizeof(float) >= (1ull << 32)))
         r.cg = conv_geom(9, a->n, d.cin, d.cout, r.hout, r.wout, d.stride, false);   // aligned 16-byte fetches, 32-bit store offsets
       // Maps without aligned 16-byte groups: tiles of stacked rows, loaded 4 bytes at a time.  Where the aligned form
@@ -242,6 +253,16 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
       return fail(PBKD_ESHAPE, "shortcut output %dx%d does not match the main branch %dx%d", r.hout, r.wout, h, w);
     r.n_w0 = (size_t)c * a->c; r.taps = 1;
     r.pg = pw_geom(a->n, a->c, c, r.hout, r.wout, r.stride);
+  }
+  // The update kernel's maps name a place of a split copy (6 bytes a weight) by a 2-byte index in 31 bits.  Students of more
+  // packed weights than that reaches keep to the fp32 kernels (4 bytes a weight, indexed by floats).
+  if (student && 2 * student_packed_floats(net) > 0x7ffffff0ull) {
+    if (a->shortcut == 1) net.sc.pg = pw_geom(a->n, a->c, c, net.sc.hout, net.sc.wout, net.sc.stride, false);
+    for (LayerRT &r : net.L)
+      if (r.kind == PBKD_DWSEP3X3) {
+        if (!r.fused_fwd) r.pg = pw_geom(a->n, r.cin, r.cout, r.hout, r.wout, 1, false);
+        r.pdg = pw_geom(a->n, r.cout, r.cin, r.hout, r.wout, 1, false);
+      }
   }
   net.out_h = a->pool == 2 ? h / 2 : h;
   net.out_w = a->pool == 2 ? w / 2 : w;
@@ -378,10 +399,6 @@ void drop_graphs(pbkd_block &b) {
 }
 
 size_t layer_slots(const LayerRT &r) { return r.kind == PBKD_DWSEP3X3 ? 4 : 3; }
-size_t pack_floats_fwd(const LayerRT &r) {
-  if (r.taps != 9) return pw_pack_floats(r.pg);
-  return r.cg.split ? conv_split_pack_floats(r.cg) : conv_pack_floats(r.cg);
-}
 
 // Assigns every device pointer of the block inside [base, base+total) and returns total.  With
 // base == nullptr the pointers are meaningless and only the size is of interest.
@@ -413,10 +430,7 @@ size_t layout(pbkd_block &b, char *base) {
   b.n_student = total; b.n_trainable = trainable;
   b.s_params = bump.take(total); b.s_grads = bump.take(total); b.s_mom = bump.take(total);
   b.map_f = reinterpret_cast<int *>(bump.take(total)); b.map_b = reinterpret_cast<int *>(bump.take(total));
-  size_t npk = 0;
-  auto pk_count = [&](const LayerRT &r) { return pack_floats_fwd(r) + (r.kind == PBKD_DWSEP3X3 ? pw_pack_floats(r.pdg) : 0); };
-  for (auto &r : b.s.L) npk += pk_count(r);
-  if (b.s.shortcut == 1) npk += pk_count(b.s.sc);
+  const size_t npk = student_packed_floats(b.s);
   b.n_pk = npk;
   b.s_pk = bump.take(npk);
   {
@@ -901,7 +915,7 @@ pbkd_status pbkd_block_create(const pbkd_arch_desc *teacher, const float *const 
   if (st != PBKD_OK) return st;
   st = upload(b->s, sp);
   if (st != PBKD_OK) return st;
-  if (2 * b->n_pk > 0x7ffffff0ull) return fail(PBKD_EUNSUPPORTED, "packed student weights exceed 2^30 floats");
+  if (b->n_pk > 0x7fffffffull) return fail(PBKD_EUNSUPPORTED, "packed student weights exceed 2^31 floats");
   {
     // packed copies of every conv weight, and the arena -> packed index maps the optimizer uses
     // (the student's copies are written on the device, through the maps)

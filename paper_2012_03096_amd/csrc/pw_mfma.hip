@@ -346,12 +346,12 @@ __global__ __launch_bounds__(256) void pw_mfma_vec_kernel(PwArgs p) {
 // Vector variants 4..9 = (WM, WP, VW): (4,1,4) (4,1,2) (2,2,4) (2,2,2) (1,4,4) (1,4,2)
 static const int kVecWM[6] = {4, 4, 2, 2, 1, 1}, kVecWP[6] = {1, 1, 2, 2, 4, 4}, kVecVW[6] = {4, 2, 4, 2, 4, 2};
 
-PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride) {
+PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, bool split) {
   const long long P = (long long)N * Ho * Wo;
   const int HW = Ho * Wo;
   int forced = -1;                                            // PBKD_PW_VARIANT: tuning aid
   if (const char *env = std::getenv("PBKD_PW_VARIANT")) forced = std::atoi(env);
-  const bool split_ok = pw_split_ok(N, Cin, Cout, stride * Ho * stride * Wo, Ho, Wo);
+  const bool split_ok = split && pw_split_ok(N, Cin, Cout, stride * Ho * stride * Wo, Ho, Wo);
   if (forced >= kPwSplitFirst && split_ok && pw_split_fits(forced - kPwSplitFirst, HW, stride))
     return pw_split_geom(forced - kPwSplitFirst, N, Cin, Cout, Ho, Wo);
   if (forced < 0 && split_ok) return pw_split_geom(pw_split_choice(P, Cout, HW, stride), N, Cin, Cout, Ho, Wo);

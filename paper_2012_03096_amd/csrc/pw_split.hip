@@ -509,7 +509,8 @@ static const int kMB[10] = {4, 2, 1, 2, 1, 2, 1, 2, 2, 1}, kVW[10] = {1, 1, 1, 2
 
 bool pw_split_ok(int N, int Cin, int Cout, int HWin, int Ho, int Wo) {
   return Cin >= 16 && (unsigned long long)N * Cin * HWin * sizeof(float) < (1ull << 32) &&
-         (unsigned long long)N * Cout * Ho * Wo * sizeof(float) < (1ull << 32) - 64;
+         (unsigned long long)N * Cout * Ho * Wo * sizeof(float) < (1ull << 32) - 64 &&
+         (unsigned long long)cdiv(Cout, 128) * 128 * cdiv(Cin, 16) * 16 * 6 < (1ull << 32);       // (weights, padded to the largest tile)
 }
 
 // Which tile.  Measured on MI355X (us, forward with statistics / data gradient, kernel events, which read about 3 us high;

@@ -115,3 +115,27 @@ def test_few_pixels_of_tiny_maps_keep_the_fp32_convolution(monkeypatch, n, h, w,
     chosen = pb.workspace_bytes(t, s)
     monkeypatch.setenv("PBKD_CONV_SPLIT", "0")
     assert (chosen == pb.workspace_bytes(t, s)) == fp32
+
+
+def test_split_weights_that_do_not_fit_their_index_keep_the_fp32_kernels(monkeypatch):
+    """Split copies take 6 bytes a weight and are addressed in 32 bits (a 3x3 image, a 1x1 image) or, all of a student's
+    together, in 31 bits of 2-byte units.  Sizes past that are still accepted, with the fp32 copies."""
+    # a teacher's 3x3 layer of 9600 x 9600 channels: 5.5 GB split, 3.3 GB in fp32 (the workspace tells which is kept)
+    small = wl.Arch(1, 9600, 5, 5, [wl.Layer(wl.DWSEP3X3, 9600, 9600, 1, 1)])
+    t = wl.Arch(1, 9600, 5, 5, [wl.Layer(wl.CONV3X3, 9600, 9600, 1, 0)])
+    chosen = pb.workspace_bytes(t, small)
+    monkeypatch.setenv("PBKD_CONV_SPLIT", "0")
+    assert chosen == pb.workspace_bytes(t, small) > 0
+    monkeypatch.delenv("PBKD_CONV_SPLIT")
+
+    # 1x1 weights: the workspace grows with them while the kind of copy stays the same, by less where it changes.  A teacher
+    # keeps one image a layer (4 GiB split at 26752 x 26752), a student two copies in one arena (2^30 floats at 18944 x 18944).
+    def workspace(tc, sc):
+        return pb.workspace_bytes(wl.Arch(1, tc, 1, 1, [wl.Layer(wl.DWSEP3X3, tc, tc, 1, 0)]), wl.Arch(1, sc, 1, 1, [wl.Layer(wl.DWSEP3X3, sc, sc, 1, 1)]))
+
+    def per_weight(c):
+        return workspace(c, c) / c ** 2
+
+    split, past_arena = per_weight(16384), per_weight(20480)
+    assert 3.5 < split - past_arena < 4.5                # two student copies of 4 bytes a weight instead of 6
+    assert 1.5 < past_arena - per_weight(28672) < 2.5    # and the teacher's

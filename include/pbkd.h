@@ -45,13 +45,12 @@
  *   PBKD_TEACHER_LAG=1      pbkd_distill_step on two streams, eager: a call's teacher starts only when the student step
  *                           before the previous one has ended (default: as early as its dependencies allow); same
  *                           results, another overlap (read at every call)
- *   PBKD_PW_VARIANT=0..9, 13..22  1x1 convolution.  On the fp32 matrix cores: 0-3 scalar kernel (channel blocks x pixel
+ *   PBKD_PW_VARIANT=0..15   1x1 convolution.  On the fp32 matrix cores: 0-3 scalar kernel (channel blocks x pixel
  *                           blocks per wave = 4x2, 4x1, 2x2, 2x1), 4-9 vector kernel (waves over channels x waves over
  *                           pixels, pixels per lane = 4x1x4, 4x1x2, 2x2x4, 2x2x2, 1x4x4, 1x4x2).  On the bf16 matrix
  *                           cores from operands split three ways, as described at PBKD_CONV_SPLIT (at least 16 input
- *                           channels, tensors below 4 GiB; the default there): 13-19 channel blocks of 32 x pixels per
- *                           lane = 4x1, 2x1, 1x1, 2x2, 1x2, 2x4, 1x4, 20-22 with K split over a workgroup's waves 2x2,
- *                           2x1, 1x1
+ *                           channels, tensors below 4 GiB; the default there): 10-13 channel blocks of 32 x pixels per
+ *                           lane = 2x1, 1x1, 2x2, 1x2, 14-15 with K split over a workgroup's waves 2x1, 1x1
  *   PBKD_WGRAD_VARIANT=0..3 pointwise weight gradient tile: bit 1 = 64 (else 128) rows, bit 0 = 64 (else 128) columns
  *   PBKD_CF_TH=4|8          first-layer 3x3 convolution (at most three input channels): rows of a workgroup's tile
  *   PBKD_CF_OCC=1..8        same kernel: workgroups per compute unit its persistent grid is sized for (default 4)

@@ -325,7 +325,7 @@ struct PwGeom {
 };
 // split: false keeps to the fp32 kernels
 PwGeom pw_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, bool split = true);
-constexpr int kPwSplitFirst = 13;
+constexpr int kPwSplitFirst = 10;
 // Split weights: [32-channel block][chunk of 16 input channels][piece 0..2][lane][8 bf16], lane l = row l%32, channels
 // 8*(l/32)..+7 of the chunk.  A ragged last chunk starts at channel K-16; what it shares with the chunk before is zero.
 constexpr int kPwSplitPiece = 512;       // bf16 values from one piece of a weight to the next

@@ -23,8 +23,8 @@
 namespace pbkd {
 
 namespace {
-// chunks of weights per LDS stage of pw_split_kernel: 48 KB, three workgroups per compute unit
-constexpr int pw_split_stage(int mb) { return mb == 4 ? 4 : 8; }
+// chunks of weights per LDS stage of pw_split_kernel: 48 KB for 64 channels, three workgroups per compute unit
+constexpr int kStage = 8;
 
 template <int VW> struct PixVec;
 template <> struct PixVec<1> {
@@ -148,11 +148,10 @@ __device__ __forceinline__ float plain_sum(const PwArgs &p, int o, long long g) 
   return s;
 }
 
-// sum over a group of GPR = 8, 16 or 32 neighbouring lanes
+// sum over a group of GPR = 8 or 32 neighbouring lanes
 template <int GPR>
 __device__ __forceinline__ float group_sum(float v) {
   if (GPR == 32) return half32_sum(v);
-  if (GPR == 16) return row16_sum(v);
   v += dpp_mov<0xB1>(v);
   v += dpp_mov<0x4E>(v);
   return v + dpp_mov<0x141>(v);
@@ -170,7 +169,7 @@ __device__ __forceinline__ float group_sum(float v) {
 template <int MB, int VW, int SV>
 __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
   constexpr int D = 2;                         // chunks of activations in flight
-  constexpr int ST = pw_split_stage(MB);
+  constexpr int ST = kStage;
   typedef typename PixVec<VW>::type vec_t;
   extern __shared__ float smem[];
   StatPart *const red = reinterpret_cast<StatPart *>(smem);               // [4 waves][32*MB]
@@ -504,8 +503,8 @@ __global__ __launch_bounds__(256) void pw_split_kwaves_kernel(PwArgs p) {
   }
 }
 
-// Variants kPwSplitFirst + i: i = 0..6 pw_split_kernel<MB, VW>, 7..9 pw_split_kwaves_kernel<MB, VW>
-static const int kMB[10] = {4, 2, 1, 2, 1, 2, 1, 2, 2, 1}, kVW[10] = {1, 1, 1, 2, 2, 4, 4, 2, 1, 1};
+// Variants kPwSplitFirst + i: i = 0..3 pw_split_kernel<MB, VW>, 4 and 5 pw_split_kwaves_kernel<MB, VW>
+static const int kMB[6] = {2, 1, 2, 1, 2, 1}, kVW[6] = {1, 1, 2, 2, 1, 1};
 
 bool pw_split_ok(int N, int Cin, int Cout, int HWin, int Ho, int Wo) {
   return Cin >= 16 && (unsigned long long)N * Cin * HWin * sizeof(float) < (1ull << 32) &&
@@ -532,12 +531,12 @@ bool pw_split_ok(int N, int Cin, int Cout, int HWin, int Ho, int Wo) {
 //   32 -> 32, 32x32 x 128:      9.9           9.2    8.6
 int pw_split_choice(long long P, int Cout, int HW, int stride) {
   auto wgs = [&](int i) {
-    const long long px = (i < 7 ? 4ll : 1ll) * 32 * kVW[i];
+    const long long px = (i < 4 ? 4ll : 1ll) * 32 * kVW[i];
     return (long long)cdiv(Cout, 32 * kMB[i]) * ((P + px - 1) / px);
   };
-  if (wgs(3) >= 1024 && pw_split_fits(3, HW, stride)) return Cout > 32 ? 3 : 4;
-  if (wgs(1) >= 256) return Cout > 32 ? 1 : 2;
-  return Cout > 32 && wgs(8) >= 256 ? 8 : 9;
+  if (wgs(2) >= 1024 && pw_split_fits(2, HW, stride)) return Cout > 32 ? 2 : 3;
+  if (wgs(0) >= 256) return Cout > 32 ? 0 : 1;
+  return Cout > 32 && wgs(4) >= 256 ? 4 : 5;
 }
 
 PwGeom pw_split_geom(int i, int N, int Cin, int Cout, int Ho, int Wo) {
@@ -549,15 +548,15 @@ PwGeom pw_split_geom(int i, int N, int Cin, int Cout, int Ho, int Wo) {
   g.bm = 32 * kMB[i];
   g.mtiles = cdiv(Cout, g.bm);
   g.nchunks = cdiv(Cin, 16);
-  const long long px = (i < 7 ? 4ll : 1ll) * 32 * kVW[i];
+  const long long px = (i < 4 ? 4ll : 1ll) * 32 * kVW[i];
   g.n_ptiles = (int)((P + px - 1) / px);
   const size_t tile = (size_t)4 * 32 * (32 * kVW[i] + 4) * sizeof(float);   // one block of 32 channels of each of four waves
-  const size_t weights = (size_t)kMB[i] * pw_split_stage(kMB[i]) * 3072;
-  g.lds_bytes = i < 7 ? (size_t)4 * g.bm * sizeof(StatPart) + (weights > tile ? weights : tile) : kMB[i] * tile;
+  const size_t weights = (size_t)kMB[i] * kStage * 3072;
+  g.lds_bytes = i < 4 ? (size_t)4 * g.bm * sizeof(StatPart) + (weights > tile ? weights : tile) : kMB[i] * tile;
   return g;
 }
 
-bool pw_split_fits(int i, int HW, int stride) { return i >= 0 && i < 10 && (kVW[i] == 1 || (stride == 1 && HW % kVW[i] == 0)); }
+bool pw_split_fits(int i, int HW, int stride) { return i >= 0 && i < 6 && (kVW[i] == 1 || (stride == 1 && HW % kVW[i] == 0)); }
 
 namespace {
 // SV: pixels per store, four where rows of pixels allow it
@@ -571,7 +570,7 @@ hipError_t split_attr() {
 template <int K, int MB, int VW>
 hipError_t split_init() {
   hipError_t e = split_attr<K, MB, VW, 4>();
-  if (VW == 4 || e != hipSuccess) return e;
+  if (e != hipSuccess) return e;
   return split_attr<K, MB, VW, VW>();
 }
 template <int K, int MB, int VW>
@@ -589,14 +588,10 @@ void split_go(const PwArgs &a, hipStream_t s) {
 
 hipError_t init_pw_split_attributes() {
   hipError_t e;
-  if ((e = split_init<0, 4, 1>()) != hipSuccess) return e;
   if ((e = split_init<0, 2, 1>()) != hipSuccess) return e;
   if ((e = split_init<0, 1, 1>()) != hipSuccess) return e;
   if ((e = split_init<0, 2, 2>()) != hipSuccess) return e;
   if ((e = split_init<0, 1, 2>()) != hipSuccess) return e;
-  if ((e = split_init<0, 2, 4>()) != hipSuccess) return e;
-  if ((e = split_init<0, 1, 4>()) != hipSuccess) return e;
-  if ((e = split_init<1, 2, 2>()) != hipSuccess) return e;
   if ((e = split_init<1, 2, 1>()) != hipSuccess) return e;
   return split_init<1, 1, 1>();
 }
@@ -610,15 +605,11 @@ hipError_t launch_pw_split(const PwArgs &a, hipStream_t s) {
       (reinterpret_cast<uintptr_t>(a.in) & 15) || (reinterpret_cast<uintptr_t>(a.out) & 15))
     return hipErrorInvalidValue;
   switch (i) {
-    case 0: split_go<0, 4, 1>(a, s); break;
-    case 1: split_go<0, 2, 1>(a, s); break;
-    case 2: split_go<0, 1, 1>(a, s); break;
-    case 3: split_go<0, 2, 2>(a, s); break;
-    case 4: split_go<0, 1, 2>(a, s); break;
-    case 5: split_go<0, 2, 4>(a, s); break;
-    case 6: split_go<0, 1, 4>(a, s); break;
-    case 7: split_go<1, 2, 2>(a, s); break;
-    case 8: split_go<1, 2, 1>(a, s); break;
+    case 0: split_go<0, 2, 1>(a, s); break;
+    case 1: split_go<0, 1, 1>(a, s); break;
+    case 2: split_go<0, 2, 2>(a, s); break;
+    case 3: split_go<0, 1, 2>(a, s); break;
+    case 4: split_go<1, 2, 1>(a, s); break;
     default: split_go<1, 1, 1>(a, s); break;
   }
   return hipGetLastError();

@@ -51,6 +51,12 @@ def conv_split_in_use():
     return os.environ.get("PBKD_CONV_SPLIT", "") != "0"
 
 
+def pointwise_split_in_use(w):
+    """Whether the student's 1x1 convolutions form their products that way too: from 16 channels on, in both directions."""
+    from paper_2012_03096_amd import workloads as wl
+    return all(min(l.cin, l.cout) >= 16 for l in w.student.layers if l.kind == wl.DWSEP3X3)
+
+
 HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of a kernel (reads + writes) from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this benchmark,
 # scaled by what the same counters read for a device copy of known size: written by
@@ -281,7 +287,9 @@ def run_block(args, w, kernel_roofline=True):
                 if wk["flops"]:
                     rec["flops_per_step"] = wk["flops"]
                     rec["TFLOPps"] = round(wk["flops"] / sec / 1e12, 2)
-                    rec["frac_of_mfma_peak"] = round(wk["flops"] / sec / 1e12 / MFMA_F32_PEAK_TFLOPS, 4)
+                    peak = MFMA_SPLIT_PEAK_TFLOPS if kind in ("conv1x1_mfma", "pw_dgrad_mfma") and pointwise_split_in_use(w) else MFMA_F32_PEAK_TFLOPS
+                    rec["mfma_peak_TFLOPps"] = peak
+                    rec["frac_of_mfma_peak"] = round(wk["flops"] / sec / 1e12 / peak, 4)
             roof["per_kind"][kind] = rec
     blk.close()
     del blk, xd, td
@@ -328,6 +336,7 @@ def hbm_list(w, roof):
                 "frac": rec["frac_of_hbm_peak"], "traffic": measured_traffic(w.name, kind)}
         if "TFLOPps" in rec:
             item["TFLOPps"] = rec["TFLOPps"]
+            item["mfma_peak_TFLOPps"] = rec["mfma_peak_TFLOPps"]
             item["frac_of_mfma_peak"] = rec["frac_of_mfma_peak"]
         out.append(item)
     return out

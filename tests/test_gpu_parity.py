@@ -1292,3 +1292,50 @@ def test_inference_on_any_map(gpu, n, h, w_, chans):
             assert relerr(o.cpu().numpy(), r) <= ACT_TOL, (mask, i, relerr(o.cpu().numpy(), r))
     for b in blocks:
         b.close()
+
+
+def test_offsets_past_two_gib(gpu):
+    """Tensors of 3.9 GB (300 images of 64 channels, 225x225, no aligned rows): teacher's 3x3 and student's depthwise and 1x1
+    kernels address them with 32-bit byte offsets.  Running statistics keep images apart, so the first, one across the
+    2 GiB line and the last are compared with the same images alone; and the weight gradients of 160 images (2.07 GB,
+    the largest the grouped kernel takes) that repeat two must be those of the two."""
+    torch, pb = gpu
+    c, h = 64, 225
+
+    def block(n, seed):
+        t, s = wl.Arch(n, c, h, h, wl._convs([c, c])), wl.Arch(n, c, h, h, wl._dws([c, c]))
+        w = wl.Workload("offsets", wl.Arch(1, c, 8, 8, t.layers), wl.Arch(1, c, 8, 8, s.layers), seed=seed)
+        _, tp, sp = w.tensors(random_affine=True)
+        return pb.Block(t, tp, s, sp)
+
+    def forward(x):
+        blk = block(x.shape[0], 71)
+        outs = []
+        for use in (0, 1):
+            out = torch.empty_like(x)
+            pb.network_forward([blk], [use], x, [out], bn_mode=1)
+            torch.cuda.synchronize()
+            outs.append(out)
+        blk.close()
+        return outs
+
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((300, c, h, h), generator=gen, device="cuda")
+    some = [0, 165, 166, 299]                      # (image 165 holds byte 2^31)
+    assert 165 * c * h * h * 4 < 2 ** 31 <= 166 * c * h * h * 4
+    large, small = forward(x), forward(x[some].contiguous())
+    for l, s in zip(large, small):
+        assert relerr(l[some].cpu().numpy(), s.cpu().numpy()) <= 1e-6
+    del large, small
+    grads = []
+    for n in (2, 160):
+        blk = block(n, 72)
+        xn = x[:2].repeat(n // 2, 1, 1, 1)
+        target = torch.linspace(0, 1, h, device="cuda").expand(n, c, h, h).contiguous()
+        blk.student_step(xn, target, 0.0)
+        grads.append([g for layer in blk.student_grads() for g in layer])
+        blk.close()
+        del xn, target
+    for a, b in zip(*grads):
+        assert relerr(b, a) <= GRAD_TOL
+    torch.cuda.empty_cache()

@@ -34,12 +34,17 @@
  * environment variables and lets them replace the kernel variant the library would pick from the layer's shape;
  * a value that does not fit the shape is ignored:
  *   PBKD_CONV_TILE=0..3     workgroup tile of the 3x3 convolution: 128 ch x 128 px, 64 x 256, 64 x 128, 64 x 64
- *   PBKD_CONV_KSPLIT=n      3x3 convolution on whole-image tiles: K = 9*Cin split over n workgroups
+ *   PBKD_CONV_KSPLIT=n      3x3 convolution on whole-image tiles: K = 9*Cin split over n workgroups (not the stacked rows)
  *   PBKD_CONV_SPLIT=0       the teacher's 3x3 convolutions on the fp32 matrix cores.  Default: on the bf16 matrix cores,
  *                           every fp32 operand written exactly as the sum of three bf16 terms and every product formed
  *                           from six of the nine cross terms (the three left out are at most 2^-24 of the product, 2^-27 rms), fp32
  *                           accumulation; measured against the fp64 oracle it is within 1.2x of the fp32 kernel's error.
+ *                           On maps whose rows are not whole 16-byte groups (tiles of the stacked rows of all images) a
+ *                           chunk's products are summed apart and the error is below the fp32 kernel's, and infinities
+ *                           and numbers above 3.39e38 give what fp32 products give (elsewhere NaN).  At most eight input
+ *                           channels, few pixels of tiny maps and weight images of 4 GiB stay on the fp32 matrix cores.
  *                           Read when a block is created.
+ *   PBKD_CONV_ROWS=1        the stacked rows for every teacher 3x3 convolution they can take
  *   PBKD_SPLIT_WGS=n        that kernel is persistent, one workgroup per compute unit: launch n workgroups instead and
  *                           leave the other compute units to the kernels of other streams (read at every launch)
  *   PBKD_TEACHER_LAG=1      pbkd_distill_step on two streams, eager: a call's teacher starts only when the student step
@@ -48,8 +53,8 @@
  *   PBKD_PW_VARIANT=0..15   1x1 convolution.  On the fp32 matrix cores: 0-3 scalar kernel (channel blocks x pixel
  *                           blocks per wave = 4x2, 4x1, 2x2, 2x1), 4-9 vector kernel (waves over channels x waves over
  *                           pixels, pixels per lane = 4x1x4, 4x1x2, 2x2x4, 2x2x2, 1x4x4, 1x4x2).  On the bf16 matrix
- *                           cores from operands split three ways, as described at PBKD_CONV_SPLIT (at least 16 input
- *                           channels, tensors below 4 GiB; the default there): 10-13 channel blocks of 32 x pixels per
+ *                           cores from operands split three ways, as described at PBKD_CONV_SPLIT for stacked rows (at least 16
+ *                           input channels, tensors below 4 GiB; the default there): 10-13 channel blocks of 32 x pixels per
  *                           lane = 2x1, 1x1, 2x2, 1x2, 14-15 with K split over a workgroup's waves 2x1, 1x1
  *   PBKD_WGRAD_VARIANT=0..3 pointwise weight gradient tile: bit 1 = 64 (else 128) rows, bit 0 = 64 (else 128) columns
  *   PBKD_CF_TH=4|8          first-layer 3x3 convolution (at most three input channels): rows of a workgroup's tile

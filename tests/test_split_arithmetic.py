@@ -1,8 +1,7 @@
 """The arithmetic the teacher's bf16-split convolution relies on, checked on the CPU with numpy: an fp32 number is
 exactly the sum of three bf16 numbers obtained by rounding to nearest three times, and the six cross products the
 kernel forms differ from the exact product by at most 2^-24 of it (2^-27 rms, no bias): no more than the rounding of
-one fp32 operation.  (The GPU kernel and the host routine that splits
-the weights do these steps in hardware / in C++; this file pins the claim itself, independent of both.)"""
+one fp32 operation.  (The GPU kernels do these steps in hardware; this file pins the claim itself, independent of them.)"""
 import numpy as np
 
 
@@ -100,7 +99,7 @@ def test_dot_product_by_six_bf16_products_matches_fp32_accuracy():
 
 def test_ninth_tap_pairing_covers_the_six_products_once():
     # The ninth tap's products are paired by piece, two per MFMA (the half-waves supply different pieces): the tables
-    # the host packer and the kernel share must name every (weight piece, activation piece) with i + j <= 2 exactly once.
+    # the packing kernel and the convolution share must name every (weight piece, activation piece) with i + j <= 2 exactly once.
     import os
     import re
     here = os.path.dirname(os.path.abspath(__file__))

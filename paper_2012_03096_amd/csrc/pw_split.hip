@@ -164,7 +164,8 @@ __device__ __forceinline__ float group_sum(float v) {
 // With one pixel per lane a stage's chunks (128 channels) are summed from zero and added to the running sum: long sums over few
 // pixels were split four ways on the fp32 matrix cores, and one running sum leaves more error than that (rms against fp64
 // at 433 -> 169 channels, 41x48, batch 7: 1.9e-7 then, 3.3e-7 with one sum, 1.7e-7 so; a sum every 32 channels 1.1e-7 but
-// 28 us for 23).  With two pixels a lane (many pixels: no sum was split) one running sum rounds 6 times per 16
+// 28 us for 23).  One block of 32 channels, where sums from 128 channels on were split, can afford a sum every 32 channels
+// (128 -> 24 at 32x34, batch 32: 1.2e-7 then, 1.7e-7 with one sum, 0.9e-7 so).  With two pixels a lane (many pixels: no sum was split) one running sum rounds 6 times per 16
 // channels, fp32 multiply-adds 16 times.
 template <int MB, int VW, int SV>
 __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[e][mb][r] = 0.f;
 
-  floatx16 sum[MB];                            // VW == 1: of this stage's chunks
+  floatx16 sum[MB];                            // VW == 1: of this stage's chunks (MB == 1: of two chunks)
   auto clear_sum = [&]() {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -276,6 +277,7 @@ __global__ __launch_bounds__(256) void pw_split_kernel(PwArgs p) {
       weights(c + 1, w1);
       chunk(0, s0 + c, w0);
       chunk(1, s0 + c + 1, w1);
+      if (MB == 1) add_sum();
     }
     if (c < ns) {                              // an odd number of chunks: only in the last stage
       uintx4 w0[MB][3];
@@ -524,7 +526,8 @@ bool pw_split_ok(int N, int Cin, int Cout, int HWin, int Ho, int Wo) {
 //   512 -> 512, 4x4 x 128:     21.5/20.5                     21.8/20.7    14.2/13.3
 //   512 -> 512, 2x2 x 128:     12.6/10.8                     23.1/20.7    11.2/10.7    32 ch x 32 px 9.9/9.4
 // So: 64 x 4*64 pixels where that is four workgroups or more per compute unit (its wider rows reach HBM's rate), else
-// 64 x 4*32 while every compute unit gets one, else K over the waves.  32 channels where there are no more of them (median of
+// 64 x 4*32 while every compute unit gets one (of 128 x 64 too: where it does not, sums from 128 channels on have always been
+// in four parts), else K over the waves.  32 channels where there are no more of them (median of
 // both directions from a kernel trace; fp32 kernel, 64 ch x 4 x 64 px, 32 ch x 4 x 64 px, 32 ch x 4 x 32 px):
 //   16 -> 16, 112x112 x 32:    16.8   19.2   13.1   15.0
 //   32 -> 32, 112x112 x 32:    24.0   26.2   20.1   21.5
@@ -535,7 +538,7 @@ int pw_split_choice(long long P, int Cout, int HW, int stride) {
     return (long long)cdiv(Cout, 32 * kMB[i]) * ((P + px - 1) / px);
   };
   if (wgs(2) >= 1024 && pw_split_fits(2, HW, stride)) return Cout > 32 ? 2 : 3;
-  if (wgs(0) >= 256) return Cout > 32 ? 0 : 1;
+  if (wgs(0) >= 256 && cdiv(Cout, 128) * ((P + 63) / 64) >= 256) return Cout > 32 ? 0 : 1;
   return Cout > 32 && wgs(4) >= 256 ? 4 : 5;
 }
 

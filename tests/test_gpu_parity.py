@@ -383,7 +383,8 @@ def fp32_matrix_product(P, u, parts):
 
 
 @pytest.mark.parametrize("n,h,w_,ci,co,parts", [(7, 41, 48, 433, 169, 4), (21, 14, 14, 512, 512, 4), (16, 4, 4, 512, 512, 4), (33, 16, 16, 128, 130, 1),
-                                                (8, 27, 23, 67, 100, 1), (4, 13, 11, 16, 24, 1), (20, 41, 48, 64, 33, 1), (130, 32, 32, 160, 64, 1)])
+                                                (8, 27, 23, 67, 100, 1), (4, 13, 11, 16, 24, 1), (20, 41, 48, 64, 33, 1), (130, 32, 32, 160, 64, 1),
+                                                (32, 32, 34, 128, 24, 4), (8, 17, 40, 128, 328, 4), (33, 32, 34, 180, 32, 4)])
 def test_pointwise_split_leaves_no_larger_error_than_fp32_products(gpu, n, h, w_, ci, co, parts):
     """rms error of the 1x1 kernel the library chooses, against fp64 on its own input, for 400 of its
     pixels: not larger than that of fp32 multiply-adds summed in `parts` parts (4: as the fp32 kernels did with long sums

@@ -44,6 +44,9 @@
  *                           and numbers above 3.39e38 give what fp32 products give (elsewhere NaN).  At most eight input
  *                           channels, few pixels of tiny maps and weight images of 4 GiB stay on the fp32 matrix cores.
  *                           Read when a block is created.
+ *   PBKD_CONV_WINO=0|1      transformed 2x2 tiles (F(2x2, 3x3)) for no / for every teacher 3x3 convolution of stride 1 that they can
+ *                           take (at least 16 input channels).  Default: on aligned maps where they are priced well below
+ *                           the direct kernel; fp32 operands split three ways as described at PBKD_CONV_SPLIT
  *   PBKD_CONV_ROWS=1        the stacked rows for every teacher 3x3 convolution they can take
  *   PBKD_SPLIT_WGS=n        that kernel is persistent, one workgroup per compute unit: launch n workgroups instead and
  *                           leave the other compute units to the kernels of other streams (read at every launch)

@@ -95,7 +95,7 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
     if (want > g.nchunks) want = g.nchunks;
     if (want > 1) g.ksplit = (int)want;
   }
-  g.rows = false;
+  g.rows = g.wino = false;
   g.TW = g.TH = g.SH = 0;
   g.stat_parts = g.n_ptiles;
   g.kchunks = cdiv(g.nchunks, g.ksplit);
@@ -254,6 +254,7 @@ hipError_t init_conv_attributes() {
   if ((e = conv_tile1_init()) != hipSuccess) return e;
   if ((e = conv_tile2_init()) != hipSuccess) return e;
   if ((e = conv_tile3_init()) != hipSuccess) return e;
+  if ((e = conv_wino_init()) != hipSuccess) return e;
   return conv_split_init();
 }
 

@@ -112,6 +112,7 @@ __global__ __launch_bounds__(256) void conv_split_pack_kernel(const float *w, ui
 }  // namespace
 
 hipError_t launch_conv_split_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s) {
+  if (g.wino) return launch_conv_wino_pack(w, wpk, g, Cout, Cin, s);
   if (!g.split || (g.rows && Cin < 9) || g.nchunks > 65535) return hipErrorInvalidValue;
   const int M = g.mtiles * g.bm;
   hipLaunchKernelGGL(conv_split_pack_kernel, dim3(cdiv(M, 256), g.nchunks), dim3(256), 0, s, w, reinterpret_cast<uintx4 *>(wpk),
@@ -129,6 +130,7 @@ hipError_t conv_split_init() {
 
 hipError_t launch_conv_split(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (!a.g.split || a.g.lds_bytes > (size_t)MAX_LDS) return hipErrorInvalidValue;
+  if (a.g.wino) return launch_conv_wino(a, s, e0, e1);
   if (!a.g.rows && (!conv_split_fits_width(a.g, a.H, a.W, a.stride) || a.g.raw_rounds > conv_split_rounds_max(conv_bslots_for(a.g.PLd)) ||
                     a.g.raw_w % 4 != 0))
     return hipErrorInvalidValue;

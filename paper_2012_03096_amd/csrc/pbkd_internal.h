@@ -220,6 +220,7 @@ struct ConvGeom {
   int raw_lead;            // columns a raw row starts left of the tile's first column: 4, or 0 where a tile is as wide as the map
   bool rows;               // split kernel on tiles of TH x TW pixels of the stacked rows of all images (conv_rows_kernel.h): any map
   int TW, TH, SH;          // rows: tile columns and rows; staged rows an image takes in the stack
+  bool wino;               // products of transformed 2x2 tiles (conv_wino_kernel.h): TW, TH count such tiles; IWS: pitch of one column parity
   int stat_parts;          // statistics partials per channel: one per pixel tile, or per group of nimg images where K is split
   int raw_plane;           // 1: a tile is whole images (stride 1) and a raw "row" is a whole channel plane of raw_w = H*W values
   size_t lds_bytes;
@@ -266,6 +267,23 @@ constexpr int conv_rows_positions(int slots) { return (slots <= 2 ? 512 : 256 * 
 constexpr size_t conv_rows_lds_bytes(int bm, int bn, int wgn, int slots) {
   return (size_t)96 * conv_rows_positions(slots) + (size_t)4 * bm * (bn + 4) + (size_t)16 * wgn * bm + 1536;
 }
+// F(2x2, 3x3) (conv_wino_kernel.h).  Weight image: [channel tile of 64][chunk of 16 input channels][position 4 i + j][channel block]
+// [piece][lane][8] of bf16.  LDS: two copies of a chunk's staged positions (a quad of channels has room for kWinoPositions, the last
+// is never read), the output transform's exchange [4 waves][2][32 channels][68], the tile table, a finished tile's places.
+constexpr int kWinoChunkBytes = 16 * 6 * 1024;
+constexpr int kWinoPositions = 656;
+constexpr int kWinoExchangeFloats = 8 * 32 * 68;
+constexpr size_t kWinoLdsBytes = 128 * kWinoPositions + 4 * kWinoExchangeFloats + 1536 + 512;
+inline size_t conv_wino_pack_floats(const ConvGeom &g) { return (size_t)g.mtiles * g.nchunks * (kWinoChunkBytes / 4); }
+// The cheapest geometry for a stride-1 convolution, and its price in shader cycles; false where the kernel cannot run it (fewer than
+// 16 input channels, 32-bit offsets).
+bool conv_wino_geom(int N, int Cin, int Cout, int Ho, int Wo, ConvGeom &g, double &cycles);
+// what the aligned split kernel costs with geometry g, in the same cycles
+double conv_split_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo);
+struct ConvArgs;
+hipError_t launch_conv_wino(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_conv_wino_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s);
+hipError_t conv_wino_init();
 // w: canonical [Cout][Cin][9] on the device -> the kernel's weight image
 hipError_t launch_conv_split_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s);
 // Weights are handed to the kernel re-packed as the exact LDS image of every (channel tile, chunk of 8

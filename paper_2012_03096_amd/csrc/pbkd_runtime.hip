@@ -153,7 +153,7 @@ struct Net {
 // packed copies of a layer's convolution weights: the one for the forward pass, and a student's of both passes
 size_t pack_floats_fwd(const LayerRT &r) {
   if (r.taps != 9) return pw_pack_floats(r.pg);
-  return r.cg.split ? conv_split_pack_floats(r.cg) : conv_pack_floats(r.cg);
+  return r.cg.wino ? conv_wino_pack_floats(r.cg) : r.cg.split ? conv_split_pack_floats(r.cg) : conv_pack_floats(r.cg);
 }
 size_t student_packed_floats(const Net &net) {
   size_t n = net.shortcut == 1 ? pack_floats_fwd(net.sc) : 0;
@@ -211,6 +211,22 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
       if (!student && !env_is("PBKD_CONV_SPLIT", 0) && ((!r.cg.split && !fp32_stays) || env_is("PBKD_CONV_ROWS", 1))) {
         ConvGeom rows{};
         if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, rows)) r.cg = rows;
+      }
+      // Aligned maps at stride 1: transformed 2x2 tiles where the price of the aligned kernel is 1.4 times theirs.  The prices
+      // tell the faster of the two on a hundred shapes from 1x12x12 to 91x68x80, 16 to 504 channels (256 channels at 56x56, batch
+      // 32, 562 -> 377 us a call; 64 at 8x8, batch 16, 13 and 23: start-up); 1.4, because the transformed tiles' workgroups fill
+      // a compute unit and a student on a second stream gets nothing beside them: 64 channels at 224x224, priced 1.33, are 4 %
+      // faster on one stream (2 325 -> 2 237 us a step) and 2 % slower on two (2 126 -> 2 168).  The stacked rows stay where they
+      // are: their sums in two levels are more accurate.  PBKD_CONV_WINO=1 takes the transformed tiles wherever they can run, 0
+      // nowhere; another forced geometry of the 3x3 convolution leaves them out.
+      const bool forced = std::getenv("PBKD_CONV_TILE") || std::getenv("PBKD_CONV_KSPLIT") || std::getenv("PBKD_CONV_ROWS");
+      if (!student && d.stride == 1 && !env_is("PBKD_CONV_SPLIT", 0) && !env_is("PBKD_CONV_WINO", 0) &&
+          (env_is("PBKD_CONV_WINO", 1) || (r.cg.split && !r.cg.rows && !forced))) {
+        ConvGeom g{};
+        double cycles = 0;
+        if (conv_wino_geom(a->n, d.cin, d.cout, r.hout, r.wout, g, cycles) &&
+            (env_is("PBKD_CONV_WINO", 1) || 1.4 * cycles < conv_split_cycles(r.cg, a->n, d.cout, r.hout, r.wout)))
+          r.cg = g;
       }
       r.cw = cw_geom(a->n, d.cin, r.hout, r.wout, d.stride);
       r.first_conv = (l == 0) && conv_first_ok(d.cin, d.stride) &&

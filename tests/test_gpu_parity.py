@@ -782,6 +782,61 @@ def test_stacked_rows_infinities(gpu, monkeypatch, n, h, w_, chans, strides, til
     blk.close()
 
 
+# whole-image, several and ragged workgroup tiles (a tile has 64 2x2 output tiles), odd heights and widths (half-empty 2x2 tiles;
+# 16-, 8- and 4-byte stores), images that end inside a workgroup tile, a last chunk of 16 channels that reaches back, K split
+# (7x7, 4x4), maps of one row, one column and more than 128 rows
+TRANSFORMED = [(3, (40, 72, 33), 14, 14), (4, (67, 100, 67), 27, 23), (5, (300, 130, 20), 7, 7), (2, (17, 16, 70), 5, 131), (6, (18, 20, 16), 13, 1),
+               (9, (16, 33, 16), 1, 11), (20, (64, 48, 32), 4, 4), (2, (48, 64, 65), 16, 32), (1, (16, 31, 16), 150, 3), (3, (32, 16, 16), 40, 36),
+               (33, (16, 64, 16), 2, 2), (1, (16, 128, 128), 12, 16)]
+
+
+@pytest.mark.parametrize("wgs", [0, 1, 3])
+@pytest.mark.parametrize("n,chans,h,w_", TRANSFORMED)
+def test_transformed_tiles_on_any_map(gpu, monkeypatch, n, chans, h, w_, wgs):
+    """Teacher forward on transformed 2x2 tiles, forced: every layer's pre-activation and statistics against the fp64 oracle at
+    ACT_TOL, with a workgroup per tile and with one and three workgroups that walk all of them."""
+    monkeypatch.setenv("PBKD_CONV_WINO", "1")
+    test_split_convolution_on_any_map(gpu, monkeypatch, n, chans, h, w_, (1, 1), wgs)
+
+
+@pytest.mark.parametrize("n,h,w_,chans", [(6, 13, 11, (16, 19, 40)), (9, 7, 7, (64, 200, 96)), (4, 8, 12, (48, 32, 130)), (40, 2, 2, (48, 64, 64))])
+def test_transformed_tiles_infinities(gpu, monkeypatch, n, h, w_, chans):
+    """Infinities and numbers past bfloat16's largest through the transformed tiles: what plain products make of them, also in the
+    outputs that share a window with one without depending on it."""
+    monkeypatch.setenv("PBKD_CONV_WINO", "1")
+    test_stacked_rows_infinities(gpu, monkeypatch, n, h, w_, chans, (1, 1), -1)
+
+
+@pytest.mark.parametrize("kind", ["plain", "small_variance", "large_channel_off", "large_mean"])
+@pytest.mark.parametrize("n,h,w_,chans", [(24, 16, 16, (128, 256, 96)), (2, 56, 56, (64, 64, 64)), (64, 4, 4, (512, 512, 256)), (3, 36, 40, (118, 48, 32)),
+                                          (8, 12, 20, (16, 32, 24))])
+def test_transformed_tiles_are_no_less_accurate_than_the_direct_kernel(gpu, monkeypatch, n, h, w_, chans, kind):
+    """On the maps where the transformed tiles stand in for the aligned direct kernel their rms error against fp64 must not be
+    the larger one.  A sum's roundings at its own size: 6 per 16 channels for 54, and 1.75 times a sum's error passes through the
+    output transform: 1.75 sqrt(6 / 54) = 0.58 of the direct kernel's, plus what does not grow with the channels (the two
+    roundings of B^T d B and of the transform back, 0.9e-7 in all: as much as 16 channels leave the direct kernel, whose sums
+    are then exact in part: 5 % for that)."""
+    t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+    w = wl.Workload("transformed_accuracy", t, s, seed=27)
+    x, tp, _ = w.tensors(random_affine=True)
+    x = np.maximum(x, 0) + np.float32(30 if kind == "large_mean" else 0)
+    if kind == "small_variance":
+        tp[0][0] = tp[0][0] * np.float32(1e-5)
+        tp[0][2] = np.zeros_like(tp[0][2])
+    if kind == "large_channel_off":
+        tp[1][0] = tp[1][0].copy()
+        tp[1][0][:, 0] *= np.float32(1e6)
+        tp[0][2] = tp[0][2].copy()
+        tp[0][2][0] = -1e3
+    errs = {}
+    for wino in (0, 1):
+        monkeypatch.setenv("PBKD_CONV_WINO", str(wino))
+        errs[wino] = teacher_layer_errors(gpu, w, tp, x)
+    print(f"[transformed tiles accuracy] {kind} {chans} {h}x{w_}: rms error of z0, z1: direct {errs[0]}, transformed {errs[1]}")
+    for a, b in zip(errs[0], errs[1]):
+        assert b <= 1.05 * a, errs
+
+
 def test_batchnorm_parameters_replaced_rescale_the_layer_behind(gpu):
     """pbkd_block_set_tensor on a teacher's gamma and beta, by seven orders of magnitude: the convolution behind follows."""
     torch, pb = gpu

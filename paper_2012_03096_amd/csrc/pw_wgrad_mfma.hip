@@ -17,6 +17,7 @@
 #include <cstdlib>
 
 #include "conv_mfma_kernel.h"
+#include "split_bf16.h"
 
 namespace pbkd {
 
@@ -35,17 +36,52 @@ constexpr int WG_LS = WG_KC + 4;    // LDS row stride in floats
 // dz.  Image and group move on by additions from chunk to chunk (MODE 0 and 1 divide 64-bit numbers per chunk, MODE 0 loads
 // single values), and all loads are 16 bytes, 4-byte aligned, through 32-bit offsets (both tensors at most 2 GiB).
 // 512x512 weights at 14x14, batch 32: 47 -> 41 us; 67x100 at 27x23, batch 77: 40 -> 21.5.
-template <int MBW, int NBW, int MODE>
-__global__ __launch_bounds__(512) void pw_wgrad_kernel(WgradArgs p) {
+//
+// SPLIT (modes 2 and 4): the products from six bf16 ones each, 384 cycles of the matrix pipe per 32 x 32 outputs and chunk for
+// 1 024 in fp32, which was what bound the kernel.  The loaders split and write three bf16 planes, rows of 64 bytes 80 apart: 16
+// lanes' 16-byte operand reads meet every bank once.  Splitting is now the most of it (160 vector instructions per SIMD and chunk:
+// 50 % of the cycles, the matrix pipe 31 %), so eight waves load instead of four, in four register sets.  64 x 64 weights a tile
+// as before: 128 x 128 split a third less per product (512x512 at 14x14, batch 32: 27.7 us for 32.4) but need four times the
+// parts of the sum, which the update kernel reads, and are slower where pixels are few (128x128 at 16x16, batch 128: 15.9 for 11.5).
+// dz's pieces are cut off and u's rounded (conv_wino_kernel.h has why cutting is cheaper; both cut would leave out terms of one sign).
+// A sum is rounded 6 times per 16 pixels where the fp32 products' is 8 times.  Sums that are NaN are formed again in fp32
+// (wgrad_plain_sum): an infinity, a number or a NaN, as plain products have it.
+// Four loaders -> eight, fp32 -> split, us: 512x512 at 14x14, batch 32: 40.5 -> 32.4; 512x512 at 4x4, batch 128: 16.0 -> 14.0;
+// 67x100 at 27x23, batch 77: 21.7 -> 17.7.
+constexpr int wg_threads(bool split) { return split ? 768 : 512; }        // four waves multiply, the others load
+constexpr int kWgSplitRow = 80;                                           // bytes from row to row of a plane
+constexpr int wg_split_copy(int rows) { return 3 * rows * kWgSplitRow; }  // bytes of the three planes of a chunk
+
+// the sum of one output of one split in fp32 multiply-adds (modes 2 and 4: groups of four pixels per image)
+__device__ __forceinline__ float wgrad_plain_sum(const WgradArgs &p, int o, int c, int split) {
+  const int G4 = (p.HW + 3) >> 2;
+  const long long g0 = (long long)split * p.g.chunks_per_split * (WG_KC / 4), g1 = g0 + (long long)p.g.chunks_per_split * (WG_KC / 4);
+  float s = 0.f;
+#pragma unroll 1
+  for (long long g = g0; g < g1 && s == s; ++g) {
+    const int n = (int)(g / G4), px = 4 * (int)(g - (long long)n * G4);
+    if (n >= p.N) break;
+    const float *a = p.dz + ((size_t)n * p.Co + o) * p.HW + px, *b = p.u + ((size_t)n * p.Ci + c) * p.HW + px;
+#pragma unroll 1
+    for (int e = 0; e < 4 && px + e < p.HW; ++e) s = fmaf(a[e], b[e], s);
+  }
+  return s;
+}
+
+template <int MBW, int NBW, int MODE, bool SPLIT = false>
+__global__ __launch_bounds__(wg_threads(SPLIT)) void pw_wgrad_kernel(WgradArgs p) {
+  static_assert(!SPLIT || MODE == 2 || MODE == 4, "");
   constexpr bool VEC = MODE >= 1;
   constexpr int BM = 2 * MBW * 32, BN = 2 * NBW * 32;
   constexpr int BUF = (BM + BN) * WG_LS;
-  constexpr int NA = BM / 32, NBL = BN / 32, NR = NA + NBL;   // 16-byte loads per loader thread and chunk
+  constexpr int RS = (wg_threads(SPLIT) - 256) / 8;           // rows that the loaders take at a time
+  constexpr int NA = BM / RS, NBL = BN / RS, NR = NA + NBL;   // 16-byte loads per loader thread and chunk
+  constexpr int SETS = SPLIT ? 4 : 2;                         // register sets: one is stashed, the others' chunks are on their way
   typedef float f4 __attribute__((ext_vector_type(4)));
   extern __shared__ float smem[];   // [2][BM + BN][WG_LS]
 
   const bool loader = threadIdx.x >= 256;
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
+  const int tid = loader ? threadIdx.x - 256 : threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l31 = lane & 31, lh = lane >> 5;
   const int wm = wave & 1, wn = wave >> 1;
   // the tiles of one split read the same rows of dz and u: the workgroups are renumbered so that they are neighbours
@@ -69,14 +105,14 @@ __global__ __launch_bounds__(512) void pw_wgrad_kernel(WgradArgs p) {
 
   if (loader) {
     // ------------------------------------------------------------------ loader waves
-    const int kq = tid & 7, r0 = tid >> 3;    // which 4 pixels of the chunk; first row (then every 32nd)
+    const int kq = tid & 7, r0 = tid >> 3;    // which 4 pixels of the chunk; first row (then every RS-th)
     size_t rowoff[NR];
     bool rok[NR];
     int tdy[NR], tdx[NR];     // MODE 3: the tap of a "u" row
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const bool isa = j < NA;
-      int row = (isa ? m0 + 32 * j : c0 + 32 * (j - NA)) + r0;
+      int row = (isa ? m0 + RS * j : c0 + RS * (j - NA)) + r0;
       const int lim = isa ? p.Co : p.Ci;
       rok[j] = row < lim;
       if (!rok[j]) row = lim - 1;
@@ -163,7 +199,7 @@ __global__ __launch_bounds__(512) void pw_wgrad_kernel(WgradArgs p) {
             // branch around any load (a group of 32 rows with no tap row in it loads zeros like everything else that
             // does not exist): the loader then knows how many loads are in flight and waits for the older chunk only.
             const int yy = ty + tdy[j];
-            const bool yok = ok && yy >= 0 && yy < H3 && c0 + 32 * (j - NA) < p.Ci;
+            const bool yok = ok && yy >= 0 && yy < H3 && c0 + RS * (j - NA) < p.Ci;
             const int xs = tx + tdx[j];
             const bool le = xs < 0, re = xs + 4 > p.W;
             const unsigned off = ((unsigned)tn * (unsigned)(p.Ci / 9) * (unsigned)HW + (unsigned)(yy * p.W + (le ? 0 : (re ? p.W - 4 : xs)))) * 4u;
@@ -248,27 +284,45 @@ __global__ __launch_bounds__(512) void pw_wgrad_kernel(WgradArgs p) {
           for (int e = 0; e < 4; ++e)
             if (!(((okmask >> e) & 1) && rok[j])) w[e] = 0.f;
         }
-        *reinterpret_cast<f4 *>(dst + (size_t)(32 * j) * WG_LS) = w;    // A rows first, B rows follow at BM
+        if constexpr (SPLIT) {
+          unsigned q[2][3];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            if (j < NA) split3_bf16_cut(w[2 * h], w[2 * h + 1], q[h]);
+            else split3_bf16(w[2 * h], w[2 * h + 1], q[h]);
+          }
+          char *const at = reinterpret_cast<char *>(smem) + (k & 1) * wg_split_copy(BM + BN) + (r0 + RS * j) * kWgSplitRow + 8 * kq;
+#pragma unroll
+          for (int pc = 0; pc < 3; ++pc) *reinterpret_cast<uintx2 *>(at + pc * ((BM + BN) * kWgSplitRow)) = uintx2{q[0][pc], q[1][pc]};
+        } else {
+          *reinterpret_cast<f4 *>(dst + (size_t)(RS * j) * WG_LS) = w;    // A rows first, B rows follow at BM
+        }
       }
     };
-    // two register sets take turns (no copies: vector ALU work is what the loaders cannot afford); every
+    // the register sets take turns (no copies: vector ALU work is what the loaders cannot afford); every
     // __syncthreads below says "copy k&1 is complete, the MFMA waves have finished chunk k-1"
-    f4 ra4[NR], rb4[NR];
-    int oka = 0, okb = 0;
-    // (the fetch after the split's last chunk is issued like any other and never stashed: a fetch under a condition
+    f4 v[SETS][NR];
+    int ok[SETS];
+    // (the fetches after the split's last chunk are issued like any other and never stashed: a fetch under a condition
     // would make the compiler wait for all loads before every stash, not knowing how many are in flight)
-    fetch(0, ra4, oka);
+#pragma unroll
+    for (int i = 0; i < SETS - 1; ++i) fetch(i, v[i], ok[i]);
     int k = 0;
-    while (k < nch) {
-      fetch(k + 1, rb4, okb);
-      stash(k, ra4, oka);
-      __syncthreads();
-      if (++k >= nch) break;
-      fetch(k + 1, ra4, oka);
-      stash(k, rb4, okb);
-      __syncthreads();
-      ++k;
+    for (; k + SETS <= nch; k += SETS) {       // (no way out in its middle, for the same reason)
+#pragma unroll
+      for (int i = 0; i < SETS; ++i) {
+        fetch(k + i + SETS - 1, v[(i + SETS - 1) % SETS], ok[(i + SETS - 1) % SETS]);
+        __builtin_amdgcn_sched_barrier(0);     // (otherwise the splitting of all sets moves in front of the loads)
+        stash(k + i, v[i], ok[i]);
+        __syncthreads();
+      }
     }
+#pragma unroll
+    for (int i = 0; i < SETS - 1; ++i)
+      if (k + i < nch) {
+        stash(k + i, v[i], ok[i]);
+        __syncthreads();
+      }
     __syncthreads();
   } else {
     // ------------------------------------------------------------------ MFMA waves
@@ -280,6 +334,34 @@ __global__ __launch_bounds__(512) void pw_wgrad_kernel(WgradArgs p) {
     __syncthreads();     // chunk 0 is staged
     for (int k = 0; k < nch; ++k) {
       if (idle) {
+        __syncthreads();
+        continue;
+      }
+      if constexpr (SPLIT) {
+        const char *const Sb = reinterpret_cast<const char *>(smem) + (k & 1) * wg_split_copy(BM + BN) + l31 * kWgSplitRow + 16 * lh;
+        constexpr int PLANE = (BM + BN) * kWgSplitRow;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          uintx4 a[3][MBW], b[3][NBW];
+#pragma unroll
+          for (int pc = 2; pc >= 0; --pc) {
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb)
+              a[pc][mb] = *reinterpret_cast<const uintx4 *>(Sb + pc * PLANE + (wm * MBW + mb) * (32 * kWgSplitRow) + 32 * s);
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb)
+              b[pc][nb] = *reinterpret_cast<const uintx4 *>(Sb + pc * PLANE + (BM + (wn * NBW + nb) * 32) * kWgSplitRow + 32 * s);
+          }
+          constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+          for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+              for (int nb = 0; nb < NBW; ++nb)
+                acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[PA[q]][mb]), __builtin_bit_cast(bf16x8, b[PB[q]][nb]),
+                                                                      acc[mb][nb], 0, 0, 0);
+        }
         __syncthreads();
         continue;
       }
@@ -321,6 +403,7 @@ __global__ __launch_bounds__(512) void pw_wgrad_kernel(WgradArgs p) {
 
     // ---- accumulator register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32
     float *dst = p.partial + (size_t)split * p.Co * p.Ci;
+    float odd = 0.f;                           // stays zero unless a sum is no number, or infinite
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
@@ -331,9 +414,21 @@ __global__ __launch_bounds__(512) void pw_wgrad_kernel(WgradArgs p) {
           for (int nb = 0; nb < NBW; ++nb) {
             const int c = c0 + (wn * NBW + nb) * 32 + l31;
             if (c < p.Ci) dst[(size_t)o * p.Ci + c] = acc[mb][nb][r];
+            if (SPLIT) odd = fmaf(acc[mb][nb][r], 0.f, odd);
           }
         }
       }
+    if (SPLIT && __any(odd != odd)) {
+#pragma unroll 1
+      for (int i = 0; i < 16 * MBW * NBW; ++i) {         // each lane's own outputs, where it has just put them
+        const int r = i & 15, mb = (i >> 4) % MBW, nb = (i >> 4) / MBW;
+        const int o = m0 + (wm * MBW + mb) * 32 + 8 * (r / 4) + 4 * lh + (r % 4), c = c0 + (wn * NBW + nb) * 32 + l31;
+        if (o < p.Co && c < p.Ci) {
+          float *const at = dst + (size_t)o * p.Ci + c;
+          if (!(*at == *at)) *at = wgrad_plain_sum(p, o, c, split);
+        }
+      }
+    }
   }
 }
 
@@ -525,6 +620,8 @@ static inline int wg_bn(int variant) { return (variant & 1) ? 64 : 128; }
 WgradGeom wgrad_taps_geom(int N, int Co, int Cin, int HW) {
   WgradGeom g = wgrad_geom(N, Co, 9 * Cin, HW);
   g.vec = 3;
+  g.split = false;
+  g.lds_bytes = (size_t)2 * (wg_bm(g.variant) + wg_bn(g.variant)) * WG_LS * sizeof(float);
   // Only dz comes from HBM here (the input has few channels and stays in cache) and the tile of dW is tiny, so the
   // kernel is bound by the bytes its loaders keep in flight: four workgroups per compute unit instead of one.
   const long long K = (long long)N * HW;
@@ -566,7 +663,10 @@ WgradGeom wgrad_geom(int N, int Co, int Ci, int HW) {
   g.chunks_per_split = cdiv(nchunks, want);
   g.splits = cdiv(nchunks, g.chunks_per_split);
   g.slabs = g.splits;
-  g.lds_bytes = (size_t)2 * (wg_bm(g.variant) + wg_bn(g.variant)) * WG_LS * sizeof(float);
+  const char *env = std::getenv("PBKD_WGRAD_SPLIT");           // tuning aid: 0 = fp32 products
+  g.split = (g.vec == 2 || g.vec == 5) && !(env && std::atoi(env) == 0);
+  const int rows = wg_bm(g.variant) + wg_bn(g.variant);
+  g.lds_bytes = g.split ? (size_t)2 * wg_split_copy(rows) : (size_t)2 * rows * WG_LS * sizeof(float);
   return g;
 }
 
@@ -576,9 +676,14 @@ hipError_t init_pw_wgrad_attributes() {
   e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pw_wgrad_kernel<MBW, NBW, MODE>),                 \
                           hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);                             \
   if (e != hipSuccess) return e;
-#define PBKD_SET3(MBW, NBW) PBKD_SET(MBW, NBW, 0) PBKD_SET(MBW, NBW, 1) PBKD_SET(MBW, NBW, 2) PBKD_SET(MBW, NBW, 3) PBKD_SET(MBW, NBW, 4)
+#define PBKD_SETS(MBW, NBW, MODE)                                                                           \
+  e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pw_wgrad_kernel<MBW, NBW, MODE, true>),           \
+                          hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);                             \
+  if (e != hipSuccess) return e;
+#define PBKD_SET3(MBW, NBW) PBKD_SET(MBW, NBW, 0) PBKD_SET(MBW, NBW, 1) PBKD_SET(MBW, NBW, 2) PBKD_SET(MBW, NBW, 3) PBKD_SET(MBW, NBW, 4) PBKD_SETS(MBW, NBW, 2) PBKD_SETS(MBW, NBW, 4)
   PBKD_SET3(2, 2) PBKD_SET3(2, 1) PBKD_SET3(1, 2) PBKD_SET3(1, 1)
 #undef PBKD_SET3
+#undef PBKD_SETS
 #undef PBKD_SET
   return hipFuncSetAttribute(reinterpret_cast<const void *>(&wgrad_taps_bn_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
 }
@@ -590,6 +695,7 @@ hipError_t launch_pw_wgrad(const WgradArgs &a, hipStream_t s) {
   if (a.g.vec && a.g.vec != 5 && (a.HW % 4 || (reinterpret_cast<uintptr_t>(a.dz) & 15) || (reinterpret_cast<uintptr_t>(a.u) & 15)))
     return hipErrorInvalidValue;
   if (a.g.vec == 2 && a.HW % WG_KC) return hipErrorInvalidValue;
+  if (a.g.split && a.g.vec != 2 && a.g.vec != 5) return hipErrorInvalidValue;
   if (a.g.vec == 3 && (a.W < 4 || a.W % 4 || a.HW % a.W || a.Ci % 9 || a.Ci > 64 || !wgrad_taps_small(a.N, a.Co, a.Ci / 9, a.HW)))
     return hipErrorInvalidValue;
   if (a.g.vec == 4) {
@@ -599,9 +705,13 @@ hipError_t launch_pw_wgrad(const WgradArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(wgrad_taps_bn_kernel, dim3(1, a.g.tiles_m, a.g.splits), dim3(512), a.g.lds_bytes, s, a);
     return hipGetLastError();
   }
-  const dim3 grid(a.g.tiles_n, a.g.tiles_m, a.g.splits), block(512);
+  const dim3 grid(a.g.tiles_n, a.g.tiles_m, a.g.splits), block(wg_threads(a.g.split));
 #define PBKD_GO(MBW, NBW)                                                                                   \
-  if (a.g.vec == 5)                                                                                         \
+  if (a.g.split && a.g.vec == 5)                                                                            \
+    hipLaunchKernelGGL((pw_wgrad_kernel<MBW, NBW, 4, true>), grid, block, a.g.lds_bytes, s, a);             \
+  else if (a.g.split)                                                                                       \
+    hipLaunchKernelGGL((pw_wgrad_kernel<MBW, NBW, 2, true>), grid, block, a.g.lds_bytes, s, a);             \
+  else if (a.g.vec == 5)                                                                                    \
     hipLaunchKernelGGL((pw_wgrad_kernel<MBW, NBW, 4>), grid, block, a.g.lds_bytes, s, a);                   \
   else if (a.g.vec == 3)                                                                                    \
     hipLaunchKernelGGL((pw_wgrad_kernel<MBW, NBW, 3>), grid, block, a.g.lds_bytes, s, a);                   \

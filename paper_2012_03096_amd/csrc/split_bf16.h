@@ -36,4 +36,14 @@ __device__ __forceinline__ void split3_bf16(float x0, float x1, unsigned (&p)[3]
   p[2] = pack_bf16_rn(s0, s1);
 }
 
+// the same with the first two pieces cut off instead of rounded: each piece the next eight bits of the number
+__device__ __forceinline__ void split3_bf16_cut(float x0, float x1, unsigned (&p)[3]) {
+  auto cut = [](float f) { return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, f) & 0xffff0000u); };
+  auto pair = [](float a, float b) { return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, b), __builtin_bit_cast(unsigned, a), 0x07060302u); };
+  p[0] = pair(x0, x1);
+  const float r0 = x0 - cut(x0), r1 = x1 - cut(x1);
+  p[1] = pair(r0, r1);
+  p[2] = pair(r0 - cut(r0), r1 - cut(r1));
+}
+
 }  // namespace pbkd

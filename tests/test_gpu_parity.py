@@ -600,6 +600,46 @@ def test_pointwise_weight_gradient_on_any_map(gpu, n, h, w_, chans):
     assert not fails, fails
 
 
+@pytest.mark.parametrize("huge", [False, True])
+@pytest.mark.parametrize("n,h,w_,ci,co", [(32, 14, 14, 96, 130), (40, 8, 8, 64, 33), (6, 27, 23, 67, 100), (3, 5, 3, 5, 70), (96, 2, 2, 130, 64),
+                                          (1, 1, 4, 3, 5), (17, 16, 32, 20, 24)])
+def test_pointwise_weight_gradient_leaves_no_larger_error_than_fp32_products(gpu, monkeypatch, n, h, w_, ci, co, huge):
+    """rms error of dP against fp64 (dz formed in fp64 from the kernel's own z, u its own): from split operands not above what the
+    fp32 matrix cores leave.  Both sum the same products in the same parts, but a sum is rounded 6 times per 16 pixels for 8, and
+    both take over the roundings of dz and u; 5 % for the drawing of them, and 3e-8 of rms where a sum is a few pixels and nearly
+    exact either way.  A number past bfloat16's largest (u = 3.4e38, weights of its channel small enough for z to be ordinary)
+    leaves a number, not a NaN.  No output reaches ReLU's corner: beta = 5, gamma = 0.1."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, ci, h, w_, wl._convs([ci, co])), wl.Arch(n, ci, h, w_, wl._dws([ci, co]))
+    x, tp, sp = wl.Workload("wgrad_error", t, s, seed=37).tensors(random_affine=True)
+    x, sp = x.copy(), [[a.copy() for a in lp] for lp in sp]
+    sp[0][2][:], sp[0][3][:] = 0.1, 5.0
+    if huge:
+        sp[0][0].reshape(ci, 9)[1] = np.eye(9)[4]
+        sp[0][1].reshape(co, ci)[:, 1] *= np.float32(1e-38)
+        x[:, 1, -1, -1] = 3.4e38
+    td = torch.from_numpy((5 + np.random.default_rng(3).standard_normal((n, co, h, w_))).astype(np.float32)).cuda()
+    errs = {}
+    for split in (0, 1):
+        monkeypatch.setenv("PBKD_WGRAD_SPLIT", str(split))
+        blk = pb.Block(t, tp, s, sp)
+        blk.student_step(torch.from_numpy(x).cuda(), td, 0.0, want_loss=False)
+        u = blk.get_tensor(pb.STUDENT_ACT, 0, 0, (n, ci, h, w_)).astype(np.float64).transpose(1, 0, 2, 3).reshape(ci, -1)
+        z = blk.get_tensor(pb.STUDENT_ACT, 0, 1, (n, co, h, w_)).astype(np.float64).transpose(1, 0, 2, 3).reshape(co, -1)
+        dP = blk.get_tensor(pb.STUDENT_GRAD, 0, 1, (co, ci)).astype(np.float64)
+        blk.close()
+        rstd = 1 / np.sqrt(z.var(1, keepdims=True) + s.bn_eps)
+        xhat = (z - z.mean(1, keepdims=True)) * rstd
+        g = 2 * (0.1 * xhat + 5 - td.cpu().numpy().astype(np.float64).transpose(1, 0, 2, 3).reshape(co, -1)) / z.size
+        dz = 0.1 * rstd * (g - g.mean(1, keepdims=True) - xhat * (g * xhat).mean(1, keepdims=True))
+        ref = dz @ u.T
+        scale = np.abs(dz) @ np.abs(u.T) if n * h * w_ < 64 else np.sqrt((dz ** 2) @ (u ** 2).T)      # (of a sum: few pixels may cancel)
+        assert np.isfinite(dP).all()
+        errs[split] = float(np.sqrt(np.mean(((dP - ref) / scale) ** 2)))
+    print(f"[pointwise weight gradient error] {ci}->{co} {h}x{w_}x{n} huge={huge}: fp32 products {errs[0]:.3e}, split {errs[1]:.3e}")
+    assert errs[1] <= 1.05 * errs[0] + 3e-8, errs
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

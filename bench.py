@@ -41,7 +41,8 @@ if ROOT not in sys.path:
 MFMA_F32_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
 MFMA_BF16_PEAK_TFLOPS = 2500.0    # MI355X dense bf16 matrix peak
 # The teacher's 3x3 convolutions form every fp32 product from six bf16 MFMA products of operands split three ways (fp32
-# accumulation): their ceiling in fp32-equivalent flops is a sixth of the bf16 peak.
+# accumulation): their ceiling in fp32-equivalent flops is a sixth of the bf16 peak.  (Layers that the library runs on transformed
+# 2x2 tiles, conv_wino_kernel, form 16 products for the 36 that the flops count; the ceiling stays that of the direct form.)
 SPLIT_PRODUCTS = 6
 MFMA_SPLIT_PEAK_TFLOPS = round(MFMA_BF16_PEAK_TFLOPS / SPLIT_PRODUCTS, 1)
 
@@ -57,6 +58,11 @@ def pointwise_split_in_use(w):
     return all(min(l.cin, l.cout) >= 16 for l in w.student.layers if l.kind == wl.DWSEP3X3)
 
 
+def weight_gradient_split_in_use():
+    """Whether pointwise weight gradients do: on every map of the workloads here (four pixels or more, tensors up to 2 GiB)."""
+    return os.environ.get("PBKD_WGRAD_SPLIT", "") != "0"
+
+
 HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of a kernel (reads + writes) from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this benchmark,
 # scaled by what the same counters read for a device copy of known size: written by
@@ -66,15 +72,19 @@ TRAFFIC_JSON = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 SINGLE = {"cfg1": "cfg1_tiny", "cfg2": "cfg2_vgg_block2", "cfg3": "cfg3_resnet_down", "cfg4": "cfg4_imagenet_vgg_block1"}
 
 
-def measured_traffic(workload_name, kernel):
-    """Counter-measured HBM bytes per launch of `kernel` in `workload_name`, or None if no profile has been summarised."""
+def measured_traffic(workload_name, *kernels):
+    """Counter-measured HBM bytes per launch of `kernels` (the mean over their launches) in `workload_name`, or None if no
+    profile has been summarised."""
+    kernel = kernels[0]
     if kernel in ("conv1x1_mfma", "pw_dgrad_mfma"):     # one kernel serves both: the counters cannot tell them apart
         kernel = "pw_mfma (forward and data gradient)"
     try:
         with open(TRAFFIC_JSON) as f:
-            rec = json.load(f)["workloads"][workload_name]["kernels"][kernel]
-        return int(rec["fetch_bytes_per_launch"] + rec["write_bytes_per_launch"])
-    except (OSError, KeyError, ValueError):
+            recs = json.load(f)["workloads"][workload_name]["kernels"]
+        recs = [recs[k] for k in (kernel, *kernels[1:]) if k in recs]
+        total = sum((r["fetch_bytes_per_launch"] + r["write_bytes_per_launch"]) * r["launches"] for r in recs)
+        return int(total / sum(r["launches"] for r in recs))
+    except (OSError, KeyError, ValueError, ZeroDivisionError):
         return None
 
 
@@ -287,7 +297,8 @@ def run_block(args, w, kernel_roofline=True):
                 if wk["flops"]:
                     rec["flops_per_step"] = wk["flops"]
                     rec["TFLOPps"] = round(wk["flops"] / sec / 1e12, 2)
-                    peak = MFMA_SPLIT_PEAK_TFLOPS if kind in ("conv1x1_mfma", "pw_dgrad_mfma") and pointwise_split_in_use(w) else MFMA_F32_PEAK_TFLOPS
+                    split = weight_gradient_split_in_use() if kind == "pw_wgrad_mfma" else kind in ("conv1x1_mfma", "pw_dgrad_mfma") and pointwise_split_in_use(w)
+                    peak = MFMA_SPLIT_PEAK_TFLOPS if split else MFMA_F32_PEAK_TFLOPS
                     rec["mfma_peak_TFLOPps"] = peak
                     rec["frac_of_mfma_peak"] = round(wk["flops"] / sec / 1e12 / peak, 4)
             roof["per_kind"][kind] = rec
@@ -312,14 +323,14 @@ def mfma_roofline(w, roof, region_note):
     if conv_split_in_use():
         # `achieved` stays the convolution's own (fp32) flops over its time; the peak is the bf16 one over the six bf16
         # products each of them costs.  The same rate against the fp32 matrix peak is given beside it.
-        out.update({"kernel": "pbkd::conv_split_kernel, on maps without aligned rows pbkd::conv_rows_kernel (3x3 implicit GEMM, "
-                              "fp32 operands split into three bf16 terms, six v_mfma_f32_32x32x16_bf16 products per fp32 "
-                              "product, fp32 accumulation)",
+        out.update({"kernel": "pbkd::conv_split_kernel, on maps without aligned rows pbkd::conv_rows_kernel, where it costs less "
+                              "pbkd::conv_wino_kernel on transformed 2x2 tiles (3x3 implicit GEMM, fp32 operands split into three "
+                              "bf16 terms, six v_mfma_f32_32x32x16_bf16 products per fp32 product, fp32 accumulation)",
                     "peak": MFMA_SPLIT_PEAK_TFLOPS, "frac": round(rec["TFLOPps"] / MFMA_SPLIT_PEAK_TFLOPS, 4),
                     "peak_is": "dense bf16 MFMA peak %.0f TFLOP/s / %d bf16 products per fp32 product" % (MFMA_BF16_PEAK_TFLOPS, SPLIT_PRODUCTS),
                     "frac_of_fp32_mfma_peak": rec["frac_of_mfma_peak"],
-                    "bf16_TFLOPps_issued": round(rec["TFLOPps"] * SPLIT_PRODUCTS, 1),
-                    "traffic": measured_traffic(w.name, "conv_split_kernel")})
+                    "bf16_TFLOPps_of_direct_form": round(rec["TFLOPps"] * SPLIT_PRODUCTS, 1),
+                    "traffic": measured_traffic(w.name, "conv_split_kernel", "conv_rows_kernel", "conv_wino_kernel")})
     return out
 
 

@@ -212,11 +212,13 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
         ConvGeom rows{};
         if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, rows)) r.cg = rows;
       }
-      // Aligned maps at stride 1: transformed 2x2 tiles where the price of the aligned kernel is 1.4 times theirs.  The prices
+      // Aligned maps at stride 1: transformed 2x2 tiles where the price of the aligned kernel is 1.4 times theirs, 1.6 with K split.  The prices
       // tell the faster of the two on a hundred shapes from 1x12x12 to 91x68x80, 16 to 504 channels (256 channels at 56x56, batch
       // 32, 562 -> 377 us a call; 64 at 8x8, batch 16, 13 and 23: start-up); 1.4, because the transformed tiles' workgroups fill
       // a compute unit and a student on a second stream gets nothing beside them: 64 channels at 224x224, priced 1.33, are 4 %
-      // faster on one stream (2 325 -> 2 237 us a step) and 2 % slower on two (2 126 -> 2 168).  The stacked rows stay where they
+      // faster on one stream (2 325 -> 2 237 us a step) and 2 % slower on two (2 126 -> 2 168).  A K split puts small maps on every
+      // compute unit: 512 channels at 4x4, batch 128, priced 1.58, are 60 -> 46 us alone and make the step of five blocks on four
+      // streams 1 % slower (1 034 -> 1 045 us; 128 at 16x16, priced 1.49, leave it as it is).  The stacked rows stay where they
       // are: their sums in two levels are more accurate.  PBKD_CONV_WINO=1 takes the transformed tiles wherever they can run, 0
       // nowhere; another forced geometry of the 3x3 convolution leaves them out.
       const bool forced = std::getenv("PBKD_CONV_TILE") || std::getenv("PBKD_CONV_KSPLIT") || std::getenv("PBKD_CONV_ROWS");
@@ -225,7 +227,7 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
         ConvGeom g{};
         double cycles = 0;
         if (conv_wino_geom(a->n, d.cin, d.cout, r.hout, r.wout, g, cycles) &&
-            (env_is("PBKD_CONV_WINO", 1) || 1.4 * cycles < conv_split_cycles(r.cg, a->n, d.cout, r.hout, r.wout)))
+            (env_is("PBKD_CONV_WINO", 1) || (g.ksplit > 1 ? 1.6 : 1.4) * cycles < conv_split_cycles(r.cg, a->n, d.cout, r.hout, r.wout)))
           r.cg = g;
       }
       r.cw = cw_geom(a->n, d.cin, r.hout, r.wout, d.stride);

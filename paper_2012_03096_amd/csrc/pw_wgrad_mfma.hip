@@ -1,4 +1,4 @@
-// Weight gradient of the student's pointwise convolution on the fp32 matrix cores:
+// Weight gradient of the student's pointwise convolution on the matrix cores (fp32, or bf16 from split operands: SPLIT below):
 //   dP[o,c] = sum_q dz[o,q] * u[c,q],   q = (image, pixel):   M = Cout, N = Cin, K = N*H*W  (split-K).
 //
 // Both operands are contiguous along the reduction index q (NCHW rows), the opposite of what an MFMA
@@ -41,7 +41,7 @@ constexpr int WG_LS = WG_KC + 4;    // LDS row stride in floats
 // 1 024 in fp32, which was what bound the kernel.  The loaders split and write three bf16 planes, rows of 64 bytes 80 apart: 16
 // lanes' 16-byte operand reads meet every bank once.  Splitting is now the most of it (160 vector instructions per SIMD and chunk:
 // 50 % of the cycles, the matrix pipe 31 %), so eight waves load instead of four, in four register sets.  64 x 64 weights a tile
-// as before: 128 x 128 split a third less per product (512x512 at 14x14, batch 32: 27.7 us for 32.4) but need four times the
+// as before: 128 x 128 split half as much per product (512x512 at 14x14, batch 32: 27.7 us for 32.4) but need four times the
 // parts of the sum, which the update kernel reads, and are slower where pixels are few (128x128 at 16x16, batch 128: 15.9 for 11.5).
 // dz's pieces are cut off and u's rounded (conv_wino_kernel.h has why cutting is cheaper; both cut would leave out terms of one sign).
 // A sum is rounded 6 times per 16 pixels where the fp32 products' is 8 times.  Sums that are NaN are formed again in fp32

@@ -60,9 +60,9 @@
  *                           input channels, tensors below 4 GiB; the default there): 10-13 channel blocks of 32 x pixels per
  *                           lane = 2x1, 1x1, 2x2, 1x2, 14-15 with K split over a workgroup's waves 2x1, 1x1
  *   PBKD_WGRAD_VARIANT=0..3 pointwise weight gradient tile: bit 1 = 64 (else 128) rows, bit 0 = 64 (else 128) columns
- *   PBKD_WGRAD_SPLIT=0      pointwise weight gradients on the fp32 matrix cores everywhere (default: on the bf16 ones from operands
- *                           split three ways where tensors and maps allow 32-bit offsets and groups of four pixels; a NaN sum is
- *                           formed again in fp32)
+ *   PBKD_WGRAD_SPLIT=0|1    pointwise weight gradients on the fp32 matrix cores everywhere / on the bf16 ones from operands split
+ *                           three ways wherever they can run: 32-bit offsets and groups of four pixels.  Default: there, except
+ *                           where a workgroup sums at most four chunks of 32 pixels.  A NaN sum is formed again in fp32
  *   PBKD_CF_TH=4|8          first-layer 3x3 convolution (at most three input channels): rows of a workgroup's tile
  *   PBKD_CF_OCC=1..8        same kernel: workgroups per compute unit its persistent grid is sized for (default 4)
  *   PBKD_DW_EDGE=0          depthwise register-window kernels on maps whose width is not 4, 8, 16, 32 or 64: a strip's

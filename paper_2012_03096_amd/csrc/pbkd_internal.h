@@ -385,7 +385,7 @@ struct WgradGeom {
   int vec;                 // 2: H*W % 32 == 0, buffer addressing; 1: H*W % 4 == 0, 16-byte vectors; 0: scalar loads;
                            // 3: the columns are the 3x3 taps of a few input channels (wgrad_taps_geom)
   int tiles_m, tiles_n, splits, chunks_per_split;   // chunks of 32 pixels
-  bool split;              // vec 2 and 5: products on the bf16 matrix cores from operands split three ways
+  bool split;              // vec 2 and 5, more than four chunks a split: products on the bf16 matrix cores from operands split three ways
   int slabs;               // partial[slab][Co][Ci] slabs written: = splits, or 2 * splits (wgrad_taps_bn_geom)
   size_t lds_bytes;
 };

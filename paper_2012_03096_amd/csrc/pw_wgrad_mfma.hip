@@ -663,8 +663,13 @@ WgradGeom wgrad_geom(int N, int Co, int Ci, int HW) {
   g.chunks_per_split = cdiv(nchunks, want);
   g.splits = cdiv(nchunks, g.chunks_per_split);
   g.slabs = g.splits;
-  const char *env = std::getenv("PBKD_WGRAD_SPLIT");           // tuning aid: 0 = fp32 products
-  g.split = (g.vec == 2 || g.vec == 5) && !(env && std::atoi(env) == 0);
+  // Sums of at most four chunks keep the fp32 products: four is what the split kernel's loaders fetch ahead (one register set
+  // each), so there is nothing left to overlap and its 768 threads and 60 KB only start later.  us a layer, fp32 minus split
+  // products, 9 pairs of channels 16 to 512 on 2x2 to 32x32 maps: 1 and 2 chunks -1.1 .. 0.0, 3 -0.5 .. +0.1, 4 -0.7 .. 0.0,
+  // 6 +0.1 .. +0.5, 8 0.0 .. +0.9, 16 +1.0 .. +2.4.
+  const char *env = std::getenv("PBKD_WGRAD_SPLIT");           // tuning aid: 0 = fp32 products, 1 = split ones wherever they can run
+  const int asked = env ? std::atoi(env) : -1;
+  g.split = (g.vec == 2 || g.vec == 5) && asked != 0 && (asked == 1 || g.chunks_per_split > 4);
   const int rows = wg_bm(g.variant) + wg_bn(g.variant);
   g.lds_bytes = g.split ? (size_t)2 * wg_split_copy(rows) : (size_t)2 * rows * WG_LS * sizeof(float);
   return g;

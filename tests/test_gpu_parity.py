@@ -640,6 +640,28 @@ def test_pointwise_weight_gradient_leaves_no_larger_error_than_fp32_products(gpu
     assert errs[1] <= 1.05 * errs[0] + 3e-8, errs
 
 
+@pytest.mark.parametrize("n,h,w_,ci,co,split", [(4, 16, 16, 16, 16, 0), (128, 16, 16, 16, 16, 0), (160, 16, 16, 16, 16, 1), (32, 4, 4, 512, 512, 0),
+                                                (33, 4, 4, 512, 512, 1), (5, 7, 7, 67, 100, 0), (170, 7, 7, 67, 100, 1)])
+def test_pointwise_weight_gradient_of_few_chunks_keeps_fp32_products(gpu, monkeypatch, n, h, w_, ci, co, split):
+    """Weight gradients whose workgroups sum at most four chunks of 32 pixels are those of the fp32 products, bit for bit, longer
+    ones those of the split products: on both kinds of map, one chunk, the last size below the line and the first above it."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, ci, h, w_, wl._convs([ci, co])), wl.Arch(n, ci, h, w_, wl._dws([ci, co]))
+    x, tp, sp = wl.Workload("wgrad_route", t, s, seed=5).tensors(random_affine=True)
+    xd = torch.from_numpy(x).cuda()
+    td = torch.zeros(wl.output_shape(t), dtype=torch.float32, device="cuda")
+    got = {}
+    for asked in ("", "0", "1"):
+        if asked:
+            monkeypatch.setenv("PBKD_WGRAD_SPLIT", asked)
+        blk = pb.Block(t, tp, s, sp)
+        blk.student_step(xd, td, 0.0, want_loss=False)
+        got[asked] = blk.get_tensor(pb.STUDENT_GRAD, 0, 1, (co, ci))
+        blk.close()
+    assert (got["0"] != got["1"]).any()
+    np.testing.assert_array_equal(got[""], got[str(split)])
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

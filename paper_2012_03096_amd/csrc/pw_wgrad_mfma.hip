@@ -4,16 +4,16 @@
 // Both operands are contiguous along the reduction index q (NCHW rows), the opposite of what an MFMA
 // operand wants (32 lanes = 32 different rows at the same q).  Loading them in operand order straight from
 // global memory makes every lane of a load touch another 128-byte line; so they are transposed through LDS
-// instead: four loader waves read whole 128-byte row segments (8 lanes x 16 bytes per row, 32 pixels per
-// chunk) and write them into a [row][36]-float image, and four MFMA waves read their operands back as
-// 16-byte vectors along q.  A sum does not care about the order of its terms: lanes 0..31 take pixels
+// instead: loader waves (four with fp32 products, eight with split ones) read whole 128-byte row segments (8 lanes x
+// 16 bytes per row, 32 pixels per chunk) and write them, in fp32, into a [row][36]-float image (split: three planes of bf16, see
+// SPLIT), and four MFMA waves read their operands back as 16-byte vectors along q.  A sum does not care about the order of its terms: lanes 0..31 take pixels
 // 8g..8g+3 of their row and lanes 32..63 pixels 8g+4..8g+7, and the four MFMA steps that follow pair
 // element e of the A vector with element e of the B vector.  The row stride of 36 floats keeps both the
 // 16-byte writes (8 lanes = one row) and the 16-byte reads (8 lanes = 8 rows, 4 banks each) conflict free.
 //
 // A workgroup owns a tile of dP (128 or 64 rows by 128 or 64 columns, a quarter per MFMA wave) and a
-// contiguous range of q; the chunks are double buffered with one barrier each and the loader fetches two
-// chunks ahead.  Every workgroup writes its tile to partial[split], summed afterwards in a fixed order.
+// contiguous range of q; the chunks are double buffered with one barrier each and the loader fetches one chunk ahead of
+// the one it stages (split: three).  Every workgroup writes its tile to partial[split], summed afterwards in a fixed order.
 #include <cstdlib>
 
 #include "conv_mfma_kernel.h"
@@ -25,8 +25,8 @@ constexpr int WG_KC = 32;           // pixels per staged chunk
 constexpr int WG_LS = WG_KC + 4;    // LDS row stride in floats
 
 // MODE 2: H*W a multiple of 32 (a chunk lies inside one image) and operands below 4 GiB: the loaders address
-// through buffer descriptors, wave-uniform scalar offset per chunk + constant lane offset, no vector ALU work
-// at all (every instruction a loader wave issues while the matrix pipe streams is expensive).
+// through buffer descriptors, wave-uniform scalar offset per chunk + constant lane offset: the addresses take no vector ALU
+// work (every instruction a loader wave issues while the matrix pipe streams is expensive; with fp32 products it issues no other).
 // MODE 1: H*W a multiple of 4 (16-byte loads, per-lane index arithmetic).  MODE 0: any shape, scalar loads.
 // MODE 3: the weight gradient of a full 3x3 convolution with few input channels: dz rows as in MODE 1; the "u"
 // row c*9 + tap is input channel c shifted by the tap, four pixels of one image row per lane, each checked
@@ -299,30 +299,48 @@ __global__ __launch_bounds__(wg_threads(SPLIT)) void pw_wgrad_kernel(WgradArgs p
         }
       }
     };
-    // the register sets take turns (no copies: vector ALU work is what the loaders cannot afford); every
+    // the register sets take turns (no copies: vector ALU work is what the loaders can least afford); every
     // __syncthreads below says "copy k&1 is complete, the MFMA waves have finished chunk k-1"
     f4 v[SETS][NR];
     int ok[SETS];
     // (the fetches after the split's last chunk are issued like any other and never stashed: a fetch under a condition
     // would make the compiler wait for all loads before every stash, not knowing how many are in flight)
-#pragma unroll
-    for (int i = 0; i < SETS - 1; ++i) fetch(i, v[i], ok[i]);
-    int k = 0;
-    for (; k + SETS <= nch; k += SETS) {       // (no way out in its middle, for the same reason)
-#pragma unroll
-      for (int i = 0; i < SETS; ++i) {
-        fetch(k + i + SETS - 1, v[(i + SETS - 1) % SETS], ok[(i + SETS - 1) % SETS]);
-        __builtin_amdgcn_sched_barrier(0);     // (otherwise the splitting of all sets moves in front of the loads)
-        stash(k + i, v[i], ok[i]);
+    if constexpr (!SPLIT && (MODE == 2 || MODE == 3)) {
+      // Chunk by chunk.  Against the loop below, us: modes 2 and 3 here, 16 -> 16 at 16x16, batch 4, four layers' step 90.5 for 90.9,
+      // first-layer taps at 224x224, batch 32, 109.9 for 112.0; the others there: mode 1 at 6x6, batch 240000, 1010 for 1065, mode 0
+      // at 7x9, batch 150000, 2365 for 2390, mode 4, 512 -> 512 at 4x4, batch 32, four layers' step 152.9 for 154.0.
+      fetch(0, v[0], ok[0]);
+      int k = 0;
+      while (k < nch) {
+        fetch(k + 1, v[1], ok[1]);
+        stash(k, v[0], ok[0]);
         __syncthreads();
+        if (++k >= nch) break;
+        fetch(k + 1, v[0], ok[0]);
+        stash(k, v[1], ok[1]);
+        __syncthreads();
+        ++k;
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < SETS - 1; ++i) fetch(i, v[i], ok[i]);
+      int k = 0;
+      for (; k + SETS <= nch; k += SETS) {       // (no way out in its middle, for the same reason)
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) {
+          fetch(k + i + SETS - 1, v[(i + SETS - 1) % SETS], ok[(i + SETS - 1) % SETS]);
+          if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);     // (otherwise the splitting of all sets moves in front of the loads)
+          stash(k + i, v[i], ok[i]);
+          __syncthreads();
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < SETS - 1; ++i)
+        if (k + i < nch) {
+          stash(k + i, v[i], ok[i]);
+          __syncthreads();
+        }
     }
-#pragma unroll
-    for (int i = 0; i < SETS - 1; ++i)
-      if (k + i < nch) {
-        stash(k + i, v[i], ok[i]);
-        __syncthreads();
-      }
     __syncthreads();
   } else {
     // ------------------------------------------------------------------ MFMA waves

@@ -662,6 +662,21 @@ def test_pointwise_weight_gradient_of_few_chunks_keeps_fp32_products(gpu, monkey
     np.testing.assert_array_equal(got[""], got[str(split)])
 
 
+@pytest.mark.parametrize("split", [0, 1])
+@pytest.mark.parametrize("variant", range(4))
+def test_every_weight_gradient_tile_with_both_products(gpu, monkeypatch, variant, split):
+    """Each tile of the pointwise weight gradient with fp32 and with split products, forced: tiles and channels that end ragged,
+    whole chunks per image and groups of four pixels that overlap, and one to ten chunks a workgroup (the loaders take them one
+    by one, in twos or in fours, with every remainder)."""
+    monkeypatch.setenv("PBKD_WGRAD_VARIANT", str(variant))
+    monkeypatch.setenv("PBKD_WGRAD_SPLIT", str(split))
+    for n, h, w_, chans in ((3, 8, 8, (20, 70, 33)), (40, 8, 12, (20, 300, 130)), (30, 5, 6, (260, 390, 140)), (6, 8, 8, (520, 515)),
+                            (10, 8, 8, (520, 515)), (17, 7, 7, (515, 520))):
+        t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+        fails = run_parity(gpu, wl.Workload("wgrad_tiles", t, s, seed=29), steps=2)
+        assert not fails, (n, h, w_, chans, fails)
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

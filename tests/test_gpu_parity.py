@@ -677,6 +677,50 @@ def test_every_weight_gradient_tile_with_both_products(gpu, monkeypatch, variant
         assert not fails, (n, h, w_, chans, fails)
 
 
+@pytest.mark.parametrize("variant", range(4))
+@pytest.mark.parametrize("n,h,w_,ci,co", [(32, 14, 14, 96, 130), (40, 8, 8, 64, 33), (6, 27, 23, 67, 100), (3, 5, 3, 5, 70)])
+def test_pointwise_weight_gradient_infinities(gpu, monkeypatch, n, h, w_, ci, co, variant):
+    """A NaN or an infinity in the target's last channel (a row that tiles past the last channel repeat), in an image's last pixel
+    (which the last group of four shares with the one before it), makes that row of dP NaN and leaves the others bit for bit;
+    a sum past fp32's largest (u = 3.4e38) is the infinity that fp32 products make of it; an infinite input makes all NaN."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, ci, h, w_, wl._convs([ci, co])), wl.Arch(n, ci, h, w_, wl._dws([ci, co]))
+    x, tp, sp = wl.Workload("wgrad_infinities", t, s, seed=61).tensors(random_affine=True)
+    x, sp = np.maximum(x, 0), [[a.copy() for a in lp] for lp in sp]
+    sp[0][2][:], sp[0][3][:] = 0.1, 5.0                                     # (no output reaches ReLU's corner)
+    sp[0][0].reshape(ci, 9)[1] = np.eye(9)[4]
+    sp[0][1].reshape(co, ci)[:, 1] *= np.float32(1e-38)
+    td = (5 + np.random.default_rng(4).standard_normal((n, co, h, w_))).astype(np.float32)
+    monkeypatch.setenv("PBKD_WGRAD_VARIANT", str(variant))
+
+    def gradient(split, xv, tv):
+        monkeypatch.setenv("PBKD_WGRAD_SPLIT", str(split))
+        blk = pb.Block(t, tp, s, sp)
+        blk.student_step(torch.from_numpy(xv).cuda(), torch.from_numpy(tv).cuda(), 0.0, want_loss=False)
+        dP = blk.get_tensor(pb.STUDENT_GRAD, 0, 1, (co, ci))
+        blk.close()
+        return dP
+
+    past, infinite = x.copy(), x.copy()
+    past[0, 1, -1, -1] = 3.4e38
+    infinite[n // 2, ci - 1, 0, 0] = np.inf
+    for split in (0, 1):
+        base = gradient(split, x, td)
+        assert np.isfinite(base).all()
+        for v in (np.nan, np.inf, -np.inf):
+            bad = td.copy()
+            bad[n // 2, co - 1, -1, -1] = v
+            got = gradient(split, x, bad)
+            assert np.isnan(got[co - 1]).all(), (split, v)
+            np.testing.assert_array_equal(got[:co - 1], base[:co - 1])
+        assert np.isnan(gradient(split, infinite, td)).all(), split
+    # dz of the order of 1e12 / rstd: products with 3.4e38 overflow, the other channels' stay numbers
+    far = (td * np.float32(1e12)).astype(np.float32)
+    fp32, split = gradient(0, past, far), gradient(1, past, far)
+    assert np.isinf(fp32[:, 1]).any() and np.isfinite(np.delete(fp32, 1, 1)).all()
+    np.testing.assert_array_equal(value_classes(split), value_classes(fp32))
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

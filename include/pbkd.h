@@ -41,7 +41,8 @@
  *                           accumulation; measured against the fp64 oracle it is within 1.2x of the fp32 kernel's error.
  *                           On maps whose rows are not whole 16-byte groups (tiles of the stacked rows of all images) a
  *                           chunk's products are summed apart and the error is below the fp32 kernel's, and infinities
- *                           and numbers above 3.39e38 give what fp32 products give (elsewhere NaN).  At most eight input
+ *                           and numbers above 3.39e38 give what fp32 products give (elsewhere NaN).  A NaN in the block's
+ *                           input gives NaN (the fp32 matrix cores take it for -infinity).  At most eight input
  *                           channels, few pixels of tiny maps and weight images of 4 GiB stay on the fp32 matrix cores.
  *                           Read when a block is created.
  *   PBKD_CONV_WINO=0|1      transformed 2x2 tiles (F(2x2, 3x3)) for no / for every teacher 3x3 convolution of stride 1 that they can

@@ -42,8 +42,10 @@ __device__ __forceinline__ float plain_conv_sum(const ConvArgs &p, int o, int n,
     for (int t = 0; t < 9; ++t) {
       const int yy = p.stride * y - 1 + t / 3, xx = p.stride * x - 1 + t % 3;
       float v = 0.f;
-      if (yy >= 0 && yy < p.H && xx >= 0 && xx < p.W)
-        v = fmaxf(fmaf(in[(size_t)yy * p.W + xx], sc, sh), p.in_scale ? 0.f : -__builtin_inff());
+      if (yy >= 0 && yy < p.H && xx >= 0 && xx < p.W) {
+        v = fmaf(in[(size_t)yy * p.W + xx], sc, sh);
+        if (p.in_scale) v = fmaxf(v, 0.f);                 // (ReLU; without one a NaN stays a NaN)
+      }
       s = fmaf(w[t], v, s);
     }
   }

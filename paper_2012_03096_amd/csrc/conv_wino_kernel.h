@@ -134,13 +134,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
   };
   // BatchNorm + ReLU of the producing layer; zeros outside the image: med3(x * scale + shift, 0, most), with most = infinity inside
-  // and 0 outside; where there is no BatchNorm, med3(x, -most, most)
+  // and 0 outside; where there is no BatchNorm, x's bits and a mask (a med3 would make an infinity of a NaN)
   auto put = [&](int copy, int sl) __attribute__((always_inline)) {
-    const float most = __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_sbfe((int)sthere, sl, 1) & 0x7f800000u);
+    const unsigned inside = (unsigned)__builtin_amdgcn_sbfe((int)sthere, sl, 1);
+    const float most = __builtin_bit_cast(float, inside & 0x7f800000u);
     f4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      o[e] = BN ? __builtin_amdgcn_fmed3f(fmaf(sv[sl][e], psc[e], psh[e]), 0.f, most) : __builtin_amdgcn_fmed3f(sv[sl][e], -most, most);
+      o[e] = BN ? __builtin_amdgcn_fmed3f(fmaf(sv[sl][e], psc[e], psh[e]), 0.f, most)
+                : __builtin_bit_cast(float, __builtin_bit_cast(unsigned, sv[sl][e]) & inside);
     const unsigned lo16 = sl & 1 ? loff[sl >> 1] >> 16 : loff[sl >> 1] & 0xffffu;
     *reinterpret_cast<f4 *>(Ss + (copy * COPY + w * QP) + lo16 * 16) = o;
   };

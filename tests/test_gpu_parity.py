@@ -903,6 +903,35 @@ def test_stacked_rows_infinities(gpu, monkeypatch, n, h, w_, chans, strides, til
     blk.close()
 
 
+@pytest.mark.parametrize("env,n,h,w_,chans", [({"PBKD_CONV_WINO": "1"}, 4, 8, 12, (48, 32)), ({"PBKD_CONV_WINO": "1"}, 6, 13, 11, (18, 70)),
+                                              ({"PBKD_CONV_WINO": "1"}, 40, 2, 2, (300, 64)), ({"PBKD_CONV_WINO": "0"}, 4, 8, 12, (48, 32)),
+                                              ({"PBKD_CONV_WINO": "0"}, 3, 13, 15, (40, 72)), ({"PBKD_CONV_ROWS": "1"}, 5, 7, 7, (300, 130))])
+def test_a_nan_in_the_input_of_a_convolution_stays_one(gpu, monkeypatch, env, n, h, w_, chans):
+    """NaNs in a block's input, beside an infinity: every output of the first layer that they reach is a NaN, the others are what
+    plain products make of them, on transformed tiles, aligned maps and stacked rows."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+    x, tp, sp = wl.Workload("nan_input", t, s, seed=47).tensors(random_affine=True)
+    rng = np.random.default_rng(11)
+    for v in (np.nan, np.nan) + ((np.inf,) if env != {"PBKD_CONV_WINO": "0"} or w_ % 4 else ()):
+        x[rng.integers(n), rng.integers(chans[0]), rng.integers(h), rng.integers(w_)] = v
+    x[0, -1, 0, 0] = x[-1, 0, -1, -1] = np.nan
+    for name, value in env.items():
+        monkeypatch.setenv(name, value)
+    blk = pb.Block(t, tp, s, sp)
+    out = torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
+    blk.teacher_forward(torch.from_numpy(x).cuda(), out)
+    got = blk.get_tensor(pb.TEACHER_ACT, 0, 1, (n, chans[1], h, w_))
+    blk.close()
+    xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
+    want = np.zeros((chans[1], n * h * w_))
+    with np.errstate(all="ignore"):
+        for tap in range(9):
+            i, j = tap // 3, tap % 3
+            want += tp[0][0][:, :, i, j].astype(np.float64) @ xp[:, :, i:i + h, j:j + w_].transpose(1, 0, 2, 3).reshape(chans[0], -1)
+    same_nonfinite(got, want.astype(np.float32).reshape(chans[1], n, h, w_).transpose(1, 0, 2, 3), env)
+
+
 # whole-image, several and ragged workgroup tiles (a tile has 64 2x2 output tiles), odd heights and widths (half-empty 2x2 tiles;
 # 16-, 8- and 4-byte stores), images that end inside a workgroup tile, a last chunk of 16 channels that reaches back, K split
 # (7x7, 4x4), maps of one row, one column and more than 128 rows

@@ -20,43 +20,43 @@ int compute_units() {
 }
 
 // Canonical weights [Cout][Cin][9] -> G w G^T, in fp64, split into three bf16 pieces, in the multiplying waves' operand order.
-// One thread per (lane of an operand, channel block, chunk, channel tile).
+// One thread per (lane of an operand, channel block, chunk, channel tile, position): bound by the latency of its scattered reads,
+// so many threads that read the same taps (from cache) beat one that forms all 16 positions in turn (64 -> 64 channels 81 -> 10
+// us, 128 -> 128 82 -> 11, 256 -> 256 83 -> 17, 512 -> 512 85 -> 52, where the cache's bandwidth is the bound).
 __global__ __launch_bounds__(128) void conv_wino_pack_kernel(const float *w, uintx4 *out, int nchunks, int Cout, int Cin) {
   const int lane = threadIdx.x & 63, no = threadIdx.x >> 6, ch = blockIdx.x, mt = blockIdx.y;
+  const int i = blockIdx.z >> 2, j = blockIdx.z & 3;
   const int o = mt * 64 + no * 32 + (lane & 31);
   const int c0 = (ch * 16 < Cin - 16 ? ch * 16 : Cin - 16) + 8 * (lane >> 5);
-  uintx4 *const dst = out + ((size_t)mt * nchunks + ch) * (kWinoChunkBytes / 16) + no * (3 * 64) + lane;
-  for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) {
-      uintx4 pp[3];
+  uintx4 *const dst = out + ((size_t)mt * nchunks + ch) * (kWinoChunkBytes / 16) + (4 * i + j) * (6 * 64) + no * (3 * 64) + lane;
+  uintx4 pp[3];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        unsigned q[3] = {0, 0, 0};
+  for (int t = 0; t < 4; ++t) {
+    unsigned q[3] = {0, 0, 0};
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int c = c0 + 2 * t + e;
-          double u = 0;
-          if (o < Cout && c >= ch * 16 && c < Cin) {
-            const float *g = w + ((size_t)o * Cin + c) * 9;
-            double r[3];
-            for (int b = 0; b < 3; ++b)
-              r[b] = i == 0 ? (double)g[b] : i == 3 ? (double)g[6 + b]
-                     : 0.5 * ((double)g[b] + (double)g[6 + b] + (i == 1 ? (double)g[3 + b] : -(double)g[3 + b]));
-            u = j == 0 ? r[0] : j == 3 ? r[2] : 0.5 * (r[0] + r[2] + (j == 1 ? r[1] : -r[1]));
-          }
-#pragma unroll
-          for (int pc = 0; pc < 3; ++pc) {
-            const unsigned b = pack_bf16_rn((float)u, 0.f) & 0xffffu;
-            q[pc] |= b << (16 * e);
-            u -= (double)__builtin_bit_cast(float, b << 16);
-          }
-        }
-#pragma unroll
-        for (int pc = 0; pc < 3; ++pc) pp[pc][t] = q[pc];
+    for (int e = 0; e < 2; ++e) {
+      const int c = c0 + 2 * t + e;
+      double u = 0;
+      if (o < Cout && c >= ch * 16 && c < Cin) {
+        const float *g = w + ((size_t)o * Cin + c) * 9;
+        double r[3];
+        for (int b = 0; b < 3; ++b)
+          r[b] = i == 0 ? (double)g[b] : i == 3 ? (double)g[6 + b]
+                 : 0.5 * ((double)g[b] + (double)g[6 + b] + (i == 1 ? (double)g[3 + b] : -(double)g[3 + b]));
+        u = j == 0 ? r[0] : j == 3 ? r[2] : 0.5 * (r[0] + r[2] + (j == 1 ? r[1] : -r[1]));
       }
 #pragma unroll
-      for (int pc = 0; pc < 3; ++pc) dst[(4 * i + j) * (6 * 64) + pc * 64] = pp[pc];
+      for (int pc = 0; pc < 3; ++pc) {
+        const unsigned b = pack_bf16_rn((float)u, 0.f) & 0xffffu;
+        q[pc] |= b << (16 * e);
+        u -= (double)__builtin_bit_cast(float, b << 16);
+      }
     }
+#pragma unroll
+    for (int pc = 0; pc < 3; ++pc) pp[pc][t] = q[pc];
+  }
+#pragma unroll
+  for (int pc = 0; pc < 3; ++pc) dst[pc * 64] = pp[pc];
 }
 
 template <int SR>
@@ -162,7 +162,7 @@ double conv_split_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo) {
 
 hipError_t launch_conv_wino_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s) {
   if (!g.wino || Cin < 16 || g.nchunks > 65535 || g.mtiles > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(conv_wino_pack_kernel, dim3(g.nchunks, g.mtiles), dim3(128), 0, s, w, reinterpret_cast<uintx4 *>(wpk), g.nchunks, Cout, Cin);
+  hipLaunchKernelGGL(conv_wino_pack_kernel, dim3(g.nchunks, g.mtiles, 16), dim3(128), 0, s, w, reinterpret_cast<uintx4 *>(wpk), g.nchunks, Cout, Cin);
   return hipGetLastError();
 }
 

@@ -741,6 +741,37 @@ def test_teacher_weights_replaced_after_creation(gpu):
     blk.close()
 
 
+@pytest.mark.parametrize("env", [{"PBKD_CONV_WINO": "1"}, {"PBKD_CONV_WINO": "0"}, {"PBKD_CONV_ROWS": "1"}])
+@pytest.mark.parametrize("n,h,w_,chans", [(3, 12, 16, (40, 72, 33)), (5, 8, 8, (64, 130, 17)), (2, 14, 14, (300, 16, 65))])
+def test_teacher_weights_replaced_reach_every_split_kernel(gpu, monkeypatch, n, h, w_, chans, env):
+    """pbkd_block_set_tensor on the weights of layers on transformed tiles, aligned maps and stacked rows: a block with its weights
+    replaced gives bit for bit what a block created with them gives, and what the fp64 oracle gives at ACT_TOL."""
+    torch, pb = gpu
+    for name, value in env.items():
+        monkeypatch.setenv(name, value)
+    t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+    w = wl.Workload("replaced", t, s, seed=67)
+    x, tp, sp = w.tensors(random_affine=True)
+    _, tp2, _ = replace(w, seed=68).tensors(random_affine=True)
+    xd, got = torch.from_numpy(x).cuda(), []
+    for first in (tp, tp2):
+        blk = pb.Block(t, first, s, sp)
+        td = torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
+        blk.teacher_forward(xd, td)
+        for l, lp in enumerate(tp2):
+            for k, a in enumerate(lp):
+                blk.set_tensor(pb.TEACHER_PARAM, l, k, a)
+        blk.teacher_forward(xd, td)
+        torch.cuda.synchronize()
+        got.append([blk.get_tensor(pb.TEACHER_ACT, l, 1, shp) for l, (_, shp, _) in enumerate(_layer_act_shapes(t))] + [td.cpu().numpy()])
+        blk.close()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+    t_ref, cache = ob.block_forward(t, [[a.astype(np.float64) for a in lp] for lp in tp2], x.astype(np.float64), keep=True)
+    for z, ref in zip(got[0], [rec["z"] for rec in cache["layers"]] + [t_ref]):
+        assert relerr(z, ref) <= ACT_TOL
+
+
 def test_split_convolution_is_as_accurate_as_fp32(gpu, monkeypatch):
     """Six bf16 products of three-way split operands leave out terms of at most 2^-24 of each product, so against the fp64
     oracle the split kernel must not be worse than the fp32 MFMA kernel by more than rounding noise.  Two layers with

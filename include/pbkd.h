@@ -311,6 +311,10 @@ pbkd_status pbkd_select_blocks(int n_blocks, pbkd_block_t *const *blocks, int bn
 unsigned long long pbkd_block_flops(const pbkd_block_t *blk, int which);
 /* The same count from descriptors alone (host only; 0 if invalid). */
 unsigned long long pbkd_arch_flops(const pbkd_arch_desc *arch, int training_step);
+/* Which kernel a teacher of this descriptor runs layer `layer`'s 3x3 convolution with, under the tuning overrides now set (host
+ * only): "first" (at most three input channels), "fp32", "aligned", "rows" (stacked rows) or "transformed" (2x2 tiles); ""
+ * if the descriptor is invalid or has no such layer.  *k_parts (may be null) <- the parts its sum over K is split into. */
+const char *pbkd_arch_conv_kernel(const pbkd_arch_desc *arch, int layer, int *k_parts);
 
 /* Copies one tensor between host and the block (synchronous on the default stream; for tests,
  * checkpoints and gathering the trained student).  n = number of floats, must match the tensor. */

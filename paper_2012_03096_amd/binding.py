@@ -23,7 +23,7 @@ STUDENT_PARAM, STUDENT_GRAD, STUDENT_MOMENTUM, TEACHER_PARAM, STUDENT_ACT, TEACH
 EXPORTS = [
     "pbkd_arch_validate", "pbkd_block_workspace_bytes", "pbkd_block_create", "pbkd_block_destroy",
     "pbkd_teacher_forward", "pbkd_student_step", "pbkd_distill_step", "pbkd_block_set_aux_stream", "pbkd_block_set_graph_mode", "pbkd_student_forward", "pbkd_block_last_loss",
-    "pbkd_schedule_blocks", "pbkd_distill_step_all", "pbkd_run_tasks_work_stealing", "pbkd_network_forward", "pbkd_feature_mse", "pbkd_feature_mse_noalloc", "pbkd_select_blocks", "pbkd_block_flops", "pbkd_arch_flops",
+    "pbkd_schedule_blocks", "pbkd_distill_step_all", "pbkd_run_tasks_work_stealing", "pbkd_network_forward", "pbkd_feature_mse", "pbkd_feature_mse_noalloc", "pbkd_select_blocks", "pbkd_block_flops", "pbkd_arch_flops", "pbkd_arch_conv_kernel",
     "pbkd_block_get_tensor", "pbkd_block_set_tensor", "pbkd_last_error",
     "pbkd_kernel_kinds", "pbkd_kernel_kind_name", "pbkd_block_profile_enable", "pbkd_block_profile_read",
 ]
@@ -112,6 +112,8 @@ def lib():
         L.pbkd_block_flops.restype = ctypes.c_ulonglong
         L.pbkd_arch_flops.argtypes = [ap, ctypes.c_int]
         L.pbkd_arch_flops.restype = ctypes.c_ulonglong
+        L.pbkd_arch_conv_kernel.argtypes = [ap, ctypes.c_int, ip]
+        L.pbkd_arch_conv_kernel.restype = ctypes.c_char_p
         L.pbkd_block_get_tensor.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.c_int, fp, ctypes.c_size_t]
         L.pbkd_block_get_tensor.restype = ctypes.c_int
         L.pbkd_block_set_tensor.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.c_int, fp, ctypes.c_size_t]
@@ -159,6 +161,12 @@ def workspace_bytes(teacher, student) -> int:
 
 def arch_flops(arch, training_step: bool) -> int:
     return lib().pbkd_arch_flops(ctypes.byref(make_arch(arch)), int(training_step))
+
+
+def arch_conv_kernel(teacher, layer: int):
+    """(name, parts K is split into) of the kernel a teacher's 3x3 convolution runs on; ("", 0) if there is none."""
+    parts = ctypes.c_int()
+    return lib().pbkd_arch_conv_kernel(ctypes.byref(make_arch(teacher)), layer, ctypes.byref(parts)).decode(), parts.value
 
 
 def schedule_blocks(weights: Optional[Sequence[int]], n_streams: int, policy: int = 0, blocks: Optional[Sequence["Block"]] = None):

@@ -868,6 +868,14 @@ unsigned long long pbkd_arch_flops(const pbkd_arch_desc *arch, int training_step
   return net_flops(n, training_step != 0);
 }
 
+const char *pbkd_arch_conv_kernel(const pbkd_arch_desc *arch, int layer, int *k_parts) {
+  Net n;
+  if (build_net(arch, false, n) != PBKD_OK || layer < 0 || layer >= (int)n.L.size() || n.L[layer].kind != PBKD_CONV3X3) return "";
+  const LayerRT &r = n.L[layer];
+  if (k_parts) *k_parts = r.first_conv ? 1 : r.cg.ksplit;
+  return r.first_conv ? "first" : r.cg.wino ? "transformed" : r.cg.rows ? "rows" : r.cg.split ? "aligned" : "fp32";
+}
+
 unsigned long long pbkd_block_flops(const pbkd_block_t *blk, int which) {
   if (!blk) return 0;
   switch (which) {

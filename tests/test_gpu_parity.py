@@ -695,8 +695,8 @@ def test_pointwise_weight_gradient_infinities(gpu, monkeypatch, n, h, w_, ci, co
 
     def gradient(split, xv, tv):
         monkeypatch.setenv("PBKD_WGRAD_SPLIT", str(split))
-        blk = pb.Block(t, tp, s, sp)
-        blk.student_step(torch.from_numpy(xv).cuda(), torch.from_numpy(tv).cuda(), 0.0, want_loss=False)
+        blk, xd, tgt = pb.Block(t, tp, s, sp), torch.from_numpy(xv).cuda(), torch.from_numpy(tv).cuda()
+        blk.student_step(xd, tgt, 0.0, want_loss=False)
         dP = blk.get_tensor(pb.STUDENT_GRAD, 0, 1, (co, ci))
         blk.close()
         return dP
@@ -950,8 +950,8 @@ def test_a_nan_in_the_input_of_a_convolution_stays_one(gpu, monkeypatch, env, n,
     for name, value in env.items():
         monkeypatch.setenv(name, value)
     blk = pb.Block(t, tp, s, sp)
-    out = torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
-    blk.teacher_forward(torch.from_numpy(x).cuda(), out)
+    xd, out = torch.from_numpy(x).cuda(), torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda")
+    blk.teacher_forward(xd, out)
     got = blk.get_tensor(pb.TEACHER_ACT, 0, 1, (n, chans[1], h, w_))
     blk.close()
     xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
@@ -969,6 +969,25 @@ def test_a_nan_in_the_input_of_a_convolution_stays_one(gpu, monkeypatch, env, n,
 TRANSFORMED = [(3, (40, 72, 33), 14, 14), (4, (67, 100, 67), 27, 23), (5, (300, 130, 20), 7, 7), (2, (17, 16, 70), 5, 131), (6, (18, 20, 16), 13, 1),
                (9, (16, 33, 16), 1, 11), (20, (64, 48, 32), 4, 4), (2, (48, 64, 65), 16, 32), (1, (16, 31, 16), 150, 3), (3, (32, 16, 16), 40, 36),
                (33, (16, 64, 16), 2, 2), (1, (16, 128, 128), 12, 16)]
+
+
+@pytest.mark.parametrize("n,chans,h,w_", TRANSFORMED + [(6, (16, 19, 40), 13, 11), (9, (64, 200, 96), 7, 7), (4, (48, 32, 130), 8, 12), (40, (48, 64, 64), 2, 2)])
+def test_forced_transformed_tiles_run(gpu, monkeypatch, n, chans, h, w_):
+    """The shapes of the tests below do run on transformed tiles when these are forced, and their pre-activations differ from the
+    other kernels' in rounding."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans))), wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)))
+    x, tp, sp = wl.Workload("forced", t, s, seed=7).tensors(random_affine=True)
+    monkeypatch.setenv("PBKD_CONV_ROWS", "1")
+    xd, td, z = torch.from_numpy(x).cuda(), torch.empty(wl.output_shape(t), dtype=torch.float32, device="cuda"), []
+    for wino in ("0", "1"):
+        monkeypatch.setenv("PBKD_CONV_WINO", wino)
+        assert all((pb.arch_conv_kernel(t, l)[0] == "transformed") == (wino == "1") for l in range(2))
+        blk = pb.Block(t, tp, s, sp)
+        blk.teacher_forward(xd, td)
+        z.append([blk.get_tensor(pb.TEACHER_ACT, l, 1, shp) for l, (_, shp, _) in enumerate(_layer_act_shapes(t))])
+        blk.close()
+    assert all((a != b).any() for a, b in zip(*z))
 
 
 @pytest.mark.parametrize("wgs", [0, 1, 3])

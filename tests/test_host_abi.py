@@ -117,6 +117,44 @@ def test_few_pixels_of_tiny_maps_keep_the_fp32_convolution(monkeypatch, n, h, w,
     assert (chosen == pb.workspace_bytes(t, s)) == fp32
 
 
+def conv_kernel(n, cin, cout, h, w, stride=1):
+    return pb.arch_conv_kernel(wl.Arch(n, cin, h, w, [wl.Layer(wl.CONV3X3, cin, cout, stride, 0)]), 0)
+
+
+@pytest.mark.parametrize("n,cin,cout,h,w,stride,name", [
+    (8, 3, 64, 32, 32, 1, "first"), (8, 8, 64, 13, 13, 1, "fp32"), (4, 64, 64, 1, 1, 1, "fp32"), (32, 64, 128, 15, 13, 1, "rows"), (16, 128, 128, 16, 16, 2, "aligned"),
+    (75, 512, 512, 16, 16, 1, "transformed"), (31, 112, 112, 112, 112, 1, "transformed"), (122, 64, 64, 36, 36, 1, "transformed"),
+    (5, 160, 160, 16, 16, 1, "aligned"), (20, 48, 48, 180, 156, 1, "aligned"), (1, 64, 64, 32, 32, 1, "aligned")])
+def test_each_convolution_runs_the_kernel_its_shape_asks_for(n, cin, cout, h, w, stride, name):
+    """Without tuning overrides: the direct kernels where a map is not aligned, strided, tiny or has few channels, transformed tiles
+    only where they are priced well below the aligned kernel."""
+    assert conv_kernel(n, cin, cout, h, w, stride)[0] == name
+
+
+def test_transformed_tiles_where_asked_for_and_where_they_cannot_run(monkeypatch):
+    shapes = [(1, 16, 16, 1, 1), (3, 40, 33, 14, 14), (2, 17, 70, 5, 131), (1, 31, 16, 150, 3), (33, 16, 64, 2, 2), (4, 300, 130, 12, 16)]
+    monkeypatch.setenv("PBKD_CONV_WINO", "0")
+    assert all(conv_kernel(*s)[0] != "transformed" for s in shapes + [(75, 512, 512, 16, 16)])
+    monkeypatch.setenv("PBKD_CONV_WINO", "1")
+    assert all(conv_kernel(*s)[0] == "transformed" for s in shapes)
+    assert conv_kernel(4, 512, 64, 4, 4)[1] == 8                              # (K split over up to eight workgroups)
+    # at most 15 input channels, a stride, outputs of 4 GiB, weight images of 4 GiB
+    for s in ((8, 15, 64, 16, 16), (8, 32, 64, 16, 16, 2), (64, 16, 128, 400, 400), (1, 6912, 6912, 8, 8)):
+        assert conv_kernel(*s)[0] not in ("transformed", ""), s
+    assert conv_kernel(64, 16, 127, 362, 364)[0] == "transformed"             # 4.28 GB, 0.01 below 4 GiB
+    for name in ("PBKD_CONV_TILE", "PBKD_CONV_KSPLIT", "PBKD_CONV_ROWS"):     # another forced geometry leaves them out by default
+        monkeypatch.delenv("PBKD_CONV_WINO", raising=False)
+        monkeypatch.setenv(name, "1")
+        assert conv_kernel(75, 512, 512, 16, 16)[0] != "transformed"
+        monkeypatch.delenv(name)
+    monkeypatch.setenv("PBKD_CONV_SPLIT", "0")
+    assert conv_kernel(75, 512, 512, 16, 16)[0] == "fp32"
+    # no 3x3 convolution, no layer, no descriptor
+    t = wl.Arch(2, 16, 8, 8, [wl.Layer(wl.DWSEP3X3, 16, 16, 1, 0)])
+    assert pb.arch_conv_kernel(t, 0) == ("", 0) and pb.arch_conv_kernel(t, 1) == ("", 0) and pb.arch_conv_kernel(t, -1) == ("", 0)
+    assert pb.lib().pbkd_arch_conv_kernel(None, 0, None) == b""
+
+
 def test_split_weights_that_do_not_fit_their_index_keep_the_fp32_kernels(monkeypatch):
     """Split copies take 6 bytes a weight and are addressed in 32 bits (a 3x3 image, a 1x1 image) or, all of a student's
     together, in 31 bits of 2-byte units.  Sizes past that are still accepted, with the fp32 copies."""

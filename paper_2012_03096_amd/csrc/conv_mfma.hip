@@ -128,6 +128,10 @@ static ConvGeom conv_geom_for_tile(int tile, int taps, int N, int Cin, int Cout,
   return g;
 }
 
+double conv_ksplit_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo) {
+  return g.ksplit > 1 ? 4000 + 600.0 * g.ksplit * cdiv(g.nimg * Ho * Wo, 64) + (g.ksplit + 1) * 4.0 * N * Cout * Ho * Wo / 1500 : 0;
+}
+
 // Tiles of stacked rows (conv_rows_kernel.h).  Every (workgroup tile, columns per tile, K split) is priced in shader
 // cycles: rounds of 256 workgroups x (chunks x stage + tile end), stage and tile end as measured per workgroup tile (the small
 // tiles' stage by staged positions per loader thread: the loaders bound it from two on, 1x1 maps stage nine for each), plus
@@ -196,7 +200,7 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGe
         const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
         const double stage = kStages[tile][slots - 1], per_wg = g.kchunks * stage + kEnd[tile];
         const double cost = (double)((items + 255) / 256) * per_wg + 2 * stage +
-                            (want > 1 ? 4000 + 600.0 * g.ksplit * cdiv(g.nimg * Ho * Wo, 64) + (g.ksplit + 1) * out_bytes / 1500 : 0);
+                            conv_ksplit_cycles(g, N, Cout, Ho, Wo);
         if (best_cost == 0 || cost < best_cost) best_cost = cost, best = g;
       }
     }

@@ -10,15 +10,6 @@
 namespace pbkd {
 
 namespace {
-int compute_units() {
-  static const int n = [] {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
-    return v;
-  }();
-  return n;
-}
-
 template <int WGM, int MB, int NB>
 struct SplitLaunch {
   template <int BSLOTS>
@@ -51,18 +42,9 @@ struct SplitLaunch {
       hipLaunchKernelGGL(kernel, grid, block, a.g.lds_bytes, s, a);
   }
   static hipError_t launch(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    // persistent: one workgroup per compute unit (their LDS allows no more), each walking every G-th tile; more
-    // workgroups only where a workgroup's tile table would overflow
     const long long items = (long long)a.g.n_ptiles * a.g.mtiles * a.g.ksplit;
-    long long cus = compute_units();
-    if (const char *env = std::getenv("PBKD_SPLIT_WGS")) {
-      const int v = std::atoi(env);
-      if (v >= 1 && v < cus) cus = v;
-    }
-    long long G = items < cus ? items : cus;
-    if (G * kSplitMaxTiles < items) G = (items + kSplitMaxTiles - 1) / kSplitMaxTiles;
     if (items < 1 || items > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)G), block(512);
+    const dim3 grid((unsigned)conv_persistent_workgroups(items)), block(512);
     switch (conv_bslots_for(a.g.PLd)) {
       case 1: go<1>(grid, block, a, s, e0, e1); break;
       case 2: go<2>(grid, block, a, s, e0, e1); break;
@@ -110,6 +92,22 @@ __global__ __launch_bounds__(256) void conv_split_pack_kernel(const float *w, ui
 }
 
 }  // namespace
+
+long long conv_persistent_workgroups(long long items) {
+  static const int units = [] {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
+    return v;
+  }();
+  long long G = units;
+  if (const char *env = std::getenv("PBKD_SPLIT_WGS")) {
+    const int v = std::atoi(env);
+    if (v >= 1 && v < G) G = v;
+  }
+  if (items < G) G = items;
+  if (G * kSplitMaxTiles < items) G = (items + kSplitMaxTiles - 1) / kSplitMaxTiles;
+  return G;
+}
 
 hipError_t launch_conv_split_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s) {
   if (g.wino) return launch_conv_wino_pack(w, wpk, g, Cout, Cin, s);

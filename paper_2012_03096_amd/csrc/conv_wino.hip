@@ -1,6 +1,5 @@
 // Frozen-weight 3x3 convolutions (stride 1) by F(2x2, 3x3) on the bf16 matrix cores (device code: conv_wino_kernel.h): weight
 // image, geometry, launch.
-#include <cstdlib>
 #include <type_traits>
 
 #include "conv_wino_kernel.h"
@@ -9,15 +8,6 @@ namespace pbkd {
 
 namespace {
 constexpr int kMaxLds = 160 * 1024;
-
-int compute_units() {
-  static const int n = [] {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
-    return v;
-  }();
-  return n;
-}
 
 // Canonical weights [Cout][Cin][9] -> G w G^T, in fp64, split into three bf16 pieces, in the multiplying waves' operand order.
 // One thread per (lane of an operand, channel block, chunk, channel tile, position): bound by the latency of its scattered reads,
@@ -146,7 +136,7 @@ bool conv_wino_geom(int N, int Cin, int Cout, int Ho, int Wo, ConvGeom &best, do
       g.stat_parts = want > 1 ? cdiv(N, g.nimg) : g.n_ptiles;
       const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
       const double cost = (double)((items + 255) / 256) * (g.kchunks * 4400.0 + 14000) + 8000 +
-                          (want > 1 ? 4000 + 600.0 * g.ksplit * cdiv(g.nimg * Ho * Wo, 64) + (g.ksplit + 1) * out_bytes / 1500 : 0);
+                          conv_ksplit_cycles(g, N, Cout, Ho, Wo);
       if (best_cost == 0 || cost < best_cost) best_cost = cost, best = g;
     }
   }
@@ -157,7 +147,7 @@ double conv_split_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo) {
   static const double kStage[4] = {4250, 4250, 2500, 1800}, kEnd[4] = {8600, 8600, 5000, 3500};       // per workgroup tile
   const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
   return (double)((items + 255) / 256) * (g.kchunks * kStage[g.tile] + kEnd[g.tile]) + 2 * kStage[g.tile] +
-         (g.ksplit > 1 ? 4000 + 600.0 * g.ksplit * cdiv(g.nimg * Ho * Wo, 64) + (g.ksplit + 1) * 4.0 * N * Cout * Ho * Wo / 1500 : 0);
+         conv_ksplit_cycles(g, N, Cout, Ho, Wo);
 }
 
 hipError_t launch_conv_wino_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s) {
@@ -186,15 +176,8 @@ hipError_t launch_conv_wino(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hip
   if ((unsigned long long)g.ksplit * a.N * a.Cout * a.Ho * a.Wo * sizeof(float) >= (1ull << 32) - 64) return hipErrorInvalidValue;
   if ((unsigned long long)g.mtiles * g.nchunks * kWinoChunkBytes >= (1ull << 32)) return hipErrorInvalidValue;
   const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
-  long long cus = compute_units();
-  if (const char *env = std::getenv("PBKD_SPLIT_WGS")) {
-    const int v = std::atoi(env);
-    if (v >= 1 && v < cus) cus = v;
-  }
   if (items < 1 || items > 0x7fffffffLL) return hipErrorInvalidValue;
-  long long G = items < cus ? items : cus;
-  if (G * kSplitMaxTiles < items) G = (items + kSplitMaxTiles - 1) / kSplitMaxTiles;
-  const dim3 grid((unsigned)G);
+  const dim3 grid((unsigned)conv_persistent_workgroups(items));
   if (sr == 6) go<6>(grid, a, s, e0, e1);
   else go<10>(grid, a, s, e0, e1);
   return hipGetLastError();

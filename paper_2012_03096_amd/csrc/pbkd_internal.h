@@ -280,6 +280,11 @@ inline size_t conv_wino_pack_floats(const ConvGeom &g) { return (size_t)g.mtiles
 bool conv_wino_geom(int N, int Cin, int Cout, int Ho, int Wo, ConvGeom &g, double &cycles);
 // what the aligned split kernel costs with geometry g, in the same cycles
 double conv_split_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo);
+// what splitting K adds in the second kernel and in partial sums written and read, in the same cycles (0 where K is not split)
+double conv_ksplit_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo);
+// The persistent kernels' grid for `items` workgroup tiles: one workgroup per compute unit (their LDS allows no more), each walking
+// every G-th tile; more only where a workgroup's tile table would overflow.  PBKD_SPLIT_WGS=n: n of them.
+long long conv_persistent_workgroups(long long items);
 struct ConvArgs;
 hipError_t launch_conv_wino(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_conv_wino_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s);

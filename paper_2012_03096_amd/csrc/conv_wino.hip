@@ -177,7 +177,7 @@ hipError_t launch_conv_wino(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hip
   if ((unsigned long long)g.mtiles * g.nchunks * kWinoChunkBytes >= (1ull << 32)) return hipErrorInvalidValue;
   const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
   if (items < 1 || items > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)conv_persistent_workgroups(items));
+  const dim3 grid((unsigned)conv_persistent_workgroups(items, a.beside));
   if (sr == 6) go<6>(grid, a, s, e0, e1);
   else go<10>(grid, a, s, e0, e1);
   return hipGetLastError();

@@ -144,6 +144,7 @@ struct Net {
   float bn_decay = 0.99f;
   bool track_running = false;       // set while a student step runs: finished statistics also move the running pair
   bool use_running = false;         // set while an inference-mode forward runs: no batch statistics at all
+  bool beside = false;              // set while a teacher forward runs beside other streams' students
   std::vector<LayerRT> L;
   LayerRT sc;                       // projection shortcut (kind = -1)
   int last_c = 0, last_h = 0, last_w = 0;   // last layer's output (before the pool)
@@ -212,15 +213,16 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
         ConvGeom rows{};
         if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, rows)) r.cg = rows;
       }
-      // Aligned maps at stride 1: transformed 2x2 tiles where the price of the aligned kernel is 1.4 times theirs, 1.6 with K split.  The prices
-      // tell the faster of the two on a hundred shapes from 1x12x12 to 91x68x80, 16 to 504 channels (256 channels at 56x56, batch
-      // 32, 562 -> 377 us a call; 64 at 8x8, batch 16, 13 and 23: start-up); 1.4, because the transformed tiles' workgroups fill
-      // a compute unit and a student on a second stream gets nothing beside them: 64 channels at 224x224, priced 1.33, are 4 %
-      // faster on one stream (2 325 -> 2 237 us a step) and 2 % slower on two (2 126 -> 2 168).  A K split puts small maps on every
-      // compute unit: 512 channels at 4x4, batch 128, priced 1.58, are 60 -> 46 us alone and make the step of five blocks on four
-      // streams 1 % slower (1 034 -> 1 045 us; 128 at 16x16, priced 1.49, leave it as it is).  The stacked rows stay where they
-      // are: their sums in two levels are more accurate.  PBKD_CONV_WINO=1 takes the transformed tiles wherever they can run, 0
-      // nowhere; another forced geometry of the 3x3 convolution leaves them out.
+      // Aligned maps at stride 1: transformed 2x2 tiles where the price of the aligned kernel is 1.4 times theirs, 1.6 times with K
+      // split.  The lines come from 108 drawn shapes, 1 to 131 images, 26 to 512 channels, 4x4 to 212x212, priced 1.15 to 2.8,
+      // timed with either kernel: the teacher alone, a step on one stream, on two, and three blocks on four streams.  Alone the
+      // price tells the faster one (256 channels at 56x56, batch 32, 562 -> 377 us).  Beside a student the transformed tiles
+      // take whole compute units from it.  Without a K split, times faster: priced 1.4 to 1.6 1.09 .. 1.35 alone, 1.01 .. 1.17 on
+      // one stream, 1.06 .. 1.52 on two, 1.02 .. 1.41 on four; 1.15 to 1.4 0.99 .. 1.31, 0.97 .. 1.14, 0.92 .. 1.34, 0.95 .. 1.27.
+      // With one (small maps, which it puts on every compute unit): 1.6 to 2 1.29 .. 1.91, 1.13 .. 1.40, 0.99 .. 1.34, 0.96 .. 1.33;
+      // 1.4 to 1.6 1.03 .. 1.60, 0.99 .. 1.27, 0.95 .. 1.20, 0.86 .. 1.39, slower on four streams for 6 of 16.  The
+      // stacked rows stay where they are: their sums in two levels are more accurate.  PBKD_CONV_WINO=1 takes the transformed tiles
+      // wherever they can run, 0 nowhere; another forced geometry of the 3x3 convolution leaves them out.
       const bool forced = std::getenv("PBKD_CONV_TILE") || std::getenv("PBKD_CONV_KSPLIT") || std::getenv("PBKD_CONV_ROWS");
       if (!student && d.stride == 1 && !env_is("PBKD_CONV_SPLIT", 0) && !env_is("PBKD_CONV_WINO", 0) &&
           (env_is("PBKD_CONV_WINO", 1) || (r.cg.split && !r.cg.rows && !forced))) {
@@ -333,7 +335,7 @@ struct Bump {
 
 // One captured step: the argument tuple it was captured for and the executable graph.
 struct StepGraph {
-  int kind = 0;                       // 0: pbkd_distill_step, 1: pbkd_student_step, 2: pbkd_teacher_forward
+  int kind = 0;                       // 0: pbkd_distill_step, 1: pbkd_student_step, 2: pbkd_teacher_forward, 3: a teacher's forward pass beside other streams
   const void *x = nullptr, *t = nullptr;
   float lr = 0.f;
   hipStream_t s0 = nullptr, s1 = nullptr, aux = nullptr;
@@ -653,7 +655,7 @@ pbkd_status forward_net(Net &net, const float *x, hipStream_t st, Prof *pf) {
       ca.Cin = r.cin; ca.H = r.hin; ca.W = r.win; ca.stride = r.stride;
       ca.out = r.z; ca.stat_partial = running ? nullptr : r.stat;
       ca.N = N; ca.Cout = r.cout; ca.Ho = r.hout; ca.Wo = r.wout; ca.g = r.cg; ca.split_out = r.conv_part;
-      ca.w_canon = r.w0;
+      ca.w_canon = r.w0; ca.beside = net.beside;
       if (r.first_conv) {
         LAUNCH_CARRYING_EVENTS(pf, KK_CONV_FIRST, launch_conv_first(ca, r.cfg, st, e0_, e1_));
       } else {
@@ -1075,8 +1077,10 @@ pbkd_status net_forward_impl(pbkd_block_t *blk, Net &net, const float *x_dev, fl
 }
 }  // namespace
 
+// beside: the caller has students at work on other streams meanwhile.
 static pbkd_status teacher_forward_impl(pbkd_block_t *blk, const float *x_dev, float *target_dev, hipStream_t st,
-                                        hipEvent_t target_free) {
+                                        hipEvent_t target_free, bool beside) {
+  FlagScope company(blk->t.beside, beside);
   return net_forward_impl(blk, blk->t, x_dev, target_dev, st, target_free, false);
 }
 
@@ -1115,13 +1119,17 @@ static pbkd_status run_step(pbkd_block &b, const StepGraph &key, hipStream_t ori
   return PBKD_OK;
 }
 
-pbkd_status pbkd_teacher_forward(pbkd_block_t *blk, const float *x_dev, float *target_dev, void *hip_stream) {
+static pbkd_status teacher_forward_any(pbkd_block_t *blk, const float *x_dev, float *target_dev, void *hip_stream, bool beside) {
   if (!blk || !x_dev || !target_dev) return fail(PBKD_EINVAL, "null argument");
   if (misaligned16(x_dev) || misaligned16(target_dev)) return fail(PBKD_EINVAL, "device tensors must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   StepGraph key;
-  key.kind = 2; key.x = x_dev; key.t = target_dev; key.s0 = st; key.s1 = st;
-  return run_step(*blk, key, st, [&]() { return teacher_forward_impl(blk, x_dev, target_dev, st, nullptr); });
+  key.kind = beside ? 3 : 2; key.x = x_dev; key.t = target_dev; key.s0 = st; key.s1 = st;
+  return run_step(*blk, key, st, [&]() { return teacher_forward_impl(blk, x_dev, target_dev, st, nullptr, beside); });
+}
+
+pbkd_status pbkd_teacher_forward(pbkd_block_t *blk, const float *x_dev, float *target_dev, void *hip_stream) {
+  return teacher_forward_any(blk, x_dev, target_dev, hip_stream, false);
 }
 
 pbkd_status pbkd_student_forward(pbkd_block_t *blk, const float *x_dev, float *out_dev, void *hip_stream) {
@@ -1181,7 +1189,7 @@ static pbkd_status issue_distill(pbkd_block &b, const float *x_dev, float *targe
                                  bool cross_call) {
   pbkd_status e;
   if (ss == ts) {
-    e = teacher_forward_impl(&b, x_dev, target_dev, ts, nullptr);
+    e = teacher_forward_impl(&b, x_dev, target_dev, ts, nullptr, false);
     if (e != PBKD_OK) return e;
     return student_step_impl(b, x_dev, target_dev, lr, ss, nullptr, nullptr);
   }
@@ -1197,7 +1205,7 @@ static pbkd_status issue_distill(pbkd_block &b, const float *x_dev, float *targe
   hipEvent_t done = b.ev_step_done[b.step_count & 1];
   if (lag) HIPCHK(hipStreamWaitEvent(ts, done, 0));       // (recorded two calls ago; never recorded: no wait)
   // only the kernel that writes target_dev waits for the previous call's last reader of it
-  e = teacher_forward_impl(&b, x_dev, target_dev, ts, cross_call ? b.ev_target_free : nullptr);
+  e = teacher_forward_impl(&b, x_dev, target_dev, ts, cross_call ? b.ev_target_free : nullptr, true);
   if (e != PBKD_OK) return e;
   HIPCHK(hipEventRecord(b.ev_teacher, ts));
   e = student_step_impl(b, x_dev, target_dev, lr, ss, b.ev_teacher, cross_call ? b.ev_target_free : nullptr);
@@ -1339,6 +1347,10 @@ pbkd_status pbkd_distill_step_all(int n_blocks, pbkd_block_t *const *blocks, con
   });
   hipStream_t ts = static_cast<hipStream_t>(teacher_stream);
   auto stream_of = [&](int i) { return static_cast<hipStream_t>(streams[stream_of_block[i]]); };
+  // The teacher chain runs beside the students of other streams.  (Not chained, every stream starts with a teacher of its own:
+  // those contend with one another, and with all compute units each they are 0 to 6 % faster on four streams.)
+  bool beside = false;
+  for (int i = 0; i < n_blocks; ++i) beside = beside || (chain && stream_of(i) != ts);
 
   // ---- graph mode (every block has it on): the whole step is one fork/join graph launched on `origin`
   hipStream_t origin = chain ? ts : stream_of(issue[0]);
@@ -1377,7 +1389,7 @@ pbkd_status pbkd_distill_step_all(int n_blocks, pbkd_block_t *const *blocks, con
         };
         if (chain) {
           for (int i = 0; i < n_blocks; ++i) {
-            pbkd_status e = teacher_forward_impl(blocks[i], x_dev[i], target_dev[i], ts, nullptr);
+            pbkd_status e = teacher_forward_impl(blocks[i], x_dev[i], target_dev[i], ts, nullptr, beside);
             if (e != PBKD_OK) return e;
             HIPCHK(hipEventRecord(blocks[i]->ev_teacher, ts));
           }
@@ -1397,7 +1409,7 @@ pbkd_status pbkd_distill_step_all(int n_blocks, pbkd_block_t *const *blocks, con
             bool seen = st == origin;
             for (hipStream_t u : used) seen = seen || u == st;
             if (!seen) HIPCHK(hipStreamWaitEvent(st, owner.ev_fork, 0));
-            pbkd_status e = teacher_forward_impl(blocks[i], x_dev[i], target_dev[i], st, nullptr);
+            pbkd_status e = teacher_forward_impl(blocks[i], x_dev[i], target_dev[i], st, nullptr, false);
             if (e != PBKD_OK) return e;
             e = student_step_impl(*blocks[i], x_dev[i], target_dev[i], lr, st, nullptr, nullptr);
             if (e != PBKD_OK) return e;
@@ -1449,7 +1461,7 @@ pbkd_status pbkd_distill_step_all(int n_blocks, pbkd_block_t *const *blocks, con
       for (int j = i; j <= i + 1 && j < n_blocks; ++j)
         for (const pbkd_block::ReaderRec &r : blocks[j]->readers)
           if (r.used && (r.t == target_dev[i] || r.x == target_dev[i])) HIPCHK(hipStreamWaitEvent(ts, r.ev, 0));
-      pbkd_status e = pbkd_teacher_forward(blocks[i], x_dev[i], target_dev[i], ts);
+      pbkd_status e = teacher_forward_any(blocks[i], x_dev[i], target_dev[i], ts, beside);
       if (e != PBKD_OK) return e;
       HIPCHK(hipEventRecord(blocks[i]->ev_teacher, ts));
     }
@@ -1588,6 +1600,9 @@ pbkd_status pbkd_run_tasks_work_stealing(int n_tasks, pbkd_block_t *const *block
     if (queue_of_task[i] < 0 || queue_of_task[i] >= n_streams) return fail(PBKD_EINVAL, "queue index of task %d out of range", i);
     if (misaligned16(x_dev[i]) || misaligned16(target_dev[i])) return fail(PBKD_EINVAL, "device tensors must be 16-byte aligned");
   }
+  bool beside = false;             // tasks of other streams run beside one another (two streams: 1 to 6 % faster so)
+  for (int w = 1; w < n_streams; ++w) beside = beside || streams[w] != streams[0];
+  beside = beside && n_tasks > 1;
   std::vector<std::deque<int>> queue(n_streams);
   for (int i = 0; i < n_tasks; ++i) queue[queue_of_task[i]].push_back(i);
   std::vector<hipEvent_t> done(n_tasks, nullptr);
@@ -1598,7 +1613,7 @@ pbkd_status pbkd_run_tasks_work_stealing(int n_tasks, pbkd_block_t *const *block
     hipStream_t st = static_cast<hipStream_t>(streams[w]);
     pbkd_status e = PBKD_OK;
     for (int k = 0; k < steps[t] && e == PBKD_OK; ++k) {
-      e = pbkd_teacher_forward(blocks[t], x_dev[t], target_dev[t], st);
+      e = teacher_forward_any(blocks[t], x_dev[t], target_dev[t], st, beside);
       if (e == PBKD_OK) e = pbkd_student_step(blocks[t], x_dev[t], target_dev[t], lr, nullptr, st);
     }
     if (e != PBKD_OK) return e;

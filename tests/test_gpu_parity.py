@@ -1313,6 +1313,51 @@ def test_distill_step_on_two_streams_is_bit_identical(gpu, monkeypatch):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("n,c,h,w_", [(96, 144, 20, 24), (84, 48, 40, 40), (64, 272, 8, 8)])
+def test_transformed_tiles_beside_other_streams_are_bit_identical(gpu, n, c, h, w_, graph):
+    """Beside other streams' kernels the transformed tiles run on fewer workgroups (more tiles than these here, with and without
+    K split): labels and trained students of two blocks are bit for bit those of calls on one stream, from pbkd_distill_step on
+    two streams, from all blocks at once, chained and not, and from whole tasks, eager and captured."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, c, h, w_, wl._convs([c, c])), wl.Arch(n, c, h, w_, wl._dws([c, c]))
+    assert pb.arch_conv_kernel(t, 0)[0] == "transformed"
+    ws = [wl.Workload("beside", t, s, seed=71 + k) for k in range(2)]
+    params = [w.tensors(random_affine=True) for w in ws]
+    xd = torch.from_numpy(np.maximum(params[0][0], 0)).cuda()
+    st = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    got = {}
+    for mode in ("one", "two", "chain", "all", "tasks"):
+        blocks = [pb.Block(t, tp, s, sp) for _, tp, sp in params]
+        td = [torch.zeros(wl.output_shape(t), device="cuda") for _ in range(2)]
+        xs = [xd, td[0] if mode == "chain" else xd]
+        torch.cuda.synchronize()
+        for b in blocks:
+            b.set_graph_mode(graph)
+        for _ in range(3):
+            if mode in ("one", "two"):
+                for b, o in zip(blocks, td):
+                    b.distill_step(xd, o, 0.01, want_loss=False, student_stream=st[0], teacher_stream=st[0 if mode == "one" else 1])
+            elif mode == "tasks":
+                pb.run_tasks_work_stealing(blocks, xs, td, 0.01, [1, 1], st[:2], [0, 1])
+            else:
+                pb.distill_step_all(blocks, xs, td, 0.01, st[:2], [0, 1], [0, 0], mode == "chain", st[2] if mode == "chain" else None)
+            torch.cuda.synchronize()
+        got[mode] = [o.cpu().numpy() for o in td] + [a.copy() for b in blocks for lp in b.student_params() for a in lp]
+        if mode == "chain":                      # (the second block's input is the first one's labels there)
+            blocks[1].teacher_forward(td[0], td[1])
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(got[mode][1], td[1].cpu().numpy())
+        for b in blocks:
+            b.close()
+    first = 1 + 1 + len([a for lp in params[0][2] for a in lp])
+    for mode in ("two", "chain", "all", "tasks"):
+        for k, (a, b) in enumerate(zip(got[mode], got["one"])):
+            if mode != "chain" or k == 0 or 2 <= k < first:
+                np.testing.assert_array_equal(a, b, err_msg=f"{mode} {k}")
+
+
 @pytest.mark.parametrize("name", ["cfg1", "ragged_residual_s2", "three_layers_skip_pool", "cfg2"])
 def test_graph_mode_replays_are_bit_identical_to_eager_steps(gpu, name):
     """pbkd_block_set_graph_mode: the captured step is replayed several times, with the program's own eager work and

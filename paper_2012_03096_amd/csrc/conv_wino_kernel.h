@@ -7,7 +7,12 @@
 // what the transforms add (B^T d B in fp32; 1.75 times the error of a sum passes into z).  rms error of z against fp64, aligned direct
 // kernel -> this one: 64 -> 128 channels at 16x16 3.5e-7 -> 1.9e-7, 64 at 56x56 3.5e-7 -> 1.8e-7, 512 at 4x4 3.2e-7 -> 2.2e-7; the
 // fp32 MFMA kernel 3.0e-7, 3.0e-7, 2.7e-7.  The stacked rows' sums in two levels are below that (1.3e-7 at 67 channels, 1.9e-7 here) and
-// stay on the maps they serve.
+// stay on the maps they serve.  These are weights and maps as a teacher has them.  B^T d B and G w G^T mix a window's pixels and a
+// filter's taps, so an output's error is relative to the window's largest pixel times the filter's largest tap, not to each
+// product: 2^-24 of 64 (11 + 6 channels / 16) times that, summed over the channels, at most (two roundings of v <= 4 pixels are 2 of its units, the
+// products left out 4, the output transform 5; an output's nine positions weigh 64 pixels x taps).  An output that meets a pixel far above
+// the others only where the tap is far below the others has that error, where the direct kernel's is of its own products.  Filters
+// that lack most of their taps are left to the direct kernel (tiles_suit, pbkd_runtime.hip).
 //
 // A workgroup has 64 output channels x 64 tiles x 16 positions of accumulators: 4 waves, a SIMD each, with all 512 registers,
 // 256 of them accumulators.  Wave i holds row i of the transformed tile, so its products need rows a and b of a window only and

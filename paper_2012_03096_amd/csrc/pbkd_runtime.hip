@@ -106,6 +106,9 @@ struct LayerRT {
   size_t n_w0 = 0, n_w1 = 0;
   int taps = 9;                     // of the MFMA conv producing z (9 full, 1 pointwise / shortcut)
   ConvGeom cg;                      // geometry of that conv when it is a 3x3
+  // transformed tiles that the weights may yet rule out (see tiles_suit): both geometries, of which cg is one
+  bool by_weights = false;
+  ConvGeom cg_tiles, cg_direct;
   PwGeom pg, pdg;                   // ... when it is a 1x1 (pointwise / shortcut): forward, data gradient
   DwGeom dwf, dwb;                  // depthwise forward / backward tiles
   WgradGeom wg;                     // pointwise weight gradient, or the full conv's when taps_wgrad
@@ -154,6 +157,7 @@ struct Net {
 // packed copies of a layer's convolution weights: the one for the forward pass, and a student's of both passes
 size_t pack_floats_fwd(const LayerRT &r) {
   if (r.taps != 9) return pw_pack_floats(r.pg);
+  if (r.by_weights) return std::max(conv_wino_pack_floats(r.cg_tiles), conv_split_pack_floats(r.cg_direct));
   return r.cg.wino ? conv_wino_pack_floats(r.cg) : r.cg.split ? conv_split_pack_floats(r.cg) : conv_pack_floats(r.cg);
 }
 size_t student_packed_floats(const Net &net) {
@@ -229,8 +233,11 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
         ConvGeom g{};
         double cycles = 0;
         if (conv_wino_geom(a->n, d.cin, d.cout, r.hout, r.wout, g, cycles) &&
-            (env_is("PBKD_CONV_WINO", 1) || (g.ksplit > 1 ? 1.6 : 1.4) * cycles < conv_split_cycles(r.cg, a->n, d.cout, r.hout, r.wout)))
-          r.cg = g;
+            (env_is("PBKD_CONV_WINO", 1) || (g.ksplit > 1 ? 1.6 : 1.4) * cycles < conv_split_cycles(r.cg, a->n, d.cout, r.hout, r.wout))) {
+          r.by_weights = !env_is("PBKD_CONV_WINO", 1);
+          r.cg_direct = r.cg;
+          r.cg = r.cg_tiles = g;
+        }
       }
       r.cw = cw_geom(a->n, d.cin, r.hout, r.wout, d.stride);
       r.first_conv = (l == 0) && conv_first_ok(d.cin, d.stride) &&
@@ -430,8 +437,10 @@ size_t layout(pbkd_block &b, char *base) {
     r.z = bump.take((size_t)N * r.cout * r.hout * r.wout);
     r.mean = bump.take(r.cout); r.rstd = bump.take(r.cout); r.scale = bump.take(r.cout); r.shift = bump.take(r.cout);
     r.rmean = bump.take(r.cout); r.rvar = bump.take(r.cout);
-    r.stat = bump.take((size_t)r.stat_parts() * r.cout * kStatFloats);
-    if (r.taps == 9 && !r.first_conv && r.cg.ksplit > 1) r.conv_part = bump.take((size_t)r.cg.ksplit * N * r.cout * r.hout * r.wout);
+    const int parts = r.by_weights ? std::max(r.cg_tiles.stat_parts, r.cg_direct.stat_parts) : r.stat_parts();
+    const int ksplit = r.by_weights ? std::max(r.cg_tiles.ksplit, r.cg_direct.ksplit) : r.cg.ksplit;
+    r.stat = bump.take((size_t)parts * r.cout * kStatFloats);
+    if (r.taps == 9 && !r.first_conv && ksplit > 1) r.conv_part = bump.take((size_t)ksplit * N * r.cout * r.hout * r.wout);
   };
   // ---- teacher
   auto tparams = [&](LayerRT &r) {
@@ -568,10 +577,27 @@ std::vector<float> pack_host_pw(const float *w, const PwGeom &g, int M, int K) {
   return out;
 }
 
+// Whether a layer's 3x3 weights suit the transformed tiles: their filters, those that are all zero aside, have at least half of
+// their taps.  A transformed tile rounds for every window, whatever its products, while the direct kernel's sums of few products
+// that are not zero are nearly exact.  rms error of z against fp64, transformed over direct, 64 to 512 channels, for maps that are
+// 50, 25 and 10 % non-zero: all taps 0.37 .. 0.53, 0.44 .. 0.61, 0.56 .. 0.76; half of them 0.42 .. 0.60, 0.52 .. 0.72, 0.70 .. 0.96;
+// a tenth 0.65 .. 0.90, 0.87 .. 1.17, 1.16 .. 1.52.
+bool tiles_suit(const float *w, size_t filters) {
+  size_t taps = 0, some = 0;
+  for (size_t f = 0; f < filters; ++f, w += 9) {
+    int n = 0;
+    for (int t = 0; t < 9; ++t) n += w[t] != 0.f;
+    taps += n;
+    some += n != 0;
+  }
+  return 2 * taps >= 9 * some;
+}
+
 // Writes the packed copy of a teacher layer's convolution weights, whose canonical tensor is already on its way to the
 // device in stream order (w_host: the same values on the host: the 3x3 or the 1x1 tensor, depthwise weights are read as
 // they are).
 pbkd_status upload_packed(LayerRT &r, const float *w_host, hipStream_t s) {
+  if (r.by_weights) r.cg = tiles_suit(w_host, (size_t)r.cout * r.cin) ? r.cg_tiles : r.cg_direct;
   if (r.taps == 9 && r.cg.split) {
     HIPCHK(launch_conv_split_pack(r.w0, r.wpk, r.cg, r.cout, r.cin, s));
     return PBKD_OK;
@@ -1736,8 +1762,13 @@ pbkd_status pbkd_block_set_tensor(pbkd_block_t *blk, int which, int layer, int s
       const size_t at = (size_t)(p - blk->s_params);
       HIPCHK(launch_pack_params(p, n, blk->map_f + at, blk->map_b + at, blk->s_pk, nullptr));
     } else if (has_copy) {
+      const bool tiles = r.cg.wino;
       e = upload_packed(r, host_in, nullptr);
       if (e != PBKD_OK) return e;
+      if (r.cg.wino != tiles) {                        // captured steps hold the other kernel, also those other blocks own
+        drop_graphs(*blk);
+        blk->uid = g_next_uid.fetch_add(1);
+      }
     }
     HIPCHK(hipDeviceSynchronize());
   }

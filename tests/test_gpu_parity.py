@@ -1037,6 +1037,107 @@ def test_transformed_tiles_are_no_less_accurate_than_the_direct_kernel(gpu, monk
         assert b <= 1.05 * a, errs
 
 
+def conv3x3_fp64(x, w):
+    n, c, h, wd = x.shape
+    xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
+    z = np.zeros((w.shape[0], n * h * wd))
+    for tap in range(9):
+        i, j = tap // 3, tap % 3
+        z += w[:, :, i, j].astype(np.float64) @ xp[:, :, i:i + h, j:j + wd].transpose(1, 0, 2, 3).reshape(c, -1)
+    return z.reshape(w.shape[0], n, h, wd).transpose(1, 0, 2, 3)
+
+
+@pytest.mark.parametrize("n,h,w_,ci,co", [(2, 12, 16, 64, 48), (3, 13, 11, 40, 72), (20, 4, 4, 300, 33)])
+def test_transformed_tiles_error_is_relative_to_window_and_filter(gpu, monkeypatch, n, h, w_, ci, co):
+    """Pixels 1e5 times the others, taps that are zero or a thousandth of the others: an error of the transformed tiles is at most
+    2^-24 of 64 (11 + 6 channels / 16) times the window's largest pixel x the filter's largest tap, summed over the channels
+    (conv_wino_kernel.h derives it), and so much larger than the direct kernel's where only such taps meet such pixels: that
+    kernel's is at most 2^-24 of (27 channels / 8 + 5) times the sum of its own products' sizes (27 roundings per eight channels;
+    products left out, K split)."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, ci, h, w_, wl._convs([ci, co])), wl.Arch(n, ci, h, w_, wl._dws([ci, co]))
+    x, tp, sp = wl.Workload("uneven", t, s, seed=73).tensors(random_affine=True)
+    rng = np.random.default_rng(13)
+    x = np.maximum(x, 0) * np.where(rng.random(x.shape) < 0.002, np.float32(1e5), np.float32(1))
+    r = rng.random(tp[0][0].shape)
+    tp[0][0] = tp[0][0] * np.where(r < 0.2, 0, np.where(r < 0.4, 1e-3, 1)).astype(np.float32)
+    w = tp[0][0]
+    ref, products = conv3x3_fp64(x, w), conv3x3_fp64(np.abs(x), np.abs(w))
+    # the window of a 2x2 tile: four rows and columns around it
+    xp = np.pad(np.abs(x), ((0, 0), (0, 0), (1, 2 + h % 2), (1, 2 + w_ % 2)))
+    largest = np.max([xp[:, :, i:i + h + h % 2:2, j:j + w_ + w_ % 2:2] for i in range(4) for j in range(4)], axis=0)
+    tiles = np.einsum("oc,nchw->nohw", np.abs(w).max((2, 3)).astype(np.float64), largest.astype(np.float64))
+    tiles = np.repeat(np.repeat(tiles, 2, 2), 2, 3)[:, :, :h, :w_]
+    xd, td, worst = torch.from_numpy(x).cuda(), torch.empty(wl.output_shape(t), device="cuda"), {}
+    for wino, bound in ((1, 64 * (11 + 6 * ci / 16) * tiles), (0, (27 * ci / 8 + 5) * products)):
+        monkeypatch.setenv("PBKD_CONV_WINO", str(wino))
+        blk = pb.Block(t, tp, s, sp)
+        blk.teacher_forward(xd, td)
+        err = np.abs(blk.get_tensor(pb.TEACHER_ACT, 0, 1, ref.shape) - ref)
+        blk.close()
+        if wino or (h * w_) % 4 == 0:
+            worst[wino] = float(np.max(err / (bound * 2.0 ** -24)))
+            assert worst[wino] <= 1, worst
+    print(f"[uneven taps and pixels] {ci}->{co} {h}x{w_}: worst share of its bound {worst}")
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("n,c,h,w_", [(30, 80, 52, 52), (64, 272, 8, 8)])
+def test_filters_without_most_of_their_taps_keep_the_direct_kernel(gpu, monkeypatch, n, c, h, w_, graph):
+    """A layer whose shape asks for transformed tiles runs them with weights that have half of their taps, also where most filters
+    are all zero, and the direct kernel bit for bit with weights that have fewer: at creation and after pbkd_block_set_tensor, in
+    captured steps too, those of a schedule that another block owns among them."""
+    torch, pb = gpu
+    t, s = wl.Arch(n, c, h, w_, wl._convs([c, c])), wl.Arch(n, c, h, w_, wl._dws([c, c]))
+    assert pb.arch_conv_kernel(t, 0)[0] == "transformed"
+    x, tp, sp = wl.Workload("pruned", t, s, seed=79).tensors(random_affine=True)
+    x = np.maximum(x, 0)
+    rng = np.random.default_rng(17)
+    full = tp[0][0]
+    keep = np.argsort(rng.random((c, c, 9)), axis=2).reshape(full.shape)
+    weights = {"all": full, "five": full * (keep < 5), "four": full * (keep < 4), "tenth": full * (rng.random(full.shape) < 0.1),
+               "filters": full * (rng.random((c, c, 1, 1)) < 0.1)}
+    tiles = {"all": True, "five": True, "four": False, "tenth": False, "filters": True}
+    xd, td = torch.from_numpy(x).cuda(), torch.zeros(wl.output_shape(t), device="cuda")
+    other = torch.zeros(wl.output_shape(t), device="cuda")
+    st = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def labels(w, wino):
+        if wino is None:
+            monkeypatch.delenv("PBKD_CONV_WINO", raising=False)
+        else:
+            monkeypatch.setenv("PBKD_CONV_WINO", wino)
+        blk = pb.Block(t, [[w] + tp[0][1:]], s, sp)
+        blk.teacher_forward(xd, td)
+        torch.cuda.synchronize()
+        blk.close()
+        return td.cpu().numpy()
+
+    want = {name: labels(w, "1" if tiles[name] else "0") for name, w in weights.items()}
+    for name, w in weights.items():
+        assert (labels(w, "0" if tiles[name] else "1") != want[name]).any(), name
+        np.testing.assert_array_equal(labels(w, None), want[name], err_msg=name)
+    monkeypatch.delenv("PBKD_CONV_WINO", raising=False)
+    blk, first = (pb.Block(t, tp, s, sp) for _ in range(2))
+    for b in (blk, first):
+        b.set_graph_mode(graph)
+    for name in ("all", "tenth", "filters", "four", "five", "all"):
+        blk.set_tensor(pb.TEACHER_PARAM, 0, 0, weights[name])
+        for call in range(2):
+            for all_at_once in (False, True):
+                td.zero_()
+                torch.cuda.synchronize()
+                if all_at_once:
+                    pb.distill_step_all([first, blk], [xd, xd], [other, td], 0.0, st, [0, 1], [0, 0], False, None)
+                else:
+                    blk.teacher_forward(xd, td, stream=st[0])
+                torch.cuda.synchronize()
+                np.testing.assert_array_equal(td.cpu().numpy(), want[name], err_msg=f"{name} {call} {all_at_once}")
+    blk.close()
+    first.close()
+
+
 def test_batchnorm_parameters_replaced_rescale_the_layer_behind(gpu):
     """pbkd_block_set_tensor on a teacher's gamma and beta, by seven orders of magnitude: the convolution behind follows."""
     torch, pb = gpu

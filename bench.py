@@ -30,6 +30,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import statistics
 import sys
 import time
@@ -47,9 +48,16 @@ SPLIT_PRODUCTS = 6
 MFMA_SPLIT_PEAK_TFLOPS = round(MFMA_BF16_PEAK_TFLOPS / SPLIT_PRODUCTS, 1)
 
 
+def tuning(name):
+    """A tuning variable as the library reads it: None if it is not set, else what C's atoi makes of it (0 for no number)."""
+    value = os.environ.get(name)
+    digits = re.match(r"\s*[+-]?\d+", value) if value is not None else None
+    return None if value is None else int(digits.group()) if digits else 0
+
+
 def conv_split_in_use():
     """The library's rule for the frozen teacher's 3x3 convolutions: the bf16-split kernel unless PBKD_CONV_SPLIT=0."""
-    return os.environ.get("PBKD_CONV_SPLIT", "") != "0"
+    return tuning("PBKD_CONV_SPLIT") != 0
 
 
 def pointwise_split_in_use(w):
@@ -58,9 +66,20 @@ def pointwise_split_in_use(w):
     return all(min(l.cin, l.cout) >= 16 for l in w.student.layers if l.kind == wl.DWSEP3X3)
 
 
-def weight_gradient_split_in_use():
-    """Whether pointwise weight gradients do: on every map of the workloads here (four pixels or more, tensors up to 2 GiB)."""
-    return os.environ.get("PBKD_WGRAD_SPLIT", "") != "0"
+def weight_gradient_split_in_use(w):
+    """Whether pointwise weight gradients do: on maps of four pixels or more and tensors up to 2 GiB (all of the workloads here),
+    where a workgroup sums more than four chunks of 32 pixels (one workgroup per compute unit, tiles of 64x64 weights)."""
+    from paper_2012_03096_amd import workloads as wl
+    asked = tuning("PBKD_WGRAD_SPLIT")
+    if asked in (0, 1):
+        return asked == 1
+    for (ci, _, _, co, ho, wo), l in zip(wl.layer_shapes(w.student), w.student.layers):
+        if l.kind == wl.DWSEP3X3:
+            chunks = -(-w.student.n * (-(-ho * wo // 4) * 4) // 32)
+            parts = min(chunks, max(1, 256 // (-(-co // 64) * -(-ci // 64))))
+            if -(-chunks // parts) <= 4:
+                return False
+    return True
 
 
 HBM_PEAK_GBS = 8000.0
@@ -297,7 +316,7 @@ def run_block(args, w, kernel_roofline=True):
                 if wk["flops"]:
                     rec["flops_per_step"] = wk["flops"]
                     rec["TFLOPps"] = round(wk["flops"] / sec / 1e12, 2)
-                    split = weight_gradient_split_in_use() if kind == "pw_wgrad_mfma" else kind in ("conv1x1_mfma", "pw_dgrad_mfma") and pointwise_split_in_use(w)
+                    split = weight_gradient_split_in_use(w) if kind == "pw_wgrad_mfma" else kind in ("conv1x1_mfma", "pw_dgrad_mfma") and pointwise_split_in_use(w)
                     peak = MFMA_SPLIT_PEAK_TFLOPS if split else MFMA_F32_PEAK_TFLOPS
                     rec["mfma_peak_TFLOPps"] = peak
                     rec["frac_of_mfma_peak"] = round(wk["flops"] / sec / 1e12 / peak, 4)

@@ -177,3 +177,20 @@ def test_split_weights_that_do_not_fit_their_index_keep_the_fp32_kernels(monkeyp
     split, past_arena = per_weight(16384), per_weight(20480)
     assert 3.5 < split - past_arena < 4.5                # two student copies of 4 bytes a weight instead of 6
     assert 1.5 < past_arena - per_weight(28672) < 2.5    # and the teacher's
+
+
+def test_bench_reads_the_tuning_variables_as_the_library_does(monkeypatch):
+    """The peaks that the benchmark reports rates against are those of the products in use: one chunk of pixels a workgroup (fp32
+    products), eight and more (split ones), and variables that are no numbers, which the library takes for 0."""
+    import bench
+    for name in ("PBKD_WGRAD_SPLIT", "PBKD_CONV_SPLIT"):
+        monkeypatch.delenv(name, raising=False)
+    tiny, large = wl.cfg1_tiny(), [wl.cfg2_vgg_block2(), wl.cfg3_resnet_down(), wl.cfg4_imagenet_vgg_block1()]
+    assert not bench.weight_gradient_split_in_use(tiny) and all(bench.weight_gradient_split_in_use(w) for w in large)
+    assert bench.conv_split_in_use()
+    for value, wgrad in (("0", [False] * 4), ("", [False] * 4), ("off", [False] * 4), ("1", [True] * 4), ("2", [False] + [True] * 3)):
+        monkeypatch.setenv("PBKD_WGRAD_SPLIT", value)
+        monkeypatch.setenv("PBKD_CONV_SPLIT", value)
+        assert [bench.weight_gradient_split_in_use(w) for w in [tiny] + large] == wgrad, value
+        t = wl.Arch(32, 64, 224, 224, [wl.Layer(wl.CONV3X3, 64, 64, 1, 0)])
+        assert bench.conv_split_in_use() == (pb.arch_conv_kernel(t, 0)[0] != "fp32"), value

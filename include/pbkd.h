@@ -47,12 +47,12 @@
  *                           Read when a block is created.
  *   PBKD_CONV_WINO=0|1      transformed 2x2 tiles (F(2x2, 3x3)) for no / for every teacher 3x3 convolution of stride 1 that they can
  *                           take (at least 16 input channels).  Default: on aligned maps where they are priced well below
- *                           the direct kernel, unless more than half of the taps of the layer's filters (those that are all zero
- *                           aside) are zero.  fp32 operands split three ways as at PBKD_CONV_SPLIT, the activations' transforms by cutting:
- *                           products left out at most 2^-22 of a transformed product.  The rms error is 0.35 to 0.95 of the direct
- *                           kernel's (dense weights; least with many channels), but an output's error is relative to its windows'
- *                           largest pixel times its filters' largest tap, not to each of its products.  Infinities and
- *                           numbers above 3.39e38 give what fp32 products give
+ *                           the direct kernel, unless more than half of the layer's weights are zero.  fp32 operands split
+ *                           three ways as at PBKD_CONV_SPLIT, the activations' transforms by cutting: products left out at most
+ *                           2^-22 of a transformed product.  The rms error is 0.35 to 0.96 of the direct kernel's (least with many
+ *                           channels and few zeros), but an output's error is relative to its windows' largest pixel times its
+ *                           filters' largest tap, not to each of its products.  Infinities and numbers above 3.39e38 give what
+ *                           fp32 products give
  *   PBKD_CONV_ROWS=1        the stacked rows for every teacher 3x3 convolution they can take
  *   PBKD_SPLIT_WGS=n        these kernels are persistent, one workgroup per compute unit: launch n workgroups instead and
  *                           leave the other compute units to the kernels of other streams (read at every launch).  By
@@ -320,7 +320,7 @@ unsigned long long pbkd_block_flops(const pbkd_block_t *blk, int which);
 unsigned long long pbkd_arch_flops(const pbkd_arch_desc *arch, int training_step);
 /* Which kernel a teacher of this descriptor runs layer `layer`'s 3x3 convolution with, under the tuning overrides now set (host
  * only): "first" (at most three input channels), "fp32", "aligned", "rows" (stacked rows) or "transformed" (2x2 tiles; by
- * default "aligned" where the weights turn out to lack most of their taps, see PBKD_CONV_WINO); ""
+ * default "aligned" where most weights turn out to be zero, see PBKD_CONV_WINO); ""
  * if the descriptor is invalid or has no such layer.  *k_parts (may be null) <- the parts its sum over K is split into. */
 const char *pbkd_arch_conv_kernel(const pbkd_arch_desc *arch, int layer, int *k_parts);
 

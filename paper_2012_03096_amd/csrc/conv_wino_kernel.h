@@ -11,8 +11,8 @@
 // filter's taps, so an output's error is relative to the window's largest pixel times the filter's largest tap, not to each
 // product: 2^-24 of 64 (11 + 6 channels / 16) times that, summed over the channels, at most (two roundings of v <= 4 pixels are 2 of its units, the
 // products left out 4, the output transform 5; an output's nine positions weigh 64 pixels x taps).  An output that meets a pixel far above
-// the others only where the tap is far below the others has that error, where the direct kernel's is of its own products.  Filters
-// that lack most of their taps are left to the direct kernel (tiles_suit, pbkd_runtime.hip).
+// the others only where the tap is far below the others has that error, where the direct kernel's is of its own products.  Weights
+// that are zero for the most part are left to the direct kernel (tiles_suit, pbkd_runtime.hip).
 //
 // A workgroup has 64 output channels x 64 tiles x 16 positions of accumulators: 4 waves, a SIMD each, with all 512 registers,
 // 256 of them accumulators.  Wave i holds row i of the transformed tile, so its products need rows a and b of a window only and

@@ -56,8 +56,8 @@
  *   PBKD_CONV_ROWS=1        the stacked rows for every teacher 3x3 convolution they can take
  *   PBKD_SPLIT_WGS=n        these kernels are persistent, one workgroup per compute unit: launch n workgroups instead and
  *                           leave the other compute units to the kernels of other streams (read at every launch).  By
- *                           themselves the transformed tiles leave 7 of 16 compute units where a call has work on
- *                           several streams; results are the same bits on any number of workgroups
+ *                           themselves the transformed tiles leave some of them where a call runs them beside students on
+ *                           other streams; results are the same bits on any number of workgroups
  *   PBKD_TEACHER_LAG=1      pbkd_distill_step on two streams, eager: a call's teacher starts only when the student step
  *                           before the previous one has ended (default: as early as its dependencies allow); same
  *                           results, another overlap (read at every call)

@@ -44,7 +44,7 @@ struct SplitLaunch {
   static hipError_t launch(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const long long items = (long long)a.g.n_ptiles * a.g.mtiles * a.g.ksplit;
     if (items < 1 || items > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)conv_persistent_workgroups(items, false)), block(512);
+    const dim3 grid((unsigned)conv_persistent_workgroups(items, Company{})), block(512);
     switch (conv_bslots_for(a.g.PLd)) {
       case 1: go<1>(grid, block, a, s, e0, e1); break;
       case 2: go<2>(grid, block, a, s, e0, e1); break;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void conv_split_pack_kernel(const float *w, ui
 
 }  // namespace
 
-long long conv_persistent_workgroups(long long items, bool beside) {
+long long conv_persistent_workgroups(long long items, const Company &beside) {
   static const int units = [] {
     int dev = 0, v = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
@@ -104,9 +104,9 @@ long long conv_persistent_workgroups(long long items, bool beside) {
     const int v = std::atoi(env);
     if (v >= 1 && v < G) G = v;
   }
-  else if (beside) {
-    const long long most = (G * 9 + 15) / 16, rounds = (items + most - 1) / most;
-    G = (items + rounds - 1) / rounds;
+  else if (beside.units < 16) {
+    const long long most = (G * beside.units + 15) / 16, rounds = (items + most - 1) / most;
+    if (4 * rounds <= beside.rounds * ((items + G - 1) / G)) G = (items + rounds - 1) / rounds;
   }
   if (items < G) G = items;
   if (G * kSplitMaxTiles < items) G = (items + kSplitMaxTiles - 1) / kSplitMaxTiles;

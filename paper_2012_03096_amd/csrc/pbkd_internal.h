@@ -282,13 +282,15 @@ bool conv_wino_geom(int N, int Cin, int Cout, int Ho, int Wo, ConvGeom &g, doubl
 double conv_split_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo);
 // what splitting K adds in the second kernel and in partial sums written and read, in the same cycles (0 where K is not split)
 double conv_ksplit_cycles(const ConvGeom &g, int N, int Cout, int Ho, int Wo);
+// What runs beside a teacher's convolutions on other streams: the sixteenths of the compute units that transformed tiles may take
+// (their workgroups leave no room on theirs), where that makes at most rounds / 4 times the rounds of workgroup tiles.
+struct Company {
+  int units = 16, rounds = 4;
+};
 // The persistent kernels' grid for `items` workgroup tiles: one workgroup per compute unit (their LDS allows no more), each walking
-// every G-th tile; more only where a workgroup's tile table would overflow.  PBKD_SPLIT_WGS=n: n of them.  beside: the workgroups leave
-// no room on their compute unit and other streams have kernels to run, so they are on nine sixteenths of the units, or fewer
-// where that takes no more rounds (two streams, transformed tiles, times faster than the direct kernel with all units -> with
-// these: 32 channels at 36x36, batch 69, 0.90 -> 1.10; 449 at 8x8, batch 22, 0.81 -> 0.96; 80 at 60x60, batch 46, 1.09 -> 1.24;
-// 416 at 20x20, batch 5, 1.22 -> 1.52; of 208, 176, 144, 112 and 80 workgroups 144 are the best on the whole).
-long long conv_persistent_workgroups(long long items, bool beside);
+// every G-th tile; fewer units as `beside` says, and no more than the rounds need; more only where a workgroup's tile table would
+// overflow.  PBKD_SPLIT_WGS=n: n of them.
+long long conv_persistent_workgroups(long long items, const Company &beside);
 struct ConvArgs;
 hipError_t launch_conv_wino(const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_conv_wino_pack(const float *w, float *wpk, const ConvGeom &g, int Cout, int Cin, hipStream_t s);
@@ -317,7 +319,7 @@ struct ConvArgs {
   ConvGeom g;
   float *split_out;        // g.ksplit > 1: [ksplit][N,Cout,Ho,Wo] partial outputs, summed by launch_conv_ksplit_finish
   const float *w_canon;    // the canonical OIHW weights (launch_conv_first, stacked rows)
-  bool beside;             // kernels of other streams run beside this one
+  Company beside;
 };
 // With g.ksplit > 1 the kernel writes partial outputs into split_out (out and stat_partial are left alone).
 // ev_start / ev_stop (both or neither): the launch itself carries the two events, which then hold the dispatch's own

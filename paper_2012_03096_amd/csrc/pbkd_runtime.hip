@@ -109,6 +109,7 @@ struct LayerRT {
   // transformed tiles that the weights may yet rule out (see tiles_suit): both geometries, of which cg is one
   bool by_weights = false;
   ConvGeom cg_tiles, cg_direct;
+  double tiles_cycles = 0;          // their price
   PwGeom pg, pdg;                   // ... when it is a 1x1 (pointwise / shortcut): forward, data gradient
   DwGeom dwf, dwb;                  // depthwise forward / backward tiles
   WgradGeom wg;                     // pointwise weight gradient, or the full conv's when taps_wgrad
@@ -147,7 +148,7 @@ struct Net {
   float bn_decay = 0.99f;
   bool track_running = false;       // set while a student step runs: finished statistics also move the running pair
   bool use_running = false;         // set while an inference-mode forward runs: no batch statistics at all
-  bool beside = false;              // set while a teacher forward runs beside other streams' students
+  Company beside;                   // set while a teacher forward runs beside other streams' students
   std::vector<LayerRT> L;
   LayerRT sc;                       // projection shortcut (kind = -1)
   int last_c = 0, last_h = 0, last_w = 0;   // last layer's output (before the pool)
@@ -217,26 +218,29 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
         ConvGeom rows{};
         if (conv_rows_geom(a->n, d.cin, d.cout, r.hout, r.wout, d.stride, rows)) r.cg = rows;
       }
-      // Aligned maps at stride 1: transformed 2x2 tiles where the price of the aligned kernel is 1.4 times theirs, 1.6 times with K
-      // split.  The lines come from 108 drawn shapes, 1 to 131 images, 26 to 512 channels, 4x4 to 212x212, priced 1.15 to 2.8,
-      // timed with either kernel: the teacher alone, a step on one stream, on two, and three blocks on four streams.  Alone the
-      // price tells the faster one (256 channels at 56x56, batch 32, 562 -> 377 us).  Beside a student the transformed tiles
-      // take whole compute units from it.  Without a K split, times faster: priced 1.4 to 1.6 1.09 .. 1.35 alone, 1.01 .. 1.17 on
-      // one stream, 1.06 .. 1.52 on two, 1.02 .. 1.41 on four; 1.15 to 1.4 0.99 .. 1.31, 0.97 .. 1.14, 0.92 .. 1.34, 0.95 .. 1.27.
-      // With one (small maps, which it puts on every compute unit): 1.6 to 2 1.29 .. 1.91, 1.13 .. 1.40, 0.99 .. 1.34, 0.96 .. 1.33;
-      // 1.4 to 1.6 1.03 .. 1.60, 0.99 .. 1.27, 0.95 .. 1.20, 0.86 .. 1.39, slower on four streams for 6 of 16.  The
-      // stacked rows stay where they are: their sums in two levels are more accurate.  PBKD_CONV_WINO=1 takes the transformed tiles
-      // wherever they can run, 0 nowhere; another forced geometry of the 3x3 convolution leaves them out.
+      // Aligned maps at stride 1: transformed 2x2 tiles where the price of the aligned kernel is 1.4 times theirs, up to 64 input
+      // channels 1.55, with K split 1.6 times.  The lines come from 108 drawn shapes, 1 to 131 images, 26 to 512 channels, 4x4 to
+      // 212x212, priced 1.15 to 2.8, timed with either kernel: the teacher alone, a step on one stream, on two, and three blocks on four
+      // streams (see company).  Alone the price tells the faster one (256 channels at 56x56, batch 32, 562 -> 377 us).  Beside a
+      // student the transformed tiles take whole compute units from it.  Times faster: over 64 channels from 1.4 on 1.09 .. 2.4
+      // alone, 1.04 .. 1.6 on one stream, 1.05 .. 1.6 on two, 1.05 .. 1.8 on four.  Few channels are bound by memory beside a
+      // student: up to 64 from 1.55 on 1.16 .. 1.7, 1.06 .. 1.26, 1.04 .. 1.27, 0.97 .. 1.22; from 1.15 to 1.55 down to 0.91 on four, and 32
+      // channels at 64x68, batch 42 (1.45), three convolutions beside a student of two layers 0.84 on two.  With K split (small maps,
+      // which it puts on every compute unit) from 1.6 to 2 1.33 .. 1.9, 1.13 .. 1.40, 1.01 .. 1.31, 0.95 .. 1.43; from 1.4 to 1.6
+      // 1.04 .. 1.6, 1.00 .. 1.27, 0.96 .. 1.18, 0.78 .. 1.45, slower on four streams for 6 of 16.  The stacked rows stay where they are:
+      // their sums in two levels are more accurate.  PBKD_CONV_WINO=1 takes the transformed tiles wherever they can run, 0 nowhere;
+      // another forced geometry of the 3x3 convolution leaves them out.
       const bool forced = std::getenv("PBKD_CONV_TILE") || std::getenv("PBKD_CONV_KSPLIT") || std::getenv("PBKD_CONV_ROWS");
       if (!student && d.stride == 1 && !env_is("PBKD_CONV_SPLIT", 0) && !env_is("PBKD_CONV_WINO", 0) &&
           (env_is("PBKD_CONV_WINO", 1) || (r.cg.split && !r.cg.rows && !forced))) {
         ConvGeom g{};
         double cycles = 0;
         if (conv_wino_geom(a->n, d.cin, d.cout, r.hout, r.wout, g, cycles) &&
-            (env_is("PBKD_CONV_WINO", 1) || (g.ksplit > 1 ? 1.6 : 1.4) * cycles < conv_split_cycles(r.cg, a->n, d.cout, r.hout, r.wout))) {
+            (env_is("PBKD_CONV_WINO", 1) || (g.ksplit > 1 ? 1.6 : g.nchunks <= 4 ? 1.55 : 1.4) * cycles < conv_split_cycles(r.cg, a->n, d.cout, r.hout, r.wout))) {
           r.by_weights = !env_is("PBKD_CONV_WINO", 1);
           r.cg_direct = r.cg;
           r.cg = r.cg_tiles = g;
+          r.tiles_cycles = cycles;
         }
       }
       r.cw = cw_geom(a->n, d.cin, r.hout, r.wout, d.stride);
@@ -329,6 +333,47 @@ unsigned long long net_flops(const Net &net, bool step) {
   return total;
 }
 
+// Sets one of a network's modes for the length of a scope.
+template <class T>
+struct ModeScope {
+  T &m;
+  ModeScope(T &mode, const T &value) : m(mode) { m = value; }
+  ~ModeScope() { m = T{}; }
+};
+
+// Roughly what a teacher's forward pass and a student's step take alone, in us: the price of transformed tiles at 1.7 GHz,
+// 190 TFLOP/s for the other convolutions; a student's reads and writes at 4.3 TB/s and 5 us a launch.  On 150 drawn blocks 0.86 to
+// 1.30 and 0.60 to 1.39 of the time.
+double teacher_estimate(const Net &net) {
+  double us = 4 + 2 * 4.0 * net.n * net.last_c * net.last_h * net.last_w / 4.3e6;
+  for (const LayerRT &r : net.L)
+    us += r.kind == PBKD_CONV3X3 && r.cg.wino ? r.tiles_cycles / 1700 : 18.0 * r.cin * r.cout * net.n * r.hout * r.wout / 190e6;
+  return us;
+}
+double student_estimate(const Net &net) {
+  double us = 0;
+  for (size_t l = 0; l < net.L.size(); ++l) {
+    const LayerRT &r = net.L[l];
+    const double pix = (double)net.n * r.hout * r.wout, z = pix * r.cout, u = pix * r.cin, x = (double)net.n * r.cin * r.hin * r.win;
+    const double bn = l + 1 < net.L.size() ? 3 * z : 5 * z;                // BatchNorm backward, or the head's two passes
+    us += 4 * (bn + 3 * z + x + (r.kind == PBKD_DWSEP3X3 ? 5 * u + (l ? 2 : 1) * x : x)) / 4.3e6 + (r.kind == PBKD_DWSEP3X3 ? 36 : 20);
+  }
+  return us;
+}
+
+// What a teacher leaves to students on other streams.  Transformed tiles hold a compute unit each, and a student that would
+// otherwise be the longer one waits for them; a teacher that is the longer one needs them all (nine sixteenths for all: down to
+// 0.80 of the direct kernel's speed with three convolutions beside a student of one layer).  The shares are the best on the whole of 256,
+// 224, 192, 176, 160, 144, 128 and 112 workgroups on 70 drawn blocks of one to four convolutions and one to three student layers.
+// On 160 others, times faster than with the direct kernel, all units -> as here: two streams 0.77 .. 2.1 -> 0.93 .. 2.1,
+// slower for 14 -> 7 of them, geometric mean 1.25 -> 1.31; three blocks, teacher chain and three student streams 0.87 .. 2.3 -> 0.86 .. 2.3,
+// slower for 5 -> 3, 1.30 -> 1.32.  (What is left slower splits K on small maps.)
+Company company(double teacher_us, double student_us, bool chain) {
+  if (teacher_us < 1.05 * student_us) return Company{chain ? 14 : 10, 8};
+  if (teacher_us < 1.8 * student_us) return Company{14, 5};
+  return Company{};
+}
+
 struct Bump {
   uintptr_t base;          // 0 when only the size is wanted: the addresses are then never formed as pointers into memory
   size_t off = 0;
@@ -407,6 +452,7 @@ struct pbkd_block {
   double *mse_scratch = nullptr;           // 256 partials + result of pbkd_feature_mse
   float *gz2 = nullptr;                    // layers alternate between gz and gz2 for their dz
   float *gbuf(int l) const { return (l & 1) ? gz2 : gz; }
+  double teacher_us = 0, student_us = 0;   // a forward pass and a training step alone, roughly (teacher_estimate, student_estimate)
   Prof prof;
 };
 
@@ -928,6 +974,8 @@ pbkd_status pbkd_block_create(const pbkd_arch_desc *teacher, const float *const 
   pbkd_status st = validate_pair(teacher, student, b->t, b->s);
   if (st != PBKD_OK) return st;
   if (reinterpret_cast<uintptr_t>(device_workspace) & 255) return fail(PBKD_ENOMEM, "workspace must be 256-byte aligned");
+  b->teacher_us = teacher_estimate(b->t);
+  b->student_us = student_estimate(b->s);
   const size_t need = layout(*b, static_cast<char *>(device_workspace));
   if (workspace_bytes < need) return fail(PBKD_ENOMEM, "workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, need);
   copy_desc(teacher, b->t_layers);
@@ -1081,17 +1129,10 @@ pbkd_status pbkd_block_destroy(pbkd_block_t *blk) {
 // Teacher forward on st; target_dev is only written by the last kernel, which waits for `target_free`
 // (the previous reader of target_dev on another stream) when one is given.
 namespace {
-// Sets one of a network's mode flags for the length of a scope.
-struct FlagScope {
-  bool &f;
-  FlagScope(bool &flag, bool on) : f(flag) { f = on; }
-  ~FlagScope() { f = false; }
-};
-
 // Forward of one network (teacher or student) into out_dev.  running: BatchNorm with the running statistics.
 pbkd_status net_forward_impl(pbkd_block_t *blk, Net &net, const float *x_dev, float *out_dev, hipStream_t st,
                              hipEvent_t out_free, bool running) {
-  FlagScope mode(net.use_running, running);
+  ModeScope<bool> mode(net.use_running, running);
   pbkd_status e = forward_net(net, x_dev, st, &blk->prof);
   if (e != PBKD_OK) return e;
   if (out_free) HIPCHK(hipStreamWaitEvent(st, out_free, 0));
@@ -1104,8 +1145,8 @@ pbkd_status net_forward_impl(pbkd_block_t *blk, Net &net, const float *x_dev, fl
 
 // beside: the caller has students at work on other streams meanwhile.
 static pbkd_status teacher_forward_impl(pbkd_block_t *blk, const float *x_dev, float *target_dev, hipStream_t st,
-                                        hipEvent_t target_free, bool beside) {
-  FlagScope company(blk->t.beside, beside);
+                                        hipEvent_t target_free, const Company &beside) {
+  ModeScope<Company> company(blk->t.beside, beside);
   return net_forward_impl(blk, blk->t, x_dev, target_dev, st, target_free, false);
 }
 
@@ -1144,17 +1185,17 @@ static pbkd_status run_step(pbkd_block &b, const StepGraph &key, hipStream_t ori
   return PBKD_OK;
 }
 
-static pbkd_status teacher_forward_any(pbkd_block_t *blk, const float *x_dev, float *target_dev, void *hip_stream, bool beside) {
+static pbkd_status teacher_forward_any(pbkd_block_t *blk, const float *x_dev, float *target_dev, void *hip_stream, const Company &beside) {
   if (!blk || !x_dev || !target_dev) return fail(PBKD_EINVAL, "null argument");
   if (misaligned16(x_dev) || misaligned16(target_dev)) return fail(PBKD_EINVAL, "device tensors must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   StepGraph key;
-  key.kind = beside ? 3 : 2; key.x = x_dev; key.t = target_dev; key.s0 = st; key.s1 = st;
+  key.kind = beside.units < 16 ? 3 : 2; key.x = x_dev; key.t = target_dev; key.s0 = st; key.s1 = st;
   return run_step(*blk, key, st, [&]() { return teacher_forward_impl(blk, x_dev, target_dev, st, nullptr, beside); });
 }
 
 pbkd_status pbkd_teacher_forward(pbkd_block_t *blk, const float *x_dev, float *target_dev, void *hip_stream) {
-  return teacher_forward_any(blk, x_dev, target_dev, hip_stream, false);
+  return teacher_forward_any(blk, x_dev, target_dev, hip_stream, Company{});
 }
 
 pbkd_status pbkd_student_forward(pbkd_block_t *blk, const float *x_dev, float *out_dev, void *hip_stream) {
@@ -1168,7 +1209,7 @@ pbkd_status pbkd_student_forward(pbkd_block_t *blk, const float *x_dev, float *o
 static pbkd_status student_step_impl(pbkd_block &b, const float *x_dev, const float *target_dev, float lr, hipStream_t st,
                                      hipEvent_t target_ready, hipEvent_t target_free) {
   Prof *pf = &b.prof;
-  FlagScope track(b.s.track_running, true);   // this pass's batch statistics also move the running ones
+  ModeScope<bool> track(b.s.track_running, true);   // this pass's batch statistics also move the running ones
   pbkd_status e = forward_net(b.s, x_dev, st, pf);
   if (e != PBKD_OK) return e;
   if (target_ready) HIPCHK(hipStreamWaitEvent(st, target_ready, 0));
@@ -1214,7 +1255,7 @@ static pbkd_status issue_distill(pbkd_block &b, const float *x_dev, float *targe
                                  bool cross_call) {
   pbkd_status e;
   if (ss == ts) {
-    e = teacher_forward_impl(&b, x_dev, target_dev, ts, nullptr, false);
+    e = teacher_forward_impl(&b, x_dev, target_dev, ts, nullptr, Company{});
     if (e != PBKD_OK) return e;
     return student_step_impl(b, x_dev, target_dev, lr, ss, nullptr, nullptr);
   }
@@ -1230,7 +1271,7 @@ static pbkd_status issue_distill(pbkd_block &b, const float *x_dev, float *targe
   hipEvent_t done = b.ev_step_done[b.step_count & 1];
   if (lag) HIPCHK(hipStreamWaitEvent(ts, done, 0));       // (recorded two calls ago; never recorded: no wait)
   // only the kernel that writes target_dev waits for the previous call's last reader of it
-  e = teacher_forward_impl(&b, x_dev, target_dev, ts, cross_call ? b.ev_target_free : nullptr, true);
+  e = teacher_forward_impl(&b, x_dev, target_dev, ts, cross_call ? b.ev_target_free : nullptr, company(b.teacher_us, b.student_us, false));
   if (e != PBKD_OK) return e;
   HIPCHK(hipEventRecord(b.ev_teacher, ts));
   e = student_step_impl(b, x_dev, target_dev, lr, ss, b.ev_teacher, cross_call ? b.ev_target_free : nullptr);
@@ -1373,9 +1414,14 @@ pbkd_status pbkd_distill_step_all(int n_blocks, pbkd_block_t *const *blocks, con
   hipStream_t ts = static_cast<hipStream_t>(teacher_stream);
   auto stream_of = [&](int i) { return static_cast<hipStream_t>(streams[stream_of_block[i]]); };
   // The teacher chain runs beside the students of other streams.  (Not chained, every stream starts with a teacher of its own:
-  // those contend with one another, and with all compute units each they are 0 to 6 % faster on four streams.)
-  bool beside = false;
-  for (int i = 0; i < n_blocks; ++i) beside = beside || (chain && stream_of(i) != ts);
+  // those contend with one another and are faster, up to 6 %, with all compute units each; so are whole tasks on several streams.)
+  Company beside;
+  if (chain) {
+    bool others = false;
+    double t = 0, st = 0;
+    for (int i = 0; i < n_blocks; ++i) others = others || stream_of(i) != ts, t += blocks[i]->teacher_us, st += blocks[i]->student_us;
+    if (others) beside = company(t, st, true);
+  }
 
   // ---- graph mode (every block has it on): the whole step is one fork/join graph launched on `origin`
   hipStream_t origin = chain ? ts : stream_of(issue[0]);
@@ -1434,7 +1480,7 @@ pbkd_status pbkd_distill_step_all(int n_blocks, pbkd_block_t *const *blocks, con
             bool seen = st == origin;
             for (hipStream_t u : used) seen = seen || u == st;
             if (!seen) HIPCHK(hipStreamWaitEvent(st, owner.ev_fork, 0));
-            pbkd_status e = teacher_forward_impl(blocks[i], x_dev[i], target_dev[i], st, nullptr, false);
+            pbkd_status e = teacher_forward_impl(blocks[i], x_dev[i], target_dev[i], st, nullptr, Company{});
             if (e != PBKD_OK) return e;
             e = student_step_impl(*blocks[i], x_dev[i], target_dev[i], lr, st, nullptr, nullptr);
             if (e != PBKD_OK) return e;
@@ -1625,9 +1671,6 @@ pbkd_status pbkd_run_tasks_work_stealing(int n_tasks, pbkd_block_t *const *block
     if (queue_of_task[i] < 0 || queue_of_task[i] >= n_streams) return fail(PBKD_EINVAL, "queue index of task %d out of range", i);
     if (misaligned16(x_dev[i]) || misaligned16(target_dev[i])) return fail(PBKD_EINVAL, "device tensors must be 16-byte aligned");
   }
-  bool beside = false;             // tasks of other streams run beside one another (two streams: 1 to 6 % faster so)
-  for (int w = 1; w < n_streams; ++w) beside = beside || streams[w] != streams[0];
-  beside = beside && n_tasks > 1;
   std::vector<std::deque<int>> queue(n_streams);
   for (int i = 0; i < n_tasks; ++i) queue[queue_of_task[i]].push_back(i);
   std::vector<hipEvent_t> done(n_tasks, nullptr);
@@ -1638,7 +1681,7 @@ pbkd_status pbkd_run_tasks_work_stealing(int n_tasks, pbkd_block_t *const *block
     hipStream_t st = static_cast<hipStream_t>(streams[w]);
     pbkd_status e = PBKD_OK;
     for (int k = 0; k < steps[t] && e == PBKD_OK; ++k) {
-      e = teacher_forward_any(blocks[t], x_dev[t], target_dev[t], st, beside);
+      e = pbkd_teacher_forward(blocks[t], x_dev[t], target_dev[t], st);
       if (e == PBKD_OK) e = pbkd_student_step(blocks[t], x_dev[t], target_dev[t], lr, nullptr, st);
     }
     if (e != PBKD_OK) return e;

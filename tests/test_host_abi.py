@@ -124,6 +124,7 @@ def conv_kernel(n, cin, cout, h, w, stride=1):
 @pytest.mark.parametrize("n,cin,cout,h,w,stride,name", [
     (8, 3, 64, 32, 32, 1, "first"), (8, 8, 64, 13, 13, 1, "fp32"), (4, 64, 64, 1, 1, 1, "fp32"), (32, 64, 128, 15, 13, 1, "rows"), (16, 128, 128, 16, 16, 2, "aligned"),
     (75, 512, 512, 16, 16, 1, "transformed"), (31, 112, 112, 112, 112, 1, "transformed"), (122, 64, 64, 36, 36, 1, "transformed"),
+    (42, 32, 32, 64, 68, 1, "aligned"), (69, 32, 32, 36, 36, 1, "transformed"), (128, 512, 512, 4, 4, 1, "aligned"), (64, 272, 272, 8, 8, 1, "transformed"),
     (5, 160, 160, 16, 16, 1, "aligned"), (20, 48, 48, 180, 156, 1, "aligned"), (1, 64, 64, 32, 32, 1, "aligned")])
 def test_each_convolution_runs_the_kernel_its_shape_asks_for(n, cin, cout, h, w, stride, name):
     """Without tuning overrides: the direct kernels where a map is not aligned, strided, tiny or has few channels, transformed tiles

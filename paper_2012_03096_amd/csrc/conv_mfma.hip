@@ -199,8 +199,7 @@ bool conv_rows_geom(int N, int Cin, int Cout, int Ho, int Wo, int stride, ConvGe
         g.stat_parts = want > 1 ? cdiv(N, g.nimg) : g.n_ptiles;
         const long long items = (long long)g.n_ptiles * g.mtiles * g.ksplit;
         const double stage = kStages[tile][slots - 1], per_wg = g.kchunks * stage + kEnd[tile];
-        const double cost = (double)((items + 255) / 256) * per_wg + 2 * stage +
-                            conv_ksplit_cycles(g, N, Cout, Ho, Wo);
+        const double cost = (double)((items + 255) / 256) * per_wg + 2 * stage + conv_ksplit_cycles(g, N, Cout, Ho, Wo);
         if (best_cost == 0 || cost < best_cost) best_cost = cost, best = g;
       }
     }

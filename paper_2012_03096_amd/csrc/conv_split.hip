@@ -103,8 +103,7 @@ long long conv_persistent_workgroups(long long items, const Company &beside) {
   if (const char *env = std::getenv("PBKD_SPLIT_WGS")) {
     const int v = std::atoi(env);
     if (v >= 1 && v < G) G = v;
-  }
-  else if (beside.units < 16) {
+  } else if (beside.units < 16) {
     const long long most = (G * beside.units + 15) / 16, rounds = (items + most - 1) / most;
     if (4 * rounds <= beside.rounds * ((items + G - 1) / G)) G = (items + rounds - 1) / rounds;
   }

@@ -121,6 +121,23 @@ def wgrad_takes_bn_backward(arch, shapes, l):
             and arch.layers[1].kind == wl.DWSEP3X3 and 4 * arch.n * co * ho * wo <= 2 ** 31)
 
 
+def pw_bwd_layers(w):
+    """Per student layer: None, or where the library forms the pointwise weight and data gradient in one kernel (split products for
+    the weight gradient, 16 to 128 output channels) how many tensors of the layer's output its dz comes from: g and z inside a
+    block, dz under a pool without aligned windows, 0 where it comes from the head's inputs."""
+    from paper_2012_03096_amd import workloads as wl
+    arch, out = w.student, []
+    for l, ((ci, _, _, co, ho, wo), L) in enumerate(zip(wl.layer_shapes(arch), arch.layers)):
+        one = wl.Workload(w.name, w.teacher, wl.Arch(arch.n, ci, ho, wo, [wl.Layer(wl.DWSEP3X3, ci, co, 1, 1)]), seed=0)
+        used = (L.kind == wl.DWSEP3X3 and L.trainable and 16 <= co <= 128 and ho * wo >= 4 and 4 * arch.n * max(ci, co) * ho * wo <= 2 ** 31
+                and weight_gradient_split_in_use(one) and tuning("PBKD_PW_BWD") != 0
+                and os.environ.get("PBKD_WGRAD_VARIANT") is None and os.environ.get("PBKD_PW_VARIANT") is None)
+        last = l + 1 == len(arch.layers)
+        aligned = arch.pool != 2 or (wo % 4 == 0 and ho % 2 == 0)
+        out.append(None if not used else 2 if not last else 0 if aligned else 1)
+    return out
+
+
 def kernel_work(w):
     """Per kernel kind of the library (pbkd_kernel_kind_name): algorithmic bytes (every input tensor read once, every
     output written once, fp32), convolution FLOPs and launches of ONE step = teacher forward + student step."""
@@ -133,7 +150,7 @@ def kernel_work(w):
         rec["flops"] += flops
         rec["launches"] += 1
 
-    def forward(arch, training):
+    def forward(arch, training, in_one=()):
         n = arch.n
         shapes = wl.layer_shapes(arch)
         for l, ((ci, hi, wi, co, ho, wo), L) in enumerate(zip(shapes, arch.layers)):
@@ -155,13 +172,18 @@ def kernel_work(w):
             zs = z
         if training:
             add("head_loss", z + zs + t)
-            add("head_bwd", z + zs + t + z)
+            if in_one and in_one[-1] == 0:
+                add("pw_bwd", z + zs + t)            # (the rest of it below)
+                work["pw_bwd"]["launches"] -= 1
+            else:
+                add("head_bwd", z + zs + t + z)
         else:
             add("head_out", z + zs + t)
 
     forward(w.teacher, False)
-    forward(w.student, True)
+    forward(w.student, True, pw_bwd_layers(w))
     arch = w.student
+    in_one = pw_bwd_layers(w)
     n = arch.n
     shapes = wl.layer_shapes(arch)
     params = 0
@@ -171,10 +193,13 @@ def kernel_work(w):
             break
         a, u, z = n * ci * hi * wi, n * ci * ho * wo, n * co * ho * wo
         if L.kind == wl.DWSEP3X3:
-            add("pw_wgrad_mfma", z + u, 2 * ci * co * n * ho * wo)
-            add("pw_dgrad_mfma", z + u, 2 * ci * co * n * ho * wo)
+            if in_one[l] is not None:                # what dz is made of, u; du
+                add("pw_bwd", in_one[l] * z + 2 * u, 4 * ci * co * n * ho * wo)
+            else:
+                add("pw_wgrad_mfma", z + u, 2 * ci * co * n * ho * wo)
+                add("pw_dgrad_mfma", z + u, 2 * ci * co * n * ho * wo)
             add("dw3x3_bwd", u + a if l == 0 else u + 2 * a, 2 * 9 * ci * n * ho * wo * (1 if l == 0 else 2))
-            if l > 0 and arch.layers[l - 1].trainable and not wgrad_takes_bn_backward(arch, shapes, l - 1):
+            if l > 0 and arch.layers[l - 1].trainable and not wgrad_takes_bn_backward(arch, shapes, l - 1) and in_one[l - 1] is None:
                 add("bn_bwd_apply", 3 * a)
             params += 9 * ci + ci * co + 2 * co
         else:
@@ -187,7 +212,7 @@ def kernel_work(w):
     return work
 
 
-HBM_KINDS = ["conv3x3_first", "dw3x3_fwd", "conv1x1_mfma", "head_out", "head_loss", "head_bwd", "pw_wgrad_mfma", "pw_dgrad_mfma",
+HBM_KINDS = ["conv3x3_first", "dw3x3_fwd", "conv1x1_mfma", "head_out", "head_loss", "head_bwd", "pw_wgrad_mfma", "pw_dgrad_mfma", "pw_bwd",
              "dw3x3_bwd", "bn_bwd_apply", "conv3x3_wgrad", "sgd_momentum"]
 
 
@@ -316,7 +341,7 @@ def run_block(args, w, kernel_roofline=True):
                 if wk["flops"]:
                     rec["flops_per_step"] = wk["flops"]
                     rec["TFLOPps"] = round(wk["flops"] / sec / 1e12, 2)
-                    split = weight_gradient_split_in_use(w) if kind == "pw_wgrad_mfma" else kind in ("conv1x1_mfma", "pw_dgrad_mfma") and pointwise_split_in_use(w)
+                    split = weight_gradient_split_in_use(w) if kind == "pw_wgrad_mfma" else kind == "pw_bwd" or kind in ("conv1x1_mfma", "pw_dgrad_mfma") and pointwise_split_in_use(w)
                     peak = MFMA_SPLIT_PEAK_TFLOPS if split else MFMA_F32_PEAK_TFLOPS
                     rec["mfma_peak_TFLOPps"] = peak
                     rec["frac_of_mfma_peak"] = round(wk["flops"] / sec / 1e12 / peak, 4)

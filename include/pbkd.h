@@ -71,6 +71,10 @@
  *   PBKD_WGRAD_SPLIT=0|1    pointwise weight gradients on the fp32 matrix cores everywhere / on the bf16 ones from operands split
  *                           three ways wherever they can run: 32-bit offsets and groups of four pixels.  Default: there, except
  *                           where a workgroup sums at most four chunks of 32 pixels.  A NaN sum is formed again in fp32
+ *   PBKD_PW_BWD=0|1         pointwise weight and data gradient in one kernel that forms dz itself: nowhere / wherever it can run (16
+ *                           to 128 output channels, maps of four pixels or more, tensors up to 2 GiB, pointwise kernels from split
+ *                           operands).  Default: there, where the weight gradient alone would take split products, unless
+ *                           PBKD_WGRAD_VARIANT or PBKD_PW_VARIANT force one of the kernels it replaces
  *   PBKD_CF_TH=4|8          first-layer 3x3 convolution (at most three input channels): rows of a workgroup's tile
  *   PBKD_CF_OCC=1..8        same kernel: workgroups per compute unit its persistent grid is sized for (default 4)
  *   PBKD_DW_EDGE=0          depthwise register-window kernels on maps whose width is not 4, 8, 16, 32 or 64: a strip's

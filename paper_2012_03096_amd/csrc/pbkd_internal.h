@@ -429,6 +429,38 @@ struct WgradArgs {
 hipError_t launch_pw_wgrad(const WgradArgs &a, hipStream_t s);
 hipError_t init_pw_wgrad_attributes();
 
+// ------------------------------------------------------------------ pointwise backward in one kernel (pw_bwd.hip)
+// dz (formed on load), dP partials as launch_pw_wgrad's, and du = P^T dz.
+struct PwBwdGeom {
+  int bm;                  // rows of dP a workgroup has, all of them: 64 or 128
+  bool pooled;             // pixels are taken in units of two rows and four columns
+  int tiles_n, splits, chunks_per_split;
+  size_t lds_bytes;
+};
+// pdg: the data gradient's geometry, whose packed weights the kernel reads.  false: a shape it does not take
+bool pw_bwd_geom(int N, int Co, int Ci, int H, int W, bool pooled, const PwGeom &pdg, PwBwdGeom &g);
+struct PwBwdArgs {
+  int src;                 // dz: 0 given, 1 BatchNorm backward of g, 2 the head's without a pool, 3 with the 2x2 pool
+  const float *g;          // 0: dz.  1: dL/d(BatchNorm output), masked by the ReLU
+  const float *z, *zs, *t; // pre-BatchNorm output; 2, 3: second input of the head or nullptr, target
+  const float *u;          // [N,Ci,H,W]
+  const float *wpk, *w;    // P packed for the data gradient (w_blocks blocks of 32 input channels), and as it is, [Co][Ci]
+  const float *scale, *shift, *mean, *rstd, *scale_s, *shift_s;
+  int identity_skip;       // zs is added as it is
+  // the channel sums: finished, or (sum_partial) partials [sum_parts][Co][sum_row] with dbeta at sum_at and dgamma behind it,
+  // which are summed and stored; loss_out: the loss kernel's partials, whose entry 0 is summed and stored too
+  float *dgamma, *dbeta, *loss_out;
+  const float *sum_partial;
+  int sum_parts, sum_row, sum_at;
+  float loss_scale, gscale;
+  float *du;               // [N,Ci,H,W]
+  float *partial;          // [splits][Co][Ci]
+  int N, Co, Ci, H, W, w_blocks;
+  PwBwdGeom geo;
+};
+hipError_t launch_pw_bwd(const PwBwdArgs &a, hipStream_t s);
+hipError_t init_pw_bwd_attributes();
+
 // ------------------------------------------------------------------ BatchNorm statistics
 // A convolution leaves the statistics of its output as per-tile partial sums.  Either launch_bn_finalize
 // turns them into (mean, rstd, scale = gamma*rstd, shift = beta - mean*scale), or the first kernel that

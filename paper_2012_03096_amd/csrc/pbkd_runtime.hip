@@ -49,11 +49,11 @@ pbkd_status fail(pbkd_status st, const char *fmt, ...) {
 // Optional per-launch timing: a pool of event pairs recorded around the launches whose kind is in the mask.
 enum KernelKind {
   KK_CONV3X3 = 0, KK_CONV1X1, KK_PW_DGRAD, KK_PW_WGRAD, KK_DW_FWD, KK_DW_BWD, KK_CONV_WGRAD, KK_BN_FINALIZE,
-  KK_HEAD_OUT, KK_HEAD_LOSS, KK_HEAD_BWD, KK_BN_BWD, KK_SGD, KK_REDUCE, KK_CONV_FIRST, KK_DWPW_FWD, KK_COUNT
+  KK_HEAD_OUT, KK_HEAD_LOSS, KK_HEAD_BWD, KK_BN_BWD, KK_SGD, KK_REDUCE, KK_CONV_FIRST, KK_DWPW_FWD, KK_PW_BWD, KK_COUNT
 };
 const char *const kKindNames[KK_COUNT] = {
   "conv3x3_mfma", "conv1x1_mfma", "pw_dgrad_mfma", "pw_wgrad_mfma", "dw3x3_fwd", "dw3x3_bwd", "conv3x3_wgrad", "bn_finalize",
-  "head_out", "head_loss", "head_bwd", "bn_bwd_apply", "sgd_momentum", "reduce_partials", "conv3x3_first", "dwpw_fwd"};
+  "head_out", "head_loss", "head_bwd", "bn_bwd_apply", "sgd_momentum", "reduce_partials", "conv3x3_first", "dwpw_fwd", "pw_bwd"};
 
 struct Prof {
   unsigned mask = 0;
@@ -120,6 +120,9 @@ struct LayerRT {
   bool wgrad_bn_fused = false;      // ... and takes its BatchNorm's backward pass along (dz of this layer is never formed)
   bool fused_fwd = false;           // depthwise + pointwise forward in one kernel; pg then only describes the packing
   DwPwGeom dpg{};
+  bool pw_bwd = false;              // pointwise weight and data gradient in one kernel, which forms dz itself (pb_src: PwBwdArgs::src)
+  int pb_src = 0;
+  PwBwdGeom pb{};
 };
 
 // tuning aid: environment variable `name` set to the integer v
@@ -165,6 +168,20 @@ size_t student_packed_floats(const Net &net) {
   size_t n = net.shortcut == 1 ? pack_floats_fwd(net.sc) : 0;
   for (const LayerRT &r : net.L) n += pack_floats_fwd(r) + (r.kind == PBKD_DWSEP3X3 ? pw_pack_floats(r.pdg) : 0);
   return n;
+}
+
+// Pointwise weight and data gradient of layer l from one kernel: where the weight gradient's own kernel would take split products
+// (sums of a few chunks stay on fp32 ones).  PBKD_PW_BWD=1 wherever it can run, 0 nowhere; a forced variant of the kernels it replaces
+// leaves it out.
+void choose_pw_bwd(Net &net, int l) {
+  LayerRT &r = net.L[l];
+  const bool forced = std::getenv("PBKD_WGRAD_VARIANT") || std::getenv("PBKD_PW_VARIANT") || !r.wg.split;
+  if (r.kind != PBKD_DWSEP3X3 || !r.trainable || env_is("PBKD_PW_BWD", 0) || (forced && !env_is("PBKD_PW_BWD", 1))) return;
+  const bool last = l + 1 == (int)net.L.size();
+  // under a pool the kernel takes aligned windows; where there are none the head kernel writes dz
+  const bool pooled = last && net.pool == 2 && r.wout % 4 == 0 && r.hout % 2 == 0;
+  r.pw_bwd = pw_bwd_geom(net.n, r.cout, r.cin, r.hout, r.wout, pooled, r.pdg, r.pb);
+  r.pb_src = !last ? 1 : net.pool != 2 ? 2 : pooled ? 3 : 0;
 }
 
 pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
@@ -295,6 +312,7 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
         r.pdg = pw_geom(a->n, r.cout, r.cin, r.hout, r.wout, 1, false);
       }
   }
+  for (int l = 0; student && l < a->n_layers; ++l) choose_pw_bwd(net, l);
   net.out_h = a->pool == 2 ? h / 2 : h;
   net.out_w = a->pool == 2 ? w / 2 : w;
   if (net.out_h < 1 || net.out_w < 1) return fail(PBKD_ESHAPE, "max-pool leaves an empty output");
@@ -548,10 +566,11 @@ size_t layout(pbkd_block &b, char *base) {
     if (r.kind == PBKD_DWSEP3X3) umax = std::max(umax, (size_t)N * r.cin * r.hout * r.wout);
     if (!r.trainable) continue;
     if (r.kind == PBKD_DWSEP3X3) {
-      r.wg_part = bump.take((size_t)r.wg.splits * r.cout * r.cin);
+      const int splits = r.pw_bwd ? r.pb.splits : r.wg.splits;
+      r.wg_part = bump.take((size_t)splits * r.cout * r.cin);
       r.dw_part = bump.take((size_t)r.dwb.n_tiles * r.cin * 11);
       add_job(r.dw_part, r.w0, r.n_w0, r.dwb.n_tiles, 1, r.cin);
-      add_job(r.wg_part, r.w1, r.n_w1, r.wg.splits, 0, 0);
+      add_job(r.wg_part, r.w1, r.n_w1, splits, 0, 0);
     } else {
       const int parts = r.taps_wgrad ? r.wg.slabs : r.cw.n_tiles;
       r.wg_part = bump.take((size_t)parts * r.cout * r.cin * 9);
@@ -798,7 +817,9 @@ HeadArgs head_args(pbkd_block &b, Net &net, bool first, const float *x) {
 // downstream depends on them before the update: with an auxiliary stream they run beside the data-gradient
 // chain.  The data gradient of layer l is written into gbuf(l-1) = gbuf(l+1), so it first waits for the
 // weight gradient of layer l+1, which reads that buffer.
-pbkd_status student_backward(pbkd_block &b, const float *x, hipStream_t st) {
+// head: the last layer's, with the loss kernel's partials; where the layer's pointwise kernel forms dz itself (pw_bwd) it reads the
+// target, and target_free (if given) is recorded behind it.
+pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head, hipStream_t st, hipEvent_t target_free) {
   Net &net = b.s;
   Prof *pf = &b.prof;
   const int N = net.n;
@@ -815,6 +836,25 @@ pbkd_status student_backward(pbkd_block &b, const float *x, hipStream_t st) {
       HIPCHK(hipStreamWaitEvent(ws, b.ev_dz[l], 0));
     }
     if (r.kind == PBKD_DWSEP3X3) {
+      if (r.pw_bwd) {
+        PwBwdArgs ba{};
+        ba.src = r.pb_src; ba.g = dz; ba.z = r.z; ba.u = r.u; ba.wpk = r.wpk_b; ba.w = r.w1;
+        ba.w_blocks = r.pdg.mtiles * (r.pdg.bm / 32);
+        ba.scale = r.scale; ba.shift = r.shift; ba.mean = r.mean; ba.rstd = r.rstd;
+        ba.dgamma = r.g_gamma; ba.dbeta = r.g_beta;
+        if (r.pb_src == 1) {
+          const LayerRT &q = net.L[l + 1];                 // its depthwise kernel has left the sums
+          if (q.dwb.n_tiles <= kBnBwdFoldMaxTiles) { ba.sum_partial = q.dw_part; ba.sum_parts = q.dwb.n_tiles; ba.sum_row = 11; ba.sum_at = 9; }
+        } else if (r.pb_src >= 2) {
+          ba.zs = head.zs; ba.t = head.t; ba.scale_s = head.scale_s; ba.shift_s = head.shift_s; ba.identity_skip = head.identity_skip;
+          ba.gscale = head.gscale; ba.loss_scale = head.loss_scale; ba.loss_out = head.partial ? head.loss_out : nullptr;
+          ba.sum_partial = head.partial; ba.sum_parts = head.n_blk; ba.sum_row = 3; ba.sum_at = 1;
+        }
+        ba.du = b.du; ba.partial = r.wg_part; ba.N = N; ba.Co = r.cout; ba.Ci = r.cin; ba.H = r.hout; ba.W = r.wout; ba.geo = r.pb;
+        LAUNCH(pf, KK_PW_BWD, st, launch_pw_bwd(ba, st));
+        if (b.aux) HIPCHK(hipEventRecord(b.ev_wg[l], st));
+        if (r.pb_src >= 2 && target_free) HIPCHK(hipEventRecord(target_free, st));
+      } else {
       WgradArgs wa{};
       wa.dz = dz; wa.u = r.u; wa.partial = r.wg_part; wa.N = N; wa.Co = r.cout; wa.Ci = r.cin; wa.HW = r.hout * r.wout; wa.g = r.wg;
       LAUNCH(pf, KK_PW_WGRAD, ws, launch_pw_wgrad(wa, ws));   // its partials are summed by the update kernel
@@ -825,6 +865,7 @@ pbkd_status student_backward(pbkd_block &b, const float *x, hipStream_t st) {
       pa.N = N; pa.Cin = r.cout; pa.Cout = r.cin; pa.HWin = r.hout * r.wout; pa.Win = r.wout; pa.Ho = r.hout; pa.Wo = r.wout;
       pa.stride = 1; pa.nchunks = r.pdg.nchunks; pa.g = r.pdg;
       LAUNCH(pf, KK_PW_DGRAD, st, launch_pw(pa, st));
+      }
       float *gprev = b.gbuf(l - 1);   // unused for l == 0
       DwBwdArgs da{};
       da.du = b.du; da.D = r.w0; da.gout = gprev; da.partial = r.dw_part;
@@ -845,7 +886,7 @@ pbkd_status student_backward(pbkd_block &b, const float *x, hipStream_t st) {
         LayerRT &q = net.L[l - 1];
         const bool fold = r.dwb.n_tiles <= kBnBwdFoldMaxTiles && !q.wgrad_bn_fused;
         if (!fold) LAUNCH(pf, KK_REDUCE, st, launch_dw_bwd_finalize(r.dw_part, r.dwb.n_tiles, r.cin, nullptr, dg_prev, db_prev, st));
-        if (!q.wgrad_bn_fused)   // (else the layer's weight-gradient kernel takes g, z and the two sums as they are)
+        if (!q.wgrad_bn_fused && !q.pw_bwd)   // (else the layer's own gradient kernel takes g, z and the two sums)
           LAUNCH(pf, KK_BN_BWD, st, launch_bn_bwd_apply(gprev, q.z, q.scale, q.mean, q.rstd, q.g_gamma, q.g_beta,
                                                         fold ? r.dw_part : nullptr, r.dwb.n_tiles, N, q.cout, q.hout * q.wout, st));
       }
@@ -990,6 +1031,7 @@ pbkd_status pbkd_block_create(const pbkd_arch_desc *teacher, const float *const 
     g_init_err = init_conv_attributes();
     if (g_init_err == hipSuccess) g_init_err = init_pw_attributes();
     if (g_init_err == hipSuccess) g_init_err = init_pw_wgrad_attributes();
+    if (g_init_err == hipSuccess) g_init_err = init_pw_bwd_attributes();
     if (g_init_err == hipSuccess) g_init_err = init_dwpw_attributes();
   });
   if (g_init_err != hipSuccess) return fail(PBKD_EHIP, "kernel attribute setup: %s", hipGetErrorString(g_init_err));
@@ -1226,6 +1268,7 @@ static pbkd_status student_step_impl(pbkd_block &b, const float *x_dev, const fl
   const bool fuse = last.trainable && (long long)b.head_nblk * b.head_nblk <= kDeferMaxReads;
   if (!fuse)
     LAUNCH(pf, KK_REDUCE, st, launch_head_finalize(b.head_partial, b.head_nblk, b.s.last_c, (float)(1.0 / cnt), last.g_gamma, last.g_beta, b.loss_dev, st));
+  const bool in_pw_bwd = last.pw_bwd && last.pb_src >= 2;      // the last layer's gradient kernel forms dz itself
   if (last.trainable) {
     h.pend = BnPending{}; h.pend_s = BnPending{};
     h.dz = b.gbuf((int)b.s.L.size() - 1); h.dgamma = last.g_gamma; h.dbeta = last.g_beta;
@@ -1234,11 +1277,11 @@ static pbkd_status student_step_impl(pbkd_block &b, const float *x_dev, const fl
     } else {
       h.partial = nullptr;
     }
-    LAUNCH(pf, KK_HEAD_BWD, st, launch_head(2, h, st));
+    if (!in_pw_bwd) LAUNCH(pf, KK_HEAD_BWD, st, launch_head(2, h, st));
   }
-  if (target_free) HIPCHK(hipEventRecord(target_free, st));
+  if (target_free && !in_pw_bwd) HIPCHK(hipEventRecord(target_free, st));
   if (last.trainable) {
-    e = student_backward(b, x_dev, st);
+    e = student_backward(b, x_dev, h, st, in_pw_bwd ? target_free : nullptr);
     if (e != PBKD_OK) return e;
     LAUNCH(pf, KK_SGD, st, launch_reduce_update(b.jobs_dev, b.job_of_block_dev, (int)b.job_of_block.size(), b.s_params, b.s_mom, b.s_grads,
                                                 lr, b.momentum, b.map_f, b.map_b, b.s_pk, st));

@@ -721,6 +721,57 @@ def test_pointwise_weight_gradient_infinities(gpu, monkeypatch, n, h, w_, ci, co
     np.testing.assert_array_equal(value_classes(split), value_classes(fp32))
 
 
+@pytest.mark.parametrize("n,h,w_,chans,pool,shortcut", [
+    (1, 1, 4, (3, 16), 0, 0), (3, 2, 2, (5, 70, 16), 0, 0), (2, 4, 4, (64, 64), 2, 0), (3, 6, 8, (16, 65, 128), 2, 0), (2, 5, 7, (40, 17, 33), 2, 0),
+    (9, 27, 23, (67, 100, 67), 0, 2), (5, 8, 12, (20, 128, 64), 2, 1), (7, 9, 5, (130, 127, 63), 0, 1), (40, 16, 16, (64, 128, 128), 2, 0),
+    (33, 12, 20, (70, 64, 64), 2, 2), (150, 7, 7, (64, 100), 0, 0), (20, 30, 28, (200, 48, 64), 2, 0)])
+def test_pointwise_gradients_in_one_kernel(gpu, monkeypatch, n, h, w_, chans, pool, shortcut):
+    """Pointwise weight and data gradient from one kernel that forms dz from g and z, from the head's inputs with and without a
+    pool and a second input, or reads it (a pool without aligned windows): 64 and 128 rows of weights, ragged channels, one to six
+    column tiles, images that end in overlapping groups of four pixels, units that wrap, one to ten chunks a workgroup."""
+    monkeypatch.setenv("PBKD_PW_BWD", "1")
+    chans = tuple(chans) if shortcut != 2 else (chans[0], *chans[1:-1], chans[0])
+    t = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans)), shortcut=1 if shortcut == 1 else 0, shortcut_stride=1, pool=pool)
+    s = wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)), shortcut=shortcut, shortcut_stride=1, pool=pool)
+    fails = run_parity(gpu, wl.Workload("pw_bwd", t, s, seed=41), steps=2)
+    assert not fails, fails
+
+
+@pytest.mark.parametrize("n,h,w_,chans,pool", [(6, 27, 23, (40, 100, 67), 0), (40, 8, 8, (20, 33, 64), 2), (3, 5, 3, (17, 70, 70), 0)])
+def test_pointwise_gradients_in_one_kernel_infinities(gpu, monkeypatch, n, h, w_, chans, pool):
+    """A target that holds a NaN or an infinity in its last channel's last pixel, an infinite input, and a depthwise output past
+    bfloat16's largest: every gradient of the block has its infinities and NaNs where the kernels apart have them."""
+    torch, pb = gpu
+    t = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans)), pool=pool)
+    s = wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)), pool=pool)
+    x, tp, sp = wl.Workload("pw_bwd_infinities", t, s, seed=61).tensors(random_affine=True)
+    x, sp = np.maximum(x, 0), [[a.copy() for a in lp] for lp in sp]
+    sp[-1][2][:], sp[-1][3][:] = 0.1, 5.0                                   # (no output reaches ReLU's corner)
+    sp[0][0].reshape(chans[0], 9)[1] = np.eye(9)[4]
+    sp[0][1].reshape(chans[1], chans[0])[:, 1] *= np.float32(1e-38)
+    td = (5 + np.random.default_rng(4).standard_normal(wl.output_shape(t))).astype(np.float32)
+
+    def gradients(mode, xv, tv):
+        monkeypatch.setenv("PBKD_PW_BWD", mode)
+        blk, xd, tgt = pb.Block(t, tp, s, sp), torch.from_numpy(xv).cuda(), torch.from_numpy(tv).cuda()
+        blk.student_step(xd, tgt, 0.0, want_loss=False)
+        got = [blk.get_tensor(pb.STUDENT_GRAD, l, k, shape) for l, shapes in enumerate(wl.param_shapes(s)) for k, shape in enumerate(shapes)]
+        blk.close()
+        return got
+
+    past, infinite = x.copy(), x.copy()
+    past[0, 1, -1, -1] = 3.4e38
+    infinite[n // 2, chans[0] - 1, 0, 0] = np.inf
+    cases = [(past, td), (infinite, td), (past, (td * np.float32(1e12)).astype(np.float32))]
+    for v in (np.nan, np.inf, -np.inf):
+        bad = td.copy()
+        bad[n // 2, -1, -1, -1] = v
+        cases.append((x, bad))
+    for i, (xv, tv) in enumerate(cases):
+        for a, b in zip(gradients("1", xv, tv), gradients("0", xv, tv)):
+            np.testing.assert_array_equal(value_classes(a), value_classes(b), err_msg=str(i))
+
+
 def test_teacher_weights_replaced_after_creation(gpu):
     """pbkd_block_set_tensor on a teacher's convolution weights re-packs them for whichever kernel the layer runs (the
     bf16-split kernel keeps three bf16 images of them): the forward pass then follows the new weights."""

@@ -121,6 +121,11 @@ def wgrad_takes_bn_backward(arch, shapes, l):
             and arch.layers[1].kind == wl.DWSEP3X3 and 4 * arch.n * co * ho * wo <= 2 ** 31)
 
 
+def first_layers_in_one(arch, shapes):
+    """The library's rule: that first layer and a depthwise convolution of stride 1 behind it have one backward kernel."""
+    return wgrad_takes_bn_backward(arch, shapes, 0) and arch.layers[1].stride == 1 and tuning("PBKD_FIRST_BWD") != 0
+
+
 def pw_bwd_layers(w):
     """Per student layer: None, or where the library forms the pointwise weight and data gradient in one kernel (split products for
     the weight gradient, 16 to 128 output channels) how many tensors of the layer's output its dz comes from: g and z inside a
@@ -198,6 +203,11 @@ def kernel_work(w):
             else:
                 add("pw_wgrad_mfma", z + u, 2 * ci * co * n * ho * wo)
                 add("pw_dgrad_mfma", z + u, 2 * ci * co * n * ho * wo)
+            if l == 1 and first_layers_in_one(arch, shapes):       # du, z of the first layer, its input; both products of its weight gradient
+                c0 = shapes[0][0]
+                add("first_bwd", u + a + n * c0 * hi * wi, (2 * 9 * 2 + 2 * 2 * 9 * c0) * ci * n * ho * wo)
+                params += 9 * ci + ci * co + 2 * co
+                continue
             add("dw3x3_bwd", u + a if l == 0 else u + 2 * a, 2 * 9 * ci * n * ho * wo * (1 if l == 0 else 2))
             if l > 0 and arch.layers[l - 1].trainable and not wgrad_takes_bn_backward(arch, shapes, l - 1) and in_one[l - 1] is None:
                 add("bn_bwd_apply", 3 * a)
@@ -206,14 +216,15 @@ def kernel_work(w):
             # behind a depthwise-separable layer the first layer's weight gradient reads g and z (BatchNorm backward
             # folded in) instead of a dz written by a kernel of its own
             fused = wgrad_takes_bn_backward(arch, shapes, l)
-            add("conv3x3_wgrad", (2 * z if fused else z) + a, 2 * 9 * ci * co * n * ho * wo * (2 if fused else 1))
+            if not first_layers_in_one(arch, shapes):
+                add("conv3x3_wgrad", (2 * z if fused else z) + a, 2 * 9 * ci * co * n * ho * wo * (2 if fused else 1))
             params += 9 * ci * co + 2 * co
     add("sgd_momentum", 5 * params)      # theta and momentum read and written, the gradient written
     return work
 
 
 HBM_KINDS = ["conv3x3_first", "dw3x3_fwd", "conv1x1_mfma", "head_out", "head_loss", "head_bwd", "pw_wgrad_mfma", "pw_dgrad_mfma", "pw_bwd",
-             "dw3x3_bwd", "bn_bwd_apply", "conv3x3_wgrad", "sgd_momentum"]
+             "dw3x3_bwd", "first_bwd", "bn_bwd_apply", "conv3x3_wgrad", "sgd_momentum"]
 
 
 # ---------------------------------------------------------------------------------------------- timing helpers

@@ -79,6 +79,9 @@
  *   PBKD_CF_OCC=1..8        same kernel: workgroups per compute unit its persistent grid is sized for (default 4)
  *   PBKD_DW_EDGE=0          depthwise register-window kernels on maps whose width is not 4, 8, 16, 32 or 64: a strip's
  *                           two edge columns by loads instead of from the neighbouring lanes of the wave
+ *   PBKD_FIRST_BWD=0        a full 3x3 first layer of at most three input channels and the depthwise convolution behind it keep a
+ *                           backward kernel each (default: one kernel, where the one below folds the BatchNorm backward in and
+ *                           the depthwise convolution has stride 1)
  *   PBKD_WGRAD_BN_FUSED=0   a full 3x3 first layer's weight gradient does not fold its BatchNorm backward in (an
  *                           elementwise kernel forms dz first, as for every other layer)
  *   PBKD_DWPW=0|1           1: depthwise + pointwise forward as one kernel wherever the layer's shape allows (stride 1,

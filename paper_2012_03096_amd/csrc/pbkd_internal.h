@@ -461,6 +461,27 @@ struct PwBwdArgs {
 hipError_t launch_pw_bwd(const PwBwdArgs &a, hipStream_t s);
 hipError_t init_pw_bwd_attributes();
 
+// ------------------------------------------------------------------ full 3x3 first layer and the depthwise convolution behind it (first_bwd.hip)
+// Stride 1, 9*Cin <= 32, W % 4 == 0, tensors up to 2 GiB: all gradients that come from du and z, and dW of the first layer.
+struct FirstBwdGeom {
+  int groups, splits, tiles_per_split;   // groups of 32 channels; tiles of eight patches of 4x4 pixels
+};
+FirstBwdGeom first_bwd_geom(int N, int C, int H, int W);
+struct FirstBwdArgs {
+  const float *du;         // [N,C,H,W] gradient of the depthwise output
+  const float *D;          // [C][9] depthwise weights
+  const float *z, *x;      // the first layer's output before BatchNorm [N,C,H,W], and its input [N,Cin,H,W]
+  const float *scale, *shift, *mean, *rstd;
+  float *dw_partial;       // [splits][C][11]: depthwise weight gradient, sum of g, sum of g * (z - mean)
+  float *partial;          // [splits][C][2][32]: sums of g and of z - mean with the tap columns
+  float *colsum;           // [splits][32]: sums of the tap columns
+  float *dW, *dgamma, *dbeta;   // [C][9*Cin], [C], [C]
+  int N, C, Cin, H, W;
+  FirstBwdGeom geo;
+};
+inline size_t first_bwd_partial_floats(const FirstBwdGeom &g, int C) { return (size_t)g.splits * 32 * (2 * (size_t)C + 1); }   // partial, then colsum
+hipError_t launch_first_bwd(const FirstBwdArgs &a, hipStream_t s);
+
 // ------------------------------------------------------------------ BatchNorm statistics
 // A convolution leaves the statistics of its output as per-tile partial sums.  Either launch_bn_finalize
 // turns them into (mean, rstd, scale = gamma*rstd, shift = beta - mean*scale), or the first kernel that

@@ -49,11 +49,11 @@ pbkd_status fail(pbkd_status st, const char *fmt, ...) {
 // Optional per-launch timing: a pool of event pairs recorded around the launches whose kind is in the mask.
 enum KernelKind {
   KK_CONV3X3 = 0, KK_CONV1X1, KK_PW_DGRAD, KK_PW_WGRAD, KK_DW_FWD, KK_DW_BWD, KK_CONV_WGRAD, KK_BN_FINALIZE,
-  KK_HEAD_OUT, KK_HEAD_LOSS, KK_HEAD_BWD, KK_BN_BWD, KK_SGD, KK_REDUCE, KK_CONV_FIRST, KK_DWPW_FWD, KK_PW_BWD, KK_COUNT
+  KK_HEAD_OUT, KK_HEAD_LOSS, KK_HEAD_BWD, KK_BN_BWD, KK_SGD, KK_REDUCE, KK_CONV_FIRST, KK_DWPW_FWD, KK_PW_BWD, KK_FIRST_BWD, KK_COUNT
 };
 const char *const kKindNames[KK_COUNT] = {
   "conv3x3_mfma", "conv1x1_mfma", "pw_dgrad_mfma", "pw_wgrad_mfma", "dw3x3_fwd", "dw3x3_bwd", "conv3x3_wgrad", "bn_finalize",
-  "head_out", "head_loss", "head_bwd", "bn_bwd_apply", "sgd_momentum", "reduce_partials", "conv3x3_first", "dwpw_fwd", "pw_bwd"};
+  "head_out", "head_loss", "head_bwd", "bn_bwd_apply", "sgd_momentum", "reduce_partials", "conv3x3_first", "dwpw_fwd", "pw_bwd", "first_bwd"};
 
 struct Prof {
   unsigned mask = 0;
@@ -102,6 +102,7 @@ struct LayerRT {
   float *conv_part = nullptr;       // partial outputs of a 3x3 convolution whose K is split over workgroups
   float *wg_part = nullptr;         // partial sums of the conv weight gradient (pointwise: [splits][cout][cin]; full: [tiles][cout][cin][9])
   float *dw_part = nullptr;         // depthwise backward partials [tiles][cin][11]
+  float *fb_part = nullptr;         // first_bwd: its partials
   int stat_parts() const { return first_conv ? cfg.n_wgs : (taps == 9 ? cg.stat_parts : pg.n_ptiles); }
   size_t n_w0 = 0, n_w1 = 0;
   int taps = 9;                     // of the MFMA conv producing z (9 full, 1 pointwise / shortcut)
@@ -123,6 +124,9 @@ struct LayerRT {
   bool pw_bwd = false;              // pointwise weight and data gradient in one kernel, which forms dz itself (pb_src: PwBwdArgs::src)
   int pb_src = 0;
   PwBwdGeom pb{};
+  bool first_bwd = false;           // full first layer whose gradients come from one kernel with those of the depthwise convolution behind it
+  FirstBwdGeom fb{};
+  int dw_parts = 0;                 // depthwise weight gradient: partials that the update kernel sums
 };
 
 // tuning aid: environment variable `name` set to the integer v
@@ -182,6 +186,17 @@ void choose_pw_bwd(Net &net, int l) {
   const bool pooled = last && net.pool == 2 && r.wout % 4 == 0 && r.hout % 2 == 0;
   r.pw_bwd = pw_bwd_geom(net.n, r.cout, r.cin, r.hout, r.wout, pooled, r.pdg, r.pb);
   r.pb_src = !last ? 1 : net.pool != 2 ? 2 : pooled ? 3 : 0;
+}
+
+// A trainable full first layer whose gradient kernel takes its BatchNorm's backward pass along, behind a depthwise convolution of stride 1:
+// one kernel for both.  PBKD_FIRST_BWD=0 keeps them apart.
+void choose_first_bwd(Net &net) {
+  for (LayerRT &r : net.L) r.dw_parts = r.dwb.n_tiles;
+  if (net.L.size() < 2 || !net.L[0].trainable || !net.L[0].wgrad_bn_fused || net.L[1].stride != 1 || env_is("PBKD_FIRST_BWD", 0)) return;
+  LayerRT &r = net.L[0];
+  r.first_bwd = true;
+  r.fb = first_bwd_geom(net.n, r.cout, r.hout, r.wout);
+  net.L[1].dw_parts = r.fb.splits;
 }
 
 pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
@@ -313,6 +328,7 @@ pbkd_status build_net(const pbkd_arch_desc *a, bool student, Net &net) {
       }
   }
   for (int l = 0; student && l < a->n_layers; ++l) choose_pw_bwd(net, l);
+  if (student) choose_first_bwd(net);
   net.out_h = a->pool == 2 ? h / 2 : h;
   net.out_w = a->pool == 2 ? w / 2 : w;
   if (net.out_h < 1 || net.out_w < 1) return fail(PBKD_ESHAPE, "max-pool leaves an empty output");
@@ -568,12 +584,13 @@ size_t layout(pbkd_block &b, char *base) {
     if (r.kind == PBKD_DWSEP3X3) {
       const int splits = r.pw_bwd ? r.pb.splits : r.wg.splits;
       r.wg_part = bump.take((size_t)splits * r.cout * r.cin);
-      r.dw_part = bump.take((size_t)r.dwb.n_tiles * r.cin * 11);
-      add_job(r.dw_part, r.w0, r.n_w0, r.dwb.n_tiles, 1, r.cin);
+      r.dw_part = bump.take((size_t)r.dw_parts * r.cin * 11);
+      add_job(r.dw_part, r.w0, r.n_w0, r.dw_parts, 1, r.cin);
       add_job(r.wg_part, r.w1, r.n_w1, splits, 0, 0);
     } else {
-      const int parts = r.taps_wgrad ? r.wg.slabs : r.cw.n_tiles;
+      const int parts = r.first_bwd ? 1 : r.taps_wgrad ? r.wg.slabs : r.cw.n_tiles;
       r.wg_part = bump.take((size_t)parts * r.cout * r.cin * 9);
+      if (r.first_bwd) r.fb_part = bump.take(first_bwd_partial_floats(r.fb, r.cout));
       add_job(r.wg_part, r.w0, r.n_w0, parts, 0, 0);
     }
     add_job(nullptr, r.gamma, 2 * (size_t)r.cout, 0, 2, 0);
@@ -866,6 +883,16 @@ pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head
       pa.stride = 1; pa.nchunks = r.pdg.nchunks; pa.g = r.pdg;
       LAUNCH(pf, KK_PW_DGRAD, st, launch_pw(pa, st));
       }
+      if (l == 1 && net.L[0].first_bwd) {
+        LayerRT &q = net.L[0];
+        FirstBwdArgs fa{};
+        fa.du = b.du; fa.D = r.w0; fa.z = q.z; fa.x = x; fa.scale = q.scale; fa.shift = q.shift; fa.mean = q.mean; fa.rstd = q.rstd;
+        fa.dw_partial = r.dw_part; fa.partial = q.fb_part; fa.colsum = q.fb_part + (size_t)q.fb.splits * q.cout * 64;
+        fa.dW = q.wg_part; fa.dgamma = q.g_gamma; fa.dbeta = q.g_beta;
+        fa.N = N; fa.C = q.cout; fa.Cin = q.cin; fa.H = q.hout; fa.W = q.wout; fa.geo = q.fb;
+        LAUNCH(pf, KK_FIRST_BWD, st, launch_first_bwd(fa, st));
+        continue;
+      }
       float *gprev = b.gbuf(l - 1);   // unused for l == 0
       DwBwdArgs da{};
       da.du = b.du; da.D = r.w0; da.gout = gprev; da.partial = r.dw_part;
@@ -890,7 +917,7 @@ pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head
           LAUNCH(pf, KK_BN_BWD, st, launch_bn_bwd_apply(gprev, q.z, q.scale, q.mean, q.rstd, q.g_gamma, q.g_beta,
                                                         fold ? r.dw_part : nullptr, r.dwb.n_tiles, N, q.cout, q.hout * q.wout, st));
       }
-    } else {
+    } else if (!r.first_bwd) {   // (else layer 1's kernel has formed it)
       if (r.taps_wgrad) {   // dW[o][c][tap] as a product over pixels with the shifted input channels as columns
         WgradArgs wa{};
         wa.dz = dz; wa.u = x; wa.partial = r.wg_part; wa.N = N; wa.Co = r.cout; wa.Ci = 9 * r.cin; wa.HW = r.hout * r.wout;
@@ -910,7 +937,8 @@ pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head
     }
   }
   if (b.aux)   // the update (and the next forward pass, which overwrites the stored activations) needs them all
-    for (int l = nl - 1; l >= lowest; --l) HIPCHK(hipStreamWaitEvent(st, b.ev_wg[l], 0));
+    for (int l = nl - 1; l >= lowest; --l)
+      if (!net.L[l].first_bwd) HIPCHK(hipStreamWaitEvent(st, b.ev_wg[l], 0));
   return PBKD_OK;
 }
 

@@ -465,7 +465,7 @@ def test_pointwise_split_infinities(gpu, monkeypatch, n, h, w_, chans, stride, v
 
 
 FIRST_LAYER_SWITCHES = [("PBKD_CF_TH", 4), ("PBKD_CF_TH", 8), ("PBKD_CF_OCC", 1), ("PBKD_CF_OCC", 6), ("PBKD_DW_EDGE", 0),
-                        ("PBKD_DW_EDGE", 2), ("PBKD_WGRAD_BN_FUSED", 0)]
+                        ("PBKD_DW_EDGE", 2), ("PBKD_WGRAD_BN_FUSED", 0), ("PBKD_FIRST_BWD", 0)]
 
 
 @pytest.mark.parametrize("var,value", FIRST_LAYER_SWITCHES, ids=[f"{k[5:].lower()}{v}" for k, v in FIRST_LAYER_SWITCHES])
@@ -770,6 +770,47 @@ def test_pointwise_gradients_in_one_kernel_infinities(gpu, monkeypatch, n, h, w_
     for i, (xv, tv) in enumerate(cases):
         for a, b in zip(gradients("1", xv, tv), gradients("0", xv, tv)):
             np.testing.assert_array_equal(value_classes(a), value_classes(b), err_msg=str(i))
+
+
+@pytest.mark.parametrize("n,h,w_,chans,pool", [
+    (1, 1, 4, (3, 5, 16), 0), (2, 3, 4, (1, 33, 20), 0), (3, 2, 8, (2, 16, 16, 16), 2), (5, 7, 12, (3, 31, 17), 0), (1, 4, 32, (3, 32, 32), 2),
+    (7, 6, 36, (1, 65, 16), 2), (9, 13, 20, (3, 100, 24), 0), (4, 33, 64, (3, 64, 64), 0), (37, 10, 28, (2, 40, 16), 2)])
+def test_first_layers_gradients_in_one_kernel(gpu, n, h, w_, chans, pool):
+    """A full first layer and the depthwise convolution behind it: one to four groups of channels, ragged ones; one, two and three input
+    channels; rows past the map in the last patch; patches that wrap from row to row and from image to image within a tile of eight; one
+    tile of which most is past the end, and several tiles a workgroup."""
+    t = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans)), pool=pool)
+    s = wl.Arch(n, chans[0], h, w_, [wl.Layer(wl.CONV3X3, chans[0], chans[1], 1, 1)] + wl._dws(list(chans[1:])), pool=pool)
+    fails = run_parity(gpu, wl.Workload("first_bwd", t, s, seed=43), steps=2)
+    assert not fails, fails
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_first_layers_gradients_not_numbers(gpu, monkeypatch, bad):
+    """An input or a target that holds a NaN or an infinity: numbers where the kernels apart have numbers, in every gradient of the
+    block.  (Not so for a number near the largest: whether fp32 sums that hold it pass the largest on the way depends on their
+    order, and here the parts are put together in 64 bits.)"""
+    torch, pb = gpu
+    chans, n, h, w_ = (3, 40, 33), 3, 9, 12
+    t = wl.Arch(n, 3, h, w_, wl._convs(list(chans)))
+    s = wl.Arch(n, 3, h, w_, [wl.Layer(wl.CONV3X3, 3, 40, 1, 1)] + wl._dws(list(chans[1:])))
+    x, tp, sp = wl.Workload("first_bwd_not_numbers", t, s, seed=47).tensors(random_affine=True)
+    td = np.random.default_rng(5).standard_normal(wl.output_shape(t)).astype(np.float32)
+
+    def gradients(mode, xv, tv):
+        monkeypatch.setenv("PBKD_FIRST_BWD", mode)
+        blk, xd, tgt = pb.Block(t, tp, s, sp), torch.from_numpy(xv).cuda(), torch.from_numpy(tv).cuda()
+        blk.student_step(xd, tgt, 0.0, want_loss=False)
+        got = [blk.get_tensor(pb.STUDENT_GRAD, l, k, shape) for l, shapes in enumerate(wl.param_shapes(s)) for k, shape in enumerate(shapes)]
+        blk.close()
+        return got
+
+    xb, tb = x.copy(), td.copy()
+    xb[1, 2, 4, 11] = bad
+    tb[2, 32, -1, -1] = bad
+    for xv, tv in ((xb, td), (x, tb)):
+        for a, b in zip(gradients("1", xv, tv), gradients("0", xv, tv)):
+            np.testing.assert_array_equal(np.isfinite(a), np.isfinite(b))
 
 
 def test_teacher_weights_replaced_after_creation(gpu):

@@ -404,8 +404,14 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
         const float *q = p.sum_partial + (size_t)o * p.sum_row + p.sum_at + which;
         const size_t step = (size_t)p.Co * p.sum_row;
         double t = 0.0;
-#pragma unroll 16
-        for (int i = 0; i < p.sum_parts; ++i) t += (double)q[(size_t)i * step];
+#pragma unroll 1
+        for (int i = 0; i < p.sum_parts; i += 16) {        // sixteen loads in flight whatever their number: a remainder loads one
+          float x[16];                                     // after the other (33.5 -> 30.3 us at 100 -> 67, 27x23, batch 77: 47 parts)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) x[j] = q[(size_t)(i + j < p.sum_parts ? i + j : p.sum_parts - 1) * step];
+#pragma unroll
+          for (int j = 0; j < 16; ++j) t += i + j < p.sum_parts ? (double)x[j] : 0.0;
+        }
         v = (float)t;
         if (lin == 0) (which ? p.dgamma : p.dbeta)[o] = v;
       } else {
@@ -415,7 +421,15 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
     }
     if (SRC > 1 && p.loss_out && lin == 0) {
       double l = 0.0;
-      for (int e = tid; e < p.sum_parts * p.Co; e += 256) l += (double)p.sum_partial[(size_t)e * 3];
+      const int all = p.sum_parts * p.Co;
+#pragma unroll 1
+      for (int e = tid; e < all; e += 16 * 256) {
+        float x[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = p.sum_partial[(size_t)(e + 256 * j < all ? e + 256 * j : all - 1) * 3];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) l += e + 256 * j < all ? (double)x[j] : 0.0;
+      }
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) l += __shfl_xor(l, d, 64);
       if (lane == 0) loss[wave] = l;

@@ -12,6 +12,7 @@
 // that one workgroup's partial sums all belong to one channel; partials go to the workspace and are
 // summed in a fixed order in fp64 -- results do not depend on scheduling.
 #include <mutex>
+#include <type_traits>
 
 #include "pbkd_internal.h"
 #include "split_bf16.h"
@@ -19,10 +20,24 @@
 namespace pbkd {
 
 __device__ __forceinline__ float wave_sum(float v) { return wave64_sum(v); }
+// in lane order within rows of 16 (the other operand comes through data-parallel moves, two a step, not through LDS), then the four rows
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
+  auto other = [](double x, auto ctrl) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, decltype(ctrl)::value, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+  };
+  v += other(v, std::integral_constant<int, 0xB1>{});     // quad_perm [1,0,3,2]
+  v += other(v, std::integral_constant<int, 0x4E>{});     // quad_perm [2,3,0,1]
+  v += other(v, std::integral_constant<int, 0x141>{});    // row_half_mirror
+  v += other(v, std::integral_constant<int, 0x140>{});    // row_mirror
+  auto row = [&](int lane) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+  };
+  return (row(0) + row(16)) + (row(32) + row(48));
 }
 
 // sum_{t < n} a[t * stride] and the same for b, in fp64: lanes take t = lane, lane + 64, ..., then a fixed
@@ -53,6 +68,8 @@ __device__ __forceinline__ BnStat bn_finalize_block(const BnPending &b, int C, i
   double s1 = 0.0, s2 = 0.0;
   const f4 *pc = reinterpret_cast<const f4 *>(b.partial) + (size_t)c * b.n_parts;   // contiguous per channel
   const double P = (double)pc[0][0];
+  const float gamma = b.gamma[c], beta = b.beta[c];    // (on their way with the partials)
+  const double inv = 1.0 / b.count;                    // (done before they arrive)
   auto add = [&](const f4 &v) {
     const double d = (double)v[0] - P, n = (double)v[3], a = (double)v[1];
     s1 += a + n * d;
@@ -77,17 +94,17 @@ __device__ __forceinline__ BnStat bn_finalize_block(const BnPending &b, int C, i
   __syncthreads();
   s1 = (sred[0] + sred[2]) + (sred[4] + sred[6]);
   s2 = (sred[1] + sred[3]) + (sred[5] + sred[7]);
-  const double dm = s1 / b.count;                      // mean - P
+  const double dm = s1 * inv;                          // mean - P
   const double mu = P + dm;
-  double var = s2 / b.count - dm * dm;
+  double var = s2 * inv - dm * dm;
   if (var < 0.0) var = 0.0;
   const double r = 1.0 / sqrt(var + (double)b.eps);
-  const double sc = (double)b.gamma[c] * r;
+  const double sc = (double)gamma * r;
   BnStat o;
   o.mean = (float)mu;
   o.rstd = (float)r;
   o.scale = (float)sc;
-  o.shift = (float)((double)b.beta[c] - mu * sc);
+  o.shift = (float)((double)beta - mu * sc);
   o.var = (float)var;
   return o;
 }

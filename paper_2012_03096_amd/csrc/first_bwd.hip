@@ -16,7 +16,8 @@
 // one, which is fetched a tile ahead: a tile is one cache line wide, and two more lines a row for its edges cost 40 us of 307.
 //
 // What bounds it: memory, which two workgroups a compute unit (their registers) do not keep busy while they multiply.  64 channels at
-// 224x224, batch 32, 3 input channels: 265 us and 8 for the finish, 0.84 GB, for 234 + 6 + 189 us apart; without the products 205 us,
+// 224x224, batch 32, 3 input channels: 265 us and 8 for the finish, 0.84 GB (1.1 with the halo rows that
+// leave L2 between two rows of tiles), for 234 + 6 + 189 us apart; without the products 205 us,
 // without most of the arithmetic 255.  Slower: three workgroups a compute unit and nothing ahead 307, multiplying waves of their own
 // beside four loading ones 310; no faster: the next window's loads ahead of the arithmetic 267, two accumulators 268.  On 36 drawn shapes,
 // 1 to 124 images, 4x4 to 214x260, 32 to 64 channels, a step is 1.02 to 1.16 times as fast, 1.046 in the mean.

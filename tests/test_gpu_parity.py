@@ -774,11 +774,12 @@ def test_pointwise_gradients_in_one_kernel_infinities(gpu, monkeypatch, n, h, w_
 
 @pytest.mark.parametrize("n,h,w_,chans,pool", [
     (1, 1, 4, (3, 5, 16), 0), (2, 3, 4, (1, 33, 20), 0), (3, 2, 8, (2, 16, 16, 16), 2), (5, 7, 12, (3, 31, 17), 0), (1, 4, 32, (3, 32, 32), 2),
-    (7, 6, 36, (1, 65, 16), 2), (9, 13, 20, (3, 100, 24), 0), (4, 33, 64, (3, 64, 64), 0), (37, 10, 28, (2, 40, 16), 2)])
+    (7, 6, 36, (1, 65, 16), 2), (9, 13, 20, (3, 100, 24), 0), (4, 33, 64, (3, 64, 64), 0), (37, 10, 28, (2, 40, 16), 2),
+    (6, 30, 44, (3, 520, 20), 0), (40, 10, 28, (2, 1000, 16), 2)])
 def test_first_layers_gradients_in_one_kernel(gpu, n, h, w_, chans, pool):
-    """A full first layer and the depthwise convolution behind it: one to four groups of channels, ragged ones; one, two and three input
+    """A full first layer and the depthwise convolution behind it: one to 32 groups of channels, ragged ones; one, two and three input
     channels; rows past the map in the last patch; patches that wrap from row to row and from image to image within a tile of eight; one
-    tile of which most is past the end, and several tiles a workgroup."""
+    tile of which most is past the end, and (520 and 1000 channels) two and four tiles a workgroup."""
     t = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans)), pool=pool)
     s = wl.Arch(n, chans[0], h, w_, [wl.Layer(wl.CONV3X3, chans[0], chans[1], 1, 1)] + wl._dws(list(chans[1:])), pool=pool)
     fails = run_parity(gpu, wl.Workload("first_bwd", t, s, seed=43), steps=2)

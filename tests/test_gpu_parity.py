@@ -300,6 +300,51 @@ def test_large_mean_channels(gpu, name):
     assert not fails, fails
 
 
+@pytest.mark.parametrize("n,h,w_,value", [(16, 14, 14, 3.5), (32, 7, 7, 3.75), (10, 14, 21, 3.5), (4, 49, 8, 3.25)])
+def test_statistics_are_sums_divided_by_the_count(gpu, n, h, w_, value):
+    """A channel's mean is the rounded quotient of its sum and its count, not a product with the count's rounded reciprocal.  Half of
+    the images are zero, half `value`, and one pixel of the first puts the mean halfway between two fp32 numbers: every sum is exact,
+    so the quotient is, and goes to the even number; for half of the channels the product falls below it (counts 49 * 2^k and 2940)."""
+    torch, pb = gpu
+    c, count = 64, n * h * w_
+    t, s = wl.Arch(n, c, h, w_, wl._convs([c, c])), wl.Arch(n, c, h, w_, wl._dws([c, c]))
+    x, tp, sp = wl.Workload("means", t, s, seed=3).tensors(random_affine=True)
+    sp = [[a.copy() for a in lp] for lp in sp]
+    sp[0][0].reshape(c, 9)[:] = np.eye(9)[4]                # z = x
+    sp[0][1].reshape(c, c)[:] = np.eye(c)
+    odd = 2.0 * np.arange(c) + 1
+    x = np.zeros_like(x)
+    x[n // 2:] = value
+    x[0, :, h // 2, w_ // 2] = count * odd * 2.0 ** -24
+    blk = pb.Block(t, tp, s, sp)
+    blk.student_forward(torch.from_numpy(x).cuda(), torch.empty((n, c, h, w_), device="cuda"))
+    got = blk.get_tensor(pb.STUDENT_ACT, 0, 2, (c,))
+    blk.close()
+    want = value / 2 + odd * 2.0 ** -24
+    assert (want.astype(np.float32) != ((count * want) * (1.0 / count)).astype(np.float32)).sum() == c // 2
+    np.testing.assert_array_equal(got, want.astype(np.float32))
+
+
+def test_sums_over_a_wave_have_one_order(gpu):
+    """The fp64 sum over a wave adds lanes 32, 16, 8, 4, 2 and 1 apart, in that order: the feature error of 65536 numbers (256
+    workgroups of 256 threads, one number a thread, then one workgroup over their sums) to the last bit."""
+    torch, pb = gpu
+
+    def group(v):                                           # [..., 256] -> [...]
+        v = v.reshape(*v.shape[:-1], 4, 64)
+        while v.shape[-1] > 1:
+            v = v[..., :v.shape[-1] // 2] + v[..., v.shape[-1] // 2:]
+        v = v[..., 0]
+        return (v[..., 0] + v[..., 1]) + (v[..., 2] + v[..., 3])
+
+    rng = np.random.default_rng(8)
+    for _ in range(8):
+        a, b = rng.standard_normal((2, 65536)).astype(np.float32)
+        d = a.astype(np.float64) - b.astype(np.float64)
+        want = group(group((d * d).reshape(256, 256))) * (1.0 / 65536)
+        assert pb.feature_mse_noalloc(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()) == want
+
+
 FORCED = ([("PBKD_PW_VARIANT", v) for v in range(10)] + [("PBKD_CONV_TILE", v) for v in range(4)] +
           [("PBKD_WGRAD_VARIANT", v) for v in range(4)] + [("PBKD_CONV_KSPLIT", v) for v in (2, 3)])
 

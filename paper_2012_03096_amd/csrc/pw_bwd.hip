@@ -8,12 +8,17 @@
 //
 // A workgroup owns 64 columns of dP (input channels), all of its rows, and a contiguous range of pixels, taken in chunks of 64 (32
 // with more than 64 output channels).  Eight loader waves fetch two chunks ahead into registers, form dz, split dz and u into three
-// bf16 pieces (split_bf16.h; dz by cutting, u by rounding) and write them to LDS, pixels along a row.  Four MFMA waves multiply: for
+// bf16 pieces (split_bf16.h, by rounding) and write them to LDS, pixels along a row.  Four MFMA waves multiply: for
 // dP both operands are rows of pixels, sixteen bytes a lane; for du the operand's k runs along the channels, across the rows, which
 // is what the transposing LDS read (ds_read_b64_tr_b16: four rows of sixteen 2-byte values, a lane receives a column) is for.  P's
 // pieces, packed for the data gradient (pw_split_pack_index), stay in registers.  Each MFMA wave has a quarter of dP and one 32 x 32
 // tile of du: (channel block, pixel block), or, with more than 64 output channels, (channel block, half of the channels summed).  The
 // tiles go to LDS, and the loader waves, which have the time, add the halves and store them a chunk later, where they read u.
+//
+// du is summed over 16 channels (32 with more than 64 output channels) from zero and these sums are added, as few pixels' are in
+// pw_split.hip: with one running sum over all channels and dz's pieces cut off du's rms error is 1.92e-7 of the root of its terms' squares
+// at 64 channels, 9x7 maps, batch 3, so it is 1.67e-7, and apart 1.67e-7 (128 channels, 16x16, batch 8: 1.92, 1.71 and 1.72e-7).  The
+// additions cost 0.3 of 21 us at 128 channels, 16x16, batch 128, nothing at 64.
 //
 // What bounds it: memory where the map is large (64 -> 64 at 224x224, batch 32, pooled head, 1.34 GB: 264 us, 5.1 TB/s, for
 // 169 + 187 + 149 us apart; 64 -> 128 at 16x16, batch 1024: 5.3 TB/s), else the first loads and the channel sums before any product
@@ -247,13 +252,10 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
         k[j].db = sums[2 * o], k[j].dg = sums[2 * o + 1];
       }
     }
-    auto put = [&](char *row, const f4 &w, bool cut) {
+    auto put = [&](char *row, const f4 &w) {
       unsigned q[2][3];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (cut) split3_bf16_cut(w[2 * h], w[2 * h + 1], q[h]);
-        else split3_bf16(w[2 * h], w[2 * h + 1], q[h]);
-      }
+      for (int h = 0; h < 2; ++h) split3_bf16(w[2 * h], w[2 * h + 1], q[h]);
 #pragma unroll
       for (int pc = 0; pc < 3; ++pc) *reinterpret_cast<uintx2 *>(row + pc * PLANE) = uintx2{q[0][pc], q[1][pc]};
     };
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
         }
 #pragma unroll
         for (int v = 0; v < VA; ++v) {
-          put(copy + (r0 + RS * j) * PITCH + 8 * (v * PER + kq), w[v], true);
+          put(copy + (r0 + RS * j) * PITCH + 8 * (v * PER + kq), w[v]);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -316,7 +318,7 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
       for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int v = 0; v < VB; ++v)
-          put(copy + (BM + rb0 + RS * j) * PITCH + 8 * ((v + half) * PER + kq), vu[s][j][v], false);
+          put(copy + (BM + rb0 + RS * j) * PITCH + 8 * ((v + half) * PER + kq), vu[s][j][v]);
     };
     // du of the next chunk to store, from LDS to where this thread's part of u was
     Cursor<POOL> done(p, first + kq, PER);
@@ -391,6 +393,7 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l31 = lane & 31, lh = lane >> 5;
   constexpr int MBW = BM / 64;                             // blocks of 32 rows of dP a wave has, 32 columns wide
+  constexpr int DU_SUM = BM == 128 ? 2 : 1;                // chunks of channels whose sum is formed from zero
   constexpr bool KH = BM == 128;                           // du: waves 2 and 3 sum the upper half of the channels
   const int wm = wave & 1, wn = wave >> 1;
   const int cb = wave & 1, hi = wave >> 1;                 // du: block of 32 input channels; upper half of the channels, or of the pixels
@@ -492,17 +495,20 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
       }
     };
     read_x(0);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) t[r] = 0.f;
+    floatx16 part;                                         // du over DU_SUM chunks of channels
     static_assert(PX / 16 * MBW == 4, "four steps each");
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       read_ab(i);
+      if (i % DU_SUM == 0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[r] = 0.f;
+      }
       __builtin_amdgcn_sched_barrier(0);
       constexpr int PW[6] = {0, 0, 1, 2, 1, 0}, PXC[6] = {2, 1, 1, 0, 0, 0};       // weights by dz, small products first
 #pragma unroll
       for (int q = 0; q < 6; ++q)
-        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x[PXC[q]]), __builtin_bit_cast(bf16x8, w[i][PW[q]]), t, 0, 0, 0);
+        part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x[PXC[q]]), __builtin_bit_cast(bf16x8, w[i][PW[q]]), part, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
       if (i < 3) read_x(i + 1);
       __builtin_amdgcn_sched_barrier(0);
@@ -511,6 +517,7 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
       for (int q = 0; q < 6; ++q)
         acc[i % MBW] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[PA[q]]), __builtin_bit_cast(bf16x8, b[PB[q]]),
                                                                acc[i % MBW], 0, 0, 0);
+      if (i % DU_SUM == DU_SUM - 1) t = i < DU_SUM ? part : t + part;
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll

@@ -782,6 +782,60 @@ def test_pointwise_gradients_in_one_kernel(gpu, monkeypatch, n, h, w_, chans, po
     assert not fails, fails
 
 
+@pytest.mark.parametrize("n,h,w_,ci,co,pool", [(8, 16, 16, 512, 16, 0), (8, 16, 16, 300, 33, 0), (3, 9, 7, 300, 64, 0), (8, 16, 16, 300, 64, 2),
+                                               (3, 9, 7, 512, 100, 0), (8, 16, 16, 512, 128, 0), (8, 16, 16, 512, 128, 2), (64, 16, 16, 300, 64, 0)])
+def test_pointwise_data_gradient_leaves_no_larger_error_than_the_kernel_apart(gpu, monkeypatch, n, h, w_, ci, co, pool):
+    """rms error of du against fp64 (dz formed in fp64 from the kernel's own z) with the gradients in one kernel, not above what the
+    pointwise kernel leaves.  A block's input that is one at a single pixel of each channel makes the depthwise weight gradient's
+    nine sums single values of du.  Where both sum in the same order they are equal, else 1 % for the drawing of the 10 to 18
+    thousand values.  No output reaches ReLU's corner: beta = 5, and gamma = 0.03 (xhat is at most the root of the 16384 pixels)."""
+    torch, pb = gpu
+    gamma = float(np.float32(0.03))
+    t, s = wl.Arch(n, ci, h, w_, wl._convs([ci, co]), pool=pool), wl.Arch(n, ci, h, w_, wl._dws([ci, co]), pool=pool)
+    err = {"0": [], "1": []}
+    for seed in range(4):
+        x, tp, sp = wl.Workload("du_error", t, s, seed=37 + seed).tensors(random_affine=True)
+        sp = [[a.copy() for a in lp] for lp in sp]
+        sp[0][2][:], sp[0][3][:] = gamma, 5.0
+        rng, ch = np.random.default_rng(seed), np.arange(ci)
+        py, px = rng.integers(1, h - 1, ci), rng.integers(1, w_ - 1, ci)
+        x = np.zeros_like(x)
+        x[n // 2, ch, py, px] = 1.0
+        td = (5 + rng.standard_normal(wl.output_shape(t))).astype(np.float32)
+        t64, P = td.astype(np.float64).transpose(1, 0, 2, 3), sp[0][1].reshape(co, ci).astype(np.float64)
+        for mode in err:
+            monkeypatch.setenv("PBKD_PW_BWD", mode)
+            blk = pb.Block(t, tp, s, sp)
+            blk.profile_enable(["pw_bwd"], 4)
+            blk.student_step(torch.from_numpy(x).cuda(), torch.from_numpy(td).cuda(), 0.0, want_loss=False)
+            assert ("pw_bwd" in blk.profile_read()) == (mode == "1")
+            z = blk.get_tensor(pb.STUDENT_ACT, 0, 1, (n, co, h, w_)).astype(np.float64).transpose(1, 0, 2, 3)
+            mean, rstd = (blk.get_tensor(pb.STUDENT_ACT, 0, k, (co, 1)).astype(np.float64) for k in (2, 3))
+            dec = gpu_decisions(pb, blk, s)
+            dD = blk.get_tensor(pb.STUDENT_GRAD, 0, 0, (ci, 9)).astype(np.float64)
+            blk.close()
+            assert dec["relu"][0].all()
+            xhat = (z.reshape(co, -1) - mean) * rstd
+            b = (gamma * xhat + 5).reshape(co, n, h, w_)
+            if pool:
+                win = lambda v: v.reshape(co, n, h // 2, 2, w_ // 2, 2).transpose(0, 1, 2, 4, 3, 5).reshape(co, n, h // 2, w_ // 2, 4)
+                arg = dec["pool_arg"].transpose(1, 0, 2, 3)[..., None]
+                g = np.zeros((co, n, h // 2, w_ // 2, 4))
+                np.put_along_axis(g, arg, 2 * (np.take_along_axis(win(b), arg, -1) - t64[..., None]) / td.size, -1)
+                g = g.reshape(co, n, h // 2, w_ // 2, 2, 2).transpose(0, 1, 2, 4, 3, 5)
+            else:
+                g = 2 * (b - t64) / td.size
+            g = g.reshape(co, -1)
+            dz = gamma * rstd * (g - g.mean(1, keepdims=True) - xhat * (g * xhat).mean(1, keepdims=True))
+            at = np.stack([(n // 2 * h + py - (k // 3 - 1)) * w_ + px - (k % 3 - 1) for k in range(9)], 1)       # [ci, 9]
+            dzs = dz[:, at]                                                                                # [co, ci, 9]
+            ref = np.einsum("oc,ock->ck", P, dzs)
+            err[mode].append((dD - ref) / np.sqrt(np.einsum("oc,ock->ck", P ** 2, dzs ** 2)))
+    rms = {k: float(np.sqrt(np.mean(np.square(v)))) for k, v in err.items()}
+    print(f"[pointwise data gradient error] {ci}->{co} {h}x{w_}x{n} pool={pool}: apart {rms['0']:.3e}, in one {rms['1']:.3e}")
+    assert rms["1"] <= 1.01 * rms["0"], rms
+
+
 @pytest.mark.parametrize("n,h,w_,chans,pool", [(6, 27, 23, (40, 100, 67), 0), (40, 8, 8, (20, 33, 64), 2), (3, 5, 3, (17, 70, 70), 0)])
 def test_pointwise_gradients_in_one_kernel_infinities(gpu, monkeypatch, n, h, w_, chans, pool):
     """A target that holds a NaN or an infinity in its last channel's last pixel, an infinite input, and a depthwise output past

@@ -216,9 +216,10 @@ pbkd_status pbkd_distill_step(pbkd_block_t *blk, const float *x_dev, float *targ
                               void *student_stream, void *teacher_stream);
 
 /* Gives the block a second stream for its backward pass (NULL: none, the default).  With one, the weight
- * gradients of every layer (which nothing but the final update consumes) run on aux_stream beside the
- * data-gradient chain on the step's own stream; events order the two, the update waits for both, and the
- * results stay bit-identical.  aux_stream must differ from the streams passed to the step calls and stay
+ * gradients (which nothing but the final update consumes) run on aux_stream beside the data-gradient chain
+ * on the step's own stream, of every layer whose two gradients are kernels of their own: layers that take
+ * one kernel for both (see PBKD_PW_BWD and PBKD_FIRST_BWD) put nothing on aux_stream.  Events order the two
+ * streams, the update waits for both, and the results stay bit-identical.  aux_stream must differ from the streams passed to the step calls and stay
  * valid while the block uses it; it costs no device memory. */
 pbkd_status pbkd_block_set_aux_stream(pbkd_block_t *blk, void *aux_stream);
 

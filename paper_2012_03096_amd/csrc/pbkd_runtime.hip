@@ -832,8 +832,9 @@ HeadArgs head_args(pbkd_block &b, Net &net, bool first, const float *x) {
 // Backward through the student block.  Layer l's dz lives in gbuf(l) (the two buffers alternate).  The
 // weight gradients (and their partial-sum reductions) depend only on dz and stored activations, nothing
 // downstream depends on them before the update: with an auxiliary stream they run beside the data-gradient
-// chain.  The data gradient of layer l is written into gbuf(l-1) = gbuf(l+1), so it first waits for the
-// weight gradient of layer l+1, which reads that buffer.
+// chain, where they are a kernel of their own.  The data gradient of layer l is written into gbuf(l-1) = gbuf(l+1), so it first waits for the
+// weight gradient of layer l+1, which reads that buffer.  (Apart and beside each other the two gradients are no faster than in one kernel: a
+// student's step at 64 -> 128 -> 128, 16x16, batch 128 132 us for 102, at 3 -> 64 -> 64, 224x224, batch 32 1531 for 1098.)
 // head: the last layer's, with the loss kernel's partials; where the layer's pointwise kernel forms dz itself (pw_bwd) it reads the
 // target, and target_free (if given) is recorded behind it.
 pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head, hipStream_t st, hipEvent_t target_free) {
@@ -842,13 +843,14 @@ pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head
   const int N = net.n;
   const int nl = (int)net.L.size();
   hipStream_t ws = b.aux ? b.aux : st;
+  auto beside = [&](const LayerRT &r) { return b.aux && !r.pw_bwd && !r.first_bwd; };   // it has a kernel on the auxiliary stream
   int lowest = nl;
   for (int l = nl - 1; l >= 0; --l) {
     LayerRT &r = net.L[l];
     if (!r.trainable) break;   // only layer 0 can be frozen; nothing below it needs a gradient
     lowest = l;
     float *dz = b.gbuf(l);
-    if (b.aux) {
+    if (beside(r)) {
       HIPCHK(hipEventRecord(b.ev_dz[l], st));
       HIPCHK(hipStreamWaitEvent(ws, b.ev_dz[l], 0));
     }
@@ -869,13 +871,12 @@ pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head
         }
         ba.du = b.du; ba.partial = r.wg_part; ba.N = N; ba.Co = r.cout; ba.Ci = r.cin; ba.H = r.hout; ba.W = r.wout; ba.geo = r.pb;
         LAUNCH(pf, KK_PW_BWD, st, launch_pw_bwd(ba, st));
-        if (b.aux) HIPCHK(hipEventRecord(b.ev_wg[l], st));
         if (r.pb_src >= 2 && target_free) HIPCHK(hipEventRecord(target_free, st));
       } else {
       WgradArgs wa{};
       wa.dz = dz; wa.u = r.u; wa.partial = r.wg_part; wa.N = N; wa.Co = r.cout; wa.Ci = r.cin; wa.HW = r.hout * r.wout; wa.g = r.wg;
       LAUNCH(pf, KK_PW_WGRAD, ws, launch_pw_wgrad(wa, ws));   // its partials are summed by the update kernel
-      if (b.aux) HIPCHK(hipEventRecord(b.ev_wg[l], ws));
+      if (beside(r)) HIPCHK(hipEventRecord(b.ev_wg[l], ws));
       PwArgs pa{};   // du[n,c,p] = sum_o P[o,c] dz[n,o,p]: a 1x1 conv with P read as [K=cout][M=cin]
       pa.in = dz; pa.wpk = r.wpk_b; pa.out = b.du; pa.stat_partial = nullptr;
       pa.w = r.w1; pa.w_row = 1; pa.w_col = r.cin;
@@ -904,7 +905,7 @@ pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head
         LayerRT &q = net.L[l - 1];
         da.first_layer = 0; da.in = q.z; da.in_scale = q.scale; da.in_shift = q.shift; da.in_mean = q.mean; da.in_rstd = q.rstd;
         dg_prev = q.g_gamma; db_prev = q.g_beta;
-        if (b.aux && l + 1 < nl) HIPCHK(hipStreamWaitEvent(st, b.ev_wg[l + 1], 0));
+        if (l + 1 < nl && beside(net.L[l + 1])) HIPCHK(hipStreamWaitEvent(st, b.ev_wg[l + 1], 0));
       }
       LAUNCH(pf, KK_DW_BWD, st, launch_dw_bwd(da, st));
       // of its partials, the depthwise weight gradient waits for the update kernel; the previous layer's dgamma and
@@ -933,12 +934,12 @@ pbkd_status student_backward(pbkd_block &b, const float *x, const HeadArgs &head
         ca.g = r.cw;
         LAUNCH(pf, KK_CONV_WGRAD, ws, launch_conv_wgrad(ca, ws));
       }
-      if (b.aux) HIPCHK(hipEventRecord(b.ev_wg[l], ws));
+      if (beside(r)) HIPCHK(hipEventRecord(b.ev_wg[l], ws));
     }
   }
   if (b.aux)   // the update (and the next forward pass, which overwrites the stored activations) needs them all
     for (int l = nl - 1; l >= lowest; --l)
-      if (!net.L[l].first_bwd) HIPCHK(hipStreamWaitEvent(st, b.ev_wg[l], 0));
+      if (beside(net.L[l])) HIPCHK(hipStreamWaitEvent(st, b.ev_wg[l], 0));
   return PBKD_OK;
 }
 

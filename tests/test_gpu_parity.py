@@ -1606,6 +1606,61 @@ def test_distill_step_on_two_streams_is_bit_identical(gpu, monkeypatch):
             assert np.array_equal(a, b)
 
 
+AUX_BLOCKS = {  # channels, first layer a full convolution, variables, launches a step of weight gradients of their own and with another one
+    "one_kernel": ((64, 128, 128), False, {}, {"pw_bwd": 2}),
+    "first_in_one_kernel": ((3, 32, 64), True, {}, {"pw_bwd": 1, "first_bwd": 1}),
+    "apart": ((64, 160, 192, 144), False, {}, {"pw_wgrad_mfma": 3}),
+    "made_apart": ((3, 64, 128, 64), True, {"PBKD_PW_BWD": "0", "PBKD_FIRST_BWD": "0"}, {"pw_wgrad_mfma": 2, "conv3x3_wgrad": 1}),
+    "mixed": ((64, 128, 160, 128), False, {}, {"pw_bwd": 2, "pw_wgrad_mfma": 1}),
+    "mixed_first": ((3, 32, 160, 64), True, {}, {"pw_bwd": 1, "pw_wgrad_mfma": 1, "first_bwd": 1})}
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("name", AUX_BLOCKS)
+def test_auxiliary_stream_is_bit_identical(gpu, monkeypatch, name, graph):
+    """Six steps with an auxiliary stream, alone and beside the teacher, eager and captured: bit for bit those on one stream, where both
+    gradients of every layer come from one kernel, from two, and in turn.  The stream gets work exactly where there is a weight
+    gradient of its own: while the step's stream is kept busy it is idle otherwise (a captured step puts none on it)."""
+    torch, pb = gpu
+    chans, full, env, launches = AUX_BLOCKS[name]
+    used = any(k.endswith(("wgrad", "wgrad_mfma")) for k in launches)
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    layers = wl._dws(list(chans))
+    if full:
+        layers[0] = wl.Layer(wl.CONV3X3, chans[0], chans[1], 1, 1)
+    t, s = wl.Arch(160, chans[0], 16, 16, wl._convs(list(chans))), wl.Arch(160, chans[0], 16, 16, layers)
+    w = wl.Workload("aux", t, s, seed=19)
+    x, tp, sp = w.tensors()
+    xd = torch.from_numpy(x).cuda()
+    results = []
+    for mode in ("plain", "aux", "aux_two_streams"):
+        s1, s2, s3 = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
+        td = torch.zeros(wl.output_shape(t), device="cuda")
+        blk = pb.Block(t, tp, s, sp, momentum=w.momentum)
+        blk.set_graph_mode(graph)
+        if mode != "plain":
+            blk.set_aux_stream(s3)
+        torch.cuda.synchronize()
+        for step in range(6):
+            blk.distill_step(xd, td, w.lr, want_loss=False, student_stream=s1, teacher_stream=s2 if mode == "aux_two_streams" else s1)
+        torch.cuda.synchronize()
+        results.append([blk.last_loss()] + [a for lp in blk.student_params() for a in lp])
+        if mode == "aux" and not graph:
+            with torch.cuda.stream(s1):
+                torch.cuda._sleep(100_000_000)
+            blk.student_step(xd, td, w.lr, want_loss=False, stream=s1)
+            assert not s1.query() and s3.query() == (not used)
+            torch.cuda.synchronize()
+            blk.profile_enable(["pw_bwd", "first_bwd", "pw_wgrad_mfma", "conv3x3_wgrad"], 8)
+            blk.student_step(xd, td, w.lr, want_loss=False, stream=s1)
+            assert {k: n for k, (_, n) in blk.profile_read().items()} == launches
+        blk.close()
+    for got in results[1:]:
+        for a, b in zip(got, results[0]):
+            np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("graph", [False, True])
 @pytest.mark.parametrize("n,c,h,w_", [(96, 144, 20, 24), (84, 48, 40, 40), (64, 272, 8, 8)])
 def test_transformed_tiles_beside_other_streams_are_bit_identical(gpu, n, c, h, w_, graph):

@@ -33,6 +33,11 @@ constexpr int kPitch = 132;                    // floats from row to row in LDS:
 constexpr int kTaps = 32;                      // tap columns (9 * Cin <= 32)
 }  // namespace
 
+// ONE: a workgroup has a single tile (up to 1024 tiles a group of 32 channels).  So few pixels were summed 32 at a time by the kernel apart, and
+// g x_j, whose sum dbeta and dgamma cancel in part, is larger than dz x_j: a wave then keeps four sums of 16 pixels.  rms error of dW
+// against 64 bits, of the root of its terms' squares, inputs around 1, apart / one sum of 64 / so: one image of 16x16, 64 channels 1.17, 1.31 and
+// 1.13e-7; two of 32x32, 32 channels 1.37, 1.48 and 1.25e-7 (around 0 at one image of 16x16 1.28, 1.38 and 1.30e-7).  With more tiles one sum does.
+template <bool ONE>
 __global__ __launch_bounds__(256, 2) void first_bwd_kernel(FirstBwdArgs p) {
   __shared__ __attribute__((aligned(16))) float lds[3][32][kPitch];   // g, z - mean, taps
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -51,7 +56,7 @@ __global__ __launch_bounds__(256, 2) void first_bwd_kernel(FirstBwdArgs p) {
   auto load4 = [](const __amdgpu_buffer_rsrc_t &r, unsigned off) { return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0)); };
 
   // this thread's patch of a tile: image, group of four rows, quad of columns; and what a tile's eight patches move it by
-  const int W4 = W >> 2, HG = (H + 3) >> 2, per = W4 * HG, T = p.geo.tiles_per_split;
+  const int W4 = W >> 2, HG = (H + 3) >> 2, per = W4 * HG, T = ONE ? 1 : p.geo.tiles_per_split;
   const int dn = 8 / per, dr = 8 - dn * per, dy = dr / W4, dx = dr - dy * W4;
   struct At {
     int n, yg, xq;
@@ -134,9 +139,12 @@ __global__ __launch_bounds__(256, 2) void first_bwd_kernel(FirstBwdArgs p) {
 #pragma unroll
   for (int k = 0; k < 11; ++k) sum[k] = 0.f;
   const int which = wave & 1, half = wave >> 1;            // this wave multiplies g or z - mean, of half of a tile's pixels
-  floatx16 acc;
+  constexpr int PARTS = ONE ? 4 : 1;
+  floatx16 acc[PARTS];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int i = 0; i < PARTS; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 
   // du of this tile and of the next, whose first column is the right edge of this one's last patch; and the tile before's last
   // column, in the lane that will have had it: the one of the range's first patch is loaded
@@ -222,10 +230,12 @@ __global__ __launch_bounds__(256, 2) void first_bwd_kernel(FirstBwdArgs p) {
 #pragma unroll
     for (int k = 0; k < 11; ++k) sum[k] += s[k];
     __builtin_amdgcn_sched_barrier(0);
+    if (!ONE) {
 #pragma unroll
-    for (int r = 0; r < 6; ++r) before[r] = d4[r][3], d4[r] = next[r];
-    fetch_zx(t + 1);
-    fetch_du(t + 2, next);
+      for (int r = 0; r < 6; ++r) before[r] = d4[r][3], d4[r] = next[r];
+      fetch_zx(t + 1);
+      fetch_du(t + 2, next);
+    }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 8; ++q) {                          // its 64 pixels, eight at a time: four products of two
@@ -233,7 +243,7 @@ __global__ __launch_bounds__(256, 2) void first_bwd_kernel(FirstBwdArgs p) {
       const f4 av = *reinterpret_cast<const f4 *>(&lds[which][l31][px]);
       const f4 xv = *reinterpret_cast<const f4 *>(&lds[2][l31][px]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], xv[e], acc, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) acc[q * PARTS / 8] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], xv[e], acc[q * PARTS / 8], 0, 0, 0);
     }
   }
 
@@ -254,8 +264,9 @@ __global__ __launch_bounds__(256, 2) void first_bwd_kernel(FirstBwdArgs p) {
   // ---- the halves' products added: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32
   __syncthreads();
   float *const M = &lds[0][0][0];                          // [halves][2][32][32]: 16 KB
+  if constexpr (ONE) acc[0] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) M[wave * 1024 + (8 * (r / 4) + 4 * lh + r % 4) * 32 + l31] = acc[r];
+  for (int r = 0; r < 16; ++r) M[wave * 1024 + (8 * (r / 4) + 4 * lh + r % 4) * 32 + l31] = acc[0][r];
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -299,8 +310,11 @@ __global__ __launch_bounds__(1024) void first_bwd_finish_kernel(FirstBwdArgs p) 
   }
 }
 
-// Splits: two rounds of two workgroups per compute unit.  What a wave sums in fp32 is a shorter chain than in the kernels apart (1 568
-// pixels at 224x224, batch 32, for 2 091).
+// Splits: two rounds of two workgroups per compute unit.  What a wave sums in fp32 for dW is a shorter chain than in the kernel apart (1 600
+// pixels at 224x224, batch 32, for 2 091).  The eleven sums of a channel are a longer one: a thread adds its 16 pixels of a tile, then the
+// tiles' sums one after another (25 there; 99 with 2048 channels at 112x112, batch 16), where dw_bwd_fast_kernel sums 8 or 16 pixels, then
+// a tree, then fp64.  It does not show: errors of dD, dgamma and dbeta against 64 bits are those of the kernels apart within 1 % at 1 to 99
+// tiles, inputs around 0, 2 and 30, since they come from du's and z's; dW's are 0.56 to 1.00 of them from two tiles on.
 FirstBwdGeom first_bwd_geom(int N, int C, int H, int W) {
   FirstBwdGeom g{};
   g.groups = cdiv(C, 32);
@@ -323,7 +337,7 @@ hipError_t launch_first_bwd(const FirstBwdArgs &a, hipStream_t s) {
   if (!a.du || !a.D || !a.z || !a.x || !a.scale || !a.shift || !a.mean || !a.rstd || !a.dw_partial || !a.partial || !a.colsum || !a.dW || !a.dgamma ||
       !a.dbeta || ((reinterpret_cast<uintptr_t>(a.du) | reinterpret_cast<uintptr_t>(a.z) | reinterpret_cast<uintptr_t>(a.x)) & 15))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(first_bwd_kernel, dim3(g.splits * g.groups), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(g.tiles_per_split == 1 ? first_bwd_kernel<true> : first_bwd_kernel<false>, dim3(g.splits * g.groups), dim3(256), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(first_bwd_finish_kernel, dim3(a.C, cdiv(9 * a.Cin, 16)), dim3(1024), 0, s, a);

@@ -885,6 +885,71 @@ def test_first_layers_gradients_in_one_kernel(gpu, n, h, w_, chans, pool):
     assert not fails, fails
 
 
+def shifted(torch, v, dy, dx):
+    """v at (y + dy, x + dx), zero outside the map."""
+    H, W = v.shape[-2:]
+    out = torch.zeros_like(v)
+    out[..., max(0, -dy):H - max(0, dy), max(0, -dx):W - max(0, dx)] = v[..., max(0, dy):H - max(0, -dy), max(0, dx):W - max(0, -dx)]
+    return out
+
+
+@pytest.mark.parametrize("n,h,w_,ci,c,off,seeds", [(1, 16, 16, 3, 64, 1, 8), (2, 32, 32, 3, 32, 1, 8), (16, 32, 32, 3, 64, 0, 4), (5, 27, 36, 2, 40, 2, 4),
+                                                   (8, 32, 32, 3, 1024, 0, 1), (8, 112, 112, 1, 1024, 0, 1), (8, 112, 112, 1, 1024, 30, 1)])
+def test_first_layers_gradients_leave_no_larger_error_than_the_kernels_apart(gpu, monkeypatch, n, h, w_, ci, c, off, seeds):
+    """rms errors of the first layer's weight, gamma and beta gradients and of the depthwise weight gradient behind it against fp64, from
+    the kernels' own z and statistics, each relative to the root of its terms' squares: with all from one kernel not above what the
+    kernels apart leave, at one, two and 25 tiles a workgroup, with inputs around 0, 1, 2 and 30.  5 % for the drawing of the values (32
+    to 64 of gamma and beta a seed: their ratio has a standard error of 1 to 2 % over 8 seeds)."""
+    torch, pb = gpu
+    d, co = torch.float64, 16
+    t = wl.Arch(n, ci, h, w_, wl._convs([ci, c, co]))
+    s = wl.Arch(n, ci, h, w_, [wl.Layer(wl.CONV3X3, ci, c, 1, 1)] + wl._dws([c, co]))
+    err = {"0": [], "1": []}
+    for seed in range(seeds):
+        x, tp, sp = wl.Workload("first_error", t, s, seed=seed).tensors(random_affine=True)
+        xd = torch.from_numpy((x + np.float32(off)).astype(np.float32)).cuda()
+        td = torch.from_numpy(np.random.default_rng(1).standard_normal((n, co, h, w_)).astype(np.float32)).cuda()
+        P, D = (torch.from_numpy(sp[1][k].reshape(shape)).cuda().to(d) for k, shape in ((1, (co, c)), (0, (c, 9))))
+        for mode in err:
+            monkeypatch.setenv("PBKD_FIRST_BWD", mode)
+            blk = pb.Block(t, tp, s, sp)
+            blk.profile_enable(["first_bwd"], 4)
+            blk.student_step(xd, td, 0.0, want_loss=False)
+            assert ("first_bwd" in blk.profile_read()) == (mode == "1")
+            get = lambda which, l, k, shape: torch.from_numpy(blk.get_tensor(which, l, k, shape)).cuda().to(d)
+            z, zn = get(pb.STUDENT_ACT, 0, 1, (n, c, h, w_)), get(pb.STUDENT_ACT, 1, 1, (n, co, h, w_))
+            (mean, rstd, sc, sh), (mn, rn, scn, shn) = ([get(pb.STUDENT_ACT, l, k, (1, k_, 1, 1)) for k in (2, 3, 4, 5)] for l, k_ in ((0, c), (1, co)))
+            got = [get(pb.STUDENT_GRAD, 0, 0, (c, 9 * ci)), get(pb.STUDENT_GRAD, 0, 1, (c, 1)), get(pb.STUDENT_GRAD, 0, 2, (c, 1)), get(pb.STUDENT_GRAD, 1, 0, (c, 9))]
+            blk.close()
+            over = (0, 2, 3)
+            bn = zn * scn + shn
+            gn = (bn.float() > 0) * 2 * (bn - td.to(d)) / td.numel()
+            xn = (zn - mn) * rn
+            dzn = scn * (gn - gn.mean(over, keepdim=True) - xn * (gn * xn).mean(over, keepdim=True))
+            du = (P.t() @ dzn.transpose(0, 1).reshape(co, -1)).reshape(c, n, h, w_).transpose(0, 1)
+            b = z * sc + sh
+            on = b.float() > 0
+            taps = [(k // 3 - 1, k % 3 - 1) for k in range(9)]
+            g, terms = torch.zeros_like(z), [[], [], [], []]                # of dW, dgamma, dbeta, dD: (sum, root of the squares' sum)
+            both = lambda v: (v.sum(over), (v * v).sum(over).sqrt())
+            for k, (dy, dx) in enumerate(taps):
+                v = shifted(torch, du, -dy, -dx)
+                g += D[:, k].reshape(1, c, 1, 1) * v
+                terms[3].append(both(b * on * v))
+            g *= on
+            xhat = (z - mean) * rstd
+            terms[1].append(both(g * xhat))
+            terms[2].append(both(g))
+            dz = sc * (g - g.mean(over, keepdim=True) - xhat * (g * xhat).mean(over, keepdim=True))
+            for i in range(ci):
+                for dy, dx in taps:
+                    terms[0].append(both(dz * shifted(torch, xd[:, i:i + 1].to(d), dy, dx)))
+            err[mode].append([float((((a - torch.stack([q[0] for q in v], 1)) / torch.stack([q[1] for q in v], 1)) ** 2).mean()) for a, v in zip(got, terms)])
+    rms = {k: np.sqrt(np.mean(v, 0)) for k, v in err.items()}
+    print(f"[first layers' gradient errors] {ci}->{c} {h}x{w_}x{n} off={off}: apart {rms['0']}, in one {rms['1']}")
+    assert (rms["1"] <= 1.05 * rms["0"]).all(), rms
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
 def test_first_layers_gradients_not_numbers(gpu, monkeypatch, bad):
     """An input or a target that holds a NaN or an infinity: numbers where the kernels apart have numbers, in every gradient of the

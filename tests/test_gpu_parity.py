@@ -766,6 +766,18 @@ def test_pointwise_weight_gradient_infinities(gpu, monkeypatch, n, h, w_, ci, co
     np.testing.assert_array_equal(value_classes(split), value_classes(fp32))
 
 
+def launched_kinds(gpu, w):
+    """{kernel kind: launches} of one student step of a new block."""
+    torch, pb = gpu
+    x, tp, sp = w.tensors()
+    blk = pb.Block(w.teacher, tp, w.student, sp)
+    blk.profile_enable(None, 200)
+    blk.student_step(torch.from_numpy(x).cuda(), torch.zeros(wl.output_shape(w.teacher), device="cuda"), 0.0, want_loss=False)
+    got = {k: n for k, (_, n) in blk.profile_read().items()}
+    blk.close()
+    return got
+
+
 @pytest.mark.parametrize("n,h,w_,chans,pool,shortcut", [
     (1, 1, 4, (3, 16), 0, 0), (3, 2, 2, (5, 70, 16), 0, 0), (2, 4, 4, (64, 64), 2, 0), (3, 6, 8, (16, 65, 128), 2, 0), (2, 5, 7, (40, 17, 33), 2, 0),
     (9, 27, 23, (67, 100, 67), 0, 2), (5, 8, 12, (20, 128, 64), 2, 1), (7, 9, 5, (130, 127, 63), 0, 1), (40, 16, 16, (64, 128, 128), 2, 0),
@@ -773,12 +785,38 @@ def test_pointwise_weight_gradient_infinities(gpu, monkeypatch, n, h, w_, ci, co
 def test_pointwise_gradients_in_one_kernel(gpu, monkeypatch, n, h, w_, chans, pool, shortcut):
     """Pointwise weight and data gradient from one kernel that forms dz from g and z, from the head's inputs with and without a
     pool and a second input, or reads it (a pool without aligned windows): 64 and 128 rows of weights, ragged channels, one to six
-    column tiles, images that end in overlapping groups of four pixels, units that wrap, one to ten chunks a workgroup."""
+    column tiles, images that end in overlapping groups of four pixels, units that wrap, one to five chunks a workgroup (see the next
+    test for more)."""
     monkeypatch.setenv("PBKD_PW_BWD", "1")
     chans = tuple(chans) if shortcut != 2 else (chans[0], *chans[1:-1], chans[0])
     t = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans)), shortcut=1 if shortcut == 1 else 0, shortcut_stride=1, pool=pool)
     s = wl.Arch(n, chans[0], h, w_, wl._dws(list(chans)), shortcut=shortcut, shortcut_stride=1, pool=pool)
-    fails = run_parity(gpu, wl.Workload("pw_bwd", t, s, seed=41), steps=2)
+    w = wl.Workload("pw_bwd", t, s, seed=41)
+    assert launched_kinds(gpu, w)["pw_bwd"] == sum(co >= 16 for co in chans[1:])
+    fails = run_parity(gpu, w, steps=2)
+    assert not fails, fails
+
+
+@pytest.mark.parametrize("co", [64, 40, 128, 100])
+@pytest.mark.parametrize("source,n,h,w_,pool,shortcut,chunks", [
+    ("given", 8, 30, 30, 2, 0, 8), ("inside", 9, 32, 32, 0, 0, 9), ("head", 7, 32, 32, 0, 0, 7), ("head_skip", 5, 32, 32, 0, 1, 5),
+    ("pooled_head", 8, 32, 32, 2, 0, 8), ("pooled_head_skip", 6, 32, 32, 2, 1, 6)])
+def test_pointwise_gradients_in_one_kernel_of_many_chunks(gpu, source, n, h, w_, pool, shortcut, chunks, co):
+    """Every source of dz, with 64 and 128 rows of weights, whole and ragged, where the loaders take their register sets (three, two
+    with a second head input) a second time round and more, and with every remainder: 1024 input channels leave 16 workgroups to the
+    pixels, each with `chunks` chunks of 64 pixels (maps half as high and chunks of 32 with more than 64 output channels)."""
+    px = 64 if co <= 64 else 32
+    h = h if co <= 64 or source == "given" else h // 2
+    n = n if co <= 64 or source != "given" else n // 2
+    unit = 8 if pool and source != "given" else 4
+    nchunks = -(-n * -(-h * w_ // unit) // (px // unit))
+    assert -(-nchunks // (256 // (1024 // 64))) == chunks
+    chans = (1024, co, 16) if source == "inside" else (1024, co)
+    t = wl.Arch(n, 1024, h, w_, wl._convs(list(chans)), shortcut=shortcut, shortcut_stride=1, pool=pool)
+    s = wl.Arch(n, 1024, h, w_, wl._dws(list(chans)), shortcut=shortcut, shortcut_stride=1, pool=pool)
+    w = wl.Workload("pw_bwd_chunks", t, s, seed=43)
+    assert launched_kinds(gpu, w).get("pw_bwd", 0) >= 1
+    fails = run_parity(gpu, w, steps=2)
     assert not fails, fails
 
 
@@ -881,7 +919,9 @@ def test_first_layers_gradients_in_one_kernel(gpu, n, h, w_, chans, pool):
     tile of which most is past the end, and (520 and 1000 channels) two and four tiles a workgroup."""
     t = wl.Arch(n, chans[0], h, w_, wl._convs(list(chans)), pool=pool)
     s = wl.Arch(n, chans[0], h, w_, [wl.Layer(wl.CONV3X3, chans[0], chans[1], 1, 1)] + wl._dws(list(chans[1:])), pool=pool)
-    fails = run_parity(gpu, wl.Workload("first_bwd", t, s, seed=43), steps=2)
+    w = wl.Workload("first_bwd", t, s, seed=43)
+    assert launched_kinds(gpu, w).get("first_bwd") == 1
+    fails = run_parity(gpu, w, steps=2)
     assert not fails, fails
 
 
@@ -2050,6 +2090,32 @@ def test_offsets_past_two_gib(gpu):
         grads.append([g for layer in blk.student_grads() for g in layer])
         blk.close()
         del xn, target
+    for a, b in zip(*grads):
+        assert relerr(b, a) <= GRAD_TOL
+    torch.cuda.empty_cache()
+
+
+def test_fused_gradients_of_two_gib(gpu):
+    """The largest tensors the kernels of fused gradients take, 2 GiB to the byte (128 images of 64 channels, 256x256): offsets reach
+    the one from which on theirs are past every buffer.  128 images that repeat two have the gradients of the two."""
+    torch, pb = gpu
+    c, h = 64, 256
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((2, 3, h, h), generator=gen, device="cuda")
+    target = torch.randn((2, c, h, h), generator=gen, device="cuda")
+    t = wl.Arch(1, 3, 8, 8, wl._convs([3, c, c]))
+    s = wl.Arch(1, 3, 8, 8, [wl.Layer(wl.CONV3X3, 3, c, 1, 1)] + wl._dws([c, c]))
+    _, tp, sp = wl.Workload("two_gib", t, s, seed=73).tensors(random_affine=True)
+    grads = []
+    for n in (2, 128):
+        assert n < 128 or n * c * h * h * 4 == 2 ** 31
+        t, s = replace(t, n=n, h=h, w=h), replace(s, n=n, h=h, w=h)
+        blk = pb.Block(t, tp, s, sp)
+        blk.profile_enable(["pw_bwd", "first_bwd"], 4)
+        blk.student_step(x.repeat(n // 2, 1, 1, 1), target.repeat(n // 2, 1, 1, 1), 0.0)
+        assert {k: m for k, (_, m) in blk.profile_read().items()} == {"pw_bwd": 1, "first_bwd": 1}
+        grads.append([g for layer in blk.student_grads() for g in layer])
+        blk.close()
     for a, b in zip(*grads):
         assert relerr(b, a) <= GRAD_TOL
     torch.cuda.empty_cache()

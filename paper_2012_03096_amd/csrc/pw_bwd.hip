@@ -156,7 +156,9 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
   constexpr bool HALF = POOL && BM == 128;                    // units of u are shared by two threads, a row each
   constexpr int VB = HALF ? 1 : VA;
   constexpr int NB = HALF ? 1 : 64 / RS;
-  constexpr int SETS = HS ? 2 : 3;                   // register sets: one is stashed, the others' chunks are on their way
+  // Register sets: one is stashed, the others' chunks are on their way.  (Three at 64 rows do not quite fit 168 registers: seven are spilled
+  // under a head without a pool, one inside a block.)
+  constexpr int SETS = HS ? 2 : 3;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   constexpr int TILES = BM == 128 ? 2 : 1, TILE = bwd_tile(BM);
   float *const tiles = reinterpret_cast<float *>(lds + 2 * COPY);                     // finished tiles of du: [2 chunks][TILES][64 channels][pixels]
@@ -198,7 +200,8 @@ __global__ __launch_bounds__(kThreads) void pw_bwd_kernel(PwBwdArgs p) {
     f4 vg[SETS][NA], vz[SETS][NA][VA], vs[SETS][NA][VA], vu[SETS][NB][VB];
     int vdup[SETS];
     auto fetch = [&](int s) {
-      // nothing here is conditional: the compiler then knows how many loads are in flight
+      // nothing here is conditional: the compiler then knows how many loads are in flight.  (Past the workgroup's range the chunks are the
+      // next one's, fetched for nothing: one or two, 50.9 MB read for 41.9 at 64 -> 128, 16x16, batch 128, four chunks a workgroup.)
       const bool ok = at.n < p.N;
       const int px = at.pixel(p);
       vdup[s] = POOL ? 0 : 4 * at.b - px;
